@@ -102,7 +102,10 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   c->B = g.n_prompts; c->R = 2 * g.n_prompts; c->d = g.d_model; c->H = g.n_heads; c->dh = dh; c->F = g.d_ff;
   c->L = g.n_layers; c->V = g.vocab; c->lo = g.logit_lo; c->veff = veff; c->P = g.prefix_len;
   c->G = g.grid_h * g.grid_w; c->Tmax = g.max_nodes + 1;
-  c->chunk = (dh > 64) ? 32 : 64;
+  // Prefill runs in chunks of this many tokens per row.  bf16: as many as give about 4096 GEMM rows (at least 64, at most 512
+  // tokens), so that a prefix is one pass over the weights and the projections run in their many-row shapes: beyond 4096
+  // rows they gain nothing more and the workspace only grows.  fp32: 64, the width of the plain attention kernel's masks.
+  c->chunk = g.dtype == VVS_BF16 ? std::min(512, std::max(64, 4096 / c->R / 32 * 32)) : (dh > 64 ? 32 : 64);
   c->Mmax = (int)align_up((size_t)c->R * std::max(c->Tmax, c->chunk), 32);   // packed operands come in 32-row blocks
   c->Mlog = (int)align_up((size_t)c->R * c->Tmax, 32);
   c->S_cap = (int)align_up((size_t)c->P + c->G + VVS_MAX_T, 32);
@@ -121,6 +124,7 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
     for (auto& sh : shapes) {
       if (sh[1] == 2 * d && !g.draft_input) continue;
       GemmPlan p = plan_gemm(c, M, sh[0], sh[1]);
+      if (g.dtype == VVS_BF16 && p.splits == 1 && sh[0] != d) continue;   // written by the projection's own epilogue
       go = std::max(go, (size_t)p.splits * M * sh[0]);
     }
   c->gemm_out_elems = go;

@@ -1100,7 +1100,7 @@ __device__ __forceinline__ void attn_step(const bf16x8 (&kf)[2][KD], const bf16x
 template <int DH, int NQB, int NW, int PD, int QG = 1>
 __global__ __launch_bounds__(NW * QG * 64, (DH * NQB >= 256 ? 1 : 2)) void k_attn_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
                                                    const bf16_t* __restrict__ vc, bf16_t* __restrict__ out, TreeDesc tree,
-                                                   PosDesc pos, int T, int d, size_t row_stride, size_t head_stride, float c_exp,
+                                                   PosDesc pos, int T_row, int d, size_t row_stride, size_t head_stride, float c_exp,
                                                    int cap_steps) {
   constexpr int KD = DH / 32, DT = DH / 16, NQ = NQB * 16;
   __shared__ float s_m[QG][NW - 1][NQ], s_l[QG][NW - 1][NQ];
@@ -1109,7 +1109,10 @@ __global__ __launch_bounds__(NW * QG * 64, (DH * NQB >= 256 ? 1 : 2)) void k_att
   const int hd = blockIdx.x, r = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) % NW, qg = (threadIdx.x >> 6) / NW, q0 = qg * NQ;
   const int g = lane >> 4, ql = lane & 15;
-  const int S = pos.kv_len ? pos.kv_len[r >> 1] : pos.kv_base;
+  // A prefill chunk of more queries than a workgroup holds is dealt to gridDim.z workgroups: queries t0 .. t0 + T - 1 of the
+  // row are a causal block of their own on top of the kv_base + t0 keys in front of them.
+  const int t0 = blockIdx.z * (NQ * QG), T = min(T_row - t0, NQ * QG), mq = r * T_row + t0;
+  const int S = pos.kv_len ? pos.kv_len[r >> 1] : pos.kv_base + t0;
   const int n_keys = S + T;
   const int nsteps = (n_keys + 31) >> 5;
   const bf16_t* kb = kc + (size_t)r * row_stride + (size_t)hd * head_stride;
@@ -1125,7 +1128,7 @@ __global__ __launch_bounds__(NW * QG * 64, (DH * NQB >= 256 ? 1 : 2)) void k_att
     mask[qb] = tree.anc[tq];
 #pragma unroll
     for (int kd = 0; kd < KD; ++kd)
-      qf[qb][kd] = as_bf16x8(*(const uint4*)(q + ((size_t)r * T + tq) * d + (size_t)hd * DH + kd * 32 + g * 8));
+      qf[qb][kd] = as_bf16x8(*(const uint4*)(q + ((size_t)mq + tq) * d + (size_t)hd * DH + kd * 32 + g * 8));
   }
   float m_run[NQB], l_run[NQB];
   floatx4 o[NQB][DT];
@@ -1221,7 +1224,7 @@ __global__ __launch_bounds__(NW * QG * 64, (DH * NQB >= 256 ? 1 : 2)) void k_att
             }
             pk[rr >> 1] = pack2bf(v0 * inv, v1 * inv);
           }
-          *(uint2*)(out + pack_index(r * T + q0 + qi, hd * DH + dt * 16 + 4 * g, d)) = make_uint2(pk[0], pk[1]);   // O-projection operand layout
+          *(uint2*)(out + pack_index(mq + q0 + qi, hd * DH + dt * 16 + 4 * g, d)) = make_uint2(pk[0], pk[1]);   // O-projection operand layout
         }
       }
     }
@@ -1650,7 +1653,8 @@ void mfma_attention(Ctx* c, int layer, const TreeDesc& tree, const PosDesc& pos,
   const bf16_t* kc = (const bf16_t*)c->kv + c->kv_layer_stride * layer;
   const bf16_t* vc = (const bf16_t*)c->kv + c->kv_v_off + c->kv_layer_stride * layer;
   const float c_exp = 1.4426950408889634f / sqrtf((float)c->dh);
-  dim3 grid(c->H, c->R);
+  const int per_wg = c->dh == 64 ? 64 : 32;                      // queries a workgroup holds; a verify call never has more
+  dim3 grid(c->H, c->R, (T + per_wg - 1) / per_wg);
   const int nqb = T <= 16 ? 1 : (T <= 32 ? 2 : 4);
 #define VVS_ATTN(DH, NQB, NW, PD, QG)                                                                                                  \
   hipLaunchKernelGGL((k_attn_mfma<DH, NQB, NW, PD, QG>), grid, dim3(NW * QG * 64), 0, s, q, kc, vc, out, tree, pos, T, c->d, c->kv_row_stride, \
@@ -1660,7 +1664,7 @@ void mfma_attention(Ctx* c, int layer, const TreeDesc& tree, const PosDesc& pos,
   if (c->dh == 64) {
     if (nqb == 1) VVS_ATTN(64, 1, 4, 2, 1); else if (nqb == 2) VVS_ATTN(64, 2, 4, 2, 1); else VVS_ATTN(64, 2, 2, 2, 2);   // 33 .. 64 queries: two groups of 32
   } else {
-    if (nqb == 1) VVS_ATTN(128, 1, 4, 2, 1); else VVS_ATTN(128, 2, 4, 2, 1);   // T <= 32 is enforced at context creation for head size 128
+    if (nqb == 1) VVS_ATTN(128, 1, 4, 2, 1); else VVS_ATTN(128, 2, 4, 2, 1);   // verify calls: T <= 32 is enforced at context creation for head size 128
   }
 #undef VVS_ATTN
 }
