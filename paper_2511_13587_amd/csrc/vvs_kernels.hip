@@ -506,21 +506,32 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
   const int pad = mfma_qkv_attention_rows(c, pos, Tq);
   const bool qa = pad > 0;
   const int pad_T = qa ? Tq : 0;
+  const GemmPlan pq = plan_gemm(c, M, 3 * d, d), pg = plan_gemm(c, M, 2 * F, d), pl = plan_gemm(c, M, c->veff, d);
+  // what each launch's idle CUs read ahead for the next one
+  auto weights = [&](const void* w, int N, int K, int bm, int bn) {
+    // at most 2.5 MB for each XCD: beside the activations more would only push itself out of its 4 MB L2
+    const int blocks = (bn / 32) * (K / 16), most = 8 * std::max(1, 2560 / blocks);
+    return WeightPrefetch{(const uint4*)w, std::min(N / bn, most), blocks, 1, 0, (M + bm - 1) / bm};
+  };
+  auto layer = [&](int l) { return c->pw + c->p.layer0 + c->p.layer_stride * l; };
+  auto pf_qkv = [&](int l) {
+    if (qa) return WeightPrefetch{(const uint4*)(layer(l) + c->p.wqkv), c->H, 2 * (d / 16), 3, (d / 32) * (d / 16), c->B};
+    return weights(layer(l) + c->p.wqkv, 3 * d, d, pq.bm, pq.bn);
+  };
   if (from_din) {             // drafter: x = [embedding ; feature] W_fc, through the residual epilogue on a zeroed x
     launch_fill_zero(x, sizeof(float) * (size_t)M * d, s);
     Timed timed(c, VVS_K_GEMM, s);
-    mfma_gemm_resid(c, (const bf16_t*)(c->ws + c->w.din), (const bf16_t*)(c->pw + c->p.fc), x, xb, ss, g_first, M, 2 * d, s, pad_T, pad);
+    mfma_gemm_resid(c, (const bf16_t*)(c->ws + c->w.din), (const bf16_t*)(c->pw + c->p.fc), x, xb, ss, g_first, M, 2 * d, s, pf_qkv(0), pad_T, pad);
   } else {
     Timed timed(c, VVS_K_ELEMENTWISE, s);
     hipLaunchKernelGGL(k_embed_packed, dim3(M), dim3(256), 0, s, x, xb, ss, NS, (const bf16_t*)(c->pw + c->p.embed),
                        (const bf16_t*)(c->pw + c->p.prefix_embed), g_first, ea, pad_T, pad);
   }
-  const GemmPlan pq = plan_gemm(c, M, 3 * d, d), pg = plan_gemm(c, M, 2 * F, d);
   for (int l = 0; l < c->L; ++l) {
     const char* lw = c->pw + c->p.layer0 + c->p.layer_stride * l;
     if (qa) {
       Timed timed(c, VVS_K_GEMM, s);
-      mfma_qkv_attention(c, l, xb, (const bf16_t*)(lw + c->p.wqkv), ss, tree, pos, Tq, s);
+      mfma_qkv_attention(c, l, xb, (const bf16_t*)(lw + c->p.wqkv), ss, tree, pos, Tq, s, weights(lw + c->p.wo, d, d, 64, 64));
     } else {
       { Timed timed(c, VVS_K_GEMM, s);
         mfma_gemm_qkv(c, l, xb, (const bf16_t*)(lw + c->p.wqkv), ss, tree, pos, Tq, pq, s);
@@ -530,15 +541,17 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
       }
     }
     { Timed timed(c, VVS_K_GEMM, s);
-      mfma_gemm_resid(c, attn, (const bf16_t*)(lw + c->p.wo), x, xb, ss, (const float*)(lw + c->p.g2), M, d, s);
+      mfma_gemm_resid(c, attn, (const bf16_t*)(lw + c->p.wo), x, xb, ss, (const float*)(lw + c->p.g2), M, d, s,
+                      weights(lw + c->p.wgu, 2 * F, d, pg.bm, pg.bn));
     }
     { Timed timed(c, VVS_K_GEMM, s);
-      mfma_gemm_swiglu(c, xb, (const bf16_t*)(lw + c->p.wgu), act, ss, M, F, d, pg, s);
+      mfma_gemm_swiglu(c, xb, (const bf16_t*)(lw + c->p.wgu), act, ss, M, F, d, pg, s, weights(lw + c->p.wd, d, F, 64, 64));
     }
     { Timed timed(c, VVS_K_GEMM, s);
       // the next reader of x is the next layer's first norm, or the final norm
       const float* g_next = l + 1 < c->L ? (const float*)(lw + c->p.layer_stride + c->p.g1) : gf;
-      mfma_gemm_resid(c, act, (const bf16_t*)(lw + c->p.wd), x, xb, ss, g_next, M, F, s, l + 1 < c->L ? pad_T : 0, pad);
+      const WeightPrefetch next = l + 1 < c->L ? pf_qkv(l + 1) : logits_mode == 1 ? weights(c->pw + c->p.wout, c->veff, d, pl.bm, pl.bn) : WeightPrefetch{};
+      mfma_gemm_resid(c, act, (const bf16_t*)(lw + c->p.wd), x, xb, ss, g_next, M, F, s, next, l + 1 < c->L ? pad_T : 0, pad);
     }
   }
   if (logits_mode == 0) return;
@@ -546,7 +559,7 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
   const bf16_t* wout = (const bf16_t*)(c->pw + c->p.wout);
   if (logits_mode == 1) {
     Timed timed(c, VVS_K_GEMM, s);
-    mfma_gemm_scaled(c, xb, wout, logits, ss, M, c->veff, d, plan_gemm(c, M, c->veff, d), s);
+    mfma_gemm_scaled(c, xb, wout, logits, ss, M, c->veff, d, pl, s);
   } else {                    // last token of every row
     bf16_t* hf = (bf16_t*)(c->ws + c->w.hf);
     float* ss2 = (float*)(c->ws + c->w.ss2);
@@ -624,7 +637,7 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
     GemmPlan pg = plan_gemm(c, M, 2 * F, d);
     if (c->cfg.dtype == VVS_BF16 && pg.splits == 1) {
       Timed timed(c, VVS_K_GEMM, s);           // projection + SwiGLU in one kernel
-      mfma_gemm_swiglu(c, (const bf16_t*)h, (const bf16_t*)(lw + c->p.wgu), (bf16_t*)act, nullptr, M, F, d, pg, s);
+      mfma_gemm_swiglu(c, (const bf16_t*)h, (const bf16_t*)(lw + c->p.wgu), (bf16_t*)act, nullptr, M, F, d, pg, s, WeightPrefetch{});
     } else {
       sp = run_gemm(c, h, lw + c->p.wgu, go, M, 2 * F, d, true, s);
       size_t n = (size_t)M * (F / 8);

@@ -81,11 +81,51 @@ struct GemmEpi {
   int xb_T, xb_pad;                                        // EPI_RESID: xb_T > 0 = xb in the row-padded layout (row m at (m / xb_T) * xb_pad + m % xb_T)
   bf16_t* q; bf16_t* kc; bf16_t* vc; const float* rope;    // EPI_QKV
   int T, d, dh, S_cap, rope_pos;
+  WeightPrefetch pf;                                       // weights of the next launch (see prefetch_weights)
   int row_owner;                                           // tile order of the direct-to-LDS kernel: 1 = an XCD owns row tiles
   size_t row_stride, head_stride;
   PosDesc pos;
   TreeDesc tree;
 };
+
+// Tile order of the projection launches.  Workgroups are dealt to the 8 XCDs round-robin by linear id, and each XCD has its own
+// L2.  Column tiles are taken in groups of 8 (one per XCD); inside a group the row tiles of one column tile get ids 8 apart:
+// they run at the same time on the same XCD, so a weight tile is fetched from memory once and then hits in that XCD's L2.  A
+// last group of fewer columns is dealt over all XCDs.
+__device__ __forceinline__ void tile_of(int id, int MT, int NT, int* tile_m, int* tile_n) {
+  const int grp = id / (8 * MT), rem = id % (8 * MT), cols = min(8, NT - grp * 8);
+  *tile_m = rem / cols;
+  *tile_n = grp * 8 + rem % cols;
+}
+
+// Weight prefetch.  A CU has about 45 KB of requests under way whatever its waves ask for, so it is filled at 45 KB per mean
+// latency: 110-150 GB/s from its XCD's L2, 42-55 GB/s from HBM (k_fill_probe).  A projection of few rows leaves CUs without a
+// tile; workgroups beyond the launch's tiles (ids n_main ..) run there and read the weight tiles of the NEXT launch, each those
+// that its own XCD will want by tile_of, so that the next launch finds them in that L2.  The rule is a matter of speed only:
+// nothing is kept, and a tile that another XCD takes after all comes from memory as before.
+template <int NW>
+__device__ void prefetch_weights(const WeightPrefetch& pf, int id, int n_main, int n_all) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, xcd = id & 7;
+  const int first = n_main + ((xcd - n_main) & 7);               // first prefetching workgroup of this XCD
+  const int mine = (id - first) >> 3, all = (n_all - first + 7) >> 3;
+  const int full = pf.n_tiles >> 3, cols = pf.n_tiles & 7;
+  // tiles xcd, xcd + 8, ... and, where the last group is dealt over all XCDs, one of that group
+  const int tiles = full + (cols && (pf.row_tiles > 1 || xcd < cols) ? 1 : 0);
+  const int per = pf.blocks * pf.sections, total = tiles * per;  // 1 KiB blocks of a tile / of this XCD
+  uint32_t acc = 0;
+  for (int k = mine * NW + wave; k < total; k += all * NW * 8) {
+    uint4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int blk = min(k + u * all * NW, total - 1), ti = blk / per, in = blk % per;
+      const int tile = ti < full ? ti * 8 + xcd : full * 8 + xcd % cols;
+      v[u] = pf.w[((size_t)(in / pf.blocks) * pf.section_blocks + (size_t)tile * pf.blocks + in % pf.blocks) * 64 + lane];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc += (v[u].x ^ v[u].y) ^ (v[u].z ^ v[u].w);
+  }
+  asm volatile("" ::"v"(acc));             // the loads stay
+}
 
 // Per-row RMSNorm factor of a tile's rows, from the per-slab sums of squares (1 when the GEMM is not
 // scaled), in two phases: the loads are issued when the kernel starts and their values are only used
@@ -411,23 +451,15 @@ __device__ __forceinline__ void tile_epilogue(const float* red, const float* rs,
 
 template <int TM, int TN, int D, int EPI>
 __global__ __launch_bounds__(256) void k_gemm_direct(const uint4* __restrict__ Ap, const uint4* __restrict__ Wp, float* __restrict__ C,
-                                                     int M, int N, int K, int kb_per_split, const GemmEpi ep) {
+                                                     int M, int N, int K, int kb_per_split, int n_main, const GemmEpi ep) {
   constexpr int BM = TM * 32, BN = TN * 32, LDC = BN + 4;
   extern __shared__ float red[];           // [4][BM][LDC]
+  if ((int)blockIdx.x >= n_main) { prefetch_weights<4>(ep.pf, blockIdx.x, n_main, gridDim.x); return; }
   VVS_PHASE_MARK(0);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // XCD-aware tile order.  Workgroups are dealt to the 8 XCDs round-robin by linear id, and each XCD
-  // has its own L2.  Column tiles are taken in groups of 8 (one per XCD); inside a group the row
-  // tiles of one column tile get ids 8 apart: they run at the same time on the same XCD, so a weight
-  // tile is fetched from HBM once and then hits in that XCD's L2.
   const int MT = (M + BM - 1) / BM, NT = N / BN;
   int tile_m, tile_n;
-  {
-    const int id = blockIdx.x, grp = id / (8 * MT), rem = id % (8 * MT);
-    const int cols = min(8, NT - grp * 8);
-    tile_m = rem / cols;
-    tile_n = grp * 8 + rem % cols;
-  }
+  tile_of(blockIdx.x, MT, NT, &tile_m, &tile_n);
   __shared__ float rs[BM];                 // per-row RMSNorm factor of this tile's rows
   __shared__ int s_pos[EPI == EPI_QKV ? 2 * BM : 2];                                  // EPI_QKV: (slot, image index) per tile row
   __shared__ __align__(16) float2 s_rope[EPI == EPI_QKV ? BM * 2 * kRopeNpMax : 2];   // EPI_QKV: rotary factors per tile row
@@ -537,12 +569,7 @@ __global__ __launch_bounds__(256) void k_gemm_shared(const uint4* __restrict__ A
   const int wr = wave >> 1, wc = wave & 1;
   const int MT = (M + BM - 1) / BM, NT = N / BN;
   int tile_m, tile_n;
-  {                                        // same XCD-aware order as k_gemm_direct
-    const int id = blockIdx.x, grp = id / (8 * MT), rem = id % (8 * MT);
-    const int cols = min(8, NT - grp * 8);
-    tile_m = rem / cols;
-    tile_n = grp * 8 + rem % cols;
-  }
+  tile_of(blockIdx.x, MT, NT, &tile_m, &tile_n);
   __shared__ float rs[BM];
   __shared__ int s_pos[EPI == EPI_QKV ? 2 * BM : 2];                                  // EPI_QKV: (slot, image index) per tile row
   __shared__ __align__(16) float2 s_rope[EPI == EPI_QKV ? BM * 2 * kRopeNpMax : 2];   // EPI_QKV: rotary factors per tile row
@@ -712,7 +739,7 @@ void launch_fill_probe(const void* src, size_t region_bytes, size_t wg_stride_by
 
 template <int WM, int WN, int NS, int EPI>
 __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict__ Ap, const uint4* __restrict__ Wp, float* __restrict__ C,
-                                                         int M, int N, int K, const GemmEpi ep) {
+                                                         int M, int N, int K, int n_main, const GemmEpi ep) {
   static_assert(NS >= 4, "at least three stages in flight");
   constexpr int BM = 2 * WM * 32, BN = 2 * WN * 32, LDC = BN + 4;
   // The output tile goes through LDS for the epilogue.  A tile too large for that (256 x 256) goes in RP = 2 passes of
@@ -724,22 +751,16 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
   extern __shared__ float red[];           // main loop: u32x4 stage[NS][NBLK][64]; afterwards: float [BM][LDC]
   u32x4* stage = (u32x4*)red;
   const uint32_t lds_base = (uint32_t)(uintptr_t)stage;
+  if ((int)blockIdx.x >= n_main) { prefetch_weights<4>(ep.pf, blockIdx.x, n_main, gridDim.x); return; }
   VVS_PHASE_MARK(0);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wr = wave >> 1, wc = wave & 1;
   const int MT = (M + BM - 1) / BM, NT = N / BN;
   int tile_m, tile_n;
-  if (!ep.row_owner) {                     // same XCD-aware order as k_gemm_direct: an XCD owns column tiles (weights fetched once,
-    const int id = blockIdx.x, grp = id / (8 * MT), rem = id % (8 * MT);   // the activation operand once per XCD)
-    const int cols = min(8, NT - grp * 8);
-    tile_m = rem / cols;
-    tile_n = grp * 8 + rem % cols;
-  } else {                                 // the transposed order: an XCD owns row tiles (activations fetched once, the weights once
-    const int id = blockIdx.x, grp = id / (8 * NT), rem = id % (8 * NT);   // per XCD): for many rows and few columns the
-    const int rows = min(8, MT - grp * 8);                                 // activation operand is the larger one
-    tile_n = rem / rows;
-    tile_m = grp * 8 + rem % rows;
-  }
+  // an XCD owns column tiles (weights fetched once, the activation operand once per XCD) or, for many rows and few columns,
+  // where the activation operand is the larger one, row tiles (the transposed order)
+  if (!ep.row_owner) tile_of(blockIdx.x, MT, NT, &tile_m, &tile_n);
+  else tile_of(blockIdx.x, NT, MT, &tile_n, &tile_m);
   __shared__ float rs[BM];
   __shared__ int s_pos[EPI == EPI_QKV ? 2 * BM : 2];    // EPI_QKV: (slot, image index) per tile row; the rotary factors are read from
                                                         // their table in memory (an LDS copy per row would keep a second workgroup off the CU)
@@ -888,6 +909,9 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
   VVS_PHASE_MARK(4);
 }
 
+// Workgroups that prefetch beside `tiles` workgroups with a tile: the rest of the 256 CUs
+static int prefetchers(const WeightPrefetch& pf, int tiles) { return pf.w && tiles <= 256 - 24 ? 256 - tiles : 0; }
+
 template <int WM, int WN, int NS, int EPI>
 static void launch_gemm_shared_dma(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, const GemmEpi& ep, hipStream_t s) {
   constexpr int BM = 2 * WM * 32, BN = 2 * WN * 32;
@@ -895,8 +919,9 @@ static void launch_gemm_shared_dma(const bf16_t* A, const bf16_t* W, float* C, i
   constexpr size_t lds_stage = (size_t)NS * (2 * (BM + BN) / 32) * 1024;
   constexpr size_t lds = lds_tile > lds_stage ? lds_tile : lds_stage;
   allow_dynamic_lds(reinterpret_cast<const void*>(&k_gemm_shared_dma<WM, WN, NS, EPI>), lds);
-  dim3 grid((N / BN) * ((M + BM - 1) / BM), 1, 1);
-  hipLaunchKernelGGL((k_gemm_shared_dma<WM, WN, NS, EPI>), grid, dim3(256), lds, s, (const uint4*)A, (const uint4*)W, C, M, N, K, ep);
+  const int tiles = (N / BN) * ((M + BM - 1) / BM);
+  hipLaunchKernelGGL((k_gemm_shared_dma<WM, WN, NS, EPI>), dim3(tiles + prefetchers(ep.pf, tiles)), dim3(256), lds, s, (const uint4*)A, (const uint4*)W,
+                     C, M, N, K, tiles, ep);
 }
 
 template <int WM, int WN, int D, int EPI>
@@ -916,8 +941,9 @@ static void launch_gemm_direct(const bf16_t* A, const bf16_t* W, float* C, int M
   allow_dynamic_lds(reinterpret_cast<const void*>(&k_gemm_direct<TM, TN, D, EPI>), lds);
   const int KB = K / 16;
   const int per = (KB + splits - 1) / splits;
-  dim3 grid((N / (TN * 32)) * ((M + TM * 32 - 1) / (TM * 32)), 1, splits);
-  hipLaunchKernelGGL((k_gemm_direct<TM, TN, D, EPI>), grid, dim3(256), lds, s, (const uint4*)A, (const uint4*)W, C, M, N, K, per, ep);
+  const int tiles = (N / (TN * 32)) * ((M + TM * 32 - 1) / (TM * 32));
+  dim3 grid(tiles + (splits == 1 ? prefetchers(ep.pf, tiles) : 0), 1, splits);
+  hipLaunchKernelGGL((k_gemm_direct<TM, TN, D, EPI>), grid, dim3(256), lds, s, (const uint4*)A, (const uint4*)W, C, M, N, K, per, tiles, ep);
 }
 
 template <int EPI>
@@ -974,8 +1000,9 @@ void mfma_gemm_scaled(Ctx* c, const bf16_t* A, const bf16_t* W, float* C, const 
 
 // x += A W; also leaves bf16(x * g_next) packed and the per-slab sums of squares of the new x
 void mfma_gemm_resid(Ctx* c, const bf16_t* A, const bf16_t* W, float* x, bf16_t* xb, float* ss_out, const float* g_next, int M, int K,
-                     hipStream_t s, int xb_T, int xb_pad) {
+                     hipStream_t s, const WeightPrefetch& pf, int xb_T, int xb_pad) {
   GemmEpi ep{};
+  ep.pf = pf;
   ep.x = x; ep.xb = xb; ep.ss_out = ss_out; ep.g_next = g_next; ep.NS = (c->d / 64 + 3) & ~3; ep.xb_T = xb_T; ep.xb_pad = xb_pad;
   // many rows: 192 x 128 tiles with the operands shared through LDS (a quarter of the bytes per flop that 64 x 64 tiles pull
   // through a CU's L1), when they give most CUs a tile - at d = 1280 and 3904 rows: 210 tiles, one round
@@ -990,8 +1017,9 @@ void mfma_gemm_resid(Ctx* c, const bf16_t* A, const bf16_t* W, float* x, bf16_t*
 
 // gate/up projection with the SwiGLU epilogue: act = silu(h Wg) * (h Wu), packed bf16 [M][F]
 void mfma_gemm_swiglu(Ctx* c, const bf16_t* A, const bf16_t* Wgu, bf16_t* act, const float* ss, int M, int F, int K, GemmPlan p,
-                      hipStream_t s) {
+                      hipStream_t s, const WeightPrefetch& pf) {
   GemmEpi ep{};
+  ep.pf = pf;
   set_scale(ep, c, ss);
   ep.act = act; ep.F = F;
   p.splits = 1;
@@ -1258,7 +1286,7 @@ __global__ __launch_bounds__(NW * QG * 64, (DH * NQB >= 256 ? 1 : 2)) void k_att
 //     its 10.4 us, without the MFMAs 10.2), tile to LDS 2.5 k, epilogue + fence 5 k, attention steps 17 k, merge + store 3 k.
 template <int NSL, int TR, int NQB>
 __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, const uint4* __restrict__ Wp, bf16_t* __restrict__ out,
-                                                  int K, const GemmEpi ep, float c_exp) {
+                                                  int K, int H, int B, const GemmEpi ep, float c_exp) {
   constexpr int GW = 4;                    // projection waves: 2 x 2 of TR x 96 (1 x 2 of 64 x 96 at TR = 32 measured 3 % slower per step)
   constexpr int RB = TR / 32;              // 32-row blocks per row of the pair
   constexpr int WM = RB, WN = 3, BM = 2 * TR, BN = 192, LDC = BN + 4, NA = 2 * (BM / 32), NBLK = NA + 12;
@@ -1282,8 +1310,11 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
   float* s_l = s_m + 2 * 4 * NQ;
   __shared__ float rs[BM];
   const uint32_t lds_base = (uint32_t)(uintptr_t)stage;
+  if ((int)blockIdx.x >= H * B) { prefetch_weights<8>(ep.pf, blockIdx.x, H * B, gridDim.x); return; }
   VVS_PHASE_MARK(0);
-  const int hd = blockIdx.x, b = blockIdx.y, T = ep.T, d = ep.d;
+  int hd, b;
+  tile_of(blockIdx.x, B, H, &b, &hd);
+  const int T = ep.T, d = ep.d;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const bool gemm_wave = wave < GW, dma_wave = wave < DW;
   const bool rs_thread = (int)threadIdx.x < BM * 4;   // the threads that own the row factors: 4 lanes per tile row
@@ -1622,8 +1653,9 @@ int mfma_qkv_attention_rows(const Ctx* c, const PosDesc& pos, int T) {
 // q/k/v projection of the row-padded operand A, rotary embedding, cache write and attention in one launch; the result is the
 // packed operand of the O projection.
 void mfma_qkv_attention(Ctx* c, int layer, const bf16_t* A, const bf16_t* Wqkv, const float* ss, const TreeDesc& tree, const PosDesc& pos,
-                        int T, hipStream_t s) {
+                        int T, hipStream_t s, const WeightPrefetch& pf) {
   GemmEpi ep{};
+  ep.pf = pf;
   set_scale(ep, c, ss);
   ep.kc = (bf16_t*)c->kv + c->kv_layer_stride * layer;
   ep.vc = (bf16_t*)c->kv + c->kv_v_off + c->kv_layer_stride * layer;
@@ -1634,13 +1666,13 @@ void mfma_qkv_attention(Ctx* c, int layer, const bf16_t* A, const bf16_t* Wqkv, 
   bf16_t* out = (bf16_t*)(c->ws + c->w.attn);
   const float c_exp = 1.4426950408889634f / sqrtf((float)c->dh);
   constexpr int NSL = 6;                   // 5 stages in flight (TR = 32: 8 slots measured the same, 4 slots 5 % slower)
-  dim3 grid(c->H, c->B);
+  dim3 grid(c->H * c->B + prefetchers(ep.pf, c->H * c->B));
 #define VVS_QA(TR, NQB)                                                                                                       \
   {                                                                                                                           \
     constexpr size_t ring = (size_t)NSL * (4 * (TR / 32) + 12) * 1024, tile = (size_t)2 * TR * 196 * sizeof(float);          \
     constexpr size_t lds = (ring > tile ? ring : tile) + (size_t)2 * TR * 72 * sizeof(bf16_t); /* ring / tile / merge, then q */ \
     allow_dynamic_lds(reinterpret_cast<const void*>(&k_qkv_attn<NSL, TR, NQB>), lds);                                         \
-    hipLaunchKernelGGL((k_qkv_attn<NSL, TR, NQB>), grid, dim3(512), lds, s, (const uint4*)A, (const uint4*)Wqkv, out, c->d, ep, c_exp); \
+    hipLaunchKernelGGL((k_qkv_attn<NSL, TR, NQB>), grid, dim3(512), lds, s, (const uint4*)A, (const uint4*)Wqkv, out, c->d, c->H, c->B, ep, c_exp); \
   }
   if (T <= 16) VVS_QA(32, 1) else if (T <= 32) VVS_QA(32, 2) else VVS_QA(64, 2)
 #undef VVS_QA
