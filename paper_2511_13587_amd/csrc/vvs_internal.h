@@ -139,6 +139,10 @@ void launch_fill_probe(const void* src, size_t region_bytes, size_t wg_stride_by
                        uint32_t* sink, hipStream_t s);
 void launch_debug_gemm(Ctx* c, int m, int n, int k, const void* a, const void* w, void* scratch, float* out, hipStream_t s);
 
+// Columns per sum of squares of the residual stream, and sums per row (padded to a multiple of 4; the padding holds zeros)
+constexpr int kSlab = 32;
+constexpr int n_slabs(int d) { return ((d + kSlab - 1) / kSlab + 3) & ~3; }
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 }  // namespace vvs

@@ -492,7 +492,7 @@ static int run_gemm(Ctx* c, const void* A, const void* W, float* C, int M, int N
 static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, const int32_t* d_tokens_bt, const void* pc,
                           const void* pu, int chunk_start, const int32_t* forced, int n_forced, int logits_mode, hipStream_t s,
                           bool from_din) {
-  const int d = c->d, F = c->F, M = c->R * Tq, NS = (d / 64 + 3) & ~3;   // slabs per row, padded to a multiple of 4 (zeros)
+  const int d = c->d, F = c->F, M = c->R * Tq, NS = n_slabs(d);
   float* x = (float*)(c->ws + c->w.x);
   bf16_t* xb = (bf16_t*)(c->ws + c->w.h);
   float* ss = (float*)(c->ws + c->w.ss);
@@ -513,6 +513,7 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
     const int blocks = (bn / 32) * (K / 16), most = 8 * std::max(1, 2560 / blocks);
     return WeightPrefetch{(const uint4*)w, std::min(N / bn, most), blocks, 1, 0, (M + bm - 1) / bm};
   };
+  const int rbn = resid_bn(c, M);
   auto layer = [&](int l) { return c->pw + c->p.layer0 + c->p.layer_stride * l; };
   auto pf_qkv = [&](int l) {
     if (qa) return WeightPrefetch{(const uint4*)(layer(l) + c->p.wqkv), c->H, 2 * (d / 16), 3, (d / 32) * (d / 16), c->B};
@@ -531,7 +532,7 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
     const char* lw = c->pw + c->p.layer0 + c->p.layer_stride * l;
     if (qa) {
       Timed timed(c, VVS_K_GEMM, s);
-      mfma_qkv_attention(c, l, xb, (const bf16_t*)(lw + c->p.wqkv), ss, tree, pos, Tq, s, weights(lw + c->p.wo, d, d, 64, 64));
+      mfma_qkv_attention(c, l, xb, (const bf16_t*)(lw + c->p.wqkv), ss, tree, pos, Tq, s, weights(lw + c->p.wo, d, d, rbn, rbn));
     } else {
       { Timed timed(c, VVS_K_GEMM, s);
         mfma_gemm_qkv(c, l, xb, (const bf16_t*)(lw + c->p.wqkv), ss, tree, pos, Tq, pq, s);
@@ -545,7 +546,7 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
                       weights(lw + c->p.wgu, 2 * F, d, pg.bm, pg.bn));
     }
     { Timed timed(c, VVS_K_GEMM, s);
-      mfma_gemm_swiglu(c, xb, (const bf16_t*)(lw + c->p.wgu), act, ss, M, F, d, pg, s, weights(lw + c->p.wd, d, F, 64, 64));
+      mfma_gemm_swiglu(c, xb, (const bf16_t*)(lw + c->p.wgu), act, ss, M, F, d, pg, s, weights(lw + c->p.wd, d, F, rbn, rbn));
     }
     { Timed timed(c, VVS_K_GEMM, s);
       // the next reader of x is the next layer's first norm, or the final norm

@@ -9,6 +9,8 @@
 // A and B always pair the same (group, element) slot, so only "8 consecutive k per lane" matters.
 #include "vvs_device.h"
 
+#include <algorithm>
+
 namespace vvs {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -48,14 +50,14 @@ __device__ __forceinline__ float rows_sum(float x) {
 // C[split][M][N] (fp32) = A[M][K] * W[N][K]^T with both operands pre-packed in MFMA fragment order:
 //   block (rb, kb) of a matrix with rows r and contraction index k = 64 lanes x 8 bf16 (1 KiB,
 //   contiguous); lane l holds row rb*32 + l%32, k = kb*16 + 8*(l/32) .. +8.        (pack_index)
-// A workgroup owns a (TM*32) x (TN*32) output tile.  Its 4 waves split the K range between them and
+// A workgroup owns a (TM*32) x (TN*32) output tile.  Its NW waves split the K range between them and
 // each wave streams ITS OWN A and B fragments straight from global memory into MFMA operand
 // registers - 1 KiB fully coalesced per load instruction, D k-steps in flight per wave, no LDS and
 // no barrier in the main loop (at these sizes a projection is bound by memory latency, not by MFMA
 // rate: the whole weight matrix is only a few MB, so what matters is how many bytes every CU keeps
-// in flight).  The 4 partial tiles are summed through LDS at the end, in a fixed order.
+// in flight).  The NW partial tiles are summed through LDS at the end, in a fixed order.
 //
-// Epilogues (after the 4-way sum):
+// Epilogues (after the sum):
 //   EPI_PARTIAL: store the fp32 tile to C[split] (consumers add the splits);
 //   EPI_SWIGLU : the weight rows are interleaved so that tile columns 0..31 are gate and 32..63 up
 //                outputs of the same 32 hidden units: write silu(gate) * up as the packed bf16
@@ -65,12 +67,12 @@ __device__ __forceinline__ float rows_sum(float x) {
 //                slots of their tokens (one K split only);
 //   EPI_RESID  : O / down projection: x += tile (fp32 residual stream, each element owned by one
 //                thread), also written, times the gain of the norm that follows, as the packed bf16
-//                operand of the next projection, plus the sum of squares of the tile's 64 columns per
+//                operand of the next projection, plus the sum of squares of every 32 columns per
 //                row (one K split only).
 // Row scale: RMSNorm is x * s_m * g with s_m = rsqrt(mean_k x_mk^2 + eps).  The operand of the projection
 // behind a norm is bf16(x * g), written by whoever produced x, and s_m - a per-row factor that commutes
 // with the contraction - multiplies the accumulated tile in the epilogue; s_m comes from the
-// per-64-column sums of squares that the producer of x (EPI_RESID or the embedding kernel) left in ss.
+// per-32-column sums of squares that the producer of x (EPI_RESID or the embedding kernel) left in ss.
 // This removes the separate normalisation pass between two projections; the weights stay as given.
 enum { EPI_PARTIAL = 0, EPI_SWIGLU = 1, EPI_QKV = 2, EPI_RESID = 3 };
 
@@ -130,15 +132,15 @@ __device__ void prefetch_weights(const WeightPrefetch& pf, int id, int n_main, i
 // Per-row RMSNorm factor of a tile's rows, from the per-slab sums of squares (1 when the GEMM is not
 // scaled), in two phases: the loads are issued when the kernel starts and their values are only used
 // after the main loop, so their latency is never waited for.  4 lanes per row (unit = row * 4 + part),
-// each takes every 4th group of 4 slabs; RU = BM * 4 / 256 units per thread.
-template <int BM>
+// each takes every 4th group of 4 slabs; RU = BM * 4 / NT units per thread.
+template <int BM, int NT = 256>
 struct RowScale {
-  static constexpr int RU = (BM * 4 + 255) / 256;
+  static constexpr int RU = (BM * 4 + NT - 1) / NT;
   float4 v[RU][4];
   __device__ __forceinline__ void load(int tile_m, int M, const GemmEpi& ep) {
 #pragma unroll
     for (int j = 0; j < RU; ++j) {
-      const int u = threadIdx.x + 256 * j, row = u >> 2, part = u & 3;
+      const int u = threadIdx.x + NT * j, row = u >> 2, part = u & 3;
       const int m = min(tile_m * BM + row, M - 1);                       // clamped rows are never stored
       const int nq = ep.NS >> 2;                                         // rows of ss are padded to a multiple of 4 slabs (zeros)
 #pragma unroll
@@ -149,7 +151,7 @@ struct RowScale {
   __device__ __forceinline__ void finish(float* rs, int tile_m, int M, const GemmEpi& ep) {
 #pragma unroll
     for (int j = 0; j < RU; ++j) {
-      const int u = threadIdx.x + 256 * j, row = u >> 2, part = u & 3;
+      const int u = threadIdx.x + NT * j, row = u >> 2, part = u & 3;
       const int m = min(tile_m * BM + row, M - 1);
       float t = 0.f;
 #pragma unroll
@@ -177,14 +179,14 @@ struct RowScale {
 //              to_lds() leaves slot, image index and factors in LDS for the epilogue, which so reads
 //              them with a few wide LDS loads instead of 16 scattered global loads per unit.
 constexpr int kRopeNpMax = 16;   // rotary pairs per position kept in LDS (head size 64); other head sizes read the table directly
-template <int BM, int BN, int EPI, bool EARLY = true>
+template <int BM, int BN, int EPI, bool EARLY = true, int NT = 256>
 struct EpiPre {
   // EARLY = false (large tiles, where the early copies would not fit the register file): EPI_RESID reads the residual
   // and the gain in the epilogue itself
-  static constexpr int UR = (BM * (BN / 8) + 255) / 256;    // EPI_RESID units (row, 8 columns) per thread
+  static constexpr int UR = (BM * (BN / 8) + NT - 1) / NT;    // EPI_RESID units (row, 8 columns) per thread
   static constexpr int URE = EARLY ? UR : 1;
-  static constexpr int G = 256 / BM;                        // threads per tile row
-  static constexpr int NR = 2 * kRopeNpMax / G / 2;         // float4 (two factor pairs) per thread
+  static constexpr int G = NT / BM;                         // threads per tile row
+  static constexpr int NR = EPI == EPI_QKV ? 2 * kRopeNpMax / G / 2 : 1;         // float4 (two factor pairs) per thread
   int kv, ne, slot, img;
   bool rope_lds = true;          // false: the epilogue reads the rotary table from memory (kernels that keep no per-row table in LDS)
   float4 rp[NR];
@@ -229,7 +231,7 @@ struct EpiPre {
     } else if constexpr (EPI == EPI_RESID && EARLY) {
 #pragma unroll
       for (int j = 0; j < UR; ++j) {
-        const int u = threadIdx.x + 256 * j, row = min(u / (BN / 8), BM - 1), c8 = (u % (BN / 8)) * 8;
+        const int u = threadIdx.x + NT * j, row = min(u / (BN / 8), BM - 1), c8 = (u % (BN / 8)) * 8;
         const float* xp = ep.x + (size_t)min(m0 + row, M - 1) * N + n0 + c8;   // clamped rows are never stored
         x0[j] = *(const float4*)xp;
         x1[j] = *(const float4*)(xp + 4);
@@ -255,9 +257,9 @@ struct EpiPre {
 
 // Epilogue of a BM x BN tile whose NP partial sums lie in LDS as red[NP][BM][BN + 4] (added in a fixed
 // order); rs holds the row factors.  Called by all 256 threads after a barrier.
-template <int BM, int BN, int NP, int EPI, bool EARLY = true>
+template <int BM, int BN, int NP, int EPI, bool EARLY = true, int NT = 256>
 __device__ __forceinline__ void tile_epilogue(const float* red, const float* rs, int tile_m, int tile_n, int M, int N, float* C,
-                                              const GemmEpi& ep, const EpiPre<BM, BN, EPI, EARLY>& pre, const int* s_pos, const float2* s_rope) {
+                                              const GemmEpi& ep, const EpiPre<BM, BN, EPI, EARLY, NT>& pre, const int* s_pos, const float2* s_rope) {
   constexpr int LDC = BN + 4;
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   constexpr int PS = BM * LDC;   // stride between the partial tiles
@@ -273,7 +275,7 @@ __device__ __forceinline__ void tile_epilogue(const float* red, const float* rs,
   };
   if constexpr (EPI == EPI_PARTIAL) {
     float* Cs = C + (size_t)blockIdx.z * M * N;
-    for (int u = threadIdx.x; u < BM * (BN / 4); u += 256) {       // one unit = (row, 4 consecutive columns)
+    for (int u = threadIdx.x; u < BM * (BN / 4); u += NT) {       // one unit = (row, 4 consecutive columns)
       const int row = u / (BN / 4), col = (u % (BN / 4)) * 4;
       if (m0 + row < M) {
         float4 v = sum4(red + row * LDC + col);
@@ -284,7 +286,7 @@ __device__ __forceinline__ void tile_epilogue(const float* red, const float* rs,
     }
   } else if constexpr (EPI == EPI_SWIGLU) {
     static_assert(BN % 64 == 0, "gate / up blocks of 32 columns alternate inside the tile");
-    for (int u = threadIdx.x; u < BM * (BN / 16); u += 256) {       // one unit = (row, 8 consecutive hidden units)
+    for (int u = threadIdx.x; u < BM * (BN / 16); u += NT) {       // one unit = (row, 8 consecutive hidden units)
       const int row = u / (BN / 16), fl = (u % (BN / 16)) * 8;      // fl: hidden unit inside the tile, 0 .. BN/2
       if (m0 + row >= M) continue;
       const float* pg = red + row * LDC + (fl >> 5) * 64 + (fl & 31);
@@ -301,10 +303,10 @@ __device__ __forceinline__ void tile_epilogue(const float* red, const float* rs,
       store8(ep.act, m0 + row, tile_n * (BN / 2) + fl, ep.F, v);
     }
   } else if constexpr (EPI == EPI_RESID) {
-    static_assert(BN % 64 == 0, "the sums of squares are kept per 64-column slab");
+    static_assert(BN % kSlab == 0 && kSlab == 32, "the sums of squares are kept per 32-column slab");
 #pragma unroll
-    for (int j = 0; j < EpiPre<BM, BN, EPI>::UR; ++j) {            // one unit = (row, 8 consecutive columns); 8 lanes share a row and slab
-      const int u = threadIdx.x + 256 * j, row = u / (BN / 8), c8 = (u % (BN / 8)) * 8;
+    for (int j = 0; j < EpiPre<BM, BN, EPI, EARLY, NT>::UR; ++j) { // one unit = (row, 8 consecutive columns); 4 lanes share a row and slab
+      const int u = threadIdx.x + NT * j, row = u / (BN / 8), c8 = (u % (BN / 8)) * 8;
       const int m = m0 + row;
       float sq = 0.f;
       if (row < BM && m < M) {
@@ -327,8 +329,12 @@ __device__ __forceinline__ void tile_epilogue(const float* red, const float* rs,
       }
       sq += __shfl_xor(sq, 1, 64);
       sq += __shfl_xor(sq, 2, 64);
-      sq += __shfl_xor(sq, 4, 64);
-      if (row < BM && m < M && (c8 & 63) == 0) ep.ss_out[(size_t)m * ep.NS + tile_n * (BN / 64) + (c8 >> 6)] = sq;
+      if (row < BM && m < M && (c8 & 31) == 0) {
+        float* so = ep.ss_out + (size_t)m * ep.NS + (n0 + c8) / kSlab;
+        *so = sq;
+        if (n0 + c8 + kSlab == N)                                  // the row's padding
+          for (int i = N / kSlab; i < ep.NS; ++i) *++so = 0.f;
+      }
     }
   } else {
     const int sec = n0 / ep.d;                                     // the tile lies inside the q (0), k (1) or v (2) third
@@ -337,7 +343,7 @@ __device__ __forceinline__ void tile_epilogue(const float* red, const float* rs,
     const int nd = n0 - sec * ep.d, dh_sh = 31 - __clz(ep.dh), dh_mask = ep.dh - 1;
     if (sec == 0) {
       const int half = ep.dh >> 1, np = ep.dh >> 2;
-      for (int u = threadIdx.x; u < BM * (BN / 16); u += 256) {    // q: one unit = (row, 16 consecutive columns), row-major output
+      for (int u = threadIdx.x; u < BM * (BN / 16); u += NT) {    // q: one unit = (row, 16 consecutive columns), row-major output
         const int row = u / (BN / 16), c0 = (u % (BN / 16)) * 16;
         const int m = m0 + row;
         if (m >= M) continue;
@@ -384,7 +390,7 @@ __device__ __forceinline__ void tile_epilogue(const float* red, const float* rs,
       // k: in the cache's operand order 4 consecutive slots of one 8-dim piece are contiguous, so a lane
       // takes one row (token) and the lanes of a wave cover consecutive tokens; a thread handles
       // 8-column pieces (one 16-byte store each) of its row.
-      constexpr int G = 256 / BM;                                  // threads per row
+      constexpr int G = NT / BM;                                   // threads per row
       const int half = ep.dh >> 1, np = ep.dh >> 2;
       const int row = threadIdx.x % BM, g4 = threadIdx.x / BM, m = m0 + row;
       const int slot = pre.slot, img = pre.img;                    // this thread's row is the one it looked up
@@ -427,7 +433,7 @@ __device__ __forceinline__ void tile_epilogue(const float* red, const float* rs,
       // v: the cache keeps the 32 slots of a dim contiguous, so a lane takes one row (token) and the lanes of
       // a wave cover consecutive tokens: one store instruction then writes runs of consecutive slots of one
       // dim instead of 64 different lines.  A thread reads 4 consecutive columns (float4) of its row.
-      constexpr int G = 256 / BM;                                  // threads per row
+      constexpr int G = NT / BM;                                   // threads per row
       const int row = threadIdx.x % BM, g = threadIdx.x / BM, m = m0 + row;
       const int slot = pre.slot;                                   // this thread's row is the one it looked up
       if (m < M && slot >= 0 && slot < ep.S_cap) {
@@ -449,26 +455,26 @@ __device__ __forceinline__ void tile_epilogue(const float* red, const float* rs,
 }
 
 
-template <int TM, int TN, int D, int EPI>
-__global__ __launch_bounds__(256) void k_gemm_direct(const uint4* __restrict__ Ap, const uint4* __restrict__ Wp, float* __restrict__ C,
+template <int TM, int TN, int D, int EPI, int NW>
+__global__ __launch_bounds__(NW * 64) void k_gemm_direct(const uint4* __restrict__ Ap, const uint4* __restrict__ Wp, float* __restrict__ C,
                                                      int M, int N, int K, int kb_per_split, int n_main, const GemmEpi ep) {
-  constexpr int BM = TM * 32, BN = TN * 32, LDC = BN + 4;
-  extern __shared__ float red[];           // [4][BM][LDC]
-  if ((int)blockIdx.x >= n_main) { prefetch_weights<4>(ep.pf, blockIdx.x, n_main, gridDim.x); return; }
+  constexpr int BM = TM * 32, BN = TN * 32, LDC = BN + 4, NT = NW * 64;
+  static_assert(EPI != EPI_QKV || NW == 4, "the rotary factors of a row are dealt to 256 / BM threads");
+  extern __shared__ float red[];           // [NW][BM][LDC]
+  if ((int)blockIdx.x >= n_main) { prefetch_weights<NW>(ep.pf, blockIdx.x, n_main, gridDim.x); return; }
   VVS_PHASE_MARK(0);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int MT = (M + BM - 1) / BM, NT = N / BN;
   int tile_m, tile_n;
-  tile_of(blockIdx.x, MT, NT, &tile_m, &tile_n);
+  tile_of(blockIdx.x, (M + BM - 1) / BM, N / BN, &tile_m, &tile_n);
   __shared__ float rs[BM];                 // per-row RMSNorm factor of this tile's rows
   __shared__ int s_pos[EPI == EPI_QKV ? 2 * BM : 2];                                  // EPI_QKV: (slot, image index) per tile row
   __shared__ __align__(16) float2 s_rope[EPI == EPI_QKV ? BM * 2 * kRopeNpMax : 2];   // EPI_QKV: rotary factors per tile row
-  EpiPre<BM, BN, EPI> pre;
+  EpiPre<BM, BN, EPI, true, NT> pre;
   pre.first(tile_m, M, ep);
   __builtin_amdgcn_sched_barrier(0);
   const int KB = K >> 4;
   const int s0 = blockIdx.z * kb_per_split, s1 = min(KB, s0 + kb_per_split);
-  const int per_w = (max(s1 - s0, 0) + 3) >> 2;
+  const int per_w = (max(s1 - s0, 0) + NW - 1) / NW;
   const int w0 = s0 + wave * per_w, w1 = min(s1, w0 + per_w);
   const int nk = max(w1 - w0, 0);
   const uint4* ap[TM];
@@ -497,24 +503,23 @@ __global__ __launch_bounds__(256) void k_gemm_direct(const uint4* __restrict__ A
     __builtin_amdgcn_sched_barrier(0);
   }
   // epilogue inputs: requested behind the first operand loads (nothing waits for them before the main loop ends)
-  RowScale<BM> rowscale;
+  RowScale<BM, NT> rowscale;
   rowscale.load(tile_m, M, ep);
   if (EPI != EPI_QKV || nk <= 0) pre.start(tile_m, tile_n, M, N, ep);
   __builtin_amdgcn_sched_barrier(0);
   VVS_PHASE_MARK(1);
-  for (int kb = 0; kb < nk; kb += D) {
+  int kb = 0;
+  for (; kb + D < nk; kb += D) {           // all groups of k-steps but the last: multiply one, request its successor D further on
     // EPI_QKV: the rotary factors depend on a loaded value (the row's cache length); asking for them after the
     // first group of k-steps instead of in front of the loop keeps that wait off the path to the first MFMA
     if (EPI == EPI_QKV && kb == D) pre.start(tile_m, tile_n, M, N, ep);
 #pragma unroll
     for (int i = 0; i < D; ++i) {
-      if (kb + i < nk) {
 #pragma unroll
-        for (int ti = 0; ti < TM; ++ti)
+      for (int ti = 0; ti < TM; ++ti)
 #pragma unroll
-          for (int tj = 0; tj < TN; ++tj)
-            acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fa[i][ti]), as_bf16x8(fb[i][tj]), acc[ti][tj], 0, 0, 0);
-      }
+        for (int tj = 0; tj < TN; ++tj)
+          acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fa[i][ti]), as_bf16x8(fb[i][tj]), acc[ti][tj], 0, 0, 0);
       const size_t kk = (size_t)min(w0 + kb + i + D, KB - 1) * 64;
 #pragma unroll
       for (int t = 0; t < TM; ++t) fa[i][t] = ap[t][kk];
@@ -523,7 +528,17 @@ __global__ __launch_bounds__(256) void k_gemm_direct(const uint4* __restrict__ A
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  if (EPI == EPI_QKV && nk > 0 && nk <= D) pre.start(tile_m, tile_n, M, N, ep);   // a K range of a single group
+  if (EPI == EPI_QKV && nk > 0 && kb <= D) pre.start(tile_m, tile_n, M, N, ep);   // a K range of one or two groups: not asked for yet
+#pragma unroll
+  for (int i = 0; i < D; ++i) {            // the last group
+    if (kb + i < nk) {
+#pragma unroll
+      for (int ti = 0; ti < TM; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < TN; ++tj)
+          acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fa[i][ti]), as_bf16x8(fb[i][tj]), acc[ti][tj], 0, 0, 0);
+    }
+  }
   VVS_PHASE_MARK(2);
   pre.to_lds(s_pos, s_rope, ep);
   rowscale.finish(rs, tile_m, M, ep);
@@ -538,7 +553,7 @@ __global__ __launch_bounds__(256) void k_gemm_direct(const uint4* __restrict__ A
         mine[(i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * LDC + j * 32 + (lane & 31)] = acc[i][j][r];
   __syncthreads();
   VVS_PHASE_MARK(3);
-  tile_epilogue<BM, BN, 4, EPI>(red, rs, tile_m, tile_n, M, N, C, ep, pre, s_pos, s_rope);
+  tile_epilogue<BM, BN, NW, EPI, true, NT>(red, rs, tile_m, tile_n, M, N, C, ep, pre, s_pos, s_rope);
   VVS_PHASE_MARK(4);
 }
 
@@ -909,8 +924,11 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
   VVS_PHASE_MARK(4);
 }
 
-// Workgroups that prefetch beside `tiles` workgroups with a tile: the rest of the 256 CUs
-static int prefetchers(const WeightPrefetch& pf, int tiles) { return pf.w && tiles <= 256 - 24 ? 256 - tiles : 0; }
+// Workgroups that prefetch beside `tiles` workgroups with a tile: the free places on the 256 CUs (per_cu workgroups each), at most 256
+static int prefetchers(const WeightPrefetch& pf, int tiles, int per_cu = 1) {
+  const int free = 256 * per_cu - tiles;
+  return pf.w && free >= 24 ? std::min(free, 256) : 0;
+}
 
 template <int WM, int WN, int NS, int EPI>
 static void launch_gemm_shared_dma(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, const GemmEpi& ep, hipStream_t s) {
@@ -934,16 +952,16 @@ static void launch_gemm_shared(const bf16_t* A, const bf16_t* W, float* C, int M
   hipLaunchKernelGGL((k_gemm_shared<WM, WN, D, EPI>), grid, dim3(256), lds, s, (const uint4*)A, (const uint4*)W, C, M, N, K, ep);
 }
 
-template <int TM, int TN, int D, int EPI>
+template <int TM, int TN, int D, int EPI, int NW = 4>
 static void launch_gemm_direct(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, int splits, const GemmEpi& ep,
                                hipStream_t s) {
-  constexpr size_t lds = (size_t)4 * TM * 32 * (TN * 32 + 4) * sizeof(float);
-  allow_dynamic_lds(reinterpret_cast<const void*>(&k_gemm_direct<TM, TN, D, EPI>), lds);
+  constexpr size_t lds = (size_t)NW * TM * 32 * (TN * 32 + 4) * sizeof(float);
+  allow_dynamic_lds(reinterpret_cast<const void*>(&k_gemm_direct<TM, TN, D, EPI, NW>), lds);
   const int KB = K / 16;
   const int per = (KB + splits - 1) / splits;
   const int tiles = (N / (TN * 32)) * ((M + TM * 32 - 1) / (TM * 32));
-  dim3 grid(tiles + (splits == 1 ? prefetchers(ep.pf, tiles) : 0), 1, splits);
-  hipLaunchKernelGGL((k_gemm_direct<TM, TN, D, EPI>), grid, dim3(256), lds, s, (const uint4*)A, (const uint4*)W, C, M, N, K, per, tiles, ep);
+  dim3 grid(tiles + (splits == 1 ? prefetchers(ep.pf, tiles, tiles > 256 && lds <= 40 * 1024 ? 2 : 1) : 0), 1, splits);
+  hipLaunchKernelGGL((k_gemm_direct<TM, TN, D, EPI, NW>), grid, dim3(NW * 64), lds, s, (const uint4*)A, (const uint4*)W, C, M, N, K, per, tiles, ep);
 }
 
 template <int EPI>
@@ -982,7 +1000,7 @@ static void gemm_dispatch(const bf16_t* A, const bf16_t* W, float* C, int M, int
 }
 
 static void set_scale(GemmEpi& ep, const Ctx* c, const float* ss) {
-  ep.ss = ss; ep.NS = (c->d / 64 + 3) & ~3; ep.eps = c->cfg.rms_eps; ep.dnorm = c->d;   // rows of ss are padded to 4 slabs
+  ep.ss = ss; ep.NS = n_slabs(c->d); ep.eps = c->cfg.rms_eps; ep.dnorm = c->d;
 }
 
 void mfma_gemm(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, GemmPlan p, hipStream_t s) {
@@ -998,12 +1016,18 @@ void mfma_gemm_scaled(Ctx* c, const bf16_t* A, const bf16_t* W, float* C, const 
   gemm_dispatch<EPI_PARTIAL>(A, W, C, M, N, K, p, ep, s);
 }
 
+// Tile columns of the O and down projections: 32 (32 x 32 tiles, 8 waves) while that gives at most 448 workgroups - a launch of few
+// tiles lasts as long as one CU takes to pull its operands in, so smaller tiles on more CUs win until two workgroups share most
+// CUs - else 64.  us per launch, O and down mean, 64 x 64 on 4 waves / 32 x 32 on 8: d 768, 48 rows 7.3 / 4.9; d 1280, 54 rows
+// 10.4 / 7.2, 300 rows (400 tiles) 10.8 / 10.1, 432 rows (560 tiles) 11.5 / 14.3.  (32 x 64 and 64 x 32 on 8 waves lie between.)
+int resid_bn(const Ctx* c, int M) { return ((M + 31) / 32) * (c->d / 32) <= 448 ? 32 : 64; }
+
 // x += A W; also leaves bf16(x * g_next) packed and the per-slab sums of squares of the new x
 void mfma_gemm_resid(Ctx* c, const bf16_t* A, const bf16_t* W, float* x, bf16_t* xb, float* ss_out, const float* g_next, int M, int K,
                      hipStream_t s, const WeightPrefetch& pf, int xb_T, int xb_pad) {
   GemmEpi ep{};
   ep.pf = pf;
-  ep.x = x; ep.xb = xb; ep.ss_out = ss_out; ep.g_next = g_next; ep.NS = (c->d / 64 + 3) & ~3; ep.xb_T = xb_T; ep.xb_pad = xb_pad;
+  ep.x = x; ep.xb = xb; ep.ss_out = ss_out; ep.g_next = g_next; ep.NS = n_slabs(c->d); ep.xb_T = xb_T; ep.xb_pad = xb_pad;
   // many rows: 192 x 128 tiles with the operands shared through LDS (a quarter of the bytes per flop that 64 x 64 tiles pull
   // through a CU's L1), when they give most CUs a tile - at d = 1280 and 3904 rows: 210 tiles, one round
   if (c->d % 128 == 0 && K % 32 == 0 && ((M + 191) / 192) * (c->d / 128) >= 160) {
@@ -1012,7 +1036,8 @@ void mfma_gemm_resid(Ctx* c, const bf16_t* A, const bf16_t* W, float* x, bf16_t*
     launch_gemm_shared_dma<3, 2, 6, EPI_RESID>(A, W, nullptr, M, c->d, K, ep, s);
     return;
   }
-  launch_gemm_direct<2, 2, 6, EPI_RESID>(A, W, nullptr, M, c->d, K, 1, ep, s);
+  if (resid_bn(c, M) == 32) launch_gemm_direct<1, 1, 8, EPI_RESID, 8>(A, W, nullptr, M, c->d, K, 1, ep, s);
+  else launch_gemm_direct<2, 2, 6, EPI_RESID>(A, W, nullptr, M, c->d, K, 1, ep, s);
 }
 
 // gate/up projection with the SwiGLU epilogue: act = silu(h Wg) * (h Wu), packed bf16 [M][F]
@@ -1326,7 +1351,8 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
   // kernel-argument loads): they are asked for only behind the first stage requests, so that nothing on the way to those
   // requests waits for memory.
   int kv, ne;
-  float4 rv[4];                            // row factor inputs
+  constexpr int RQ = 5;                    // groups of 4 lanes x 4 slabs: d <= 2560
+  float4 rv[RQ];                           // row factor inputs
   // attention operands (see k_attn_mfma): K and V of a 32-key step straight into MFMA operand registers
   const int r = 2 * b + ar;
   const int g = lane >> 4, ql = lane & 15;
@@ -1348,7 +1374,7 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
     const int row = threadIdx.x >> 2, part = threadIdx.x & 3, nq = ep.NS >> 2;   // kernel arguments only, older than the stage requests
     const int m = (2 * b + row / TR) * T + min(row % TR, T - 1);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < RQ; ++i)
       rv[i] = part + 4 * i < nq ? ((const float4*)(ep.ss + (size_t)m * ep.NS))[part + 4 * i] : make_float4(0.f, 0.f, 0.f, 0.f);
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -1460,7 +1486,7 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
     const int row = threadIdx.x >> 2, part = threadIdx.x & 3;
     float t = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) t += (rv[i].x + rv[i].y) + (rv[i].z + rv[i].w);
+    for (int i = 0; i < RQ; ++i) t += (rv[i].x + rv[i].y) + (rv[i].z + rv[i].w);
     t += __shfl_xor(t, 1, 64);
     t += __shfl_xor(t, 2, 64);
     if (part == 0) rs[row] = 1.0f / sqrtf(t / (float)ep.dnorm + ep.eps);
@@ -1641,7 +1667,7 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
 // Tile rows per row of a pair in the fused projection + attention kernel (the padding of its activation operand), or 0
 // when a verify call of T block tokens per row does not take that kernel.
 int mfma_qkv_attention_rows(const Ctx* c, const PosDesc& pos, int T) {
-  if (c->cfg.dtype != VVS_BF16 || c->dh != 64 || T > 64 || !pos.kv_len || !pos.n_emitted || c->d % 64 || c->d / 64 > 64) return 0;
+  if (c->cfg.dtype != VVS_BF16 || c->dh != 64 || T > 64 || !pos.kv_len || !pos.n_emitted || c->d % 64 || c->d > 2560) return 0;
   // 33 .. 64 tokens per row: a workgroup fills a CU (141 KB of LDS), so (head, prompt) pairs beyond the 256 CUs run in rounds,
   // and a poorly filled third round loses to the separate kernels.  Measured at 20 heads, 61 tokens, ms per step fused /
   // separate: 8 prompts 3.99 / 4.30, 12: 4.94 / 5.78, 16: 7.25 / 7.32, 24: 8.73 / 9.02, 28: 10.10 / 9.65, 32: 10.63 / 10.25.
