@@ -383,10 +383,15 @@ __global__ void k_rope_kv(const float* __restrict__ qkv, int splits, size_t spli
 }
 
 // ------------------------------------------------------------------------------------------------ attention, one query per workgroup
+// Bound by chains of loads: a thread takes whole keys for the scores (16-byte pieces of the key, all requested before the
+// first is used), and the P V sum is dealt to 256 / dh groups of dh threads by chunks of 8 keys - contiguous in the cache's V
+// order - whose partial sums are added in a fixed order.  One group over all keys, one element at a time, took 11.9 us at 40
+// keys and head size 32; 5.8 us.
 template <typename T>
-__global__ void k_attn_simple(const T* __restrict__ q, const T* __restrict__ kc, const T* __restrict__ vc, T* __restrict__ out,
+__global__ __launch_bounds__(256) void k_attn_simple(const T* __restrict__ q, const T* __restrict__ kc, const T* __restrict__ vc, T* __restrict__ out,
                               TreeDesc tree, PosDesc pos, int T_, int d, int dh, size_t row_stride, size_t head_stride, int S_cap) {
   extern __shared__ float sc[];          // [S_cap] scores, then 16 floats for reductions
+  __shared__ float part[256];            // [group][dim]
   float* red = sc + S_cap;
   const int t = blockIdx.x, hd = blockIdx.y, r = blockIdx.z, m = r * T_ + t;
   const int S = pos.kv_len ? pos.kv_len[r >> 1] : pos.kv_base;
@@ -397,12 +402,16 @@ __global__ void k_attn_simple(const T* __restrict__ q, const T* __restrict__ kc,
   const T* vb = vc + (size_t)r * row_stride + (size_t)hd * head_stride;
   const float scale = 1.0f / sqrtf((float)dh);
   float mx = -INFINITY;
-  for (int k = threadIdx.x; k < n; k += blockDim.x) {
+  for (int k = threadIdx.x; k < n; k += 256) {
     bool vis = k < S || ((mask >> (k - S)) & 1ull);
     float sv = -INFINITY;
     if (vis) {
       float dot = 0.f;
-      for (int e = 0; e < dh; ++e) dot += ld(qv + e) * ld(kb + k_index(k, e, dh));
+#pragma unroll 8
+      for (int e = 0; e < dh; e += 4) {    // the head size is a multiple of 4, and 4 dims of a key are contiguous in either K order
+        const float4 a = *(const float4*)(qv + e), kk = *(const float4*)(kb + k_index(k, e, dh));
+        dot += (a.x * kk.x + a.y * kk.y) + (a.z * kk.z + a.w * kk.w);
+      }
       sv = dot * scale;
     }
     sc[k] = sv;
@@ -410,15 +419,26 @@ __global__ void k_attn_simple(const T* __restrict__ q, const T* __restrict__ kc,
   }
   mx = block_max(mx, red);
   float sum = 0.f;
-  for (int k = threadIdx.x; k < n; k += blockDim.x) {
+  for (int k = threadIdx.x; k < n; k += 256) {
     float e = sc[k] == -INFINITY ? 0.f : expf(sc[k] - mx);
     sc[k] = e;
     sum += e;
   }
-  sum = block_sum(sum, red);
-  for (int e = threadIdx.x; e < dh; e += blockDim.x) {
-    float o = 0.f;
-    for (int k = 0; k < n; ++k) o += sc[k] * ld(vb + v_index(k, e, dh));
+  sum = block_sum(sum, red);               // its barriers also publish the weights
+  const int ng = 256 / dh, g = threadIdx.x / dh, e = threadIdx.x % dh;   // head sizes up to 256
+  float o = 0.f;
+  if (g < ng)
+    for (int k0 = 8 * g; k0 < n; k0 += 8 * ng) {
+      const float4* vp = (const float4*)(vb + v_index(k0, e, dh));       // 8 consecutive slots of a dim; the region holds whole steps of 32
+      const float4 v0 = vp[0], v1 = vp[1];
+      const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) o += k0 + i < n ? sc[k0 + i] * v[i] : 0.f;   // slots from n on hold anything
+    }
+  part[threadIdx.x] = o;                   // [g][e]
+  __syncthreads();
+  if (g == 0) {
+    for (int j = 1; j < ng; ++j) o += part[j * dh + e];
     st(out + (size_t)m * d + (size_t)hd * dh + e, o / sum);
   }
 }
@@ -447,26 +467,69 @@ __global__ void k_swiglu(const float* __restrict__ gu, int splits, size_t split_
 }
 
 // ------------------------------------------------------------------------------------------------ GEMM, one wave per output column
-// C[m][n] = sum_k A[m][k] * W[n][k]; lanes stride over k (coalesced), 8 rows of A per pass.
-template <typename T>
-__global__ void k_gemm_simple(const T* __restrict__ A, const T* __restrict__ W, float* __restrict__ C, int M, int N, int K) {
+// C[m][n] = sum_k A[m][k] * W[n][k] in fp32; a wave owns one column for 8 rows of A, its lanes stride over k.  The matrices of
+// this path are small and a launch lasts as long as its chain of loads, so everything is asked for before the first product:
+// rows past M repeat the last one instead of being skipped behind a branch each, VEC lanes take 16 bytes at a time and 2 x 64
+// such pieces (K = 512) are under way at once.  Launch of 128 columns and 10 rows, K 128 and 344 on average: 11.4 us with
+// 4-byte loads behind the row tests, 3.5 us so.  !VEC: a K that is not a multiple of 4, or operands not on 16 bytes.
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_gemm_simple(const float* __restrict__ A, const float* __restrict__ W, float* __restrict__ C, int M, int N, int K) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = blockIdx.x * 4 + wave, m0 = blockIdx.y * 8;
   if (n >= N) return;
+  const float* w = W + (size_t)n * K;
+  const float* a[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = A + (size_t)min(m0 + i, M - 1) * K;
   float acc[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-  for (int k = lane; k < K; k += 64) {
-    const float w = ld(W + (size_t)n * K + k);
+  if constexpr (VEC) {
+    const int K4 = K >> 2;
+    for (int k0 = 0; k0 < K4; k0 += 128) {
+      float4 wv[2], av[2][8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (m0 + i < M) acc[i] += ld(A + (size_t)(m0 + i) * K + k) * w;
-  }
+      for (int u = 0; u < 2; ++u) {
+        const int k = k0 + 64 * u + lane;
+        if (k < K4) {
+          wv[u] = ((const float4*)w)[k];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    float v = wave_sum(acc[i]);
-    if (lane == 0 && m0 + i < M) C[(size_t)(m0 + i) * N + n] = v;
+          for (int i = 0; i < 8; ++i) av[u][i] = ((const float4*)a[i])[k];
+        } else {
+          wv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) av[u][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          acc[i] += (av[u][i].x * wv[u].x + av[u][i].y * wv[u].y) + (av[u][i].z * wv[u].z + av[u][i].w * wv[u].w);
+    }
+  } else {
+    for (int k = lane; k < K; k += 64) {
+      const float wk = w[k];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] += a[i][k] * wk;
+    }
   }
+  // sum over the lanes: the first three exchanges halve the rows a lane carries (4 + 2 + 1 + 3 exchanges instead of 8 x 6);
+  // lanes 8 j .. 8 j + 7 end with row j
+#pragma unroll
+  for (int half = 4; half >= 1; half >>= 1) {
+    const bool hi = lane & (8 * half);
+#pragma unroll
+    for (int i = 0; i < half; ++i) {
+      const float keep = hi ? acc[i + half] : acc[i], give = hi ? acc[i] : acc[i + half];
+      acc[i] = keep + __shfl_xor(give, 8 * half, 64);
+    }
+  }
+  float v = acc[0];
+#pragma unroll
+  for (int o = 4; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  const int m = m0 + (lane >> 3);
+  if ((lane & 7) == 0 && m < M) C[(size_t)m * N + n] = v;
 }
 
 // C[splits][M][N] (fp32 partial sums) = A[M][K] * W[N][K]^T (bf16: both operands in packed fragment order)
@@ -479,7 +542,10 @@ static int run_gemm(Ctx* c, const void* A, const void* W, float* C, int M, int N
     return p.splits;
   }
   dim3 grid((N + 3) / 4, (M + 7) / 8);
-  hipLaunchKernelGGL(k_gemm_simple<float>, grid, dim3(256), 0, s, (const float*)A, (const float*)W, C, M, N, K);
+  if (K % 4 == 0 && ((uintptr_t)A | (uintptr_t)W) % 16 == 0)
+    hipLaunchKernelGGL(k_gemm_simple<true>, grid, dim3(256), 0, s, (const float*)A, (const float*)W, C, M, N, K);
+  else
+    hipLaunchKernelGGL(k_gemm_simple<false>, grid, dim3(256), 0, s, (const float*)A, (const float*)W, C, M, N, K);
   return 1;
 }
 

@@ -126,6 +126,20 @@ def test_largest_tree_fp32(gc, kind):
     pair.close()
 
 
+@pytest.mark.parametrize("heads,head", [(2, 4), (3, 24), (2, 36), (1, 160), (1, 256)])
+def test_attention_head_sizes_fp32(gc, heads, head):
+    """The plain attention at head sizes off the cache's blocks of 16 / 32 dims, at one group of threads over all keys
+    (head sizes above 128), over a key count that ends inside a chunk of 8.  Logits 1e-4."""
+    shape = synth.TINY.replace(n_layers=1, d_model=heads * head, n_heads=heads, d_ff=64, n_nodes=5)
+    pair = gc.Pair(shape, gain_jitter=0.1)
+    pair.prefill(n_forced=13)
+    parent = np.array([0, 0, 1, 1, 3], dtype=np.int32)
+    q, toks = synth.make_draft(shape, parent, 0)
+    pair.verify(parent, toks, q, synth.make_uniforms(shape, 5, 0))
+    gc.check_logits(pair, f"{heads} heads of {head}")
+    pair.close()
+
+
 def test_ragged_prompts_some_finished_fp32(gc):
     """Three prompts on a 3 x 3 grid driven to the end: they accept different numbers of tokens per
     call, so their cache lengths diverge and they finish in different calls; a finished prompt must

@@ -39,7 +39,8 @@ def test_gemm_bf16_mfma(gc, m, n, k):
     pair.close()
 
 
-@pytest.mark.parametrize("m,n,k", [(10, 384, 128), (7, 1024, 344), (3, 5, 9)])
+@pytest.mark.parametrize("m,n,k", [(10, 384, 128), (7, 1024, 344), (3, 5, 9),
+                                   (1, 4, 4), (8, 6, 512), (9, 33, 516), (17, 64, 1100)])
 def test_gemm_fp32(gc, m, n, k):
     pair = gc.Pair(synth.TINY, with_oracle=False)
     rng = np.random.default_rng(m + n + k)
