@@ -557,150 +557,15 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_direct(const uint4* __restrict
   VVS_PHASE_MARK(4);
 }
 
-// Shared-operand variant for projections with enough output tiles: a workgroup owns a
-// (2*WM*32) x (2*WN*32) tile, its 4 waves form a 2 x 2 grid of (WM*32) x (WN*32) sub-tiles and all of
-// them read the A and B fragments from LDS, so every operand byte that comes through the CU's L1 feeds
-// twice as many MFMAs as in k_gemm_direct.  A stage is 32 contraction indices = 2 fragment blocks per
-// 32 rows; the blocks are copied global -> registers -> LDS as they are (the packed layout is already
-// the LDS layout the MFMA lanes want).
-// Software pipeline (one wave per SIMD, so nothing else hides latencies): global loads run D stages
-// ahead in registers; LDS holds 3 stages; in iteration s a wave requests the second half of stage s from
-// LDS, moves stage s+2 from registers to LDS and re-requests those registers from memory, multiplies
-// the first half of stage s, requests the first half of stage s+1 and multiplies the second half:
-// every MFMA group runs on fragments requested one group earlier.  One barrier per stage: it orders
-// the LDS writes of stage s+2 before their reads in iteration s+1 and the reads of stage s before the
-// slot is overwritten in iteration s+1.  The epilogues are the same as above with a single partial tile.
-template <int WM, int WN, int D, int EPI>
-__global__ __launch_bounds__(256) void k_gemm_shared(const uint4* __restrict__ Ap, const uint4* __restrict__ Wp, float* __restrict__ C,
-                                                     int M, int N, int K, const GemmEpi ep) {
-  constexpr int BM = 2 * WM * 32, BN = 2 * WN * 32, LDC = BN + 4;
-  constexpr int NA = 2 * (BM / 32), NBLK = NA + 2 * (BN / 32), PER = NBLK / 4;   // 1 KiB blocks per stage; per wave
-  static_assert(NBLK % 4 == 0, "blocks of a stage are dealt to 4 waves");
-  static_assert(D % 3 == 0, "register ring and LDS ring indices are both static after unrolling by D");
-  extern __shared__ float red[];           // main loop: u32x4 stage[3][NBLK][64]; afterwards: float [BM][LDC]
-  u32x4* stage = (u32x4*)red;
-  VVS_PHASE_MARK(0);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wr = wave >> 1, wc = wave & 1;
-  const int MT = (M + BM - 1) / BM, NT = N / BN;
-  int tile_m, tile_n;
-  tile_of(blockIdx.x, MT, NT, &tile_m, &tile_n);
-  __shared__ float rs[BM];
-  __shared__ int s_pos[EPI == EPI_QKV ? 2 * BM : 2];                                  // EPI_QKV: (slot, image index) per tile row
-  __shared__ __align__(16) float2 s_rope[EPI == EPI_QKV ? BM * 2 * kRopeNpMax : 2];   // EPI_QKV: rotary factors per tile row
-  EpiPre<BM, BN, EPI> pre;
-  pre.first(tile_m, M, ep);
-  __builtin_amdgcn_sched_barrier(0);
-  const int KB = K >> 4, nst = KB >> 1;
-  const int last_rb = (M - 1) >> 5;        // row blocks past the end of A repeat the last one (their rows are never stored)
-  // block j of a stage: j < NA: A row block j/2, else B row block (j-NA)/2; contraction block 2*s + j%2
-  const u32x4* src[PER];
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int j = wave + 4 * i;
-    const int rb = j < NA ? min(tile_m * (BM / 32) + (j >> 1), last_rb) : tile_n * (BN / 32) + ((j - NA) >> 1);
-    src[i] = (const u32x4*)(j < NA ? Ap : Wp) + ((size_t)rb * KB + (j & 1)) * 64 + lane;
-  }
-  floatx16 acc[WM][WN];
-#pragma unroll
-  for (int i = 0; i < WM; ++i)
-#pragma unroll
-    for (int j = 0; j < WN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  // stage t lives in st[t % D] until it is written to LDS slot t % 3; stages past the end repeat the last one
-  u32x4 st[D][PER];
-#define VVS_G2R(RD, T)                                                                                                \
-  {                                                                                                                   \
-    const size_t kk = (size_t)min((T), nst - 1) * 128;                                                                \
-    _Pragma("unroll") for (int i = 0; i < PER; ++i) st[RD][i] = src[i][kk];                                           \
-    __builtin_amdgcn_sched_barrier(0); /* load groups stay in program order: waits are partial */                     \
-  }
-#define VVS_R2S(RD, SL) \
-  { _Pragma("unroll") for (int i = 0; i < PER; ++i) stage[((SL) * NBLK + wave + 4 * i) * 64 + lane] = st[RD][i]; }
-#define VVS_S2F(FA, FB, SL, KBO)                                                                                      \
-  {                                                                                                                   \
-    _Pragma("unroll") for (int t = 0; t < WM; ++t)                                                                    \
-        FA[t] = __builtin_bit_cast(bf16x8, stage[((SL) * NBLK + (wr * WM + t) * 2 + (KBO)) * 64 + lane]);             \
-    _Pragma("unroll") for (int t = 0; t < WN; ++t)                                                                    \
-        FB[t] = __builtin_bit_cast(bf16x8, stage[((SL) * NBLK + NA + (wc * WN + t) * 2 + (KBO)) * 64 + lane]);        \
-  }
-#define VVS_MMA(FA, FB)                                                                                               \
-  {                                                                                                                   \
-    _Pragma("unroll") for (int ti = 0; ti < WM; ++ti)                                                                 \
-        _Pragma("unroll") for (int tj = 0; tj < WN; ++tj)                                                             \
-            acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(FA[ti], FB[tj], acc[ti][tj], 0, 0, 0);              \
-  }
-#pragma unroll
-  for (int d = 0; d < D; ++d) VVS_G2R(d, d)
-  // epilogue inputs: requested behind the first operand loads (nothing waits for them before the main loop ends)
-  RowScale<BM> rowscale;
-  rowscale.load(tile_m, M, ep);
-  pre.start(tile_m, tile_n, M, N, ep);
-  __builtin_amdgcn_sched_barrier(0);
-  VVS_PHASE_MARK(1);
-  VVS_R2S(0, 0)
-  VVS_G2R(0, D)
-  VVS_R2S(1, 1)
-  VVS_G2R(1, D + 1)
-  __syncthreads();
-  bf16x8 fa0[WM], fb0[WN], fa1[WM], fb1[WN];
-  VVS_S2F(fa0, fb0, 0, 0)
-  // iteration S with d = S % D (so S % 3 == d % 3)
-#define VVS_ITER(S)                                                                                                   \
-  {                                                                                                                   \
-    VVS_S2F(fa1, fb1, d % 3, 1)                                                                                       \
-    __builtin_amdgcn_sched_barrier(0);                                                                                \
-    VVS_R2S((d + 2) % D, (d + 2) % 3)                                                                                 \
-    VVS_G2R((d + 2) % D, (S) + 2 + D)                                                                                 \
-    VVS_MMA(fa0, fb0)                                                                                                 \
-    __builtin_amdgcn_sched_barrier(0);                                                                                \
-    VVS_S2F(fa0, fb0, (d + 1) % 3, 0)                                                                                 \
-    __builtin_amdgcn_sched_barrier(0);                                                                                \
-    VVS_MMA(fa1, fb1)                                                                                                 \
-    __syncthreads();                                                                                                  \
-  }
-  // whole groups of D iterations run without any condition, so that the wait before a stage's LDS
-  // write is "all but the D-1 younger load groups"
-  int s0 = 0;
-  for (; s0 + D <= nst; s0 += D) {
-#pragma unroll
-    for (int d = 0; d < D; ++d) VVS_ITER(s0 + d)
-  }
-#pragma unroll
-  for (int d = 0; d < D; ++d)
-    if (s0 + d < nst) VVS_ITER(s0 + d)                         // uniform over the workgroup
-#undef VVS_ITER
-#undef VVS_MMA
-#undef VVS_S2F
-#undef VVS_R2S
-#undef VVS_G2R
-  VVS_PHASE_MARK(2);
-  pre.to_lds(s_pos, s_rope, ep);
-  rowscale.finish(rs, tile_m, M, ep);
-  __syncthreads();                         // the stage buffers become the output tile
-#pragma unroll
-  for (int i = 0; i < WM; ++i)
-#pragma unroll
-    for (int j = 0; j < WN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        red[((wr * WM + i) * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * LDC + (wc * WN + j) * 32 + (lane & 31)] = acc[i][j][r];
-  __syncthreads();
-  VVS_PHASE_MARK(3);
-  tile_epilogue<BM, BN, 1, EPI>(red, rs, tile_m, tile_n, M, N, C, ep, pre, s_pos, s_rope);
-  VVS_PHASE_MARK(4);
-}
-
-// The same tile with the stages loaded straight from global memory into LDS (global_load_lds_dwordx4: lane l
-// of a wave writes the 16 bytes it asked for to LDS address M0 + 16 l, which is exactly the packed block
-// layout).  In k_gemm_shared every operand byte crosses the vector registers twice - once on its way from
-// memory to LDS, once as a fragment - and the register file's ports, shared with the MFMA operand reads, are
-// what that kernel's main loop is bound by; here the staging hop is gone, and so are its registers, so NS = 8
-// stages can be in flight in LDS.  The compiler knows nothing of these loads (inline asm): the waits are
-// written out by hand.  Iteration s: request stage s + NS - 1 into the slot stage s - 1 has left; multiply
-// (fragments as in k_gemm_shared); wait until this wave's part of stage s + 2 has landed - loads return in
-// order, so "at most PER * (NS - 3) younger loads outstanding" - and meet the other waves at the barrier.
+// Shared-operand variant for projections with enough output tiles: a workgroup owns a (2*WM*32) x (2*WN*32) tile, its 4 waves
+// form a 2 x 2 grid of (WM*32) x (WN*32) sub-tiles and all of them read the A and B fragments from LDS, so every operand byte
+// that comes through the CU's L1 feeds twice as many MFMAs as in k_gemm_direct.  A stage is 32 contraction indices = 2 fragment
+// blocks per 32 rows, loaded straight from global memory into LDS (global_load_lds_dwordx4: lane l of a wave writes the 16
+// bytes it asked for to LDS address M0 + 16 l, which is exactly the packed block layout), NS stages in a ring.  The compiler
+// knows nothing of these loads (inline asm): the waits are written out by hand.  Iteration s: request stage s + NS - 1 into the
+// slot stage s - 1 has left; multiply the first half of stage s on fragments read during the stage before, read and multiply
+// the second half; wait until this wave's part of stage s + 2 has landed - loads return in order, so "at most PER * (NS - 3)
+// younger loads outstanding" - and meet the other waves at the barrier.  The epilogue works on the accumulators.
 // M0 is written here, so it is on the clobber list: the compiler must not keep a value of its own in it across
 // the statement (it names M0 "reserved" and warns about any clobber of it; that warning is silenced for this
 // one statement).
@@ -752,19 +617,182 @@ void launch_fill_probe(const void* src, size_t region_bytes, size_t wg_stride_by
   }
 }
 
+// 8 consecutive columns of a row per lane from transposed accumulators: a holds, packed to bf16, columns 8 q + 4 (l / 32) .. + 3 of
+// an accumulator and b those 8 further on; afterwards lane l holds columns 8 q + 8 (l / 32) .. + 7 of its row l % 32.
+__device__ __forceinline__ uint4 pair_columns(uint2 a, uint2 b) {
+  const uintx2 x = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false), y = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false);
+  return make_uint4(x[0], y[0], x[1], y[1]);
+}
+
+// Epilogue of a wave's (WM * 32) x (WN * 32) sub-tile straight from its accumulators.  The main loop multiplies W * A^T, so a lane
+// holds one activation row (l % 32 of each row-block) and, per accumulator, the columns 8 q + 4 (l / 32) + 0 .. 3 of q = 0 .. 3:
+// gate and up of a hidden unit are the same register of neighbouring accumulators, rotary pairs are neighbouring registers, and
+// one row-swap gives a lane 8 consecutive columns - a 16-byte chunk of the packed operand order (a wave's store is 1 KiB
+// contiguous) or of the cache's K order.  Nothing goes through LDS but the row factors and positions, and no barrier stands
+// between the main loop and the stores.  Against tiles that went through LDS: QKV 62 -> 56 us (3904 x 3840 x 1280), 84 -> 64
+// (388 x 12288 x 4096) and 43 -> 29 (960 x 3840 x 1280; these two against a kernel that also staged its operands through
+// registers), gate / up 79 -> 75 (3904 x 6912 x 1280).  m0 / n0: first row / column of the sub-tile; rs, s_pos: row factor and
+// (slot, image index) of its rows.
+template <int WM, int WN, int EPI>
+__device__ __forceinline__ void register_epilogue(const floatx16 (&acc)[WM][WN], const float* rs, int m0, int n0, int M, int N, float* C,
+                                                  const GemmEpi& ep) {
+  const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
+#pragma unroll
+  for (int i = 0; i < WM; ++i) {
+    const int m = m0 + i * 32 + lo;
+    const bool in = m < M;
+    const float sc = rs[i * 32 + lo];
+    if constexpr (EPI == EPI_PARTIAL) {
+      // not transposed (A * W^T): a lane holds one column, and a store covers two whole 128-byte lines; the transposed order's
+      // 32-byte pieces of 32 rows took 236 us instead of 181 for 3904 x 16384 fp32 results
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 s4 = *(const float4*)(rs + i * 32 + 8 * q + 4 * hi);
+        const float sr[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int mm = m0 + i * 32 + 8 * q + 4 * hi + k;
+          if (mm < M) {
+            float* row = C + (size_t)mm * N + n0 + lo;
+#pragma unroll
+            for (int j = 0; j < WN; ++j) row[j * 32] = acc[i][j][4 * q + k] * sr[k];
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else if constexpr (EPI == EPI_SWIGLU) {
+      static_assert(WN % 2 == 0, "gate / up blocks of 32 columns alternate");
+#pragma unroll
+      for (int j = 0; j < WN; j += 2) {
+        uint2 pk[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float v[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float g = acc[i][j][4 * q + k] * sc, up = acc[i][j + 1][4 * q + k] * sc;
+            // silu(g) * up with the hardware exp2 and reciprocal (1 ulp each)
+            v[k] = g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * up;
+          }
+          pk[q] = make_uint2(pack2bf(v[0], v[1]), pack2bf(v[2], v[3]));
+        }
+#pragma unroll
+        for (int q = 0; q < 4; q += 2) {
+          const uint4 o = pair_columns(pk[q], pk[q + 1]);
+          if (in) *(uint4*)(ep.act + pack_index(m, n0 / 2 + j * 16 + 8 * q + 8 * hi, ep.F)) = o;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else if constexpr (EPI == EPI_RESID) {
+      static_assert(kSlab == 32, "one accumulator is one slab of the sums of squares");
+      const int mc = min(m, M - 1);
+      float* xrow = ep.x + (size_t)mc * N + n0 + 4 * hi;
+      const int xr = ep.xb_T > 0 ? (mc / ep.xb_T) * ep.xb_pad + mc % ep.xb_T : mc;
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        float4 xv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) xv[q] = *(const float4*)(xrow + j * 32 + 8 * q);
+        float sq = 0.f;
+        uint2 pk[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const floatx16& a = acc[i][j];
+          const float4 g = *(const float4*)(ep.g_next + n0 + j * 32 + 8 * q + 4 * hi);
+          const float4 v = make_float4(xv[q].x + a[4 * q], xv[q].y + a[4 * q + 1], xv[q].z + a[4 * q + 2], xv[q].w + a[4 * q + 3]);
+          if (in) *(float4*)(xrow + j * 32 + 8 * q) = v;
+          sq += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+          pk[q] = make_uint2(pack2bf(v.x * g.x, v.y * g.y), pack2bf(v.z * g.z, v.w * g.w));
+        }
+#pragma unroll
+        for (int q = 0; q < 4; q += 2) {
+          const uint4 o = pair_columns(pk[q], pk[q + 1]);
+          if (in) *(uint4*)(ep.xb + pack_index(xr, n0 + j * 32 + 8 * q + 8 * hi, N)) = o;
+        }
+        const uintx2 p = __builtin_amdgcn_permlane32_swap(__float_as_uint(sq), __float_as_uint(sq), false, false);
+        if (in && hi == 0) {
+          float* so = ep.ss_out + (size_t)m * ep.NS + (n0 + j * 32) / kSlab;
+          *so = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+          if (n0 + j * 32 + kSlab == N)                            // the row's padding
+            for (int k = N / kSlab; k < ep.NS; ++k) *++so = 0.f;
+        }
+      }
+    }
+  }
+}
+
+// The same for EPI_QKV.  The rotary factors of an accumulator (4 x 16 bytes of the row's table) are requested while the one
+// before it is worked on; the scheduling barriers keep the compiler from asking for all of them at once, which does not fit the registers.
+template <int WM, int WN>
+__device__ __forceinline__ void register_epilogue_qkv(const floatx16 (&acc)[WM][WN], const float* rs, const int* s_pos, int m0, int n0, int M,
+                                                      const GemmEpi& ep) {
+  const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
+  const int sec = n0 / ep.d, nd = n0 - sec * ep.d;                 // the tile lies inside the q (0), k (1) or v (2) third
+  const int dh_sh = 31 - __clz(ep.dh), dh_mask = ep.dh - 1, half = ep.dh >> 1, np = ep.dh >> 2;
+  float4 cs[2][4];
+  int slot, img;
+  auto factors = [&](int i, int j, float4 (&f)[4]) {
+    const int im = max(s_pos[2 * (i * 32 + lo) + 1], 0);
+    const int gr = min(im / ep.pos.grid_w, ep.rope_pos - 1), gc = im % ep.pos.grid_w;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {          // 4 columns stay inside one head and one half of it
+      const int e = (nd + j * 32 + 8 * q + 4 * hi) & dh_mask;
+      f[q] = *(const float4*)(ep.rope + ((size_t)((e >> (dh_sh - 1)) ? gc : gr) * np + ((e & (half - 1)) >> 1)) * 2);
+    }
+  };
+  if (sec < 2) factors(0, 0, cs[0]);
+#pragma unroll
+  for (int st = 0; st < WM * WN; ++st) {
+    const int i = st / WN, j = st % WN, m = m0 + i * 32 + lo;
+    if (sec < 2 && st + 1 < WM * WN) factors((st + 1) / WN, (st + 1) % WN, cs[(st + 1) & 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    const float sc = rs[i * 32 + lo];
+    slot = s_pos[2 * (i * 32 + lo)];
+    img = s_pos[2 * (i * 32 + lo) + 1];
+    const size_t r = EpiPre<32, 32, EPI_QKV>::div_T(min(m, M - 1), ep);
+    const bool in = m < M, cached = in && slot >= 0 && slot < ep.S_cap;
+    if (sec < 2) {
+      uint2 pk[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 c = cs[st & 1][q];
+        const float v0 = acc[i][j][4 * q] * sc, v1 = acc[i][j][4 * q + 1] * sc, v2 = acc[i][j][4 * q + 2] * sc, v3 = acc[i][j][4 * q + 3] * sc;
+        const bool rot = img >= 0;
+        pk[q] = make_uint2(pack2bf(rot ? v0 * c.x - v1 * c.y : v0, rot ? v0 * c.y + v1 * c.x : v1),
+                           pack2bf(rot ? v2 * c.z - v3 * c.w : v2, rot ? v2 * c.w + v3 * c.z : v3));
+      }
+#pragma unroll
+      for (int q = 0; q < 4; q += 2) {
+        const uint4 o = pair_columns(pk[q], pk[q + 1]);
+        const int eg = nd + j * 32 + 8 * q + 8 * hi;
+        if (sec == 0) {
+          if (in) *(uint4*)(ep.q + (size_t)m * ep.d + eg) = o;
+        } else if (cached) {
+          *(uint4*)(ep.kc + r * ep.row_stride + (size_t)(eg >> dh_sh) * ep.head_stride + k_index(slot, eg & dh_mask, ep.dh)) = o;
+        }
+      }
+    } else if (cached) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int eg = nd + j * 32 + 8 * q + 4 * hi, e = eg & dh_mask;
+        bf16_t* vh = ep.vc + r * ep.row_stride + (size_t)(eg >> dh_sh) * ep.head_stride + v_index(slot, e, ep.dh);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) vh[8 * k] = f2bf(acc[i][j][4 * q + k] * sc);   // the 8 slots of a dim are contiguous, dims 8 apart
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 template <int WM, int WN, int NS, int EPI>
 __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict__ Ap, const uint4* __restrict__ Wp, float* __restrict__ C,
                                                          int M, int N, int K, int n_main, const GemmEpi ep) {
   static_assert(NS >= 4, "at least three stages in flight");
-  constexpr int BM = 2 * WM * 32, BN = 2 * WN * 32, LDC = BN + 4;
-  // The output tile goes through LDS for the epilogue.  A tile too large for that (256 x 256) goes in RP = 2 passes of
-  // BM / 2 rows - the rows of one wave row - so that LDS only ever holds half of it.
-  constexpr int RP = (size_t)BM * LDC * sizeof(float) > 140 * 1024 ? 2 : 1, EM = BM / RP;
+  constexpr int BM = 2 * WM * 32, BN = 2 * WN * 32;
   constexpr int NA = 2 * (BM / 32), NBLK = NA + 2 * (BN / 32), PER = NBLK / 4;
   static_assert(NBLK % 4 == 0, "blocks of a stage are dealt to 4 waves");
   static_assert(PER * (NS - 1) <= 60, "the load counter has 6 bits");
-  extern __shared__ float red[];           // main loop: u32x4 stage[NS][NBLK][64]; afterwards: float [BM][LDC]
-  u32x4* stage = (u32x4*)red;
+  extern __shared__ u32x4 stage[];         // [NS][NBLK][64]
   const uint32_t lds_base = (uint32_t)(uintptr_t)stage;
   if ((int)blockIdx.x >= n_main) { prefetch_weights<4>(ep.pf, blockIdx.x, n_main, gridDim.x); return; }
   VVS_PHASE_MARK(0);
@@ -776,23 +804,17 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
   // where the activation operand is the larger one, row tiles (the transposed order)
   if (!ep.row_owner) tile_of(blockIdx.x, MT, NT, &tile_m, &tile_n);
   else tile_of(blockIdx.x, NT, MT, &tile_n, &tile_m);
-  __shared__ float rs[BM];
+  __shared__ __align__(16) float rs[BM];
   __shared__ int s_pos[EPI == EPI_QKV ? 2 * BM : 2];    // EPI_QKV: (slot, image index) per tile row; the rotary factors are read from
                                                         // their table in memory (an LDS copy per row would keep a second workgroup off the CU)
-  constexpr bool EARLY = EPI != EPI_RESID;   // the residual tile is read in the epilogue: early copies of a tile this size do not fit the registers
-  EpiPre<EM, BN, EPI, EARLY> pre[RP];        // epilogue inputs of each pass (a pass is a tile of EM rows at row tile tile_m * RP + p)
-#pragma unroll
-  for (int p = 0; p < RP; ++p) pre[p].rope_lds = false;
+  // the residual tile is read in the epilogue: early copies of a tile this size do not fit the registers
+  EpiPre<BM, BN, EPI, EPI != EPI_RESID> pre;
+  pre.rope_lds = false;
   const int KB = K >> 4, nst = KB >> 1;
   const int last_rb = (M - 1) >> 5;
   RowScale<BM> rowscale;                   // the epilogue's inputs first: they are the oldest loads and so never wait behind a stage
-#pragma unroll
-  for (int p = 0; p < RP; ++p) pre[p].first(tile_m * RP + p, M, ep);
+  pre.first(tile_m, M, ep);
   rowscale.load(tile_m, M, ep);
-  if (EPI != EPI_QKV) {
-#pragma unroll
-    for (int p = 0; p < RP; ++p) pre[p].start(tile_m * RP + p, tile_n, M, N, ep);
-  }
   __builtin_amdgcn_sched_barrier(0);
   const u32x4* src[PER];
 #pragma unroll
@@ -820,10 +842,7 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
   // EPI_QKV: the row's position depends on a loaded value (its cache length); it is turned into (slot, image index) only
   // now, behind the first stage requests, so that this wait is not on the path to them.  (Loads the compiler issues are
   // counted by the same counter as the stage loads: its waits and the hand-written ones below can only become stricter.)
-  if (EPI == EPI_QKV) {
-#pragma unroll
-    for (int p = 0; p < RP; ++p) pre[p].start(tile_m * RP + p, tile_n, M, N, ep);
-  }
+  if (EPI == EPI_QKV) pre.start(tile_m, tile_n, M, N, ep);
   __builtin_amdgcn_sched_barrier(0);
   VVS_PHASE_MARK(1);
 #define VVS_WAIT_STAGES asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 3)) : "memory")
@@ -836,12 +855,6 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
         FA[t] = __builtin_bit_cast(bf16x8, stage[(sl + (wr * WM + t) * 2 + (KBO)) * 64 + lane]);                      \
     _Pragma("unroll") for (int t = 0; t < WN; ++t)                                                                    \
         FB[t] = __builtin_bit_cast(bf16x8, stage[(sl + NA + (wc * WN + t) * 2 + (KBO)) * 64 + lane]);                 \
-  }
-#define VVS_MMA(FA, FB)                                                                                               \
-  {                                                                                                                   \
-    _Pragma("unroll") for (int ti = 0; ti < WM; ++ti)                                                                 \
-        _Pragma("unroll") for (int tj = 0; tj < WN; ++tj)                                                             \
-            acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(FA[ti], FB[tj], acc[ti][tj], 0, 0, 0);              \
   }
   bf16x8 fa0[WM], fb0[WN], fa1[WM], fb1[WN];
   VVS_S2F(fa0, fb0, 0, 0)
@@ -862,12 +875,16 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
     const int sl = (t % NS) * NBLK;
     return __builtin_bit_cast(bf16x8, stage[(sl + (i < WM ? (wr * WM + i) * 2 : NA + (wc * WN + (i - WM)) * 2) + kbo) * 64 + lane]);
   };
+  // W * A^T (see register_epilogue); EPI_PARTIAL: A * W^T
+  auto mul = [](bf16x8 a, bf16x8 b, floatx16 c) {
+    return EPI == EPI_PARTIAL ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c, 0, 0, 0);
+  };
   for (int s = 0; s < nst; ++s) {
     const size_t kk = (size_t)min(s + NS - 1, nst - 1) * 128;
     const uint32_t slot = lds_base + (uint32_t)(((s + NS - 1) % NS) * NBLK) * 1024u;
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
-      acc[m / WN][m % WN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa0[m / WN], fb0[m % WN], acc[m / WN][m % WN], 0, 0, 0);
+      acc[m / WN][m % WN] = mul(fa0[m / WN], fb0[m % WN], acc[m / WN][m % WN]);
 #pragma unroll
       for (int it = m * IA; it < (m + 1) * IA; ++it) {
         if (it < NR) {
@@ -881,7 +898,7 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
     }
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
-      acc[m / WN][m % WN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa1[m / WN], fb1[m % WN], acc[m / WN][m % WN], 0, 0, 0);
+      acc[m / WN][m % WN] = mul(fa1[m / WN], fb1[m % WN], acc[m / WN][m % WN]);
 #pragma unroll
       for (int it = m * IB; it < (m + 1) * IB; ++it) {
         if (it < NR) {
@@ -896,31 +913,17 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-#undef VVS_MMA
 #undef VVS_S2F
   VVS_PHASE_MARK(2);
-#pragma unroll
-  for (int p = 0; p < RP; ++p) pre[p].to_lds(s_pos + p * 2 * EM, nullptr, ep);
+  pre.to_lds(s_pos, nullptr, ep);
   rowscale.finish(rs, tile_m, M, ep);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the repeated last stages still in flight must land before the tile reuses their LDS
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no request may be under way when the workgroup gives its LDS back
 #undef VVS_WAIT_STAGES
-  __syncthreads();                         // the stage buffers become the output tile
-#pragma unroll
-  for (int p = 0; p < RP; ++p) {
-    if (RP == 1 || wr == p) {              // RP == 2: pass p holds the rows of wave row p
-#pragma unroll
-      for (int i = 0; i < WM; ++i)
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            red[(((RP == 1 ? wr * WM : 0) + i) * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * LDC + (wc * WN + j) * 32 + (lane & 31)] = acc[i][j][r];
-    }
-    __syncthreads();
-    VVS_PHASE_MARK(3);
-    tile_epilogue<EM, BN, 1, EPI, EARLY>(red, rs + p * EM, tile_m * RP + p, tile_n, M, N, C, ep, pre[p], s_pos + p * 2 * EM, nullptr);
-    if (p + 1 < RP) __syncthreads();       // the next pass overwrites the tile
-  }
+  __syncthreads();                         // row factors and positions
+  VVS_PHASE_MARK(3);
+  const int m0 = tile_m * BM + wr * WM * 32, n0 = tile_n * BN + wc * WN * 32;
+  if constexpr (EPI == EPI_QKV) register_epilogue_qkv<WM, WN>(acc, rs + wr * WM * 32, s_pos + 2 * wr * WM * 32, m0, n0, M, ep);
+  else register_epilogue<WM, WN, EPI>(acc, rs + wr * WM * 32, m0, n0, M, N, C, ep);
   VVS_PHASE_MARK(4);
 }
 
@@ -933,23 +936,11 @@ static int prefetchers(const WeightPrefetch& pf, int tiles, int per_cu = 1) {
 template <int WM, int WN, int NS, int EPI>
 static void launch_gemm_shared_dma(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, const GemmEpi& ep, hipStream_t s) {
   constexpr int BM = 2 * WM * 32, BN = 2 * WN * 32;
-  constexpr size_t lds_full = (size_t)BM * (BN + 4) * sizeof(float), lds_tile = lds_full > 140 * 1024 ? lds_full / 2 : lds_full;   // two passes
-  constexpr size_t lds_stage = (size_t)NS * (2 * (BM + BN) / 32) * 1024;
-  constexpr size_t lds = lds_tile > lds_stage ? lds_tile : lds_stage;
+  constexpr size_t lds = (size_t)NS * (2 * (BM + BN) / 32) * 1024;
   allow_dynamic_lds(reinterpret_cast<const void*>(&k_gemm_shared_dma<WM, WN, NS, EPI>), lds);
   const int tiles = (N / BN) * ((M + BM - 1) / BM);
   hipLaunchKernelGGL((k_gemm_shared_dma<WM, WN, NS, EPI>), dim3(tiles + prefetchers(ep.pf, tiles)), dim3(256), lds, s, (const uint4*)A, (const uint4*)W,
                      C, M, N, K, tiles, ep);
-}
-
-template <int WM, int WN, int D, int EPI>
-static void launch_gemm_shared(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, const GemmEpi& ep, hipStream_t s) {
-  constexpr int BM = 2 * WM * 32, BN = 2 * WN * 32;
-  constexpr size_t lds_tile = (size_t)BM * (BN + 4) * sizeof(float), lds_stage = (size_t)3 * (2 * (BM + BN) / 32) * 1024;
-  constexpr size_t lds = lds_tile > lds_stage ? lds_tile : lds_stage;
-  allow_dynamic_lds(reinterpret_cast<const void*>(&k_gemm_shared<WM, WN, D, EPI>), lds);
-  dim3 grid((N / BN) * ((M + BM - 1) / BM), 1, 1);
-  hipLaunchKernelGGL((k_gemm_shared<WM, WN, D, EPI>), grid, dim3(256), lds, s, (const uint4*)A, (const uint4*)W, C, M, N, K, ep);
 }
 
 template <int TM, int TN, int D, int EPI, int NW = 4>
@@ -976,22 +967,12 @@ static void gemm_dispatch(const bf16_t* A, const bf16_t* W, float* C, int M, int
       return;
     }
   }
-  if constexpr (EPI == EPI_QKV) {
-    // many rows (two or more full rounds of 128 x 128 tiles): the direct-to-LDS kernel, two workgroups per CU
-    const int tiles = ((M + 127) / 128) * (N / 128);
-    if (p.bm == 128 && p.bn == 128 && tiles >= 512) { launch_gemm_shared_dma<2, 2, 4, EPI>(A, W, C, M, N, K, ep, s); return; }
-  }
-  if constexpr (EPI == EPI_PARTIAL || EPI == EPI_SWIGLU) {
-    // the stages are loaded straight into LDS.  A single round of tiles (at most one workgroup per CU): 8 slots, 6
-    // stages in flight.  Two or more full rounds: 4 slots, so that the LDS (the 68 KB of the output tile) lets two
-    // workgroups share a CU and cover each other's barrier waits.  In between (257 .. 511 tiles) the variant that
-    // stages through registers is the faster one (384 tiles: 28 against 32 us).
+  if constexpr (EPI != EPI_RESID) {
+    // A single round of tiles (at most one workgroup per CU): 8 slots, 6 stages in flight.  More: 4 slots, so that the LDS
+    // lets two workgroups share a CU and cover each other's barrier waits.
     const int tiles = ((M + 127) / 128) * (N / 128);
     if (p.bm == 128 && p.bn == 128 && tiles <= 256) { launch_gemm_shared_dma<2, 2, 8, EPI>(A, W, C, M, N, K, ep, s); return; }
-    if (p.bm == 128 && p.bn == 128 && tiles >= 512) { launch_gemm_shared_dma<2, 2, 4, EPI>(A, W, C, M, N, K, ep, s); return; }
-  }
-  if constexpr (EPI != EPI_RESID) {
-    if (p.bm == 128 && p.bn == 128) { launch_gemm_shared<2, 2, 6, EPI>(A, W, C, M, N, K, ep, s); return; }
+    if (p.bm == 128 && p.bn == 128) { launch_gemm_shared_dma<2, 2, 4, EPI>(A, W, C, M, N, K, ep, s); return; }
   }
   if (p.bm == 32 && p.bn == 128) launch_gemm_direct<1, 4, 4, EPI>(A, W, C, M, N, K, p.splits, ep, s);
   else if (p.bm == 32) launch_gemm_direct<1, 2, 8, EPI>(A, W, C, M, N, K, p.splits, ep, s);
@@ -1333,7 +1314,7 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
   float* s_o = red;                                            // [2 rows][4 waves][NQ][DH + 1]
   float* s_m = s_o + 2 * 4 * NQ * (DH + 1);                    // [2 rows][4 waves][NQ]
   float* s_l = s_m + 2 * 4 * NQ;
-  __shared__ float rs[BM];
+  __shared__ __align__(16) float rs[BM];
   const uint32_t lds_base = (uint32_t)(uintptr_t)stage;
   if ((int)blockIdx.x >= H * B) { prefetch_weights<8>(ep.pf, blockIdx.x, H * B, gridDim.x); return; }
   VVS_PHASE_MARK(0);
