@@ -107,9 +107,13 @@ __device__ int inverse_cdf(const float* __restrict__ P, int n, float u, float* r
 
 // LDS_PQ: the running target and draft distributions of the node live in (dynamic) LDS, 2 * veff
 // floats; otherwise in the global scratch rows.
-template <bool LDS_PQ>
+// A workgroup per CU and no second round: what counts is the chain of memory round trips inside a workgroup.  Both logit rows,
+// the draft row of a node whose children are tested, and those children's ids and uniforms are all requested before the first
+// is used.  WIDE (a slice of a multiple of 4 ids, rows on 16 bytes): a thread owns groups of 4 consecutive ids and moves 16 bytes
+// at a time.  8 prompts x 27 nodes x 16384 ids: 26.6 us with 4-byte loads and the draft row asked for behind the softmax, 25.2 us so.
+template <bool LDS_PQ, bool WIDE>
 __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tree) {
-  extern __shared__ float pq_lds[];
+  extern __shared__ __align__(16) float pq_lds[];
   __shared__ float red[32];
   __shared__ int ired[16];
   __shared__ float scan[16];
@@ -136,41 +140,72 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
   // inverse-CDF draw).  Larger slices take the generic loops over P and Q.
   constexpr int RK = 16;
   const bool regs = V <= RK * nt;
+  auto id_of = [&](int k) { return WIDE ? ((k >> 2) * nt + tid) * 4 + (k & 3) : tid + k * nt; };
+  auto load_row = [&](const float* row, float (&v)[RK]) {    // clamped: ids past the slice repeat the last ones
+    if constexpr (WIDE) {
+#pragma unroll
+      for (int k = 0; k < RK; k += 4) {
+        const float4 w = ((const float4*)row)[min((k >> 2) * nt + tid, (V >> 2) - 1)];
+        v[k] = w.x; v[k + 1] = w.y; v[k + 2] = w.z; v[k + 3] = w.w;
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < RK; ++k) v[k] = row[min(tid + k * nt, V - 1)];
+    }
+  };
+  auto store_row = [&](float* row, const float (&v)[RK]) {
+    if constexpr (WIDE) {
+#pragma unroll
+      for (int k = 0; k < RK; k += 4)
+        if (id_of(k) < V) ((float4*)row)[(k >> 2) * nt + tid] = make_float4(v[k], v[k + 1], v[k + 2], v[k + 3]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < RK; ++k)
+        if (id_of(k) < V) row[id_of(k)] = v[k];
+    }
+  };
+  const bool tested = tree.first_child[j] > tree.n_forced;   // this node's children are tested (unless the image ends first)
+  const int ne = a.n_emitted ? a.n_emitted[b] : 0;
+  // the children (ascending node id = the order in which they are tried), their drafted ids and uniforms: one lane each
+  const bool child = tested && tid < VVS_MAX_T && tid > 0 && tid < T && tree.parent[tid] == j;
   float p[RK], q[RK];
 #pragma unroll
   for (int k = 0; k < RK; ++k) p[k] = q[k] = 0.f;
+  float lcv[RK], luv[RK];
   if (regs) {
-    float lcv[RK], luv[RK];
-#pragma unroll
-    for (int k = 0; k < RK; ++k) {
-      const int v = min(tid + k * nt, V - 1);                // clamped: repeats are masked below
-      lcv[k] = lc[v];
-      luv[k] = lu[v];
-    }
+    load_row(lc, lcv);
+    load_row(lu, luv);
+    if (tested) load_row(a.q + (size_t)(b * T + j) * V, q);
+  }
+  int child_x = 0;
+  float child_u = 0.f;
+  if (child) {
+    child_x = min(max(a.draft[b * (T - 1) + tid - 1] - a.lo, 0), V - 1);
+    child_u = a.u[(size_t)b * a.usb + (size_t)tid * a.usj + a.uoa];
+  }
+  if (regs) {
     float mx = -INFINITY;
 #pragma unroll
     for (int k = 0; k < RK; ++k) {
-      p[k] = tid + k * nt < V ? luv[k] + a.scale * (lcv[k] - luv[k]) : -INFINITY;
+      p[k] = id_of(k) < V ? luv[k] + a.scale * (lcv[k] - luv[k]) : -INFINITY;
       mx = fmaxf(mx, p[k]);
     }
     mx = block_max(mx, red);
     float sum = 0.f;
 #pragma unroll
     for (int k = 0; k < RK; ++k) {
-      p[k] = tid + k * nt < V ? expf(p[k] - mx) : 0.f;
+      p[k] = id_of(k) < V ? expf(p[k] - mx) : 0.f;
       sum += p[k];
     }
     sum = block_sum(sum, red);
     const float inv_sum = 1.0f / sum;
 #pragma unroll
     for (int k = 0; k < RK; ++k) {
-      const int v = tid + k * nt;
       p[k] = p[k] * inv_sum;
-      if (v < V) {
-        P[v] = p[k];
-        prow[v] = p[k];
-      }
+      q[k] = id_of(k) < V ? q[k] : 0.f;
     }
+    store_row(P, p);
+    store_row(prow, p);
   } else {
     float mx = -INFINITY;
     for (int v = tid; v < V; v += nt) {
@@ -192,13 +227,22 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
       prow[v] = pv;
     }
   }
+  if (tid < VVS_MAX_T) {                     // the first wave
+    const unsigned long long m = __ballot(child);
+    if (child) {
+      const int rank = __popcll(m & ((1ull << tid) - 1ull));
+      sh_cn[rank] = tid;
+      sh_cx[rank] = child_x;
+      sh_cu[rank] = child_u;
+    }
+    if (tid == 0) sh_nc = __popcll(m);
+  }
   __syncthreads();
 
   VVS_PHASE_MARK(1);
   int32_t* res = a.node_result + ((size_t)b * VVS_MAX_T + j) * 2;
   int cap = INT_MAX;
   if (a.n_emitted) {
-    const int ne = a.n_emitted[b];
     if (ne >= a.G) {                       // image complete: nothing to accept, nothing to draw
       if (tid == 0) { res[0] = 0; res[1] = -1; }
       return;
@@ -212,24 +256,7 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
     accepted = tree.first_child[j];          // post verification: accepted without a test, nothing is read or changed
   } else if (tree.first_child[j] >= 0 && tree.depth[j] < cap) {
     const float* qrow = a.q + (size_t)(b * T + j) * V;
-    const int N = T - 1;
-    // the children (ascending node id = the order in which they are tried), their drafted ids and
-    // uniforms: found by the first wave in parallel, one memory round trip for all of them
-    if (tid < VVS_MAX_T) {
-      const bool child = tid > 0 && tid < T && tree.parent[tid] == j;
-      const unsigned long long m = __ballot(child);
-      if (child) {
-        const int rank = __popcll(m & ((1ull << tid) - 1ull));
-        sh_cn[rank] = tid;
-        sh_cx[rank] = min(max(a.draft[b * N + tid - 1] - a.lo, 0), V - 1);
-        sh_cu[rank] = a.u[(size_t)b * a.usb + (size_t)tid * a.usj + a.uoa];
-      }
-      if (tid == 0) sh_nc = __popcll(m);
-    }
-    if (regs) {
-#pragma unroll
-      for (int k = 0; k < RK; ++k) q[k] = tid + k * nt < V ? qrow[tid + k * nt] : 0.f;
-    } else {
+    if (!regs) {
       for (int v0 = tid; v0 < V; v0 += 8 * nt) {             // 8 independent requests per thread and pass
         float qv[8];
 #pragma unroll
@@ -238,20 +265,18 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
         for (int k = 0; k < 8; ++k)
           if (v0 + k * nt < V) Q[v0 + k * nt] = qv[k];
       }
+      __syncthreads();
     }
-    __syncthreads();
     const int n_children = sh_nc;
     for (int ci = 0; ci < n_children; ++ci) {
       const int c = sh_cn[ci];
       const int x = sh_cx[ci];
       const float ua = sh_cu[ci];
-      const int xo = x % nt, xk = x / nt;                    // owner thread and register of id x
+      const int xo = WIDE ? (x >> 2) % nt : x % nt, xk = WIDE ? (x >> 2) / nt * 4 + (x & 3) : x / nt;   // owner thread and register of id x
       if (a.mode == VVS_RELAXED && a.relax_k > 0) {
         // absorb neighbour mass in ascending distance while the absorbed total stays <= delta
         if (regs && !p_in_memory) {
-#pragma unroll
-          for (int k = 0; k < RK; ++k)
-            if (tid + k * nt < V) P[tid + k * nt] = p[k];
+          store_row(P, p);
           __syncthreads();
           p_in_memory = true;
         }
@@ -285,7 +310,7 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
         if (regs) {
 #pragma unroll
           for (int k = 0; k < RK; ++k)
-            if (tid + k * nt < V) p[k] = P[tid + k * nt];
+            if (id_of(k) < V) p[k] = P[id_of(k)];
         }
       }
       float num, qx;
@@ -353,9 +378,7 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
   }
   if (regs && !p_in_memory) {                                // the draw addresses ids in ascending order: bring P up to date
     __syncthreads();
-#pragma unroll
-    for (int k = 0; k < RK; ++k)
-      if (tid + k * nt < V) P[tid + k * nt] = p[k];
+    store_row(P, p);
   }
   __syncthreads();
   const float ut = a.u[(size_t)b * a.usb + (size_t)j * a.usj + a.uot];
@@ -411,11 +434,14 @@ static void launch_accept_on(Ctx* c, const TreeDesc& tree, int T, const float* d
   a.T = T; a.veff = c->veff; a.lo = c->lo; a.mode = mode; a.relax_k = c->cfg.relax_k; a.G = c->G;
   a.scale = c->cfg.cfg_scale; a.delta = c->cfg.relax_delta;
   const size_t pq_bytes = (size_t)2 * c->veff * sizeof(float);
+  // rows of a multiple of 4 ids that all start on 16 bytes
+  const bool wide = c->veff % 4 == 0 && ((uintptr_t)a.logits | (uintptr_t)a.q | (uintptr_t)a.probs) % 16 == 0;
   if (pq_bytes <= kAcceptLdsMax) {
-    if (pq_bytes > 64 * 1024) allow_dynamic_lds((const void*)k_accept_node<true>, kAcceptLdsMax);
-    hipLaunchKernelGGL(k_accept_node<true>, dim3(T, c->B), dim3(1024), pq_bytes, s, a, tree);
-  } else {
-    hipLaunchKernelGGL(k_accept_node<false>, dim3(T, c->B), dim3(1024), 0, s, a, tree);
+    const auto kernel = wide ? k_accept_node<true, true> : k_accept_node<true, false>;
+    if (pq_bytes > 64 * 1024) allow_dynamic_lds((const void*)kernel, kAcceptLdsMax);
+    hipLaunchKernelGGL(kernel, dim3(T, c->B), dim3(1024), pq_bytes, s, a, tree);
+  } else {                                   // wider slices than the registers hold: the loops over ids
+    hipLaunchKernelGGL((k_accept_node<false, false>), dim3(T, c->B), dim3(1024), 0, s, a, tree);
   }
   hipLaunchKernelGGL(k_walk, dim3(c->B), dim3(64), 0, s, (const int32_t*)a.node_result, c->B, d_accept_len, d_path, d_next, keep);
 }

@@ -126,6 +126,36 @@ def test_largest_tree_fp32(gc, kind):
     pair.close()
 
 
+@pytest.mark.parametrize("vocab,mode", [(4, 0), (1021, 0), (1021, 1), (1028, 0), (4100, 1), (16380, 0), (16384, 1)])
+def test_accept_stage_widths_and_alignment(gc, vocab, mode):
+    """Slices that are and are not a multiple of 4 ids, down to one group and up to all the registers hold, with rows on
+    16 bytes and rows that are not: decisions as the checker's either way."""
+    shape = synth.TINY.replace(n_layers=1, vocab=vocab, logit_hi=vocab, n_prompts=3, n_nodes=7, relax_k=8 if mode else 0, relax_delta=0.2)
+    parent = np.array([0, 0, 0, 1, 1, 2, 4], dtype=np.int32)
+    pair = gc.Pair(shape, with_oracle=False)
+    nbr = None
+    if mode:
+        nbr = synth.make_codebook_neighbours(vocab, shape.relax_k)
+        pair.set_neighbors(nbr)
+    rng = np.random.default_rng(vocab)
+    raw = rng.standard_normal((6, 8, vocab)).astype(np.float32)
+    mixed = raw[1::2] + shape.cfg_scale * (raw[0::2] - raw[1::2])
+    q, toks = synth.make_draft(shape.replace(draft_noise_std=0.5), parent, 5, base_logits=mixed)
+    u = synth.make_uniforms(shape, 7, 3)
+    out, oout, traces = run_accept(gc, pair, shape, parent, raw, toks, q, u, mode, nbr)
+    gc.decisions_match(out, oout, traces, 0)
+
+    def shifted(x):                          # the same values four bytes past a 16-byte boundary
+        t = torch.empty(x.size + 1, dtype=torch.float32, device=pair.dev)[1:].view(x.shape)
+        return t.copy_(torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)))
+
+    pair.ctx.vvs_accept_from_logits(7, parent, None, shifted(raw), torch.from_numpy(toks).to(pair.dev), shifted(q),
+                                    torch.from_numpy(u).to(pair.dev), mode, pair.accept_len, pair.path, pair.next_token)
+    torch.cuda.synchronize()
+    gc.decisions_match((pair.accept_len.cpu().numpy(), pair.path.cpu().numpy(), pair.next_token.cpu().numpy()), oout, traces, 0)
+    pair.close()
+
+
 @pytest.mark.parametrize("heads,head", [(2, 4), (3, 24), (2, 36), (1, 160), (1, 256)])
 def test_attention_head_sizes_fp32(gc, heads, head):
     """The plain attention at head sizes off the cache's blocks of 16 / 32 dims, at one group of threads over all keys
