@@ -1017,6 +1017,13 @@ void mfma_gemm_resid(Ctx* c, const bf16_t* A, const bf16_t* W, float* x, bf16_t*
     launch_gemm_shared_dma<3, 2, 6, EPI_RESID>(A, W, nullptr, M, c->d, K, ep, s);
     return;
   }
+  // more 64 x 64 tiles than CUs: some CUs would pull two tiles' operands while the others wait; 128 x 128 tiles pull the bytes of
+  // one and a third.  960 rows at d 1280, O and down mean: 300 tiles of 64 x 64 32.7 us, 80 of 128 x 128 30.3; 432 rows (140 / 40
+  // tiles): 11.4 / 24.8
+  if (c->d % 128 == 0 && K % 32 == 0 && ((M + 63) / 64) * (c->d / 64) > 256) {
+    launch_gemm_shared_dma<2, 2, 8, EPI_RESID>(A, W, nullptr, M, c->d, K, ep, s);
+    return;
+  }
   if (resid_bn(c, M) == 32) launch_gemm_direct<1, 1, 8, EPI_RESID, 8>(A, W, nullptr, M, c->d, K, 1, ep, s);
   else launch_gemm_direct<2, 2, 6, EPI_RESID>(A, W, nullptr, M, c->d, K, 1, ep, s);
 }
