@@ -95,7 +95,9 @@ enum { VVS_NORM_AUTO = 0, VVS_NORM_SEPARATE = 1 };
 
 /* Sizes in bytes of the three device buffers a context needs.  VVS_ESIZE if the shape is not
  * supported (bf16 needs d_model % 64 == 0, d_ff % 64 == 0, V_eff % 64 == 0, head size 64 or 128;
- * any dtype needs head size % 4 == 0, max_nodes < VVS_MAX_T). */
+ * any dtype needs head size % 4 == 0, max_nodes < VVS_MAX_T).  The workspace holds the activations of the widest call: a
+ * verify or drafting call of max_nodes + 1 tokens per row or, in a target context, a prefill chunk - in bf16 up to 512 tokens per
+ * row (about 4096 rows in all), never more than the prefix and the grid. */
 vvs_status vvs_query_sizes(const vvs_config* cfg, size_t* kv_bytes, size_t* workspace_bytes,
                            size_t* packed_weight_bytes);
 

@@ -105,8 +105,14 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   // Prefill runs in chunks of this many tokens per row.  bf16: as many as give about 4096 GEMM rows (at least 64, at most 512
   // tokens), so that a prefix is one pass over the weights and the projections run in their many-row shapes: beyond 4096
   // rows they gain nothing more and the workspace only grows.  fp32: 64, the width of the plain attention kernel's masks.
+  // Never more than the longest prefill there is (the prefix and all image tokens but one).
   c->chunk = g.dtype == VVS_BF16 ? std::min(512, std::max(64, 4096 / c->R / 32 * 32)) : (dh > 64 ? 32 : 64);
-  c->Mmax = (int)align_up((size_t)c->R * std::max(c->Tmax, c->chunk), 32);   // packed operands come in 32-row blocks
+  c->chunk = std::min(c->chunk, c->P + c->G - 1);
+  // Rows of the activations: the widest verify or drafting call, its tokens padded to the 32 or 64 rows that each row takes in the
+  // operand of the fused projection + attention launch, or a prefill chunk; a drafter context never prefills.  Packed operands come
+  // in blocks of 32 rows.
+  const int call = (int)align_up(c->Tmax, 32);
+  c->Mmax = (int)align_up((size_t)c->R * (g.draft_input ? call : std::max(call, c->chunk)), 32);
   c->Mlog = (int)align_up((size_t)c->R * c->Tmax, 32);
   c->S_cap = (int)align_up((size_t)c->P + c->G + VVS_MAX_T, 32);
   c->rope_pos = std::max(g.grid_h + VVS_MAX_T / g.grid_w + 2, g.grid_w);

@@ -32,13 +32,16 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t) { memset(p, 0, bytes);
 void launch_copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t) { memmove(dst, src, bytes); ++g_launches; }
 void launch_fill_probe(const void*, size_t, size_t, int, int, int, int, uint32_t*, hipStream_t) { ++g_launches; }
 void launch_pack_weights(Ctx*, const void* const*, hipStream_t) { ++g_launches; }
-void launch_forward(Ctx* c, const TreeDesc& tree, const PosDesc&, int T, const int32_t*, const void*, const void*, int, const int32_t*, int,
+void launch_forward(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, const int32_t*, const void*, const void*, int, const int32_t*, int,
                     int, hipStream_t, bool from_din) {
   if (T < 1 || T > c->Tmax && T > c->chunk) abort();            // a forward never exceeds what the workspace was sized for
   if (tree.T != T) abort();
   for (int t = 0; t < T; ++t)
     if (!((tree.anc[t] >> t) & 1ull) || (t && tree.parent[t] >= t)) abort();
   memset(c->ws + c->w.x, 0, sizeof(float) * (size_t)c->R * T * c->d);
+  // a verify or drafting call may lay its normalised operand out with 32 or 64 rows per row; gemm_out is the next buffer
+  const size_t rows = (size_t)c->R * (pos.kv_len && c->esz == 2 ? (T <= 32 ? 32 : 64) : T);
+  if (rows * c->d * c->esz > c->w.gemm_out - c->w.h) abort();
   if (from_din) memset(c->ws + c->w.din, 0, c->esz * (size_t)c->R * T * 2 * c->d);
   ++g_launches;
 }

@@ -51,6 +51,24 @@ def test_query_sizes_for_the_five_workloads(binding):
         assert kv % 256 == 0 and ws % 256 == 0 and pw % 256 == 0 and ws > 0
 
 
+@pytest.mark.parametrize("drafter", [False, True])
+def test_workspace_holds_only_rows_that_a_call_can_use(binding, drafter):
+    """A drafter context never prefills, and a target never prefills more than its prefix and grid: at 8 prompts the chunk that
+    would fill the many-row projections is 256 tokens, here no call has more than 64 per row (an 8 x 8 image behind one class)."""
+    shape = synth.XL_TREE.replace(n_prompts=8, grid_h=8, grid_w=8, prefix_len=1, prefix_kind=synth.PREFIX_CLASS, n_layers=1)
+    if drafter:
+        cfg = binding.make_config(shape, max_nodes=31, feature_slots=0, draft_input=1)
+    else:
+        cfg = binding.make_config(shape, max_nodes=31)
+    _, ws, _ = binding.vvs_query_sizes(cfg)
+    d, f, v, b, t = shape.d_model, shape.d_ff, shape.v_eff, 8, 32
+    rows = 2 * b * (32 if drafter else 64)
+    activations = rows * (4 * d + 3 * 2 * d + 2 * f + 4 * (d // 32 + 3) + (2 * 2 * d if drafter else 0))
+    partial_sums = max(4 * rows * d, 4 * 512 * 64 * 64)      # split projections: fewer than 512 tiles of 64 x 64
+    scores = 4 * v * (2 * b * t + 3 * b * t) + 2 * 2 * b * t * 2 * d
+    assert ws <= activations + partial_sums + scores + (1 << 20), (ws, activations, partial_sums, scores)
+
+
 @pytest.mark.parametrize("field,value,status", [
     ("d_ff", 2000, -3),        # bf16: not a multiple of 64
     ("n_heads", 7, -1),        # does not divide d_model
