@@ -387,9 +387,8 @@ __global__ void k_rope_kv(const float* __restrict__ qkv, int splits, size_t spli
 // first is used), and the P V sum is dealt to 256 / dh groups of dh threads by chunks of 8 keys - contiguous in the cache's V
 // order - whose partial sums are added in a fixed order.  One group over all keys, one element at a time, took 11.9 us at 40
 // keys and head size 32; 5.8 us.
-template <typename T>
-__global__ __launch_bounds__(256) void k_attn_simple(const T* __restrict__ q, const T* __restrict__ kc, const T* __restrict__ vc, T* __restrict__ out,
-                              TreeDesc tree, PosDesc pos, int T_, int d, int dh, size_t row_stride, size_t head_stride, int S_cap) {
+__global__ __launch_bounds__(256) void k_attn_simple(const float* __restrict__ q, const float* __restrict__ kc, const float* __restrict__ vc,
+                              float* __restrict__ out, TreeDesc tree, PosDesc pos, int T_, int d, int dh, size_t row_stride, size_t head_stride, int S_cap) {
   extern __shared__ float sc[];          // [S_cap] scores, then 16 floats for reductions
   __shared__ float part[256];            // [group][dim]
   float* red = sc + S_cap;
@@ -397,9 +396,9 @@ __global__ __launch_bounds__(256) void k_attn_simple(const T* __restrict__ q, co
   const int S = pos.kv_len ? pos.kv_len[r >> 1] : pos.kv_base;
   const int n = min(S + T_, S_cap);
   const uint64_t mask = tree.anc[t];
-  const T* qv = q + (size_t)m * d + (size_t)hd * dh;
-  const T* kb = kc + (size_t)r * row_stride + (size_t)hd * head_stride;
-  const T* vb = vc + (size_t)r * row_stride + (size_t)hd * head_stride;
+  const float* qv = q + (size_t)m * d + (size_t)hd * dh;
+  const float* kb = kc + (size_t)r * row_stride + (size_t)hd * head_stride;
+  const float* vb = vc + (size_t)r * row_stride + (size_t)hd * head_stride;
   const float scale = 1.0f / sqrtf((float)dh);
   float mx = -INFINITY;
   for (int k = threadIdx.x; k < n; k += 256) {
@@ -439,7 +438,7 @@ __global__ __launch_bounds__(256) void k_attn_simple(const T* __restrict__ q, co
   __syncthreads();
   if (g == 0) {
     for (int j = 1; j < ng; ++j) o += part[j * dh + e];
-    st(out + (size_t)m * d + (size_t)hd * dh + e, o / sum);
+    out[(size_t)m * d + (size_t)hd * dh + e] = o / sum;
   }
 }
 
@@ -688,13 +687,13 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
       hipLaunchKernelGGL(k_rope_kv<T>, dim3(M, ((d >> 1) + 255) / 256), dim3(256), 0, s, go, sp, (size_t)M * 3 * d, q, kc, vc, rope, tree, pos, Tq, d, c->dh,
                          c->kv_row_stride, c->kv_head_stride, c->S_cap, c->rope_pos);
     }
-    if (c->cfg.dtype == VVS_BF16) {
+    if constexpr (sizeof(T) == 2) {
       Timed timed(c, VVS_K_ATTENTION, s);
       mfma_attention(c, l, tree, pos, Tq, s);
     } else {
       Timed timed(c, VVS_K_ATTENTION, s);
       size_t lds = sizeof(float) * (c->S_cap + 16);
-      hipLaunchKernelGGL(k_attn_simple<T>, dim3(Tq, c->H, c->R), dim3(256), lds, s, q, kc, vc, attn, tree, pos, Tq, d, c->dh,
+      hipLaunchKernelGGL(k_attn_simple, dim3(Tq, c->H, c->R), dim3(256), lds, s, q, kc, vc, attn, tree, pos, Tq, d, c->dh,
                          c->kv_row_stride, c->kv_head_stride, c->S_cap);
     }
     sp = run_gemm(c, attn, lw + c->p.wo, go, M, d, d, true, s);

@@ -38,6 +38,13 @@ def test_library_exports_every_declared_symbol(binding):
     assert set(binding.EXPORTS) == set(names)
 
 
+def test_plain_attention_is_built_for_fp32_only(binding):
+    """The one-query attention kernel reads 16-byte pieces of four floats; bf16 contexts have a kernel of their own."""
+    code = open(LIB, "rb").read()
+    assert b"13k_attn_simple" in code                            # the mangled kernel name ...
+    assert b"13k_attn_simpleI" not in code                       # ... and no instantiation for another element type
+
+
 def test_query_sizes_for_the_five_workloads(binding):
     for shape in synth.SHAPES.values():
         cfg = binding.make_config(shape)
