@@ -180,7 +180,6 @@ void mfma_gemm(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, 
 void mfma_gemm_scaled(Ctx* c, const bf16_t* A, const bf16_t* W, float* C, const float* ss, int M, int N, int K, GemmPlan p, hipStream_t s);
 void mfma_gemm_resid(Ctx* c, const bf16_t* A, const bf16_t* W, float* x, bf16_t* xb, float* ss_out, const float* g_next, int M, int K,
                      hipStream_t s, const WeightPrefetch& pf, int xb_T = 0, int xb_pad = 0 /* xb_T > 0: xb row-padded to xb_pad rows per xb_T tokens */);
-int resid_bn(const Ctx* c, int M);
 int mfma_qkv_attention_rows(const Ctx* c, const PosDesc& pos, int T);
 void mfma_qkv_attention(Ctx* c, int layer, const bf16_t* A, const bf16_t* Wqkv, const float* ss, const TreeDesc& tree, const PosDesc& pos,
                         int T, hipStream_t s, const WeightPrefetch& pf);

@@ -20,7 +20,9 @@ static vvs_status fail(std::string* err, vvs_status st, const std::string& msg) 
   return st;
 }
 
-GemmPlan plan_gemm(const Ctx* c, int M, int N, int K) {
+// Every launch of a projection and every prefetch of its weights takes its tiles from here (or from plan_resid), so that the two
+// cannot disagree about which XCD reads which weight tile.
+GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section) {
   GemmPlan p{64, 64, 1};
   if (c->cfg.dtype != VVS_BF16) return p;           // fp32 path: one wave per output column, no split
   // bf16: 64 x 64 output tiles (32 x 64 for up to 32 rows); every workgroup already splits its K range
@@ -29,7 +31,13 @@ GemmPlan plan_gemm(const Ctx* c, int M, int N, int K) {
   p.bm = M <= 32 ? 32 : 64;
   // 128 x 128 tiles with the operands shared through LDS when that still gives most CUs a workgroup:
   // half the operand bytes per MFMA come through a CU's L1
-  if (M > 192 && N % 128 == 0 && K % 32 == 0 && ((M + 127) / 128) * (N / 128) >= 160) { p.bm = p.bn = 128; return p; }
+  if (M > 192 && N % 128 == 0 && K % 32 == 0 && ((M + 127) / 128) * (N / 128) >= 160) {
+    // very many rows: 256 x 256 tiles (128 x 128 per wave, the accumulators fill the 256 AGPRs; half the operand bytes per flop of
+    // a 128 x 128 tile come through a CU's L1), when they give (nearly) every CU a tile
+    const int t256 = ((M + 255) / 256) * (N / 256);
+    p.bm = p.bn = N % 256 == 0 && t256 >= 224 && section % 256 == 0 ? 256 : 128;
+    return p;
+  }
   // 64 x 128 tiles when they give one workgroup for (nearly) every CU and no second round: a CU then
   // pulls (64 + 128) K-rows through its L1 instead of 2 x (64 + 64)
   if (p.bm == 64 && N % 128 == 0) {
@@ -49,6 +57,24 @@ GemmPlan plan_gemm(const Ctx* c, int M, int N, int K) {
   }
   p.splits = splits;
   return p;
+}
+
+// The projections that end in the residual epilogue (fused layer: O, down, a drafter's input map); d columns.
+GemmPlan plan_resid(const Ctx* c, int M) {
+  const int d = c->d;
+  // many rows: 192 x 128 tiles with the operands shared through LDS (a quarter of the bytes per flop that 64 x 64 tiles pull
+  // through a CU's L1), when they give most CUs a tile - at d = 1280 and 3904 rows: 210 tiles, one round.
+  // Tile order by fabric traffic: the operand an XCD does not own is fetched by all 8 of them (M + 8 d rows against 8 M + d)
+  if (d % 128 == 0 && ((M + 191) / 192) * (d / 128) >= 160) return GemmPlan{192, 128, 1, M > d};
+  // more 64 x 64 tiles than CUs: 1920 rows at d 1280, O and down mean: 600 tiles of 64 x 64 32.7 us, 150 of 128 x 128 30.3; 432 rows
+  // (140 / 40 tiles): 11.4 / 24.8
+  if (d % 128 == 0 && ((M + 63) / 64) * (d / 64) > 256) return GemmPlan{128, 128, 1};
+  // 32 x 32 tiles on 8 waves while that gives at most 448 workgroups - a launch of few tiles lasts as long as one CU takes to
+  // pull its operands in, so smaller tiles on more CUs win until two workgroups share most CUs - else 64 x 64 on 4.  us per launch,
+  // O and down mean, 64 x 64 on 4 waves / 32 x 32 on 8: d 768, 48 rows 7.3 / 4.9; d 1280, 54 rows 10.4 / 7.2, 300 rows (400 tiles)
+  // 10.8 / 10.1, 432 rows (560 tiles) 11.5 / 14.3.  (32 x 64 and 64 x 32 on 8 waves lie between.)
+  const int bm = ((M + 31) / 32) * (d / 32) <= 448 ? 32 : 64;
+  return GemmPlan{bm, bm, 1};
 }
 
 // The fused layer (5 kernels, no separate normalisation) is taken when a layer's weights are so small (below

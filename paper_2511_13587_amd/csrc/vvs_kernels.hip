@@ -571,18 +571,18 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
   const int pad = mfma_qkv_attention_rows(c, pos, Tq);
   const bool qa = pad > 0;
   const int pad_T = qa ? Tq : 0;
-  const GemmPlan pq = plan_gemm(c, M, 3 * d, d), pg = plan_gemm(c, M, 2 * F, d), pl = plan_gemm(c, M, c->veff, d);
-  // what each launch's idle CUs read ahead for the next one
-  auto weights = [&](const void* w, int N, int K, int bm, int bn) {
+  const GemmPlan pq = plan_gemm(c, M, 3 * d, d, d), pr = plan_resid(c, M), pg = plan_gemm(c, M, 2 * F, d), pl = plan_gemm(c, M, c->veff, d);
+  // what each launch's idle CUs read ahead for the next one (nothing where no XCD owns a weight tile)
+  auto weights = [&](const void* w, int N, int K, const GemmPlan& p) {
+    if (p.row_owner) return WeightPrefetch{};
     // at most 2.5 MB for each XCD: beside the activations more would only push itself out of its 4 MB L2
-    const int blocks = (bn / 32) * (K / 16), most = 8 * std::max(1, 2560 / blocks);
-    return WeightPrefetch{(const uint4*)w, std::min(N / bn, most), blocks, 1, 0, (M + bm - 1) / bm};
+    const int blocks = (p.bn / 32) * (K / 16), most = 8 * std::max(1, 2560 / blocks);
+    return WeightPrefetch{(const uint4*)w, std::min(N / p.bn, most), blocks, 1, 0, (M + p.bm - 1) / p.bm};
   };
-  const int rbn = resid_bn(c, M);
   auto layer = [&](int l) { return c->pw + c->p.layer0 + c->p.layer_stride * l; };
   auto pf_qkv = [&](int l) {
     if (qa) return WeightPrefetch{(const uint4*)(layer(l) + c->p.wqkv), c->H, 2 * (d / 16), 3, (d / 32) * (d / 16), c->B};
-    return weights(layer(l) + c->p.wqkv, 3 * d, d, pq.bm, pq.bn);
+    return weights(layer(l) + c->p.wqkv, 3 * d, d, pq);
   };
   if (from_din) {             // drafter: x = [embedding ; feature] W_fc, through the residual epilogue on a zeroed x
     launch_fill_zero(x, sizeof(float) * (size_t)M * d, s);
@@ -597,7 +597,7 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
     const char* lw = c->pw + c->p.layer0 + c->p.layer_stride * l;
     if (qa) {
       Timed timed(c, VVS_K_GEMM, s);
-      mfma_qkv_attention(c, l, xb, (const bf16_t*)(lw + c->p.wqkv), ss, tree, pos, Tq, s, weights(lw + c->p.wo, d, d, rbn, rbn));
+      mfma_qkv_attention(c, l, xb, (const bf16_t*)(lw + c->p.wqkv), ss, tree, pos, Tq, s, weights(lw + c->p.wo, d, d, pr));
     } else {
       { Timed timed(c, VVS_K_GEMM, s);
         mfma_gemm_qkv(c, l, xb, (const bf16_t*)(lw + c->p.wqkv), ss, tree, pos, Tq, pq, s);
@@ -608,15 +608,15 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
     }
     { Timed timed(c, VVS_K_GEMM, s);
       mfma_gemm_resid(c, attn, (const bf16_t*)(lw + c->p.wo), x, xb, ss, (const float*)(lw + c->p.g2), M, d, s,
-                      weights(lw + c->p.wgu, 2 * F, d, pg.bm, pg.bn));
+                      weights(lw + c->p.wgu, 2 * F, d, pg));
     }
     { Timed timed(c, VVS_K_GEMM, s);
-      mfma_gemm_swiglu(c, xb, (const bf16_t*)(lw + c->p.wgu), act, ss, M, F, d, pg, s, weights(lw + c->p.wd, d, F, rbn, rbn));
+      mfma_gemm_swiglu(c, xb, (const bf16_t*)(lw + c->p.wgu), act, ss, M, F, d, pg, s, weights(lw + c->p.wd, d, F, pr));
     }
     { Timed timed(c, VVS_K_GEMM, s);
       // the next reader of x is the next layer's first norm, or the final norm
       const float* g_next = l + 1 < c->L ? (const float*)(lw + c->p.layer_stride + c->p.g1) : gf;
-      const WeightPrefetch next = l + 1 < c->L ? pf_qkv(l + 1) : logits_mode == 1 ? weights(c->pw + c->p.wout, c->veff, d, pl.bm, pl.bn) : WeightPrefetch{};
+      const WeightPrefetch next = l + 1 < c->L ? pf_qkv(l + 1) : logits_mode == 1 ? weights(c->pw + c->p.wout, c->veff, d, pl) : WeightPrefetch{};
       mfma_gemm_resid(c, act, (const bf16_t*)(lw + c->p.wd), x, xb, ss, g_next, M, F, s, next, l + 1 < c->L ? pad_T : 0, pad);
     }
   }
@@ -674,7 +674,7 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
     launch_add_rmsnorm<T>(M, x, go, splits, sstride, d, (const float*)(lw + c->p.g1), c->cfg.rms_eps, h, 1, 0, s);
     }
     int sp;
-    GemmPlan pq = plan_gemm(c, M, 3 * d, d);
+    GemmPlan pq = plan_gemm(c, M, 3 * d, d, d);
     // with 160+ tiles an unsplit projection streams its weights as fast as a split one, and its epilogue
     // does the rotary embedding and the cache write: one kernel less
     if (pq.splits > 1 && ((M + pq.bm - 1) / pq.bm) * (3 * d / pq.bn) >= 160) pq.splits = 1;

@@ -957,22 +957,13 @@ static void launch_gemm_direct(const bf16_t* A, const bf16_t* W, float* C, int M
 
 template <int EPI>
 static void gemm_dispatch(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, GemmPlan p, const GemmEpi& ep, hipStream_t s) {
-  if constexpr (EPI != EPI_RESID) {
-    // very many rows: 256 x 256 tiles (128 x 128 per wave, the accumulators fill the 256 AGPRs; half the operand bytes per
-    // flop of a 128 x 128 tile come through a CU's L1), when they give (nearly) every CU a tile.  EPI_QKV: a tile must lie
-    // inside one of the q / k / v thirds.
-    const int t256 = ((M + 255) / 256) * (N / 256);
-    if (p.bm == 128 && p.bn == 128 && N % 256 == 0 && t256 >= 224 && (EPI != EPI_QKV || ep.d % 256 == 0)) {
-      launch_gemm_shared_dma<4, 4, 4, EPI>(A, W, C, M, N, K, ep, s);
-      return;
-    }
-  }
-  if constexpr (EPI != EPI_RESID) {
+  if (p.bm == 256) { launch_gemm_shared_dma<4, 4, 4, EPI>(A, W, C, M, N, K, ep, s); return; }
+  if (p.bm == 128) {
     // A single round of tiles (at most one workgroup per CU): 8 slots, 6 stages in flight.  More: 4 slots, so that the LDS
     // lets two workgroups share a CU and cover each other's barrier waits.
-    const int tiles = ((M + 127) / 128) * (N / 128);
-    if (p.bm == 128 && p.bn == 128 && tiles <= 256) { launch_gemm_shared_dma<2, 2, 8, EPI>(A, W, C, M, N, K, ep, s); return; }
-    if (p.bm == 128 && p.bn == 128) { launch_gemm_shared_dma<2, 2, 4, EPI>(A, W, C, M, N, K, ep, s); return; }
+    if (((M + 127) / 128) * (N / 128) <= 256) launch_gemm_shared_dma<2, 2, 8, EPI>(A, W, C, M, N, K, ep, s);
+    else launch_gemm_shared_dma<2, 2, 4, EPI>(A, W, C, M, N, K, ep, s);
+    return;
   }
   if (p.bm == 32 && p.bn == 128) launch_gemm_direct<1, 4, 4, EPI>(A, W, C, M, N, K, p.splits, ep, s);
   else if (p.bm == 32) launch_gemm_direct<1, 2, 8, EPI>(A, W, C, M, N, K, p.splits, ep, s);
@@ -997,34 +988,17 @@ void mfma_gemm_scaled(Ctx* c, const bf16_t* A, const bf16_t* W, float* C, const 
   gemm_dispatch<EPI_PARTIAL>(A, W, C, M, N, K, p, ep, s);
 }
 
-// Tile columns of the O and down projections: 32 (32 x 32 tiles, 8 waves) while that gives at most 448 workgroups - a launch of few
-// tiles lasts as long as one CU takes to pull its operands in, so smaller tiles on more CUs win until two workgroups share most
-// CUs - else 64.  us per launch, O and down mean, 64 x 64 on 4 waves / 32 x 32 on 8: d 768, 48 rows 7.3 / 4.9; d 1280, 54 rows
-// 10.4 / 7.2, 300 rows (400 tiles) 10.8 / 10.1, 432 rows (560 tiles) 11.5 / 14.3.  (32 x 64 and 64 x 32 on 8 waves lie between.)
-int resid_bn(const Ctx* c, int M) { return ((M + 31) / 32) * (c->d / 32) <= 448 ? 32 : 64; }
-
 // x += A W; also leaves bf16(x * g_next) packed and the per-slab sums of squares of the new x
 void mfma_gemm_resid(Ctx* c, const bf16_t* A, const bf16_t* W, float* x, bf16_t* xb, float* ss_out, const float* g_next, int M, int K,
                      hipStream_t s, const WeightPrefetch& pf, int xb_T, int xb_pad) {
   GemmEpi ep{};
   ep.pf = pf;
   ep.x = x; ep.xb = xb; ep.ss_out = ss_out; ep.g_next = g_next; ep.NS = n_slabs(c->d); ep.xb_T = xb_T; ep.xb_pad = xb_pad;
-  // many rows: 192 x 128 tiles with the operands shared through LDS (a quarter of the bytes per flop that 64 x 64 tiles pull
-  // through a CU's L1), when they give most CUs a tile - at d = 1280 and 3904 rows: 210 tiles, one round
-  if (c->d % 128 == 0 && K % 32 == 0 && ((M + 191) / 192) * (c->d / 128) >= 160) {
-    // fabric traffic of the two tile orders: the operand an XCD does not own is fetched by all 8 of them
-    ep.row_owner = (size_t)M + 8 * (size_t)c->d < 8 * (size_t)M + (size_t)c->d;
-    launch_gemm_shared_dma<3, 2, 6, EPI_RESID>(A, W, nullptr, M, c->d, K, ep, s);
-    return;
-  }
-  // more 64 x 64 tiles than CUs: some CUs would pull two tiles' operands while the others wait; 128 x 128 tiles pull the bytes of
-  // one and a third.  960 rows at d 1280, O and down mean: 300 tiles of 64 x 64 32.7 us, 80 of 128 x 128 30.3; 432 rows (140 / 40
-  // tiles): 11.4 / 24.8
-  if (c->d % 128 == 0 && K % 32 == 0 && ((M + 63) / 64) * (c->d / 64) > 256) {
-    launch_gemm_shared_dma<2, 2, 8, EPI_RESID>(A, W, nullptr, M, c->d, K, ep, s);
-    return;
-  }
-  if (resid_bn(c, M) == 32) launch_gemm_direct<1, 1, 8, EPI_RESID, 8>(A, W, nullptr, M, c->d, K, 1, ep, s);
+  const GemmPlan p = plan_resid(c, M);
+  ep.row_owner = p.row_owner;
+  if (p.bm == 192) launch_gemm_shared_dma<3, 2, 6, EPI_RESID>(A, W, nullptr, M, c->d, K, ep, s);
+  else if (p.bm == 128) launch_gemm_shared_dma<2, 2, 8, EPI_RESID>(A, W, nullptr, M, c->d, K, ep, s);
+  else if (p.bm == 32) launch_gemm_direct<1, 1, 8, EPI_RESID, 8>(A, W, nullptr, M, c->d, K, 1, ep, s);
   else launch_gemm_direct<2, 2, 6, EPI_RESID>(A, W, nullptr, M, c->d, K, 1, ep, s);
 }
 
