@@ -66,9 +66,17 @@ GemmPlan plan_resid(const Ctx* c, int M) {
   // through a CU's L1), when they give most CUs a tile - at d = 1280 and 3904 rows: 210 tiles, one round.
   // Tile order by fabric traffic: the operand an XCD does not own is fetched by all 8 of them (M + 8 d rows against 8 M + d)
   if (d % 128 == 0 && ((M + 191) / 192) * (d / 128) >= 160) return GemmPlan{192, 128, 1, M > d};
-  // more 64 x 64 tiles than CUs: 1920 rows at d 1280, O and down mean: 600 tiles of 64 x 64 32.7 us, 150 of 128 x 128 30.3; 432 rows
-  // (140 / 40 tiles): 11.4 / 24.8
-  if (d % 128 == 0 && ((M + 63) / 64) * (d / 64) > 256) return GemmPlan{128, 128, 1};
+  // Two 64 x 64 workgroups fit a CU, so up to 512 of them run at once; beyond that some CUs work through a third tile while the
+  // others wait, and 128 x 128 tiles through LDS, which leave 90 to 130 CUs without a tile, are the better choice.  us per launch, mean of
+  // O and down, 64 x 64 / 128 x 128:
+  //   d 1280, d_ff 3456: 864 rows (280 tiles of 64 x 64) 17.9 / 28.7, 1296 (420) 22.0 / 27.3, 1586 (500) 24.1 / 29.0, 1620 (520) 29.3 / 30.3,
+  //                      1728 (540) 30.7 / 29.1, 1920 (600) 33.2 / 30.8, 2304 (720) 37.7 / 31.8, 2560 (800) 44.7 / 32.0
+  //   d 768, d_ff 2048:  2560 rows (480) 17.9 / 21.3, 2720 (516) 21.0 / 21.5, 2880 (540) 22.5 / 21.8, 3840 (720) 26.7 / 23.5
+  //   d 1024, d_ff 2816: 2048 rows (512) 23.4 / 26.6, 2160 (544) 29.0 / 26.7;  d 1408, d_ff 3840: 1392 (484) 25.0 / 32.4, 1488 (528) 31.8 / 32.0,
+  //   1568 (550) 32.8 / 30.8;  d 1536, d_ff 2048: 1280 (480) 19.6 / 25.2, 1360 (528) 24.1 / 24.9, 1440 (552) 25.0 / 24.2
+  // (A whole pass is faster from 513 tiles on also where the two are level: the launches before have CUs free to read ahead.)
+  // Column tiles per XCD: the transposed order measured within 2 % of it either way, and nothing could be read ahead.
+  if (d % 128 == 0 && ((M + 63) / 64) * (d / 64) > 512) return GemmPlan{128, 128, 1};
   // 32 x 32 tiles on 8 waves while that gives at most 448 workgroups - a launch of few tiles lasts as long as one CU takes to
   // pull its operands in, so smaller tiles on more CUs win until two workgroups share most CUs - else 64 x 64 on 4.  us per launch,
   // O and down mean, 64 x 64 on 4 waves / 32 x 32 on 8: d 768, 48 rows 7.3 / 4.9; d 1280, 54 rows 10.4 / 7.2, 300 rows (400 tiles)

@@ -165,7 +165,7 @@ int main() {
     if (st == VVS_OK && (a == 0 || b == 0 || d == 0)) { printf("empty buffer sizes accepted\n"); return 1; }
   }
   // 2b. tiles: every plan covers its columns exactly and stays inside a section; the residual projections change their tiles where
-  // measurement put the line (rows of d 1280: more than 256 tiles of 64 x 64; at least 160 of 192 x 128)
+  // measurement put the line (rows of d 1280: more than 512 tiles of 64 x 64; at least 160 of 192 x 128)
   {
     vvs_config c = base_config(true, false);
     c.d_model = 1280; c.n_heads = 20; c.d_ff = 3456; c.n_prompts = 32;
@@ -173,7 +173,7 @@ int main() {
     std::string err;
     if (vvs::plan_sizes(&c, &xl, &err) != VVS_OK) { printf("XL plan: %s\n", err.c_str()); return 1; }
     for (int m = 1; m <= 6000; ++m) {
-      const int want = m <= 352 ? 32 : m <= 768 ? 64 : m <= 2880 ? 128 : 192;
+      const int want = m <= 352 ? 32 : m <= 1600 ? 64 : m <= 2880 ? 128 : 192;
       const vvs::GemmPlan r = vvs::plan_resid(&xl, m), q = vvs::plan_gemm(&xl, m, 3 * 1280, 1280, 1280), g = vvs::plan_gemm(&xl, m, 2 * 3456, 1280);
       if (r.bm != want || 1280 % r.bn) { printf("residual projection of %d rows: tiles of %d x %d\n", m, r.bm, r.bn); return 1; }
       if (1280 % q.bn || 6912 % g.bn) { printf("%d rows: a tile of %d or %d columns\n", m, q.bn, g.bn); return 1; }
