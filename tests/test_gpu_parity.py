@@ -256,6 +256,15 @@ def test_projection_and_attention_in_one_launch(gc, n_nodes, widths, n_forced):
     show(f"projection + attention, {n_nodes + 1} tokens per row", run_bf16_case(gc, shape, n_forced=n_forced, calls=2))
 
 
+@pytest.mark.parametrize("prompts", [17, 31, 54])
+def test_projection_and_attention_in_one_launch_many_rows(gc, prompts):
+    """Two layers at 27 tokens per row and so many rows that the O and down projections, whose epilogue leaves the row-padded
+    operand of the next layer's launch, take each of their many-row tiles: 918 rows 64 x 64, 1674 rows 128 x 128, 2916 rows
+    192 x 128 (a last tile of 22, 10 and 36 rows).  The checker computes the first and the last prompt."""
+    shape = synth.XL_TREE.replace(n_layers=2, n_prompts=prompts, prefix_len=20, vocab=1024, logit_lo=0, logit_hi=1024)
+    show(f"{prompts * 54} rows", run_bf16_case(gc, shape, n_forced=20, calls=1, sample=[0, prompts - 1], gain_jitter=0.1))
+
+
 @pytest.mark.parametrize("kv_len", [64, 512, 1000])
 def test_7b_slice_full_width_two_layers(gc, kv_len):
     """Config 4 as specified - full width (d = 4096, 32 heads of 128, d_ff = 11008, 65536 ids with the 8192-id
