@@ -156,11 +156,12 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   c->kv_row_stride = c->kv_head_stride * c->H;
   c->kv_layer_stride = c->kv_row_stride * c->R;
   c->kv_v_off = c->kv_layer_stride * c->L;
-  // GEMM partial-sum buffer: worst case over every M this context can be asked for
+  // GEMM partial-sum buffer: worst case over every M this context can be asked for.  All limits of a plan lie on multiples of 32
+  // rows, so the largest M of each block of 32 stands for the block.
   size_t go = 0;
   int d = c->d, F = c->F;
   const int shapes[5][2] = {{3 * d, d}, {d, d}, {2 * F, d}, {d, F}, {d, 2 * d}};   // the last one: a drafter's input map
-  for (int M = 1; M <= c->Mmax; ++M)
+  for (int M = 32; M <= c->Mmax; M += 32)
     for (auto& sh : shapes) {
       if (sh[1] == 2 * d && !g.draft_input) continue;
       GemmPlan p = plan_gemm(c, M, sh[0], sh[1]);

@@ -178,6 +178,19 @@ int main() {
       if (r.bm != want || 1280 % r.bn) { printf("residual projection of %d rows: tiles of %d x %d\n", m, r.bm, r.bn); return 1; }
       if (1280 % q.bn || 6912 % g.bn) { printf("%d rows: a tile of %d or %d columns\n", m, q.bn, g.bn); return 1; }
     }
+    // the partial-sum buffer holds every number of rows, not only the multiples of 32 it was planned at
+    for (int wide = 0; wide < 2; ++wide) {
+      vvs_config w = c;
+      if (wide) { w.d_model = 4096; w.n_heads = 32; w.d_ff = 11008; w.max_nodes = 31; w.n_prompts = 6; }
+      vvs::Ctx k;
+      if (vvs::plan_sizes(&w, &k, &err) != VVS_OK) { printf("plan: %s\n", err.c_str()); return 1; }
+      const int d = w.d_model, shapes[4][2] = {{3 * d, d}, {d, d}, {2 * w.d_ff, d}, {d, w.d_ff}};
+      for (int m = 1; m <= k.Mmax; ++m)
+        for (auto& sh : shapes) {
+          const vvs::GemmPlan p = vvs::plan_gemm(&k, m, sh[0], sh[1]);
+          if ((p.splits > 1 || sh[0] == d) && (size_t)p.splits * m * sh[0] > k.gemm_out_elems) { printf("%d rows: partial sums do not fit\n", m); return 1; }
+        }
+    }
     vvs::Ctx odd = xl;                                       // a third of 640 columns: 256-column tiles would cross it
     odd.d = 640;
     for (int m = 1; m <= 20000; m += 97)
