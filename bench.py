@@ -405,12 +405,12 @@ def main():
         n_launch = classes["gemm"]["launches_per_step"]
         t_launch = classes["gemm"]["ms_per_step"] * 1e-3 / n_launch
         bytes_launch, flops_launch = cnt["w_bytes"] / n_launch, cnt["gemm_flops"] / n_launch
-        kernel = "k_gemm_direct + k_gemm_shared (all bf16 projection GEMMs of one verify call)"
+        kernel = "k_gemm_direct + k_gemm_shared_dma (all bf16 projection GEMMs of one verify call)"
         if classes["attention"]["launches_per_step"] == 0:
             # the q/k/v projection and attention run in one launch (k_qkv_attn): its cache traffic and flops belong to these launches
             bytes_launch += (cnt["kv_read"] + cnt["kv_write"]) / n_launch
             flops_launch += cnt["attn_flops"] / n_launch
-            kernel = "k_qkv_attn + k_gemm_direct + k_gemm_shared (all projection launches of one verify call; attention runs inside the first)"
+            kernel = "k_qkv_attn + k_gemm_direct + k_gemm_shared_dma (all projection launches of one verify call; attention runs inside the first)"
     else:
         n_launch = classes["attention"]["launches_per_step"]
         t_launch = classes["attention"]["ms_per_step"] * 1e-3 / n_launch
