@@ -630,7 +630,7 @@ __device__ __forceinline__ uint4 pair_columns(uint2 a, uint2 b) {
 // one row-swap gives a lane 8 consecutive columns - a 16-byte chunk of the packed operand order (a wave's store is 1 KiB
 // contiguous) or of the cache's K order.  Nothing goes through LDS but the row factors and positions, and no barrier stands
 // between the main loop and the stores.  Against tiles that went through LDS: QKV 62 -> 56 us (3904 x 3840 x 1280), 84 -> 64
-// (388 x 12288 x 4096) and 43 -> 29 (960 x 3840 x 1280; these two against a kernel that also staged its operands through
+// (388 x 12288 x 4096) and 43 -> 29 (1920 x 3840 x 1280; these two against a kernel that also staged its operands through
 // registers), gate / up 79 -> 75 (3904 x 6912 x 1280).  m0 / n0: first row / column of the sub-tile; rs, s_pos: row factor and
 // (slot, image index) of its rows.
 template <int WM, int WN, int EPI>
