@@ -75,7 +75,7 @@ GemmPlan plan_resid(const Ctx* c, int M) {
   //   d 1024, d_ff 2816: 2048 rows (512) 23.4 / 26.6, 2160 (544) 29.0 / 26.7;  d 1408, d_ff 3840: 1392 (484) 25.0 / 32.4, 1488 (528) 31.8 / 32.0,
   //   1568 (550) 32.8 / 30.8;  d 1536, d_ff 2048: 1280 (480) 19.6 / 25.2, 1360 (528) 24.1 / 24.9, 1440 (552) 25.0 / 24.2
   // (A whole pass is faster from 513 tiles on also where the two are level: the launches before have CUs free to read ahead.)
-  // Column tiles per XCD: the transposed order measured within 2 % of it either way, and nothing could be read ahead.
+  // Column tiles per XCD: the transposed order took 3 % less (d 768, 3520 rows: 22.9 -> 22.2) to 2 % more (d 1280, 1920 rows: 30.8 -> 31.4).
   if (d % 128 == 0 && ((M + 63) / 64) * (d / 64) > 512) return GemmPlan{128, 128, 1};
   // 32 x 32 tiles on 8 waves while that gives at most 448 workgroups - a launch of few tiles lasts as long as one CU takes to
   // pull its operands in, so smaller tiles on more CUs win until two workgroups share most CUs - else 64 x 64 on 4.  us per launch,
