@@ -111,6 +111,7 @@ __device__ int inverse_cdf(const float* __restrict__ P, int n, float u, float* r
 // the draft row of a node whose children are tested, and those children's ids and uniforms are all requested before the first
 // is used.  WIDE (a slice of a multiple of 4 ids, rows on 16 bytes): a thread owns groups of 4 consecutive ids and moves 16 bytes
 // at a time.  8 prompts x 27 nodes x 16384 ids: 26.6 us with 4-byte loads and the draft row asked for behind the softmax, 25.2 us so.
+// Relaxed (the target goes through LDS once per tested child), 32 x 61 x 16384: 265 us and 243.
 template <bool LDS_PQ, bool WIDE>
 __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tree) {
   extern __shared__ __align__(16) float pq_lds[];

@@ -260,7 +260,7 @@ def test_projection_and_attention_in_one_launch(gc, n_nodes, widths, n_forced):
 def test_projection_and_attention_in_one_launch_many_rows(gc, prompts):
     """Two layers at 27 tokens per row and so many rows that the O and down projections, whose epilogue leaves the row-padded
     operand of the next layer's launch, take each of their many-row tiles: 918 rows 64 x 64, 1674 rows 128 x 128, 2916 rows
-    192 x 128 (a last tile of 22, 10 and 36 rows).  The checker computes the first and the last prompt."""
+    192 x 128 (a last tile of 22, 10 and 36 rows).  The oracle computes the first and the last prompt."""
     shape = synth.XL_TREE.replace(n_layers=2, n_prompts=prompts, prefix_len=20, vocab=1024, logit_lo=0, logit_hi=1024)
     show(f"{prompts * 54} rows", run_bf16_case(gc, shape, n_forced=20, calls=1, sample=[0, prompts - 1], gain_jitter=0.1))
 
@@ -276,6 +276,15 @@ def test_7b_slice_full_width_two_layers(gc, kv_len):
     shape = synth.SEVEN_B.replace(n_layers=2)
     stats = run_bf16_case(gc, shape, n_forced=kv_len - shape.prefix_len, calls=1, sample=[1])
     show(f"7b full width L=2 kv {kv_len}", stats)
+
+
+@pytest.mark.parametrize("n_nodes,widths", [(20, (4, 6, 6, 4)), (40, (6, 8, 8, 8, 6, 4))])
+def test_image_shorter_than_a_prefill_chunk(gc, n_nodes, widths):
+    """A 6 x 6 image behind one class: the activations then hold 36 tokens per row (the longest prefill) or the 32 or 64 rows per
+    row that the padded operand of a call of 21 or 41 tokens takes."""
+    shape = synth.B_SHAPE.replace(n_layers=2, n_prompts=3, grid_h=6, grid_w=6, n_nodes=n_nodes, tree_widths=widths, vocab=1024,
+                                  logit_lo=0, logit_hi=1024)
+    show(f"6 x 6 image, {n_nodes + 1} tokens per row", run_bf16_case(gc, shape, n_forced=8, calls=1, gain_jitter=0.1))
 
 
 def test_many_rows_prefill_chunk_bf16(gc):
