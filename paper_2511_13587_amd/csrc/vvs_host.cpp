@@ -12,6 +12,8 @@
 
 namespace vvs {
 
+constexpr size_t kStreamed = (size_t)24 << 20;   // bytes of a weight matrix from which on it is streamed rather than held near the CUs
+
 static std::string g_last_error;   // for failures that have no context (query / create)
 
 static vvs_status fail(std::string* err, vvs_status st, const std::string& msg) {
@@ -22,22 +24,52 @@ static vvs_status fail(std::string* err, vvs_status st, const std::string& msg) 
 
 // Every launch of a projection and every prefetch of its weights takes its tiles from here (or from plan_resid), so that the two
 // cannot disagree about which XCD reads which weight tile.
-GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section) {
+//
+// Tiles whose operands are shared through LDS (k_gemm_shared_dma).  A CU is filled at about 64 GB/s whatever the tile, so a stage of 32
+// contraction values costs about 1 ns per tile row and column until the matrix cores are the slower side (256 x 256); a launch
+// lasts as many of these as its fullest CU works through, no less than its weights take from HBM (6 TB/s), and what start,
+// epilogue and the partial sums of a K split take beside.  The table is measured (us per stage of a bare product, weights from HBM,
+// at M from 48 to 4096 and the N and K of d 4096, d_ff 11008 and d 1280, d_ff 3456); the tile of least cost is taken.  us per launch with
+// the rule before (64-row tiles up to 192 rows, then 128 x 128 or 256 x 256) / with this one:
+//   126 rows, d 4096: gate/up 57.8 / 49.2 (128 x 128), QKV 36.5 / 37.1 (128 x 64), O and down, mean, 22.4 / 21.2 (128 x 64, K in 4)
+//   388 rows, d 4096: gate/up 112 / 94 (256 x 256), QKV 67 / 68 (256 x 128), O 26 / 23.5 (128 x 128, K in 2), down 66 / 50 (256 x 128, K in 4)
+//   1920 rows, d 1280: gate/up 43.5 / 42.0 (256 x 256)
+static GemmPlan plan_shared(int M, int N, int K, int section, bool may_split, int min_bn) {
+  struct Tile { int bm, bn; double stage, lone; bool pair; };      // pair: two workgroups fit a CU; lone: one of such a pair by itself
+  static const Tile tiles[] = {{64, 64, 0.155, 0.155, true},   {64, 128, 0.215, 0.215, true},   {128, 64, 0.19, 0.19, true},  {128, 128, 0.215, 0.34, true},
+                               {128, 128, 0.25, 0.25, false},  {192, 64, 0.24, 0.24, false},    {192, 128, 0.33, 0.33, false},
+                               {256, 128, 0.415, 0.415, false}, {256, 256, 0.69, 0.69, false}};
+  const int rows = (int)align_up(M, 32), nst = K / 32;             // limits on multiples of 32 rows (plan_sizes)
+  GemmPlan best{0, 0, 1};
+  double least = 1e30;
+  for (const Tile& t : tiles) {
+    if (t.bn < min_bn || N % t.bn || section % t.bn) continue;
+    const int n = (rows + t.bm - 1) / t.bm * (N / t.bn);
+    for (int want = 1; want <= (may_split ? 8 : 1); ++want) {
+      const int per = (nst + want - 1) / want, splits = (nst + per - 1) / per, all = n * splits;
+      if (splits != want || (splits > 1 && per < 16)) continue;
+      // 128 x 128 stands twice: 8 slots, one workgroup per CU, for a single round; 4 slots, two per CU, for more
+      if (t.bm == 128 && t.bn == 128 && t.pair != (all > 256)) continue;
+      const int pairs = all / 512, rest = all % 512;
+      const double rounds = t.pair ? 2 * t.stage * pairs + (rest == 0 ? 0 : rest <= 256 ? t.lone : 2 * t.stage) : t.stage * ((all + 255) / 256);
+      const double cost = std::max(rounds * per, 2e-6 * N * K / 6.0) + 3.0 + 4e-5 * t.bm * t.bn + (may_split ? 8e-6 * rows * N * splits / 5.0 : 0.0);
+      if (cost < least) { least = cost; best = GemmPlan{t.bm, t.bn, splits, false, true}; }
+    }
+  }
+  return best;
+}
+
+GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section, bool may_split, int min_bn) {
   GemmPlan p{64, 64, 1};
   if (c->cfg.dtype != VVS_BF16) return p;           // fp32 path: one wave per output column, no split
   // bf16: 64 x 64 output tiles (32 x 64 for up to 32 rows); every workgroup already splits its K range
   // over its 4 waves.  Add grid-level K splits until there is about one workgroup per CU, keeping at
   // least 8 k-steps of 16 per wave.
   p.bm = M <= 32 ? 32 : 64;
-  // 128 x 128 tiles with the operands shared through LDS when that still gives most CUs a workgroup:
-  // half the operand bytes per MFMA come through a CU's L1
-  if (M > 192 && N % 128 == 0 && K % 32 == 0 && ((M + 127) / 128) * (N / 128) >= 160) {
-    // very many rows: 256 x 256 tiles (128 x 128 per wave, the accumulators fill the 256 AGPRs; half the operand bytes per flop of
-    // a 128 x 128 tile come through a CU's L1), when they give (nearly) every CU a tile
-    const int t256 = ((M + 255) / 256) * (N / 256);
-    p.bm = p.bn = N % 256 == 0 && t256 >= 224 && section % 256 == 0 ? 256 : 128;
-    return p;
-  }
+  // Operands shared through LDS where a launch has many 128 x 128 tiles, or where the weights are large and the rows more than one
+  // row-block: a CU then has whole rows of stages to work through, and each weight byte feeds twice the MFMAs
+  if (M > 32 && N % 128 == 0 && ((M > 192 && ((M + 127) / 128) * (N / 128) >= 160) || (size_t)N * K * 2 >= kStreamed))
+    return plan_shared(M, N, K, section, may_split, min_bn);
   // 64 x 128 tiles when they give one workgroup for (nearly) every CU and no second round: a CU then
   // pulls (64 + 128) K-rows through its L1 instead of 2 x (64 + 64)
   if (p.bm == 64 && N % 128 == 0) {
@@ -58,6 +90,10 @@ GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section) {
   p.splits = splits;
   return p;
 }
+
+GemmPlan plan_qkv(const Ctx* c, int M) { return plan_gemm(c, M, 3 * c->d, c->d, c->d); }
+// a tile of the SwiGLU epilogue holds gate and up of its hidden units in one wave: 128 columns
+GemmPlan plan_gate_up(const Ctx* c, int M) { return plan_gemm(c, M, 2 * c->F, c->d, 0, false, 128); }
 
 // The projections that end in the residual epilogue (fused layer: O, down, a drafter's input map); d columns.
 GemmPlan plan_resid(const Ctx* c, int M) {
@@ -164,7 +200,7 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   for (int M = 32; M <= c->Mmax; M += 32)
     for (auto& sh : shapes) {
       if (sh[1] == 2 * d && !g.draft_input) continue;
-      GemmPlan p = plan_gemm(c, M, sh[0], sh[1]);
+      GemmPlan p = sh[0] == 3 * d ? plan_qkv(c, M) : sh[0] == 2 * F ? plan_gate_up(c, M) : plan_gemm(c, M, sh[0], sh[1], 0, true);
       if (g.dtype == VVS_BF16 && p.splits == 1 && sh[0] != d) continue;   // written by the projection's own epilogue
       go = std::max(go, (size_t)p.splits * M * sh[0]);
     }
@@ -782,7 +818,7 @@ vvs_status vvs_debug_fill_probe(vvs_ctx* ctx, const void* d_src, size_t region_b
 size_t vvs_debug_gemm_scratch_bytes(const vvs_ctx* ctx, int32_t m, int32_t n, int32_t k) {
   const Ctx* c = reinterpret_cast<const Ctx*>(ctx);
   if (!c || m < 1 || n < 1 || k < 1) return 0;
-  GemmPlan p = plan_gemm(c, m, n, k);
+  GemmPlan p = plan_gemm(c, m, n, k, 0, true);
   return align_up((size_t)n * k * c->esz, 256) + align_up(align_up((size_t)m, 32) * k * c->esz, 256) +
          align_up((size_t)p.splits * m * n * sizeof(float), 256);
 }

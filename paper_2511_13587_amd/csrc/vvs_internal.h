@@ -32,8 +32,9 @@ struct PosDesc {
   int32_t grid_w;
 };
 
-// Tiles of a projection launch.  row_owner: the tiles are dealt so that an XCD owns row tiles instead of column tiles.
-struct GemmPlan { int bm, bn, splits; bool row_owner = false; };
+// Tiles of a projection launch.  row_owner: the tiles are dealt so that an XCD owns row tiles instead of column tiles.  shared: the
+// kernel that shares its operands through LDS (else every wave streams its own).
+struct GemmPlan { int bm, bn, splits; bool row_owner = false, shared = false; };
 
 // Byte offsets into the caller's workspace.
 struct Workspace {
@@ -89,7 +90,10 @@ struct Timed {
 
 // ---- host planner (vvs_host.cpp)
 vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err);
-GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section = 0 /* > 0: no tile may reach across a multiple of it */);
+GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section = 0 /* > 0: no tile may reach across a multiple of it */,
+                   bool may_split = false /* operands shared through LDS: the contraction may be split (else the epilogue takes whole sums) */, int min_bn = 64);
+GemmPlan plan_qkv(const Ctx* c, int M);
+GemmPlan plan_gate_up(const Ctx* c, int M);
 GemmPlan plan_resid(const Ctx* c, int M);   // O, down and input-map projections of the fused layer
 bool plan_fused(const Ctx* c, int M);   // true: the fused 5-kernel layer runs for M GEMM rows
 vvs_status build_tree(int n_nodes, const int32_t* h_parent, const uint8_t* h_mask, TreeDesc* out, std::string* err);

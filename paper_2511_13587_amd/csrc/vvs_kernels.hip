@@ -533,7 +533,7 @@ __global__ __launch_bounds__(256) void k_gemm_simple(const float* __restrict__ A
 
 // C[splits][M][N] (fp32 partial sums) = A[M][K] * W[N][K]^T (bf16: both operands in packed fragment order)
 static int run_gemm(Ctx* c, const void* A, const void* W, float* C, int M, int N, int K, bool allow_split, hipStream_t s) {
-  GemmPlan p = plan_gemm(c, M, N, K);
+  GemmPlan p = plan_gemm(c, M, N, K, 0, allow_split);
   if (!allow_split) p.splits = 1;
   Timed timed(c, VVS_K_GEMM, s);
   if (c->cfg.dtype == VVS_BF16) {
@@ -571,7 +571,7 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
   const int pad = mfma_qkv_attention_rows(c, pos, Tq);
   const bool qa = pad > 0;
   const int pad_T = qa ? Tq : 0;
-  const GemmPlan pq = plan_gemm(c, M, 3 * d, d, d), pr = plan_resid(c, M), pg = plan_gemm(c, M, 2 * F, d), pl = plan_gemm(c, M, c->veff, d);
+  const GemmPlan pq = plan_qkv(c, M), pr = plan_resid(c, M), pg = plan_gate_up(c, M), pl = plan_gemm(c, M, c->veff, d);
   // what each launch's idle CUs read ahead for the next one (nothing where no XCD owns a weight tile)
   auto weights = [&](const void* w, int N, int K, const GemmPlan& p) {
     if (p.row_owner) return WeightPrefetch{};
@@ -674,7 +674,7 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
     launch_add_rmsnorm<T>(M, x, go, splits, sstride, d, (const float*)(lw + c->p.g1), c->cfg.rms_eps, h, 1, 0, s);
     }
     int sp;
-    GemmPlan pq = plan_gemm(c, M, 3 * d, d, d);
+    GemmPlan pq = plan_qkv(c, M);
     // with 160+ tiles an unsplit projection streams its weights as fast as a split one, and its epilogue
     // does the rotary embedding and the cache write: one kernel less
     if (pq.splits > 1 && ((M + pq.bm - 1) / pq.bm) * (3 * d / pq.bn) >= 160) pq.splits = 1;
@@ -700,7 +700,7 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
     { Timed timed(c, VVS_K_ELEMENTWISE, s);
     launch_add_rmsnorm<T>(M, x, go, sp, (size_t)M * d, d, (const float*)(lw + c->p.g2), c->cfg.rms_eps, h, 1, 0, s);
     }
-    GemmPlan pg = plan_gemm(c, M, 2 * F, d);
+    GemmPlan pg = plan_gate_up(c, M);
     if (c->cfg.dtype == VVS_BF16 && pg.splits == 1) {
       Timed timed(c, VVS_K_GEMM, s);           // projection + SwiGLU in one kernel
       mfma_gemm_swiglu(c, (const bf16_t*)h, (const bf16_t*)(lw + c->p.wgu), (bf16_t*)act, nullptr, M, F, d, pg, s, WeightPrefetch{});

@@ -187,7 +187,7 @@ struct EpiPre {
   static constexpr int URE = EARLY ? UR : 1;
   static constexpr int G = NT / BM;                         // threads per tile row
   static constexpr int NR = EPI == EPI_QKV ? 2 * kRopeNpMax / G / 2 : 1;         // float4 (two factor pairs) per thread
-  int kv, ne, slot, img;
+  int kv, ne, dep, slot, img;
   bool rope_lds = true;          // false: the epilogue reads the rotary table from memory (kernels that keep no per-row table in LDS)
   float4 rp[NR];
   float4 x0[URE], x1[URE], g0[URE], g1[URE];
@@ -196,27 +196,33 @@ struct EpiPre {
   // value is at least 0.5 / T away from one)
   __device__ __forceinline__ static int div_T(int m, const GemmEpi& ep) { return (int)(((float)m + 0.5f) * (1.0f / (float)ep.T)); }
 
-  __device__ __forceinline__ void first(int tile_m, int M, const GemmEpi& ep) {
+  // Without branches - without a scale or positions the values come from `any`, memory that is there: a register loaded behind a
+  // branch and free again is believed to be still under way inside the main loop, where its reuse got a wait for all loads, operand
+  // stages included (QKV of 126 x 12288 x 4096 70 us instead of 36).  Depths past the table's end belong to prefill chunks, which
+  // do not use them.
+  __device__ __forceinline__ void first(int tile_m, int M, const GemmEpi& ep, const void* any) {
     if constexpr (EPI == EPI_QKV) {
-      kv = ne = 0;
-      if (ep.pos.kv_len) {
-        const int b = div_T(min(tile_m * BM + (int)threadIdx.x % BM, M - 1), ep) >> 1;
-        kv = ep.pos.kv_len[b];
-        ne = ep.pos.n_emitted[b];
-      }
+      const int m = min(tile_m * BM + (int)threadIdx.x % BM, M - 1), r = div_T(m, ep), b = ep.pos.kv_len ? r >> 1 : 0;
+      kv = (ep.pos.kv_len ? ep.pos.kv_len : (const int32_t*)any)[b];
+      ne = (ep.pos.kv_len ? ep.pos.n_emitted : (const int32_t*)any)[b];
+      dep = ep.tree.depth[min(m - r * ep.T, VVS_MAX_T - 1)];
+    }
+  }
+  // (slot, image index) of this thread's row from what first() asked for
+  __device__ __forceinline__ void position(int tile_m, int M, const GemmEpi& ep) {
+    const int m = min(tile_m * BM + (int)threadIdx.x % BM, M - 1), t = m - div_T(m, ep) * ep.T;
+    if (ep.pos.kv_len) {
+      slot = kv + t;
+      img = ne - 1 + dep;
+    } else {
+      slot = ep.pos.kv_base + t;
+      img = slot - ep.pos.prefix_len;
     }
   }
   __device__ __forceinline__ void start(int tile_m, int tile_n, int M, int N, const GemmEpi& ep) {
     const int m0 = tile_m * BM, n0 = tile_n * BN;
     if constexpr (EPI == EPI_QKV) {
-      const int m = min(m0 + (int)threadIdx.x % BM, M - 1), t = m - div_T(m, ep) * ep.T;
-      if (ep.pos.kv_len) {
-        slot = kv + t;
-        img = ne - 1 + ep.tree.depth[t];
-      } else {
-        slot = ep.pos.kv_base + t;
-        img = slot - ep.pos.prefix_len;
-      }
+      position(tile_m, M, ep);
       const int np = ep.dh >> 2;
       if (n0 / ep.d < 2 && np == kRopeNpMax && rope_lds) {   // q and k columns are rotated
         const int im = max(img, 0), gr = min(im / ep.pos.grid_w, ep.rope_pos - 1), gc = im % ep.pos.grid_w;
@@ -470,7 +476,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_direct(const uint4* __restrict
   __shared__ int s_pos[EPI == EPI_QKV ? 2 * BM : 2];                                  // EPI_QKV: (slot, image index) per tile row
   __shared__ __align__(16) float2 s_rope[EPI == EPI_QKV ? BM * 2 * kRopeNpMax : 2];   // EPI_QKV: rotary factors per tile row
   EpiPre<BM, BN, EPI, true, NT> pre;
-  pre.first(tile_m, M, ep);
+  pre.first(tile_m, M, ep, Ap);
   __builtin_amdgcn_sched_barrier(0);
   const int KB = K >> 4;
   const int s0 = blockIdx.z * kb_per_split, s1 = min(KB, s0 + kb_per_split);
@@ -786,7 +792,7 @@ __device__ __forceinline__ void register_epilogue_qkv(const floatx16 (&acc)[WM][
 
 template <int WM, int WN, int NS, int EPI>
 __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict__ Ap, const uint4* __restrict__ Wp, float* __restrict__ C,
-                                                         int M, int N, int K, int n_main, const GemmEpi ep) {
+                                                         int M, int N, int K, int st_per_split, int n_main, const GemmEpi ep) {
   static_assert(NS >= 4, "at least three stages in flight");
   constexpr int BM = 2 * WM * 32, BN = 2 * WN * 32;
   constexpr int NA = 2 * (BM / 32), NBLK = NA + 2 * (BN / 32), PER = NBLK / 4;
@@ -810,10 +816,12 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
   // the residual tile is read in the epilogue: early copies of a tile this size do not fit the registers
   EpiPre<BM, BN, EPI, EPI != EPI_RESID> pre;
   pre.rope_lds = false;
-  const int KB = K >> 4, nst = KB >> 1;
+  // EPI_PARTIAL: blockIdx.z takes st_per_split stages of the contraction
+  const int KB = K >> 4, s_first = EPI == EPI_PARTIAL ? (int)blockIdx.z * st_per_split : 0;
+  const int nst = EPI == EPI_PARTIAL ? min(st_per_split, (KB >> 1) - s_first) : KB >> 1;
   const int last_rb = (M - 1) >> 5;
   RowScale<BM> rowscale;                   // the epilogue's inputs first: they are the oldest loads and so never wait behind a stage
-  pre.first(tile_m, M, ep);
+  pre.first(tile_m, M, ep, Ap);
   rowscale.load(tile_m, M, ep);
   __builtin_amdgcn_sched_barrier(0);
   const u32x4* src[PER];
@@ -821,7 +829,7 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
   for (int i = 0; i < PER; ++i) {
     const int j = wave + 4 * i;
     const int rb = j < NA ? min(tile_m * (BM / 32) + (j >> 1), last_rb) : tile_n * (BN / 32) + ((j - NA) >> 1);
-    src[i] = (const u32x4*)(j < NA ? Ap : Wp) + ((size_t)rb * KB + (j & 1)) * 64 + lane;
+    src[i] = (const u32x4*)(j < NA ? Ap : Wp) + ((size_t)rb * KB + 2 * s_first + (j & 1)) * 64 + lane;
   }
   // stage t -> slot t % NS; stages past the end repeat the last one (never read)
   auto request = [&](int t) {
@@ -839,10 +847,6 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 #pragma unroll
   for (int t = 0; t < NS - 1; ++t) request(t);
-  // EPI_QKV: the row's position depends on a loaded value (its cache length); it is turned into (slot, image index) only
-  // now, behind the first stage requests, so that this wait is not on the path to them.  (Loads the compiler issues are
-  // counted by the same counter as the stage loads: its waits and the hand-written ones below can only become stricter.)
-  if (EPI == EPI_QKV) pre.start(tile_m, tile_n, M, N, ep);
   __builtin_amdgcn_sched_barrier(0);
   VVS_PHASE_MARK(1);
 #define VVS_WAIT_STAGES asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 3)) : "memory")
@@ -915,6 +919,9 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
   }
 #undef VVS_S2F
   VVS_PHASE_MARK(2);
+  // EPI_QKV: only now, behind the main loop, is a row's position made of the loads in front of it (the compiler counts its loads with
+  // the stage requests': a wait for them any earlier waits for stages too)
+  if constexpr (EPI == EPI_QKV) pre.position(tile_m, M, ep);
   pre.to_lds(s_pos, nullptr, ep);
   rowscale.finish(rs, tile_m, M, ep);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no request may be under way when the workgroup gives its LDS back
@@ -923,7 +930,7 @@ __global__ __launch_bounds__(256) void k_gemm_shared_dma(const uint4* __restrict
   VVS_PHASE_MARK(3);
   const int m0 = tile_m * BM + wr * WM * 32, n0 = tile_n * BN + wc * WN * 32;
   if constexpr (EPI == EPI_QKV) register_epilogue_qkv<WM, WN>(acc, rs + wr * WM * 32, s_pos + 2 * wr * WM * 32, m0, n0, M, ep);
-  else register_epilogue<WM, WN, EPI>(acc, rs + wr * WM * 32, m0, n0, M, N, C, ep);
+  else register_epilogue<WM, WN, EPI>(acc, rs + wr * WM * 32, m0, n0, M, N, EPI == EPI_PARTIAL ? C + (size_t)blockIdx.z * M * N : C, ep);
   VVS_PHASE_MARK(4);
 }
 
@@ -934,13 +941,13 @@ static int prefetchers(const WeightPrefetch& pf, int tiles, int per_cu = 1) {
 }
 
 template <int WM, int WN, int NS, int EPI>
-static void launch_gemm_shared_dma(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, const GemmEpi& ep, hipStream_t s) {
+static void launch_gemm_shared_dma(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, const GemmEpi& ep, hipStream_t s, int splits = 1) {
   constexpr int BM = 2 * WM * 32, BN = 2 * WN * 32;
   constexpr size_t lds = (size_t)NS * (2 * (BM + BN) / 32) * 1024;
   allow_dynamic_lds(reinterpret_cast<const void*>(&k_gemm_shared_dma<WM, WN, NS, EPI>), lds);
   const int tiles = (N / BN) * ((M + BM - 1) / BM);
-  hipLaunchKernelGGL((k_gemm_shared_dma<WM, WN, NS, EPI>), dim3(tiles + prefetchers(ep.pf, tiles)), dim3(256), lds, s, (const uint4*)A, (const uint4*)W,
-                     C, M, N, K, tiles, ep);
+  hipLaunchKernelGGL((k_gemm_shared_dma<WM, WN, NS, EPI>), dim3(tiles + (splits == 1 ? prefetchers(ep.pf, tiles) : 0), 1, splits), dim3(256), lds, s,
+                     (const uint4*)A, (const uint4*)W, C, M, N, K, (K / 32 + splits - 1) / splits, tiles, ep);
 }
 
 template <int TM, int TN, int D, int EPI, int NW = 4>
@@ -957,12 +964,22 @@ static void launch_gemm_direct(const bf16_t* A, const bf16_t* W, float* C, int M
 
 template <int EPI>
 static void gemm_dispatch(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, GemmPlan p, const GemmEpi& ep, hipStream_t s) {
-  if (p.bm == 256) { launch_gemm_shared_dma<4, 4, 4, EPI>(A, W, C, M, N, K, ep, s); return; }
-  if (p.bm == 128) {
-    // A single round of tiles (at most one workgroup per CU): 8 slots, 6 stages in flight.  More: 4 slots, so that the LDS
-    // lets two workgroups share a CU and cover each other's barrier waits.
-    if (((M + 127) / 128) * (N / 128) <= 256) launch_gemm_shared_dma<2, 2, 8, EPI>(A, W, C, M, N, K, ep, s);
-    else launch_gemm_shared_dma<2, 2, 4, EPI>(A, W, C, M, N, K, ep, s);
+  if (p.shared) {
+    const int at = p.bm * 1000 + p.bn;
+    if (at == 256256) launch_gemm_shared_dma<4, 4, 4, EPI>(A, W, C, M, N, K, ep, s, p.splits);
+    else if (at == 256128) launch_gemm_shared_dma<4, 2, 6, EPI>(A, W, C, M, N, K, ep, s, p.splits);
+    else if (at == 192128) launch_gemm_shared_dma<3, 2, 6, EPI>(A, W, C, M, N, K, ep, s, p.splits);
+    else if (at == 64128) launch_gemm_shared_dma<1, 2, 6, EPI>(A, W, C, M, N, K, ep, s, p.splits);
+    else if (at == 128128) {
+      // A single round of tiles (at most one workgroup per CU): 8 slots, 6 stages in flight.  More: 4 slots, so that the LDS
+      // lets two workgroups share a CU and cover each other's barrier waits.
+      if (((M + 127) / 128) * (N / 128) * p.splits <= 256) launch_gemm_shared_dma<2, 2, 8, EPI>(A, W, C, M, N, K, ep, s, p.splits);
+      else launch_gemm_shared_dma<2, 2, 4, EPI>(A, W, C, M, N, K, ep, s, p.splits);
+    } else if constexpr (EPI != EPI_SWIGLU) {      // 64 columns: plan_gate_up asks for 128
+      if (at == 192064) launch_gemm_shared_dma<3, 1, 8, EPI>(A, W, C, M, N, K, ep, s, p.splits);
+      else if (at == 128064) launch_gemm_shared_dma<2, 1, 6, EPI>(A, W, C, M, N, K, ep, s, p.splits);
+      else launch_gemm_shared_dma<1, 1, 8, EPI>(A, W, C, M, N, K, ep, s, p.splits);
+    }
     return;
   }
   if (p.bm == 32 && p.bn == 128) launch_gemm_direct<1, 4, 4, EPI>(A, W, C, M, N, K, p.splits, ep, s);

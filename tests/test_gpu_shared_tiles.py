@@ -1,0 +1,54 @@
+"""GPU parity of the projections that share their operands through LDS, at the edges of the tiles that large weights take:
+plain products with and without a split of the contraction, and the q/k/v and gate/up epilogues."""
+import numpy as np
+import pytest
+
+from paper_2511_13587_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gc():
+    import gpu_common
+    return gpu_common
+
+
+def bf16_round(a):
+    return synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(np.asarray(a, dtype=np.float32)))
+
+
+# 64 x 64, 128 x 64, 192 x 64, 128 x 128, 192 x 128 and 256 x 128 tiles, one row into the next tile, and 130 stages of the
+# contraction in 4 (the last share is shorter)
+@pytest.mark.parametrize("m,n,k", [(33, 4096, 4096), (64, 4096, 4160), (65, 4096, 4096), (128, 4096, 4160), (129, 4096, 4096), (192, 4096, 11008),
+                                   (193, 4096, 4096), (257, 4096, 4160), (388, 4096, 11008), (513, 4096, 4096)])
+def test_product_of_large_weights_bf16(gc, m, n, k):
+    pair = gc.Pair(synth.B_SHAPE.replace(n_layers=1, n_prompts=1, vocab=1024, logit_hi=1024), with_oracle=False)
+    rng = np.random.default_rng(m + n + k)
+    a = bf16_round(rng.standard_normal((m, k)))
+    w = bf16_round(rng.standard_normal((k, n)) * 0.05)
+    got = pair.ctx.vvs_debug_gemm(gc.vb.to_device(a, 1), gc.vb.to_device(w, 1), m, n, k).cpu().numpy()
+    want = a.astype(np.float64) @ w.astype(np.float64)
+    # fp32 sums of k exact products of size 0.05: rounding noise of about sqrt(k) * 2^-24 times the sums' size sqrt(k) * 0.05
+    scale = np.sqrt(k) * 0.05
+    assert np.abs(got - want).max() < 2e-5 * scale * 10, np.abs(got - want).max()
+    pair.close()
+
+
+# rows = 2 x tokens.  d 2048: q/k/v on 64 x 64, 128 x 64, 64 x 128, 128 x 128, 192 x 128 and 256 x 128 tiles, gate/up on 64 x 128,
+# 128 x 128, 192 x 128 and 256 x 128; d 4096: q/k/v on 192 x 64, and gate/up on 64 x 128
+@pytest.mark.parametrize("d,heads,d_ff,tokens", [(2048, 32, 3072, 24), (2048, 16, 3072, 65), (2048, 16, 3072, 150), (2048, 32, 3072, 200),
+                                                 (2048, 32, 3072, 345), (2048, 16, 3072, 497), (4096, 32, 1536, 90)])
+def test_epilogues_of_large_weights_bf16(gc, d, heads, d_ff, tokens):
+    shape = synth.SEVEN_B.replace(d_model=d, n_heads=heads, d_ff=d_ff, n_layers=1, n_prompts=1, n_nodes=2, tree_widths=None, vocab=1024, logit_lo=0,
+                                  logit_hi=1024, grid_h=32, grid_w=32, prefix_len=1, prefix_kind=synth.PREFIX_CLASS)
+    pair = gc.Pair(shape, gain_jitter=0.1, shadow=True, sample=[0])
+    pair.prefill(n_forced=tokens - 1)
+    raw, _, _ = pair.gpu_logits()
+    diff = raw[pair.rows(), 0] - pair.oracle.prefill_logits
+    err = float(np.abs(diff).max())
+    print("prefill", d, tokens, "logit error", err, "floor", pair.floor)
+    assert err <= gc.logit_tol(shape, pair.floor, pair.fused), (err, pair.floor)
+    assert gc.rms(diff) <= gc.logit_rms_tol(shape, pair.floor_rms, pair.fused)
+    gc.check_kv(pair, 0, tokens, "prefill", prompts=[0])
+    pair.close()
