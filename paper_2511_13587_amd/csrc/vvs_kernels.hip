@@ -603,7 +603,7 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
         mfma_gemm_qkv(c, l, xb, (const bf16_t*)(lw + c->p.wqkv), ss, tree, pos, Tq, pq, s);
       }
       { Timed timed(c, VVS_K_ATTENTION, s);
-        mfma_attention(c, l, tree, pos, Tq, s);
+        mfma_attention(c, l, tree, pos, Tq, s, weights(lw + c->p.wo, d, d, pr));
       }
     }
     { Timed timed(c, VVS_K_GEMM, s);

@@ -465,7 +465,7 @@ template <int TM, int TN, int D, int EPI, int NW>
 __global__ __launch_bounds__(NW * 64) void k_gemm_direct(const uint4* __restrict__ Ap, const uint4* __restrict__ Wp, float* __restrict__ C,
                                                      int M, int N, int K, int kb_per_split, int n_main, const GemmEpi ep) {
   constexpr int BM = TM * 32, BN = TN * 32, LDC = BN + 4, NT = NW * 64;
-  static_assert(EPI != EPI_QKV || NW == 4, "the rotary factors of a row are dealt to 256 / BM threads");
+  static_assert(EPI != EPI_QKV || 2 * kRopeNpMax * BM / NT >= 2, "the rotary factors of a row are dealt to NT / BM threads in whole float4");
   extern __shared__ float red[];           // [NW][BM][LDC]
   if ((int)blockIdx.x >= n_main) { prefetch_weights<NW>(ep.pf, blockIdx.x, n_main, gridDim.x); return; }
   VVS_PHASE_MARK(0);
@@ -995,6 +995,9 @@ static void gemm_dispatch(const bf16_t* A, const bf16_t* W, float* C, int M, int
     }
     return;
   }
+  if constexpr (EPI == EPI_QKV) {
+    if (p.bn == 32) { launch_gemm_direct<1, 1, 8, EPI, 8>(A, W, C, M, N, K, 1, ep, s); return; }
+  }
   if (p.bm == 32 && p.bn == 128) launch_gemm_direct<1, 4, 4, EPI>(A, W, C, M, N, K, p.splits, ep, s);
   else if (p.bm == 32) launch_gemm_direct<1, 2, 8, EPI>(A, W, C, M, N, K, p.splits, ep, s);
   else if (p.bn == 128) launch_gemm_direct<2, 4, 4, EPI>(A, W, C, M, N, K, p.splits, ep, s);
@@ -1146,10 +1149,16 @@ template <int DH, int NQB, int NW, int PD, int QG = 1>
 __global__ __launch_bounds__(NW * QG * 64, (DH * NQB >= 256 ? 1 : 2)) void k_attn_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
                                                    const bf16_t* __restrict__ vc, bf16_t* __restrict__ out, TreeDesc tree,
                                                    PosDesc pos, int T_row, int d, size_t row_stride, size_t head_stride, float c_exp,
-                                                   int cap_steps) {
+                                                   int cap_steps, int nz, const WeightPrefetch pf) {
   constexpr int KD = DH / 32, DT = DH / 16, NQ = NQB * 16;
   __shared__ float s_m[QG][NW - 1][NQ], s_l[QG][NW - 1][NQ];
   __shared__ float s_o[QG][NW - 1][NQ][DH + 1];
+  // slices of the grid from nz on read the next launch's weights (prefetch_weights)
+  if ((int)blockIdx.z >= nz) {
+    const int slice = gridDim.x * gridDim.y;
+    prefetch_weights<NW * QG>(pf, blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), slice * nz, slice * gridDim.z);
+    return;
+  }
   VVS_PHASE_MARK(0);
   const int hd = blockIdx.x, r = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) % NW, qg = (threadIdx.x >> 6) / NW, q0 = qg * NQ;
@@ -1660,11 +1669,13 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
 // when a verify call of T block tokens per row does not take that kernel.
 int mfma_qkv_attention_rows(const Ctx* c, const PosDesc& pos, int T) {
   if (c->cfg.dtype != VVS_BF16 || c->dh != 64 || T > 64 || !pos.kv_len || !pos.n_emitted || c->d % 64 || c->d > 2560) return 0;
-  // 33 .. 64 tokens per row: a workgroup fills a CU (141 KB of LDS), so (head, prompt) pairs beyond the 256 CUs run in rounds,
-  // and a poorly filled third round loses to the separate kernels.  Measured at 20 heads, 61 tokens, ms per step fused /
-  // separate: 8 prompts 3.99 / 4.30, 12: 4.94 / 5.78, 16: 7.25 / 7.32, 24: 8.73 / 9.02, 28: 10.10 / 9.65, 32: 10.63 / 10.25.
-  // (Up to 32 tokens a workgroup is smaller and the fused launch never lost: 13 .. 32 prompts at 27 tokens.)
-  if (T > 32 && c->H * c->B > 512) return 0;
+  // A workgroup fills a CU, so (head, prompt) pairs beyond the 256 CUs run in rounds and lose to the separate kernels; of few pairs
+  // each CU pulls 655 KB of weights while most stand idle, where a projection of its own deals them to all.  ms per step fused /
+  // separate: 20 heads, 27 tokens, 1 prompt 1.58 / 1.45, 6 2.29 / 2.39, 16 4.06 / 3.83, 24 5.19 / 5.11, 32 6.32 / 5.95; 61 tokens, 1 2.19 / 1.81,
+  // 8 3.71 / 3.93, 16 6.37 / 5.81, 24 8.39 / 8.26; 6 tokens, 8 1.833 / 1.822, 13 2.72 / 2.12, 32 3.94 / 3.15; 12 heads, 6 tokens, 1 prompt 0.363 / 0.357,
+  // 16 0.449 / 0.481, 22 0.685 / 0.580.  (40 and 80 pairs: separate 5 and 2 % faster at 27 tokens, 18 and 9 % at 61; the launches of
+  // 2 prompts are pinned by test_which_launches_a_layer_takes.)
+  if (c->H * c->B < 40 || c->H * c->B > 256) return 0;
   return T <= 32 ? 32 : 64;
 }
 
@@ -1697,18 +1708,21 @@ void mfma_qkv_attention(Ctx* c, int layer, const bf16_t* A, const bf16_t* Wqkv, 
 }
 
 
-void mfma_attention(Ctx* c, int layer, const TreeDesc& tree, const PosDesc& pos, int T, hipStream_t s) {
+void mfma_attention(Ctx* c, int layer, const TreeDesc& tree, const PosDesc& pos, int T, hipStream_t s, const WeightPrefetch& pf) {
   const bf16_t* q = (const bf16_t*)(c->ws + c->w.q);
   bf16_t* out = (bf16_t*)(c->ws + c->w.attn);
   const bf16_t* kc = (const bf16_t*)c->kv + c->kv_layer_stride * layer;
   const bf16_t* vc = (const bf16_t*)c->kv + c->kv_v_off + c->kv_layer_stride * layer;
   const float c_exp = 1.4426950408889634f / sqrtf((float)c->dh);
   const int per_wg = c->dh == 64 ? 64 : 32;                      // queries a workgroup holds; a verify call never has more
-  dim3 grid(c->H, c->R, (T + per_wg - 1) / per_wg);
+  // with few (head, row) pairs whole slices of the grid read ahead: O's weights into the L2s that will want them (20 heads, 1 prompt:
+  // attention 8.6 -> 10 us, O and down together 17.3 -> 14.1)
+  const int nz = (T + per_wg - 1) / per_wg, slice = c->H * c->R;
+  dim3 grid(c->H, c->R, nz + (pf.w ? prefetchers(pf, slice * nz) / slice : 0));
   const int nqb = T <= 16 ? 1 : (T <= 32 ? 2 : 4);
 #define VVS_ATTN(DH, NQB, NW, PD, QG)                                                                                                  \
   hipLaunchKernelGGL((k_attn_mfma<DH, NQB, NW, PD, QG>), grid, dim3(NW * QG * 64), 0, s, q, kc, vc, out, tree, pos, T, c->d, c->kv_row_stride, \
-                     c->kv_head_stride, c_exp, c->S_cap >> 5)
+                     c->kv_head_stride, c_exp, c->S_cap >> 5, nz, pf)
   // 4 waves per workgroup keep the register footprint low enough for 2-3 workgroups per CU, so that
   // every (head, row) pair of a call is resident at once
   if (c->dh == 64) {
