@@ -150,7 +150,7 @@ __device__ __forceinline__ int block_max_int(int v, int* red) {
 __device__ __forceinline__ void token_pos(const PosDesc& pos, const TreeDesc& tree, int r, int t, int* slot, int* img) {
   if (pos.kv_len) {
     int b = r >> 1;
-    *slot = pos.kv_len[b] + t;
+    *slot = pos.kv_len[b] + tree.first + t;
     *img = pos.n_emitted[b] - 1 + tree.depth[t];
   } else {
     *slot = pos.kv_base + t;
@@ -176,10 +176,17 @@ inline void allow_dynamic_lds(const void* kernel, size_t bytes) {
 // What the next projection launch reads of its packed weights, for the idle CUs of this one (w == nullptr: nothing): n_tiles
 // column tiles, each `sections` runs of `blocks` 1 KiB blocks, section_blocks apart; row_tiles: the next launch's row tiles.
 struct WeightPrefetch { const uint4* w; int n_tiles, blocks, sections, section_blocks, row_tiles; };
-void mfma_gemm(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, GemmPlan p, hipStream_t s);
-void mfma_gemm_scaled(Ctx* c, const bf16_t* A, const bf16_t* W, float* C, const float* ss, int M, int N, int K, GemmPlan p, hipStream_t s);
+// Row m of an fp32 result goes to row (m / T) * all + first + m % T (all == 0: to row m).
+struct RowMap {
+  int T, all, first;
+  __device__ __forceinline__ int operator()(int m) const { return all ? m / T * all + first + m % T : m; }
+};
+void mfma_gemm_scaled(Ctx* c, const bf16_t* A, const bf16_t* W, float* C, const float* ss, int M, int N, int K, GemmPlan p, hipStream_t s,
+                      RowMap out = RowMap{});
+void mfma_gemm(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, GemmPlan p, hipStream_t s, RowMap out = RowMap{});
 void mfma_gemm_resid(Ctx* c, const bf16_t* A, const bf16_t* W, float* x, bf16_t* xb, float* ss_out, const float* g_next, int M, int K,
-                     hipStream_t s, const WeightPrefetch& pf, int xb_T = 0, int xb_pad = 0 /* xb_T > 0: xb row-padded to xb_pad rows per xb_T tokens */);
+                     hipStream_t s, const WeightPrefetch& pf, int xb_T = 0, int xb_pad = 0 /* xb_T > 0: xb row-padded to xb_pad rows per xb_T tokens */,
+                     bool fresh = false /* x = A W, whatever x held */);
 int mfma_qkv_attention_rows(const Ctx* c, const PosDesc& pos, int T);
 void mfma_qkv_attention(Ctx* c, int layer, const bf16_t* A, const bf16_t* Wqkv, const float* ss, const TreeDesc& tree, const PosDesc& pos,
                         int T, hipStream_t s, const WeightPrefetch& pf);

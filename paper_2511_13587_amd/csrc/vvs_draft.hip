@@ -1,8 +1,10 @@
 // Draft side (Algorithm 2: "C_t <- M_D(f_t, a)"; Section 3, "Stale Feature Reusability"): the kernels
-// around the drafter's forwards.  A drafting call runs the drafter level by level; every level is one
-// forward of the ordinary kind (ancestor-masked block, the drafter context's own small KV region, cached
-// length 0) over the n_ctx (feature, token) pairs and every node expanded so far.  These kernels build the
+// around the drafter's forwards.  A drafting call runs the drafter level by level over one ancestor-masked block (the drafter
+// context's own small KV region, cached length 0): level 0 is a forward of the n_ctx (feature, token) pairs, every further
+// level one of the nodes it expands, whose attention finds the K and V of the earlier levels in the cache.  These kernels build the
 // forward's input rows and turn its logits into the distributions and tokens of the next level.
+// (Forwards over all tokens so far, every level again, took 80 to 336 rows per level where 16 to 80 are new: 26-node tree, 8
+// prompts of the XL width. The call took 631 us, 478 so.)
 #include "vvs_device.h"
 
 namespace vvs {
@@ -39,7 +41,7 @@ void launch_draft_zero_leaves(Ctx* dr, const TreeDesc& shape, float* d_probs, hi
   hipLaunchKernelGGL(k_draft_zero_rows, dim3(dr->B, leaves.n), dim3(256), 0, s, d_probs, leaves, shape.T, dr->veff);
 }
 
-// One workgroup per block token m = r * Tq + t: writes the row [embedding of the token ; feature] of the
+// One workgroup per block token of this level, m = r * Tq + t - first: writes the row [embedding of the token ; feature] of the
 // input map's operand (row-major fp32, or the packed bf16 operand order).
 //   t <  k: token = recent[b][t]; feature = the (k - t)-th newest entry of the target's ring of row r
 //           (zeros when the ring holds fewer entries);
@@ -53,7 +55,7 @@ __global__ __launch_bounds__(256) void k_draft_input(T* __restrict__ din, const 
                                                      const int32_t* __restrict__ draft_tokens, DraftLevel lv, int R, int d, int V,
                                                      int slots, int pre_norm, float eps) {
   __shared__ float red[16];
-  const int m = blockIdx.x, r = m / lv.Tq, t = m % lv.Tq, b = r >> 1;
+  const int m = blockIdx.x, r = m / lv.Tq, t = lv.first + m % lv.Tq, b = r >> 1;   // block token t of row r
   int tok;
   const T* feat = nullptr;
   const float* xr = nullptr;
@@ -63,7 +65,7 @@ __global__ __launch_bounds__(256) void k_draft_input(T* __restrict__ din, const 
     if (e >= 0) feat = ring + ((size_t)r * slots + (oldest + e) % slots) * d;
   } else {
     tok = draft_tokens[b * lv.n_nodes + lv.node[t] - 1];
-    xr = x + ((size_t)r * lv.Tq_prev + lv.parent_slot[t]) * d;
+    xr = x + ((size_t)r * lv.Tq_prev + lv.parent_slot[t] - lv.first_prev) * d;
   }
   tok = min(max(tok, 0), V - 1);
   const T* emb = embed + (size_t)tok * d;
@@ -119,8 +121,8 @@ __global__ __launch_bounds__(1024) void k_draft_select(const float* __restrict__
   __shared__ int s_bi[16];
   __shared__ int s_taken[VVS_MAX_T];
   const int b = blockIdx.x, j = lv.sel_node[blockIdx.y], t = lv.sel_slot[blockIdx.y];
-  const float* lc = logits + ((size_t)(2 * b) * lv.Tq + t) * V;
-  const float* lu = logits + ((size_t)(2 * b + 1) * lv.Tq + t) * V;
+  const float* lc = logits + ((size_t)(2 * b) * lv.all + t) * V;
+  const float* lu = logits + ((size_t)(2 * b + 1) * lv.all + t) * V;
   float* out = probs + ((size_t)b * shape.T + j) * V;
   float mx = -INFINITY;
   for (int i = threadIdx.x; i < V; i += blockDim.x) mx = fmaxf(mx, lu[i] + cfg_scale * (lc[i] - lu[i]));
@@ -169,8 +171,8 @@ __global__ __launch_bounds__(1024) void k_draft_select_regs(const float* __restr
   __shared__ int s_bi[16];
   __shared__ int s_win;
   const int b = blockIdx.x, j = lv.sel_node[blockIdx.y], t = lv.sel_slot[blockIdx.y];
-  const float* lc = logits + ((size_t)(2 * b) * lv.Tq + t) * V;
-  const float* lu = logits + ((size_t)(2 * b + 1) * lv.Tq + t) * V;
+  const float* lc = logits + ((size_t)(2 * b) * lv.all + t) * V;
+  const float* lu = logits + ((size_t)(2 * b + 1) * lv.all + t) * V;
   float* out = probs + ((size_t)b * shape.T + j) * V;
   float mixed[NR];
   float mx = -INFINITY;

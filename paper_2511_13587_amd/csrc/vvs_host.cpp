@@ -740,21 +740,32 @@ vvs_status vvs_draft(vvs_ctx* drafter, vvs_ctx* target, int32_t n_nodes, const i
   memset(&lv, 0, sizeof(lv));
   lv.k = k;
   lv.n_nodes = n_nodes;
+  lv.all = k + (int)order.size();
+  std::vector<int32_t> bp(lv.all > 1 ? lv.all - 1 : 1);
+  for (int t = 1; t < lv.all; ++t) {
+    if (t < k) { bp[t - 1] = t - 1; continue; }
+    const int j = order[t - k];
+    lv.node[t] = (int8_t)j;
+    lv.parent_slot[t] = (int8_t)slot[shape.parent[j]];
+    bp[t - 1] = slot[shape.parent[j]];
+  }
+  TreeDesc block;
+  rc = build_tree(lv.all - 1, bp.data(), nullptr, &block, &dr->err);
+  if (rc != VVS_OK) return rc;
   int n_in = 0;
   for (int level = 0; level <= last_level; ++level) {
+    // level 0: the pairs; level l: the nodes of depth l that have children (no level up to the last is without)
+    lv.first = level ? k + n_in : 0;
     while (n_in < (int)order.size() && shape.depth[order[n_in]] <= level) ++n_in;
-    lv.Tq = k + n_in;
-    std::vector<int32_t> bp(lv.Tq > 1 ? lv.Tq - 1 : 1);
-    for (int t = 1; t < lv.Tq; ++t) {
-      if (t < k) { bp[t - 1] = t - 1; continue; }
-      const int j = order[t - k];
-      lv.node[t] = (int8_t)j;
-      lv.parent_slot[t] = (int8_t)slot[shape.parent[j]];
-      bp[t - 1] = slot[shape.parent[j]];
+    lv.Tq = k + n_in - lv.first;
+    TreeDesc part{};
+    part.T = lv.Tq;
+    part.first = lv.first;
+    part.all = lv.all;
+    for (int t = 0; t < lv.Tq; ++t) {
+      part.depth[t] = block.depth[lv.first + t];
+      part.anc[t] = block.anc[lv.first + t];
     }
-    TreeDesc blk;
-    rc = build_tree(lv.Tq - 1, bp.data(), nullptr, &blk, &dr->err);
-    if (rc != VVS_OK) return rc;
     lv.n_sel = 0;
     for (int j = 0; j < T; ++j)
       if (shape.first_child[j] >= 0 && shape.depth[j] == level) {
@@ -763,13 +774,14 @@ vvs_status vvs_draft(vvs_ctx* drafter, vvs_ctx* target, int32_t n_nodes, const i
         ++lv.n_sel;
       }
     launch_draft_input(dr, tg, lv, d_recent_tokens, d_draft_tokens, st);
-    launch_forward(dr, blk, pos, lv.Tq, nullptr, nullptr, nullptr, 0, nullptr, 0, 1, st, true);
+    launch_forward(dr, part, pos, lv.Tq, nullptr, nullptr, nullptr, 0, nullptr, 0, 1, st, true);
     launch_draft_select(dr, lv, shape, d_given_tokens, d_draft_tokens, d_draft_probs, st);
     lv.Tq_prev = lv.Tq;
+    lv.first_prev = lv.first;
   }
   rc = check_launch(dr, "draft");
   if (rc != VVS_OK) return rc;
-  dr->last_T = lv.Tq;
+  dr->last_T = lv.all;
   return VVS_OK;
 }
 

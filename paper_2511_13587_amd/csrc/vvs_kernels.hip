@@ -394,7 +394,7 @@ __global__ __launch_bounds__(256) void k_attn_simple(const float* __restrict__ q
   float* red = sc + S_cap;
   const int t = blockIdx.x, hd = blockIdx.y, r = blockIdx.z, m = r * T_ + t;
   const int S = pos.kv_len ? pos.kv_len[r >> 1] : pos.kv_base;
-  const int n = min(S + T_, S_cap);
+  const int n = min(S + tree.first + T_, S_cap);
   const uint64_t mask = tree.anc[t];
   const float* qv = q + (size_t)m * d + (size_t)hd * dh;
   const float* kb = kc + (size_t)r * row_stride + (size_t)hd * head_stride;
@@ -472,7 +472,7 @@ __global__ void k_swiglu(const float* __restrict__ gu, int splits, size_t split_
 // such pieces (K = 512) are under way at once.  Launch of 128 columns and 10 rows, K 128 and 344 on average: 11.4 us with
 // 4-byte loads behind the row tests, 3.5 us so.  !VEC: a K that is not a multiple of 4, or operands not on 16 bytes.
 template <bool VEC>
-__global__ __launch_bounds__(256) void k_gemm_simple(const float* __restrict__ A, const float* __restrict__ W, float* __restrict__ C, int M, int N, int K) {
+__global__ __launch_bounds__(256) void k_gemm_simple(const float* __restrict__ A, const float* __restrict__ W, float* __restrict__ C, int M, int N, int K, RowMap out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = blockIdx.x * 4 + wave, m0 = blockIdx.y * 8;
   if (n >= N) return;
@@ -528,23 +528,23 @@ __global__ __launch_bounds__(256) void k_gemm_simple(const float* __restrict__ A
 #pragma unroll
   for (int o = 4; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   const int m = m0 + (lane >> 3);
-  if ((lane & 7) == 0 && m < M) C[(size_t)m * N + n] = v;
+  if ((lane & 7) == 0 && m < M) C[(size_t)out(m) * N + n] = v;
 }
 
 // C[splits][M][N] (fp32 partial sums) = A[M][K] * W[N][K]^T (bf16: both operands in packed fragment order)
-static int run_gemm(Ctx* c, const void* A, const void* W, float* C, int M, int N, int K, bool allow_split, hipStream_t s) {
+static int run_gemm(Ctx* c, const void* A, const void* W, float* C, int M, int N, int K, bool allow_split, hipStream_t s, RowMap out = RowMap{}) {
   GemmPlan p = plan_gemm(c, M, N, K, 0, allow_split);
   if (!allow_split) p.splits = 1;
   Timed timed(c, VVS_K_GEMM, s);
   if (c->cfg.dtype == VVS_BF16) {
-    mfma_gemm((const bf16_t*)A, (const bf16_t*)W, C, M, N, K, p, s);
+    mfma_gemm((const bf16_t*)A, (const bf16_t*)W, C, M, N, K, p, s, out);
     return p.splits;
   }
   dim3 grid((N + 3) / 4, (M + 7) / 8);
   if (K % 4 == 0 && ((uintptr_t)A | (uintptr_t)W) % 16 == 0)
-    hipLaunchKernelGGL(k_gemm_simple<true>, grid, dim3(256), 0, s, (const float*)A, (const float*)W, C, M, N, K);
+    hipLaunchKernelGGL(k_gemm_simple<true>, grid, dim3(256), 0, s, (const float*)A, (const float*)W, C, M, N, K, out);
   else
-    hipLaunchKernelGGL(k_gemm_simple<false>, grid, dim3(256), 0, s, (const float*)A, (const float*)W, C, M, N, K);
+    hipLaunchKernelGGL(k_gemm_simple<false>, grid, dim3(256), 0, s, (const float*)A, (const float*)W, C, M, N, K, out);
   return 1;
 }
 
@@ -584,10 +584,9 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
     if (qa) return WeightPrefetch{(const uint4*)(layer(l) + c->p.wqkv), c->H, 2 * (d / 16), 3, (d / 32) * (d / 16), c->B};
     return weights(layer(l) + c->p.wqkv, 3 * d, d, pq);
   };
-  if (from_din) {             // drafter: x = [embedding ; feature] W_fc, through the residual epilogue on a zeroed x
-    launch_fill_zero(x, sizeof(float) * (size_t)M * d, s);
+  if (from_din) {             // drafter: x = [embedding ; feature] W_fc
     Timed timed(c, VVS_K_GEMM, s);
-    mfma_gemm_resid(c, (const bf16_t*)(c->ws + c->w.din), (const bf16_t*)(c->pw + c->p.fc), x, xb, ss, g_first, M, 2 * d, s, pf_qkv(0), pad_T, pad);
+    mfma_gemm_resid(c, (const bf16_t*)(c->ws + c->w.din), (const bf16_t*)(c->pw + c->p.fc), x, xb, ss, g_first, M, 2 * d, s, pf_qkv(0), pad_T, pad, true);
   } else {
     Timed timed(c, VVS_K_ELEMENTWISE, s);
     hipLaunchKernelGGL(k_embed_packed, dim3(M), dim3(256), 0, s, x, xb, ss, NS, (const bf16_t*)(c->pw + c->p.embed),
@@ -625,7 +624,7 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
   const bf16_t* wout = (const bf16_t*)(c->pw + c->p.wout);
   if (logits_mode == 1) {
     Timed timed(c, VVS_K_GEMM, s);
-    mfma_gemm_scaled(c, xb, wout, logits, ss, M, c->veff, d, pl, s);
+    mfma_gemm_scaled(c, xb, wout, logits, ss, M, c->veff, d, pl, s, RowMap{Tq, tree.all, tree.first});
   } else {                    // last token of every row
     bf16_t* hf = (bf16_t*)(c->ws + c->w.hf);
     float* ss2 = (float*)(c->ws + c->w.ss2);
@@ -730,7 +729,7 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
     launch_add_rmsnorm<T>(Ml, x, go, splits, sstride, d, gf, c->cfg.rms_eps, hf, Tq, Tq - 1, s);
     }
   }
-  run_gemm(c, hf, c->pw + c->p.wout, logits, Ml, c->veff, d, false, s);
+  run_gemm(c, hf, c->pw + c->p.wout, logits, Ml, c->veff, d, false, s, logits_mode == 1 ? RowMap{Tq, tree.all, tree.first} : RowMap{});
 }
 
 void launch_forward(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, const int32_t* d_tokens_bt, const void* pc,

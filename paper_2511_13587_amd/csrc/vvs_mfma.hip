@@ -80,6 +80,8 @@ struct GemmEpi {
   const float* ss; int NS; float eps; int dnorm;           // row scale (ss == nullptr: no scaling); ss[M][NS]
   bf16_t* act; int F;                                      // EPI_SWIGLU
   float* x; bf16_t* xb; float* ss_out; const float* g_next; // EPI_RESID (g_next: gain of the norm that reads x next)
+  int fresh;                                               // EPI_RESID: x = tile, whatever x held
+  RowMap out;                                              // EPI_PARTIAL: rows of C
   int xb_T, xb_pad;                                        // EPI_RESID: xb_T > 0 = xb in the row-padded layout (row m at (m / xb_T) * xb_pad + m % xb_T)
   bf16_t* q; bf16_t* kc; bf16_t* vc; const float* rope;    // EPI_QKV
   int T, d, dh, S_cap, rope_pos;
@@ -212,7 +214,7 @@ struct EpiPre {
   __device__ __forceinline__ void position(int tile_m, int M, const GemmEpi& ep) {
     const int m = min(tile_m * BM + (int)threadIdx.x % BM, M - 1), t = m - div_T(m, ep) * ep.T;
     if (ep.pos.kv_len) {
-      slot = kv + t;
+      slot = kv + ep.tree.first + t;
       img = ne - 1 + dep;
     } else {
       slot = ep.pos.kv_base + t;
@@ -287,7 +289,7 @@ __device__ __forceinline__ void tile_epilogue(const float* red, const float* rs,
         float4 v = sum4(red + row * LDC + col);
         const float sc = rs[row];
         v.x *= sc; v.y *= sc; v.z *= sc; v.w *= sc;
-        *(float4*)(Cs + (size_t)(m0 + row) * N + n0 + col) = v;
+        *(float4*)(Cs + (size_t)ep.out(m0 + row) * N + n0 + col) = v;
       }
     }
   } else if constexpr (EPI == EPI_SWIGLU) {
@@ -325,6 +327,7 @@ __device__ __forceinline__ void tile_epilogue(const float* red, const float* rs,
           xa = *(const float4*)xp; xb4 = *(const float4*)(xp + 4);
           ga = *(const float4*)(ep.g_next + n0 + c8); gb = *(const float4*)(ep.g_next + n0 + c8 + 4);
         }
+        if (ep.fresh) xa = xb4 = make_float4(0.f, 0.f, 0.f, 0.f);
         float v[8] = {xa.x + a.x, xa.y + a.y, xa.z + a.z, xa.w + a.w, xb4.x + b.x, xb4.y + b.y, xb4.z + b.z, xb4.w + b.w};
         *(float4*)xp = make_float4(v[0], v[1], v[2], v[3]);
         *(float4*)(xp + 4) = make_float4(v[4], v[5], v[6], v[7]);
@@ -675,7 +678,7 @@ __device__ __forceinline__ void register_epilogue(const floatx16 (&acc)[WM][WN],
         for (int k = 0; k < 4; ++k) {
           const int mm = m0 + i * 32 + 8 * q + 4 * hi + k;
           if (mm < M) {
-            float* row = C + (size_t)mm * N + n0 + lo;
+            float* row = C + (size_t)ep.out(mm) * N + n0 + lo;
 #pragma unroll
             for (int j = 0; j < WN; ++j) row[j * 32] = acc[i][j][4 * q + k] * sr[k];
           }
@@ -717,7 +720,7 @@ __device__ __forceinline__ void register_epilogue(const floatx16 (&acc)[WM][WN],
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const floatx16& a = acc[i][j];
-          const float4 g = gv[j][q], x0 = xv[i][j][q];
+          const float4 g = gv[j][q], x0 = ep.fresh ? make_float4(0.f, 0.f, 0.f, 0.f) : xv[i][j][q];
           const float4 v = make_float4(x0.x + a[4 * q], x0.y + a[4 * q + 1], x0.z + a[4 * q + 2], x0.w + a[4 * q + 3]);
           if (in) *(float4*)(xrow + j * 32 + 8 * q) = v;
           sq += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
@@ -1008,14 +1011,17 @@ static void set_scale(GemmEpi& ep, const Ctx* c, const float* ss) {
   ep.ss = ss; ep.NS = n_slabs(c->d); ep.eps = c->cfg.rms_eps; ep.dnorm = c->d;
 }
 
-void mfma_gemm(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, GemmPlan p, hipStream_t s) {
+void mfma_gemm(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, GemmPlan p, hipStream_t s, RowMap out) {
   GemmEpi ep{};
+  ep.out = out;
   gemm_dispatch<EPI_PARTIAL>(A, W, C, M, N, K, p, ep, s);
 }
 
 // C = s_m * (A W): projection of the un-normalised bf16 residual with the RMSNorm factor applied afterwards
-void mfma_gemm_scaled(Ctx* c, const bf16_t* A, const bf16_t* W, float* C, const float* ss, int M, int N, int K, GemmPlan p, hipStream_t s) {
+void mfma_gemm_scaled(Ctx* c, const bf16_t* A, const bf16_t* W, float* C, const float* ss, int M, int N, int K, GemmPlan p, hipStream_t s,
+                      RowMap out) {
   GemmEpi ep{};
+  ep.out = out;
   set_scale(ep, c, ss);
   p.splits = 1;
   gemm_dispatch<EPI_PARTIAL>(A, W, C, M, N, K, p, ep, s);
@@ -1023,8 +1029,9 @@ void mfma_gemm_scaled(Ctx* c, const bf16_t* A, const bf16_t* W, float* C, const 
 
 // x += A W; also leaves bf16(x * g_next) packed and the per-slab sums of squares of the new x
 void mfma_gemm_resid(Ctx* c, const bf16_t* A, const bf16_t* W, float* x, bf16_t* xb, float* ss_out, const float* g_next, int M, int K,
-                     hipStream_t s, const WeightPrefetch& pf, int xb_T, int xb_pad) {
+                     hipStream_t s, const WeightPrefetch& pf, int xb_T, int xb_pad, bool fresh) {
   GemmEpi ep{};
+  ep.fresh = fresh;
   ep.pf = pf;
   ep.x = x; ep.xb = xb; ep.ss_out = ss_out; ep.g_next = g_next; ep.NS = n_slabs(c->d); ep.xb_T = xb_T; ep.xb_pad = xb_pad;
   const GemmPlan p = plan_resid(c, M);
@@ -1167,7 +1174,7 @@ __global__ __launch_bounds__(NW * QG * 64, (DH * NQB >= 256 ? 1 : 2)) void k_att
   // row are a causal block of their own on top of the kv_base + t0 keys in front of them.
   const int t0 = blockIdx.z * (NQ * QG), T = min(T_row - t0, NQ * QG), mq = r * T_row + t0;
   const int S = pos.kv_len ? pos.kv_len[r >> 1] : pos.kv_base + t0;
-  const int n_keys = S + T;
+  const int n_keys = S + tree.first + T;
   const int nsteps = (n_keys + 31) >> 5;
   const bf16_t* kb = kc + (size_t)r * row_stride + (size_t)hd * head_stride;
   const bf16_t* vb = vc + (size_t)r * row_stride + (size_t)hd * head_stride;
@@ -1482,7 +1489,7 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  const int S = kv, n_keys = S + T, nsteps = (n_keys + 31) >> 5;
+  const int S = kv, n_keys = S + ep.tree.first + T, nsteps = (n_keys + 31) >> 5;
   if (rs_thread) {                         // row factors
     const int row = threadIdx.x >> 2, part = threadIdx.x & 3;
     float t = 0.f;
@@ -1542,7 +1549,7 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
 #pragma unroll
   for (int u = threadIdx.x; u < BM * 8; u += 512) {     // k: one unit = (tile row, 8 dims), one 16-byte store each
     const int row = u % BM, c8 = (u / BM) * 8, t = row % TR;
-    const int slot = kv + t;
+    const int slot = kv + ep.tree.first + t;
     if (t < T && slot >= 0 && slot < ep.S_cap) {
       const float sc = rs[row];
       bf16_t* kh = ep.kc + (size_t)(2 * b + row / TR) * ep.row_stride + (size_t)hd * ep.head_stride;
@@ -1565,7 +1572,7 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
 #pragma unroll
   for (int u = threadIdx.x; u < BM * 16; u += 512) {    // v: one unit = (tile row, 4 dims); a store instruction covers runs of consecutive slots
     const int row = u % BM, c4 = (u / BM) * 4, t = row % TR;
-    const int slot = kv + t;
+    const int slot = kv + ep.tree.first + t;
     if (t < T && slot >= 0 && slot < ep.S_cap) {
       const float sc = rs[row];
       bf16_t* vh = ep.vc + (size_t)(2 * b + row / TR) * ep.row_stride + (size_t)hd * ep.head_stride;
