@@ -93,8 +93,11 @@ GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section, bool may_spli
 
 // q/k/v: 32 x 32 tiles on 8 waves while every tile has a CU of its own - a launch of few tiles lasts as long as one CU takes to pull its
 // operands in.  us per launch, 64 x 64 on 4 waves / 32 x 32 on 8: d 1280, 54 rows 10.2 / 9.0 (240 tiles); a step of 96 rows (360 tiles) 1823 / 1913.
+bool qkv_small_tiles(const Ctx* c, int M) {
+  return c->cfg.dtype == VVS_BF16 && (size_t)6 * c->d * c->d < kStreamed && (M + 31) / 32 * (3 * c->d / 32) <= 256;
+}
 GemmPlan plan_qkv(const Ctx* c, int M) {
-  if (c->cfg.dtype == VVS_BF16 && (size_t)6 * c->d * c->d < kStreamed && (M + 31) / 32 * (3 * c->d / 32) <= 256) return GemmPlan{32, 32, 1};
+  if (qkv_small_tiles(c, M)) return GemmPlan{32, 32, 1};
   return plan_gemm(c, M, 3 * c->d, c->d, c->d);
 }
 // a tile of the SwiGLU epilogue holds gate and up of its hidden units in one wave: 128 columns

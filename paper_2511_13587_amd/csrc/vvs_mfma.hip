@@ -1679,10 +1679,15 @@ int mfma_qkv_attention_rows(const Ctx* c, const PosDesc& pos, int T) {
   // A workgroup fills a CU, so (head, prompt) pairs beyond the 256 CUs run in rounds and lose to the separate kernels; of few pairs
   // each CU pulls 655 KB of weights while most stand idle, where a projection of its own deals them to all.  ms per step fused /
   // separate: 20 heads, 27 tokens, 1 prompt 1.58 / 1.45, 6 2.29 / 2.39, 16 4.06 / 3.83, 24 5.19 / 5.11, 32 6.32 / 5.95; 61 tokens, 1 2.19 / 1.81,
-  // 8 3.71 / 3.93, 16 6.37 / 5.81, 24 8.39 / 8.26; 6 tokens, 8 1.833 / 1.822, 13 2.72 / 2.12, 32 3.94 / 3.15; 12 heads, 6 tokens, 1 prompt 0.363 / 0.357,
-  // 16 0.449 / 0.481, 22 0.685 / 0.580.  (40 and 80 pairs: separate 5 and 2 % faster at 27 tokens, 18 and 9 % at 61; the launches of
+  // 8 3.71 / 3.93, 16 6.37 / 5.81, 24 8.39 / 8.26; 6 tokens, 8 1.833 / 1.822, 13 2.72 / 2.12, 32 3.94 / 3.15; 12 heads, 6 tokens,
+  // 16 prompts 0.449 / 0.481, 22 0.685 / 0.580.  (40 and 80 pairs: separate 5 and 2 % faster at 27 tokens, 18 and 9 % at 61; the launches of
   // 2 prompts are pinned by test_which_launches_a_layer_takes.)
-  if (c->H * c->B < 40 || c->H * c->B > 256) return 0;
+  // The same where the projection's 32 x 32 tiles all have a CU of their own (up to 64 rows at d 1280): 20 heads, 6 tokens, 2 prompts
+  // 1.51 / 1.34, 4 1.55 / 1.45; the drafting call of 8 prompts 0.462 / 0.446.  Not at small d, where the fused launch pulls no more than a
+  // launch's worth through a CU: 12 heads, 4 prompts x 6 0.390 / 0.383, 8 x 5 0.412 / 0.418, and a first pass on new buffers, which waits
+  // for the host, 0.54 / 0.63.
+  const int pairs = c->H * c->B;
+  if (pairs > 256 || (c->d >= 1024 && (pairs < 40 || qkv_small_tiles(c, c->R * T)))) return 0;
   return T <= 32 ? 32 : 64;
 }
 

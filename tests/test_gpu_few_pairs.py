@@ -8,10 +8,10 @@ from test_gpu_parity import gc, run_bf16_case, show  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-# 20 pairs: 14, 54, 64, 66 and 122 rows (one row-block, two, the last with every tile on a CU, one more); 36 pairs of 12 heads; 264 pairs
+# 20 pairs: 14, 54, 64, 66 and 122 rows (one row-block, two, the last with every tile on a CU, one more); 40 pairs and 64 rows; 264 pairs
 @pytest.mark.parametrize("model,prompts,n_nodes,widths,n_forced", [("xl", 1, 6, None, 33), ("xl", 1, 26, (4, 6, 6, 5, 5), 45), ("xl", 1, 31, (4, 6, 8, 8, 5), 20),
                                                                   ("xl", 1, 32, (4, 6, 8, 8, 6), 20), ("xl", 1, 60, (8, 12, 12, 10, 10, 8), 31),
-                                                                  ("b", 3, 5, None, 40), ("b", 22, 5, None, 9)])
+                                                                  ("xl", 2, 15, (4, 5, 6), 40), ("b", 22, 5, None, 9)])
 def test_projection_and_attention_apart(gc, model, prompts, n_nodes, widths, n_forced):  # noqa: F811
     base = synth.XL_TREE if model == "xl" else synth.B_SHAPE
     shape = base.replace(n_layers=2, n_prompts=prompts, n_nodes=n_nodes, tree_widths=widths)
