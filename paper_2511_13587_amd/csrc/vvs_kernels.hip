@@ -531,6 +531,143 @@ __global__ __launch_bounds__(256) void k_gemm_simple(const float* __restrict__ A
   if ((lane & 7) == 0 && m < M) C[(size_t)out(m) * N + n] = v;
 }
 
+// The same product with what stands around it in a launch-bound fp32 layer (K a multiple of 4, operands on 16 bytes):
+//   NORM   : A is the residual stream; its rows are normalised on the way in - the wave that multiplies a row holds all of it, so
+//            the sum of squares falls out of the same loads, the gain goes into the weight and the row factor into the result;
+//   F_RESID: C += A W^T (fresh: C = A W^T), the residual stream itself; an element belongs to one wave;
+//   F_SWIGLU: a wave takes the gate column n and the up column N + n and writes silu(gate) * up;
+//   F_QKV  : rotary embedding (the pair's other column is the neighbouring wave's), q in place, k and v into their cache slots.
+// Row i of A is row i * in_stride + in_off.  Against a norm, an add and a swiglu launch of their own a layer takes 5 launches instead
+// of 9; a launch is 3.5 us on the host and 2.5 to 4 on the GPU whatever it does (d 128: the loop of draft, similarity, verify and
+// commit 349 us with 92 launches, 234 with 58).  Larger fp32 models are bound by the products themselves.
+enum { F_STORE = 0, F_RESID = 1, F_SWIGLU = 2, F_QKV = 3 };
+struct SmallQkv { float *kc, *vc; const float* rope_tab; int T, d, dh, S_cap, rope_pos; size_t row_stride, head_stride; PosDesc pos; TreeDesc tree; };
+struct NoQkv {};
+template <bool NORM, int EPI, typename QKV>
+__global__ __launch_bounds__(256) void k_gemm_small(const float* __restrict__ A, const float* __restrict__ W, const float* __restrict__ g, float* C, int M,
+                                                    int N, int K, float eps, int in_stride, int in_off, int fresh, RowMap out, QKV qkv) {
+  constexpr int NC = EPI == F_SWIGLU ? 2 : 1;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = blockIdx.x * 4 + wave, m0 = blockIdx.y * 8;
+  if (n >= N) return;
+  const int m = m0 + (lane >> 3);          // the row whose result this lane ends with
+  const bool owner = (lane & 7) == 0 && m < M;
+  float old = 0.f;
+  if (EPI == F_RESID && owner && !fresh) old = C[(size_t)m * N + n];
+  // F_QKV: N = 3 d is a multiple of 4, so all waves of a workgroup are here; position and rotary factor while the operands come
+  int r = 0, sec = 0, slot = 0, img = -1;
+  float2 f = make_float2(1.f, 0.f);
+  if constexpr (EPI == F_QKV) {
+    r = min(m, M - 1) / qkv.T;
+    sec = n / qkv.d;
+    token_pos(qkv.pos, qkv.tree, r, min(m, M - 1) - r * qkv.T, &slot, &img);
+  }
+  const float4 *w[NC], *a[8];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) w[c] = (const float4*)(W + (size_t)(c * N + n) * K);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = (const float4*)(A + ((size_t)min(m0 + i, M - 1) * in_stride + in_off) * K);
+  float acc[NC + (NORM ? 1 : 0)][8];       // the columns' products, then the sums of squares
+#pragma unroll
+  for (auto& row : acc)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) row[i] = 0.f;
+  const int K4 = K >> 2;
+  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int k0 = 0; k0 < K4; k0 += 128) {
+    float4 wv[2][NC], gv[2], av[2][8];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (u == 1 && k0 + 64 >= K4) break;    // (uniform)
+      const int k = min(k0 + 64 * u + lane, K4 - 1);   // lanes past the end repeat the last piece
+#pragma unroll
+      for (int c = 0; c < NC; ++c) wv[u][c] = w[c][k];
+      if constexpr (NORM) gv[u] = ((const float4*)g)[k];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) av[u][i] = a[i][k];
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (u == 1 && k0 + 64 >= K4) break;
+      if (k0 + 64 * u + lane >= K4) {        // ... and add nothing
+#pragma unroll
+        for (int c = 0; c < NC; ++c) wv[u][c] = zero;
+        if constexpr (NORM) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) av[u][i] = zero;
+        }
+      }
+      if constexpr (NORM) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) wv[u][c] = make_float4(wv[u][c].x * gv[u].x, wv[u][c].y * gv[u].y, wv[u][c].z * gv[u].z, wv[u][c].w * gv[u].w);
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float4 x = av[u][i];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[c][i] += (x.x * wv[u][c].x + x.y * wv[u][c].y) + (x.z * wv[u][c].z + x.w * wv[u][c].w);
+        if constexpr (NORM) acc[NC][i] += (x.x * x.x + x.y * x.y) + (x.z * x.z + x.w * x.w);
+      }
+    }
+  }
+  if constexpr (EPI == F_QKV) {
+    if (img >= 0 && sec < 2) {
+      const int half = qkv.dh >> 1, e = n % qkv.dh, pv = e >= half ? img % qkv.pos.grid_w : min(img / qkv.pos.grid_w, qkv.rope_pos - 1);
+      f = *(const float2*)(qkv.rope_tab + ((size_t)pv * (qkv.dh >> 2) + ((e % half) >> 1)) * 2);
+    }
+  }
+  // sums over the lanes; lanes 8 j .. 8 j + 7 end with row j.  The first three steps halve the rows a lane carries (a row swap exchanges
+  // what two registers' halves do not keep), the last three add inside 8 lanes (as wave_reduce)
+#pragma unroll
+  for (auto& row : acc) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uintx2_t p = __builtin_amdgcn_permlane32_swap(__float_as_uint(row[i]), __float_as_uint(row[i + 4]), false, false);
+      row[i] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uintx2_t p = __builtin_amdgcn_permlane16_swap(__float_as_uint(row[i]), __float_as_uint(row[i + 2]), false, false);
+      row[i] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    }
+    const bool hi = lane & 8;
+    row[0] = (hi ? row[1] : row[0]) + dpp_move<0x128>(hi ? row[0] : row[1]);   // row_ror:8
+    row[0] += dpp_move<0x141>(row[0]);     // row_half_mirror
+    row[0] += dpp_move<0x4E>(row[0]);      // quad_perm:[2,3,0,1]
+    row[0] += dpp_move<0xB1>(row[0]);      // quad_perm:[1,0,3,2]
+  }
+  if constexpr (EPI == F_QKV) {
+    __shared__ float col[4][8];
+    const float v = acc[0][0] / sqrtf(acc[NC][0] / (float)K + eps);
+    if ((lane & 7) == 0) col[wave][lane >> 3] = v;
+    __syncthreads();
+    if (!owner) return;
+    const float p = col[wave ^ 1][lane >> 3], w0 = n & 1 ? p * f.y + v * f.x : v * f.x - p * f.y;
+    const int nd = n - sec * qkv.d, hd = nd / qkv.dh, e = nd % qkv.dh;
+    const size_t head = (size_t)r * qkv.row_stride + (size_t)hd * qkv.head_stride;
+    if (sec == 0) C[(size_t)m * qkv.d + nd] = w0;
+    else if (slot >= 0 && slot < qkv.S_cap) {
+      if (sec == 1) qkv.kc[head + k_index(slot, e, qkv.dh)] = w0;
+      else qkv.vc[head + v_index(slot, e, qkv.dh)] = v;
+    }
+    return;
+  }
+  if (!owner) return;
+  const float scale = NORM ? 1.0f / sqrtf(acc[NC][0] / (float)K + eps) : 1.f;
+  const float v = acc[0][0] * scale;
+  if constexpr (EPI == F_SWIGLU) C[(size_t)m * N + n] = v / (1.0f + expf(-v)) * (acc[NC - 1][0] * scale);
+  else if constexpr (EPI == F_RESID) C[(size_t)m * N + n] = old + v;
+  else C[(size_t)out(m) * N + n] = v;
+}
+
+template <bool NORM, int EPI, typename QKV = NoQkv>
+static void gemm_small(Ctx* c, const float* A, const char* W, const char* g, float* C, int M, int N, int K, hipStream_t s, int fresh = 0,
+                       RowMap out = RowMap{}, int in_stride = 1, int in_off = 0, const QKV& qkv = QKV{}) {
+  Timed timed(c, VVS_K_GEMM, s);
+  hipLaunchKernelGGL((k_gemm_small<NORM, EPI, QKV>), dim3((N + 3) / 4, (M + 7) / 8), dim3(256), 0, s, A, (const float*)W, (const float*)g, C, M, N, K,
+                     c->cfg.rms_eps, in_stride, in_off, fresh, out, qkv);
+}
+
 // C[splits][M][N] (fp32 partial sums) = A[M][K] * W[N][K]^T (bf16: both operands in packed fragment order)
 static int run_gemm(Ctx* c, const void* A, const void* W, float* C, int M, int N, int K, bool allow_split, hipStream_t s, RowMap out = RowMap{}) {
   GemmPlan p = plan_gemm(c, M, N, K, 0, allow_split);
@@ -636,6 +773,42 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
   }
 }
 
+// fp32, few rows of a narrow model: 5 launches per layer.
+static void forward_small(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, const int32_t* d_tokens_bt, const void* pc, const void* pu,
+                          int chunk_start, const int32_t* forced, int n_forced, int logits_mode, hipStream_t s, bool from_din) {
+  const int d = c->d, F = c->F, M = c->R * Tq;
+  float* x = (float*)(c->ws + c->w.x);
+  float* q = (float*)(c->ws + c->w.q);
+  float* attn = (float*)(c->ws + c->w.attn);
+  float* act = (float*)(c->ws + c->w.act);
+  if (from_din) {             // drafter: x = [embedding ; feature] W_fc
+    gemm_small<false, F_RESID>(c, (const float*)(c->ws + c->w.din), c->pw + c->p.fc, nullptr, x, M, d, 2 * d, s, 1);
+  } else {
+    Timed timed(c, VVS_K_ELEMENTWISE, s);
+    EmbedArgs ea{Tq, d, c->V, d_tokens_bt ? 0 : 1, d_tokens_bt, pc, pu, c->cfg.prefix_kind, c->cfg.n_classes, c->P, chunk_start, n_forced, forced};
+    hipLaunchKernelGGL(k_embed<float>, dim3(M), dim3(256), 0, s, x, (const float*)(c->pw + c->p.embed), (const float*)(c->pw + c->p.prefix_embed), ea);
+  }
+  for (int l = 0; l < c->L; ++l) {
+    const char* lw = c->pw + c->p.layer0 + c->p.layer_stride * l;
+    float *kc = (float*)c->kv + c->kv_layer_stride * l, *vc = kc + c->kv_v_off;
+    gemm_small<true, F_QKV>(c, x, lw + c->p.wqkv, lw + c->p.g1, q, M, 3 * d, d, s, 0, RowMap{}, 1, 0,
+                            SmallQkv{kc, vc, (const float*)(c->ws + c->w.rope_tab), Tq, d, c->dh, c->S_cap, c->rope_pos, c->kv_row_stride,
+                                     c->kv_head_stride, pos, tree});
+    { Timed timed(c, VVS_K_ATTENTION, s);
+      hipLaunchKernelGGL(k_attn_simple, dim3(Tq, c->H, c->R), dim3(256), sizeof(float) * (c->S_cap + 16), s, q, kc, vc, attn, tree, pos, Tq, d, c->dh,
+                         c->kv_row_stride, c->kv_head_stride, c->S_cap);
+    }
+    gemm_small<false, F_RESID>(c, attn, lw + c->p.wo, nullptr, x, M, d, d, s);
+    gemm_small<true, F_SWIGLU>(c, x, lw + c->p.wgu, lw + c->p.g2, act, M, F, d, s);
+    gemm_small<false, F_RESID>(c, act, lw + c->p.wd, nullptr, x, M, d, F, s);
+  }
+  if (logits_mode == 0) return;
+  float* logits = (float*)(c->ws + c->w.logits);
+  const char *wout = c->pw + c->p.wout, *gf = c->pw + c->p.gf;
+  if (logits_mode == 1) gemm_small<true, F_STORE>(c, x, wout, gf, logits, M, c->veff, d, s, 0, RowMap{Tq, tree.all, tree.first});
+  else gemm_small<true, F_STORE>(c, x, wout, gf, logits, c->R, c->veff, d, s, 0, RowMap{}, Tq, Tq - 1);   // last token of every row
+}
+
 template <typename T>
 static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, const int32_t* d_tokens_bt, const void* pc,
                       const void* pu, int chunk_start, const int32_t* forced, int n_forced, int logits_mode, hipStream_t s,
@@ -643,6 +816,11 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
   const int d = c->d, F = c->F, M = c->R * Tq;
   if (plan_fused(c, M)) {
     forward_fused(c, tree, pos, Tq, d_tokens_bt, pc, pu, chunk_start, forced, n_forced, logits_mode, s, from_din);
+    return;
+  }
+  // (wide models and many rows are bound by their products: the plain kernels, with the normalisation done once per row)
+  if (sizeof(T) == 4 && M <= 128 && d <= 1024 && F <= 4096) {
+    forward_small(c, tree, pos, Tq, d_tokens_bt, pc, pu, chunk_start, forced, n_forced, logits_mode, s, from_din);
     return;
   }
   float* x = (float*)(c->ws + c->w.x);

@@ -1,0 +1,41 @@
+"""GPU parity of the launch-bound fp32 layer (normalisation, rotary embedding, SwiGLU and residual sum inside the products) at the
+edges of its tiles: contraction lengths around 64 and 128 pieces of 4, rows around the 8 of a wave, and both sides of the
+limits beyond which the plain kernels run."""
+import numpy as np
+import pytest
+
+from paper_2511_13587_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gc():
+    import gpu_common
+    return gpu_common
+
+
+# (d, heads, d_ff, prompts, draft nodes, prefilled tokens): d and d_ff of 8, 256 and 264, 512 and 520 and 1024 values (2, 64, 66, 128, 130
+# and 256 pieces); 8, 10, 16, 18 and 128 rows; 130 rows (plain kernels); a cache almost full
+@pytest.mark.parametrize("d,heads,d_ff,prompts,nodes,tokens", [(8, 1, 8, 1, 3, 5), (256, 8, 264, 1, 4, 9), (264, 3, 256, 2, 3, 12), (512, 4, 520, 2, 7, 20),
+                                                              (520, 5, 1024, 3, 2, 7), (1024, 8, 512, 1, 4, 33), (128, 4, 344, 1, 63, 31),
+                                                              (128, 4, 344, 5, 12, 6), (128, 4, 344, 1, 5, 57)])
+def test_small_layer_fp32(gc, d, heads, d_ff, prompts, nodes, tokens):
+    shape = synth.TINY.replace(n_layers=2, d_model=d, n_heads=heads, d_ff=d_ff, n_prompts=prompts, n_nodes=nodes, grid_h=8 if nodes < 63 else 12,
+                               grid_w=8 if nodes < 63 else 12, tree_widths=None)
+    pair = gc.Pair(shape, gain_jitter=0.1)
+    pair.prefill(n_forced=tokens)
+    raw, _, _ = pair.gpu_logits()
+    assert np.abs(raw[:, 0] - pair.oracle.prefill_logits).max() < 1e-4
+    for call in range(2):
+        parent = synth.tree_parents(None, nodes) if call else np.maximum(np.arange(nodes) - 2, 0).astype(np.int32)
+        q, toks = synth.make_draft(shape, parent, call)
+        pair.verify(parent, toks, q, synth.make_uniforms(shape, nodes, call))
+        gc.check_logits(pair, f"d {d}, call {call}")
+        for r in (0, 2 * prompts - 1):
+            n = pair.oracle.kv_len(r // 2)
+            k, v = pair.ctx.vvs_debug_kv(1, r, n)
+            assert np.abs(k.cpu().numpy() - pair.oracle.kc[r][1][:n].reshape(n, -1)).max() < 1e-4
+            assert np.abs(v.cpu().numpy() - pair.oracle.vc[r][1][:n].reshape(n, -1)).max() < 1e-4
+        pair.commit()
+    pair.close()
