@@ -151,7 +151,7 @@ __device__ __forceinline__ void token_pos(const PosDesc& pos, const TreeDesc& tr
   if (pos.kv_len) {
     int b = r >> 1;
     *slot = pos.kv_len[b] + tree.first + t;
-    *img = pos.n_emitted[b] - 1 + tree.depth[t];
+    *img = pos.n_emitted[b] - 1 + tree.depth[tree.first + t];
   } else {
     *slot = pos.kv_base + t;
     *img = *slot - pos.prefix_len;

@@ -41,7 +41,7 @@ void launch_draft_zero_leaves(Ctx* dr, const TreeDesc& shape, float* d_probs, hi
   hipLaunchKernelGGL(k_draft_zero_rows, dim3(dr->B, leaves.n), dim3(256), 0, s, d_probs, leaves, shape.T, dr->veff);
 }
 
-// One workgroup per block token of this level, m = r * Tq + t - first: writes the row [embedding of the token ; feature] of the
+// One workgroup per block token of this level, m = r * (Tq - first) + t - first: writes the row [embedding of the token ; feature] of the
 // input map's operand (row-major fp32, or the packed bf16 operand order).
 //   t <  k: token = recent[b][t]; feature = the (k - t)-th newest entry of the target's ring of row r
 //           (zeros when the ring holds fewer entries);
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256) void k_draft_input(T* __restrict__ din, const 
                                                      const int32_t* __restrict__ draft_tokens, DraftLevel lv, int R, int d, int V,
                                                      int slots, int pre_norm, float eps) {
   __shared__ float red[16];
-  const int m = blockIdx.x, r = m / lv.Tq, t = lv.first + m % lv.Tq, b = r >> 1;   // block token t of row r
+  const int m = blockIdx.x, n = lv.Tq - lv.first, r = m / n, t = lv.first + m % n, b = r >> 1;   // block token t of row r
   int tok;
   const T* feat = nullptr;
   const float* xr = nullptr;
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256) void k_draft_input(T* __restrict__ din, const 
     if (e >= 0) feat = ring + ((size_t)r * slots + (oldest + e) % slots) * d;
   } else {
     tok = draft_tokens[b * lv.n_nodes + lv.node[t] - 1];
-    xr = x + ((size_t)r * lv.Tq_prev + lv.parent_slot[t] - lv.first_prev) * d;
+    xr = x + ((size_t)r * (lv.Tq_prev - lv.first_prev) + lv.parent_slot[t] - lv.first_prev) * d;
   }
   tok = min(max(tok, 0), V - 1);
   const T* emb = embed + (size_t)tok * d;
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(256) void k_draft_input(T* __restrict__ din, const 
 void launch_draft_input(Ctx* dr, const Ctx* tg, const DraftLevel& lv, const int32_t* d_recent, const int32_t* d_draft_tokens,
                         hipStream_t s) {
   Timed timed(dr, VVS_K_ELEMENTWISE, s);
-  const int M = dr->R * lv.Tq;
+  const int M = dr->R * (lv.Tq - lv.first);
   const float* x = (const float*)(dr->ws + dr->w.x);
   const float* gf = (const float*)(dr->pw + dr->p.gf);
   const int32_t* ring_state = (const int32_t*)(tg->ws + tg->w.ring_state);

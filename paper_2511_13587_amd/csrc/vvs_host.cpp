@@ -760,15 +760,10 @@ vvs_status vvs_draft(vvs_ctx* drafter, vvs_ctx* target, int32_t n_nodes, const i
     // level 0: the pairs; level l: the nodes of depth l that have children (no level up to the last is without)
     lv.first = level ? k + n_in : 0;
     while (n_in < (int)order.size() && shape.depth[order[n_in]] <= level) ++n_in;
-    lv.Tq = k + n_in - lv.first;
-    TreeDesc part{};
-    part.T = lv.Tq;
-    part.first = lv.first;
-    part.all = lv.all;
-    for (int t = 0; t < lv.Tq; ++t) {
-      part.depth[t] = block.depth[lv.first + t];
-      part.anc[t] = block.anc[lv.first + t];
-    }
+    lv.Tq = k + n_in;
+    block.T = lv.Tq;
+    block.first = lv.first;
+    block.all = lv.all;
     lv.n_sel = 0;
     for (int j = 0; j < T; ++j)
       if (shape.first_child[j] >= 0 && shape.depth[j] == level) {
@@ -777,7 +772,7 @@ vvs_status vvs_draft(vvs_ctx* drafter, vvs_ctx* target, int32_t n_nodes, const i
         ++lv.n_sel;
       }
     launch_draft_input(dr, tg, lv, d_recent_tokens, d_draft_tokens, st);
-    launch_forward(dr, part, pos, lv.Tq, nullptr, nullptr, nullptr, 0, nullptr, 0, 1, st, true);
+    launch_forward(dr, block, pos, lv.Tq, nullptr, nullptr, nullptr, 0, nullptr, 0, 1, st, true);
     launch_draft_select(dr, lv, shape, d_given_tokens, d_draft_tokens, d_draft_probs, st);
     lv.Tq_prev = lv.Tq;
     lv.first_prev = lv.first;

@@ -16,7 +16,7 @@ struct TreeDesc {
   int32_t T;                       // query tokens per row (root + N)
   int32_t causal;                  // 1: chain / prefill chunk (token i sees tokens 0..i of the block)
   int32_t n_forced;                // nodes 1..n_forced are accepted without a test (post verification)
-  int32_t first, all;              // drafting: the block's tokens first .. first + T - 1 of `all` (the others' K / V and logits stand already); else 0
+  int32_t first, all;              // drafting: a forward over tokens first .. T - 1 (K / V and logits of those in front stand already) of a block of `all`; else 0
   int8_t parent[VVS_MAX_T];        // parent[0] = -1
   int8_t depth[VVS_MAX_T];
   int8_t first_child[VVS_MAX_T];   // -1 = leaf
@@ -126,8 +126,8 @@ void launch_path_similarity(Ctx* c, const TreeDesc& tree, int n_nodes, const int
 // One level of a drafting call: which block token is which node of the candidate tree.
 struct DraftLevel {
   int32_t k;                        // context pairs (block tokens 0 .. k-1)
-  int32_t Tq, Tq_prev;              // block tokens per row of this level's forward and of the previous one
-  int32_t first, first_prev;        // the first of them
+  int32_t Tq, Tq_prev;              // block tokens per row up to this level and up to the previous one
+  int32_t first, first_prev;        // the first that is new
   int32_t all;                      // block tokens per row of the whole call
   int32_t n_nodes;                  // N of the candidate tree
   int8_t node[VVS_MAX_T];           // block token t >= k: its node id

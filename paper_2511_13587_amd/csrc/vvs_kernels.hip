@@ -395,7 +395,7 @@ __global__ __launch_bounds__(256) void k_attn_simple(const float* __restrict__ q
   const int t = blockIdx.x, hd = blockIdx.y, r = blockIdx.z, m = r * T_ + t;
   const int S = pos.kv_len ? pos.kv_len[r >> 1] : pos.kv_base;
   const int n = min(S + tree.first + T_, S_cap);
-  const uint64_t mask = tree.anc[t];
+  const uint64_t mask = tree.anc[tree.first + t];
   const float* qv = q + (size_t)m * d + (size_t)hd * dh;
   const float* kb = kc + (size_t)r * row_stride + (size_t)hd * head_stride;
   const float* vb = vc + (size_t)r * row_stride + (size_t)hd * head_stride;
@@ -913,8 +913,8 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
 void launch_forward(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, const int32_t* d_tokens_bt, const void* pc,
                     const void* pu, int chunk_start, const int32_t* forced, int n_forced, int logits_mode, hipStream_t s, bool from_din) {
   if (c->cfg.dtype == VVS_BF16)
-    forward_t<bf16_t>(c, tree, pos, T, d_tokens_bt, pc, pu, chunk_start, forced, n_forced, logits_mode, s, from_din);
-  else forward_t<float>(c, tree, pos, T, d_tokens_bt, pc, pu, chunk_start, forced, n_forced, logits_mode, s, from_din);
+    forward_t<bf16_t>(c, tree, pos, T - tree.first, d_tokens_bt, pc, pu, chunk_start, forced, n_forced, logits_mode, s, from_din);
+  else forward_t<float>(c, tree, pos, T - tree.first, d_tokens_bt, pc, pu, chunk_start, forced, n_forced, logits_mode, s, from_din);
 }
 
 // ------------------------------------------------------------------------------------------------ KV commit

@@ -207,7 +207,7 @@ struct EpiPre {
       const int m = min(tile_m * BM + (int)threadIdx.x % BM, M - 1), r = div_T(m, ep), b = ep.pos.kv_len ? r >> 1 : 0;
       kv = (ep.pos.kv_len ? ep.pos.kv_len : (const int32_t*)any)[b];
       ne = (ep.pos.kv_len ? ep.pos.n_emitted : (const int32_t*)any)[b];
-      dep = ep.tree.depth[min(m - r * ep.T, VVS_MAX_T - 1)];
+      dep = ep.tree.depth[min(ep.tree.first + m - r * ep.T, VVS_MAX_T - 1)];
     }
   }
   // (slot, image index) of this thread's row from what first() asked for
@@ -1186,7 +1186,7 @@ __global__ __launch_bounds__(NW * QG * 64, (DH * NQB >= 256 ? 1 : 2)) void k_att
     // query rows past T repeat row T - 1: a query only ever touches its own lanes' columns and rows >= T
     // are not stored, so nothing has to be zeroed - and no load result is needed before the first MFMA
     const int tq = min(q0 + qb * 16 + ql, T - 1);
-    mask[qb] = tree.anc[tq];
+    mask[qb] = tree.anc[tree.first + tq];
 #pragma unroll
     for (int kd = 0; kd < KD; ++kd)
       qf[qb][kd] = as_bf16x8(*(const uint4*)(q + ((size_t)mq + tq) * d + (size_t)hd * DH + kd * 32 + g * 8));
@@ -1525,7 +1525,7 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
       float v[16] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w, s2.x, s2.y, s2.z, s2.w, s3.x, s3.y, s3.z, s3.w};
 #pragma unroll
       for (int i = 0; i < 16; ++i) v[i] *= rs[row];
-      const int img = ne - 1 + ep.tree.depth[t];
+      const int img = ne - 1 + ep.tree.depth[ep.tree.first + t];
       if (img >= 0) {
         const int gr = min(img / ep.pos.grid_w, ep.rope_pos - 1), gc = img % ep.pos.grid_w;
         // 16 dims = 8 pairs inside one half of the head: 8 consecutive pairs of one table row
@@ -1553,7 +1553,7 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
     if (t < T && slot >= 0 && slot < ep.S_cap) {
       const float sc = rs[row];
       bf16_t* kh = ep.kc + (size_t)(2 * b + row / TR) * ep.row_stride + (size_t)hd * ep.head_stride;
-      const int img = ne - 1 + ep.tree.depth[t];
+      const int img = ne - 1 + ep.tree.depth[ep.tree.first + t];
       const float4 a = *(const float4*)(red + row * LDC + DH + c8), bq = *(const float4*)(red + row * LDC + DH + c8 + 4);
       float v[8] = {a.x * sc, a.y * sc, a.z * sc, a.w * sc, bq.x * sc, bq.y * sc, bq.z * sc, bq.w * sc};
       if (img >= 0) {
@@ -1594,7 +1594,7 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) {
     const int tq = min(q0 + qb * 16 + ql, T - 1);      // query rows past T repeat row T - 1 and are not stored
-    mask[qb] = ep.tree.anc[tq];
+    mask[qb] = ep.tree.anc[ep.tree.first + tq];
 #pragma unroll
     for (int kd = 0; kd < KD; ++kd) qf[qb][kd] = as_bf16x8(*(const uint4*)(q_s + (ar * TR + tq) * QLD + kd * 32 + g * 8));
   }
