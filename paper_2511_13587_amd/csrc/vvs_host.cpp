@@ -26,19 +26,20 @@ static vvs_status fail(std::string* err, vvs_status st, const std::string& msg) 
 // cannot disagree about which XCD reads which weight tile.
 //
 // Tiles whose operands are shared through LDS (k_gemm_shared_dma).  A CU is filled at about 64 GB/s whatever the tile, so a stage of 32
-// contraction values costs about 1 ns per tile row and column until the matrix cores are the slower side (256 x 256); a launch
-// lasts as many of these as its fullest CU works through, no less than its weights take from HBM (6 TB/s), and what start,
-// epilogue and the partial sums of a K split take beside.  The table is measured (us per stage of a bare product, weights from HBM,
-// at M from 48 to 4096 and the N and K of d 4096, d_ff 11008 and d 1280, d_ff 3456); the tile of least cost is taken.  us per launch with
-// the rule before (64-row tiles up to 192 rows, then 128 x 128 or 256 x 256) / with this one:
-//   126 rows, d 4096: gate/up 57.8 / 49.2 (128 x 128), QKV 36.5 / 37.1 (128 x 64), O and down, mean, 22.4 / 21.2 (128 x 64, K in 4)
-//   388 rows, d 4096: gate/up 112 / 94 (256 x 256), QKV 67 / 68 (256 x 128), O 26 / 23.5 (128 x 128, K in 2), down 66 / 50 (256 x 128, K in 4)
-//   1920 rows, d 1280: gate/up 43.5 / 42.0 (256 x 256)
+// contraction values costs about 1 ns per tile row and column until the matrix cores are the slower side (256 x 256); start and
+// epilogue cost every round of tiles again, by the tile's area and what is written; a launch lasts as many rounds as its fullest CU works
+// through, and no less than its weights take from HBM (6 TB/s).  The tile of least cost is taken.  us per launch, measured / by this
+// table, at 3904 and 1920 rows of d 1280, d_ff 3456 and 388 of d 4096, d_ff 11008:
+//   gate/up  128 x 128: 85, 44, 114 / 80, 44, 103   192 x 128: 100, 56, 133 / 96, 57, 139   256 x 128: 98, 48, 116 / 95, 48, 115   256 x 256: 79, 41, 94 / 80, 40, 95
+//   q/k/v    128 x 128: 61, 30, 68 / 60, 30, 68     192 x 128: 76, 45, 99 / 77, 51, 106     256 x 128: 67, 34, 68 / 65, 33, 66     256 x 256: 57, 51, 98 / 58, 58, 112
+// Launches of a d 4096 step with the rule before (64-row tiles up to 192 rows) / with this one: 126 rows gate/up 57.8 / 49.2 (128 x 128), O and
+// down, mean, 22.4 / 21.2 (128 x 64, K in 4); 388 rows gate/up 112 / 94, O 26 / 23.5 (128 x 128, K in 2), down 66 / 50 (256 x 128, K in 4).
 static GemmPlan plan_shared(int M, int N, int K, int section, bool may_split, int min_bn) {
   struct Tile { int bm, bn; double stage, lone; bool pair; };      // pair: two workgroups fit a CU; lone: one of such a pair by itself
-  static const Tile tiles[] = {{64, 64, 0.155, 0.155, true},   {64, 128, 0.215, 0.215, true},   {128, 64, 0.19, 0.19, true},  {128, 128, 0.215, 0.34, true},
-                               {128, 128, 0.25, 0.25, false},  {192, 64, 0.24, 0.24, false},    {192, 128, 0.33, 0.33, false},
-                               {256, 128, 0.415, 0.415, false}, {256, 256, 0.69, 0.69, false}};
+  static const Tile tiles[] = {{64, 64, 0.155, 0.155, true},   {64, 128, 0.21, 0.21, true},    {128, 64, 0.19, 0.19, true},  {128, 128, 0.215, 0.34, true},
+                               {128, 128, 0.245, 0.245, false}, {192, 64, 0.23, 0.23, false},   {192, 128, 0.31, 0.31, false},
+                               {256, 128, 0.385, 0.385, false}, {256, 256, 0.62, 0.62, false}};
+  const double area = section ? 4.8e-4 : min_bn > 64 ? 2.1e-4 : 4.5e-4;   // us per value: q/k/v in cache order, one bf16 for two, fp32
   const int rows = (int)align_up(M, 32), nst = K / 32;             // limits on multiples of 32 rows (plan_sizes)
   GemmPlan best{0, 0, 1};
   double least = 1e30;
@@ -50,10 +51,16 @@ static GemmPlan plan_shared(int M, int N, int K, int section, bool may_split, in
       if (splits != want || (splits > 1 && per < 16)) continue;
       // 128 x 128 stands twice: 8 slots, one workgroup per CU, for a single round; 4 slots, two per CU, for more
       if (t.bm == 128 && t.bn == 128 && t.pair != (all > 256)) continue;
-      const int pairs = all / 512, rest = all % 512;
-      const double rounds = t.pair ? 2 * t.stage * pairs + (rest == 0 ? 0 : rest <= 256 ? t.lone : 2 * t.stage) : t.stage * ((all + 255) / 256);
-      const double cost = std::max(rounds * per, 2e-6 * N * K / 6.0) + 3.0 + 4e-5 * t.bm * t.bn + (may_split ? 8e-6 * rows * N * splits / 5.0 : 0.0);
-      if (cost < least) { least = cost; best = GemmPlan{t.bm, t.bn, splits, false, true}; }
+      const double once = 1.5 + area * t.bm * t.bn;                // start and epilogue
+      double us;
+      if (t.pair && all > 256) {                                   // rounds of two per CU; a rest of up to one per CU runs beside the others' epilogues
+        const int pairs = all / 512 + (all % 512 > 256), rest = all % 512 > 256 ? 0 : all % 512;
+        us = pairs * (2 * t.stage * per + 1.5 + 1.45 * area * t.bm * t.bn) + (rest ? t.lone * per : 0.0);
+      } else {
+        us = (all + 255) / 256 * (t.stage * per + once);
+      }
+      us = std::max(us, 2e-6 * N * K / 6.0 + once) + (may_split ? 4e-6 * rows * N * splits / 5.0 : 0.0);   // ... and the sums are read again
+      if (us < least) { least = us; best = GemmPlan{t.bm, t.bn, splits, false, true}; }
     }
   }
   return best;
@@ -68,7 +75,7 @@ GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section, bool may_spli
   p.bm = M <= 32 ? 32 : 64;
   // Operands shared through LDS where a launch has many 128 x 128 tiles, or where the weights are large and the rows more than one
   // row-block: a CU then has whole rows of stages to work through, and each weight byte feeds twice the MFMAs
-  if (M > 32 && N % 128 == 0 && ((M > 192 && ((M + 127) / 128) * (N / 128) >= 160) || (size_t)N * K * 2 >= kStreamed))
+  if (N % 128 == 0 && ((M > 192 && ((M + 127) / 128) * (N / 128) >= 160) || ((size_t)N * K * 2 >= kStreamed && (M > 32 || K >= 2048))))
     return plan_shared(M, N, K, section, may_split, min_bn);
   // 64 x 128 tiles when they give one workgroup for (nearly) every CU and no second round: a CU then
   // pulls (64 + 128) K-rows through its L1 instead of 2 x (64 + 64)
