@@ -1738,7 +1738,11 @@ void mfma_attention(Ctx* c, int layer, const TreeDesc& tree, const PosDesc& pos,
   // 4 waves per workgroup keep the register footprint low enough for 2-3 workgroups per CU, so that
   // every (head, row) pair of a call is resident at once
   if (c->dh == 64) {
-    if (nqb == 1) VVS_ATTN(64, 1, 4, 2, 1); else if (nqb == 2) VVS_ATTN(64, 2, 4, 2, 1); else VVS_ATTN(64, 2, 2, 2, 2);   // 33 .. 64 queries: two groups of 32
+    if (nqb == 1) VVS_ATTN(64, 1, 4, 2, 1); else if (nqb == 2) VVS_ATTN(64, 2, 4, 2, 1); else if (!pos.kv_len && slice * nz >= 512) VVS_ATTN(64, 2, 2, 1, 2);   // 33 .. 64 queries: two groups of 32
+    // a prefill of two workgroups per CU and more: one operand set is enough, its registers keep another workgroup resident, which covers the
+    // loads better than a second set (20 heads, prefix of 120 tokens: 8 prompts 11.4 -> 9.7 us).  Few workgroups lose (40 of them 8.75 -> 9.6),
+    // and so do verify calls on long caches (step of 32 x 61 tokens on 620 keys 10.46 -> 10.64 ms, on 408 level).
+    else VVS_ATTN(64, 2, 2, 2, 2);
   } else {
     if (nqb == 1) VVS_ATTN(128, 1, 4, 2, 1); else VVS_ATTN(128, 2, 4, 2, 1);   // verify calls: T <= 32 is enforced at context creation for head size 128
   }
