@@ -1687,7 +1687,10 @@ int mfma_qkv_attention_rows(const Ctx* c, const PosDesc& pos, int T) {
   // launch's worth through a CU: 12 heads, 4 prompts x 6 0.390 / 0.383, 8 x 5 0.412 / 0.418, and a first pass on new buffers, which waits
   // for the host, 0.54 / 0.63.
   const int pairs = c->H * c->B;
-  if (pairs > 256 || (c->d >= 1024 && (pairs < 40 || qkv_small_tiles(c, c->R * T)))) return 0;
+  // (a narrow model fills a second round of nearly whole tiles well: 12 heads, 32 prompts x 61 tokens 1.94 / 2.01, but 30 x 51 1.77 / 1.70 and
+  // 24 x 41 1.40 / 1.30)
+  const bool two_rounds = c->d < 1024 && T > 56 && pairs > 372 && pairs <= 512;
+  if ((pairs > 256 && !two_rounds) || (c->d >= 1024 && (pairs < 40 || qkv_small_tiles(c, c->R * T)))) return 0;
   return T <= 32 ? 32 : 64;
 }
 
