@@ -917,6 +917,66 @@ void launch_forward(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, con
   else forward_t<float>(c, tree, pos, T - tree.first, d_tokens_bt, pc, pu, chunk_start, forced, n_forced, logits_mode, s, from_din);
 }
 
+// ------------------------------------------------------------------------------------------------ token-level feature cache
+// Section 4.3 / Algorithm 2 "UpdateCache".  The features of n tokens of the last forward (rows
+// r * Tq + node of the residual stream x) are appended to the ring of row r: a feature is
+// rmsnorm(x) * gf - the input of the output head - or x itself (pre_norm), stored like an activation
+// of the model.  Ring state per row: (entries held, slot of the oldest); the token appended as the
+// k-th since the oldest goes to slot (oldest + held + k) % slots.  One workgroup per (row, appended
+// token); only the last `slots` tokens of a push are written (older ones would be overwritten by it).
+//   path != nullptr: commit - the tokens are path[b][0 .. accept_len[b]] (skipped for finished prompts); a slice of the launch
+//                    that moves the cache, of which it needs nothing (a launch of its own: 5 us behind it); the ring state is
+//                    advanced afterwards by k_commit_state;
+//   path == nullptr: prefill - the single token fixed_node into an emptied ring (state written here).
+struct PushArgs {
+  const float *x, *gf;
+  void* ring;
+  int32_t* ring_state;
+  const int32_t *accept_len, *next_token, *path;
+  int Tq, fixed_node, R, d, slots, pre_norm;
+  float eps;
+};
+
+// row r, appended token `at`
+template <typename T>
+__device__ __forceinline__ void push_feature(const PushArgs& a, int r, int at) {
+  __shared__ float red[16];
+  const int b = r >> 1;
+  int n = 1, held = 0, oldest = 0;
+  if (a.path) {
+    if (a.next_token[b] < 0) return;
+    n = a.accept_len[b] + 1;
+    held = a.ring_state[r];
+    oldest = a.ring_state[a.R + r];
+  }
+  const int i = max(0, n - a.slots) + at;
+  if (i >= n) return;
+  const int node = a.path ? a.path[b * VVS_MAX_T + i] : a.fixed_node;
+  const float* xr = a.x + ((size_t)r * a.Tq + node) * a.d;
+  float scale = 1.f;
+  if (!a.pre_norm) {
+    float ss = 0.f;
+    for (int k = threadIdx.x; k < a.d; k += blockDim.x) ss += xr[k] * xr[k];
+    ss = block_sum(ss, red);
+    scale = 1.0f / sqrtf(ss / (float)a.d + a.eps);
+  }
+  T* dst = (T*)a.ring + ((size_t)r * a.slots + (oldest + held + i) % a.slots) * a.d;
+  for (int k = threadIdx.x; k < a.d; k += blockDim.x) st(dst + k, a.pre_norm ? xr[k] : xr[k] * scale * a.gf[k]);
+  if (!a.path && threadIdx.x == 0) {
+    a.ring_state[r] = 1;
+    a.ring_state[a.R + r] = 0;
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_push_features(PushArgs a) { push_feature<T>(a, blockIdx.x, blockIdx.y); }
+
+static PushArgs push_args(Ctx* c, const int32_t* path, int Tq, int fixed_node) {
+  const int32_t* oc = (const int32_t*)(c->ws + c->w.outcome);
+  return PushArgs{(const float*)(c->ws + c->w.x), (const float*)(c->pw + c->p.gf), c->ws + c->w.ring, (int32_t*)(c->ws + c->w.ring_state), oc, oc + c->B, path,
+                  Tq, fixed_node, c->R, c->d, c->cfg.feature_slots, c->cfg.feature_pre_norm, c->cfg.rms_eps};
+}
+
 // ------------------------------------------------------------------------------------------------ KV commit
 // Slot S + path[i] moves to slot S + i for the accepted positions i = 1..a.  path is strictly
 // increasing with path[i] >= i, so a destination is never a source of a later position.  A thread
@@ -927,10 +987,14 @@ template <typename T, typename CT>
 __global__ __launch_bounds__(256) void k_commit_kv(T* __restrict__ kcache, T* __restrict__ vcache, const int32_t* __restrict__ kv_len,
                                                    const int32_t* __restrict__ accept_len, const int32_t* __restrict__ next_token,
                                                    const int32_t* __restrict__ path, int H, int dh, size_t layer_stride,
-                                                   size_t row_stride, size_t head_stride, int S_cap) {
+                                                   size_t row_stride, size_t head_stride, int S_cap, int n_layers, PushArgs push) {
   constexpr int CH = sizeof(CT) / sizeof(T);   // elements per K chunk
   __shared__ int s_src[VVS_MAX_T];
   const int r = blockIdx.x, l = blockIdx.y, b = r >> 1;
+  if (l == n_layers) {                         // the slice behind the layers: the feature ring
+    if ((int)blockIdx.z < push.slots) push_feature<T>(push, r, blockIdx.z);
+    return;
+  }
   if (next_token[b] < 0) return;
   const int S = kv_len[b], a = accept_len[b];
   if (threadIdx.x < VVS_MAX_T) s_src[threadIdx.x] = path[b * VVS_MAX_T + threadIdx.x];
@@ -993,8 +1057,6 @@ __global__ void k_commit_state(int32_t* __restrict__ state, int32_t* __restrict_
   }
 }
 
-static void launch_push_features(Ctx* c, const int32_t* path, int Tq, int fixed_node, hipStream_t s);
-
 void launch_commit(Ctx* c, hipStream_t s) {
   Timed timed(c, VVS_K_COMMIT, s);
   int32_t* state = (int32_t*)(c->ws + c->w.state);
@@ -1004,84 +1066,30 @@ void launch_commit(Ctx* c, hipStream_t s) {
   const int32_t* path = oc + 2 * c->B;
   const bool vec = (c->dh * c->esz) % 16 == 0;
   const int items = c->H * c->dh / (vec ? 16 / (int)c->esz : 1) + c->H * c->dh;   // K chunks + V elements per (row, layer)
-  dim3 grid(c->R, c->L, (items + 255) / 256);
+  const int slots = std::max(c->cfg.feature_slots, 0);
+  const PushArgs push = push_args(c, path, c->last_T, -1);
+  dim3 grid(c->R, c->L + (slots > 0), std::max((items + 255) / 256, slots));
   if (c->cfg.dtype == VVS_BF16 && vec)
     hipLaunchKernelGGL((k_commit_kv<bf16_t, uint4>), grid, dim3(256), 0, s, (bf16_t*)c->kv, (bf16_t*)c->kv + c->kv_v_off, state, accept_len,
-                       next_token, path, c->H, c->dh, c->kv_layer_stride, c->kv_row_stride, c->kv_head_stride, c->S_cap);
+                       next_token, path, c->H, c->dh, c->kv_layer_stride, c->kv_row_stride, c->kv_head_stride, c->S_cap, c->L, push);
   else if (c->cfg.dtype == VVS_BF16)
     hipLaunchKernelGGL((k_commit_kv<bf16_t, bf16_t>), grid, dim3(256), 0, s, (bf16_t*)c->kv, (bf16_t*)c->kv + c->kv_v_off, state, accept_len,
-                       next_token, path, c->H, c->dh, c->kv_layer_stride, c->kv_row_stride, c->kv_head_stride, c->S_cap);
+                       next_token, path, c->H, c->dh, c->kv_layer_stride, c->kv_row_stride, c->kv_head_stride, c->S_cap, c->L, push);
   else if (vec)
     hipLaunchKernelGGL((k_commit_kv<float, uint4>), grid, dim3(256), 0, s, (float*)c->kv, (float*)c->kv + c->kv_v_off, state, accept_len,
-                       next_token, path, c->H, c->dh, c->kv_layer_stride, c->kv_row_stride, c->kv_head_stride, c->S_cap);
+                       next_token, path, c->H, c->dh, c->kv_layer_stride, c->kv_row_stride, c->kv_head_stride, c->S_cap, c->L, push);
   else
     hipLaunchKernelGGL((k_commit_kv<float, float>), grid, dim3(256), 0, s, (float*)c->kv, (float*)c->kv + c->kv_v_off, state, accept_len,
-                       next_token, path, c->H, c->dh, c->kv_layer_stride, c->kv_row_stride, c->kv_head_stride, c->S_cap);
-  launch_push_features(c, path, c->last_T, -1, s);
+                       next_token, path, c->H, c->dh, c->kv_layer_stride, c->kv_row_stride, c->kv_head_stride, c->S_cap, c->L, push);
   hipLaunchKernelGGL(k_commit_state, dim3((c->B + 63) / 64), dim3(64), 0, s, state, (int32_t*)(c->ws + c->w.ring_state),
                      c->cfg.feature_slots, accept_len, next_token, c->B);
 }
 
-// ------------------------------------------------------------------------------------------------ token-level feature cache
-// Section 4.3 / Algorithm 2 "UpdateCache".  The features of n tokens of the last forward (rows
-// r * Tq + node of the residual stream x) are appended to the ring of row r: a feature is
-// rmsnorm(x) * gf - the input of the output head - or x itself (pre_norm), stored like an activation
-// of the model.  Ring state per row: (entries held, slot of the oldest); the token appended as the
-// k-th since the oldest goes to slot (oldest + held + k) % slots.  One workgroup per (row, appended
-// token); only the last `slots` tokens of a push are written (older ones would be overwritten by it).
-//   path != nullptr: commit - the tokens are path[b][0 .. accept_len[b]] (skipped for finished prompts);
-//                    the ring state is advanced afterwards by k_commit_state;
-//   path == nullptr: prefill - the single token fixed_node into an emptied ring (state written here).
-template <typename T>
-__global__ __launch_bounds__(256) void k_push_features(const float* __restrict__ x, const float* __restrict__ gf, T* __restrict__ ring,
-                                                       int32_t* __restrict__ ring_state, const int32_t* __restrict__ accept_len,
-                                                       const int32_t* __restrict__ next_token, const int32_t* __restrict__ path, int Tq,
-                                                       int fixed_node, int R, int d, int slots, int pre_norm, float eps) {
-  __shared__ float red[16];
-  const int r = blockIdx.x, b = r >> 1;
-  int n = 1, held = 0, oldest = 0;
-  if (path) {
-    if (next_token[b] < 0) return;
-    n = accept_len[b] + 1;
-    held = ring_state[r];
-    oldest = ring_state[R + r];
-  }
-  const int i = max(0, n - slots) + blockIdx.y;
-  if (i >= n) return;
-  const int node = path ? path[b * VVS_MAX_T + i] : fixed_node;
-  const float* xr = x + ((size_t)r * Tq + node) * d;
-  float scale = 1.f;
-  if (!pre_norm) {
-    float ss = 0.f;
-    for (int k = threadIdx.x; k < d; k += blockDim.x) ss += xr[k] * xr[k];
-    ss = block_sum(ss, red);
-    scale = 1.0f / sqrtf(ss / (float)d + eps);
-  }
-  T* dst = ring + ((size_t)r * slots + (oldest + held + i) % slots) * d;
-  for (int k = threadIdx.x; k < d; k += blockDim.x) st(dst + k, pre_norm ? xr[k] : xr[k] * scale * gf[k]);
-  if (!path && threadIdx.x == 0) {
-    ring_state[r] = 1;
-    ring_state[R + r] = 0;
-  }
-}
-
-static void launch_push_features(Ctx* c, const int32_t* path, int Tq, int fixed_node, hipStream_t s) {
-  if (c->cfg.feature_slots < 1) return;
-  const int32_t* oc = (const int32_t*)(c->ws + c->w.outcome);
-  const float* x = (const float*)(c->ws + c->w.x);
-  const float* gf = (const float*)(c->pw + c->p.gf);
-  int32_t* rstate = (int32_t*)(c->ws + c->w.ring_state);
-  dim3 grid(c->R, path ? c->cfg.feature_slots : 1);
-  if (c->cfg.dtype == VVS_BF16)
-    hipLaunchKernelGGL(k_push_features<bf16_t>, grid, dim3(256), 0, s, x, gf, (bf16_t*)(c->ws + c->w.ring), rstate, oc, oc + c->B, path,
-                       Tq, fixed_node, c->R, c->d, c->cfg.feature_slots, c->cfg.feature_pre_norm, c->cfg.rms_eps);
-  else
-    hipLaunchKernelGGL(k_push_features<float>, grid, dim3(256), 0, s, x, gf, (float*)(c->ws + c->w.ring), rstate, oc, oc + c->B, path,
-                       Tq, fixed_node, c->R, c->d, c->cfg.feature_slots, c->cfg.feature_pre_norm, c->cfg.rms_eps);
-}
-
 void launch_push_prefill_feature(Ctx* c, int T_last_chunk, hipStream_t s) {
-  launch_push_features(c, nullptr, T_last_chunk, T_last_chunk - 1, s);
+  if (c->cfg.feature_slots < 1) return;
+  const PushArgs push = push_args(c, nullptr, T_last_chunk, T_last_chunk - 1);
+  if (c->cfg.dtype == VVS_BF16) hipLaunchKernelGGL(k_push_features<bf16_t>, dim3(c->R), dim3(256), 0, s, push);
+  else hipLaunchKernelGGL(k_push_features<float>, dim3(c->R), dim3(256), 0, s, push);
 }
 
 template <typename T>
