@@ -48,6 +48,7 @@ static GemmPlan plan_shared(int M, int N, int K, int section, bool may_split, in
     const int n = (rows + t.bm - 1) / t.bm * (N / t.bn);
     for (int want = 1; want <= (may_split ? 8 : 1); ++want) {
       const int per = (nst + want - 1) / want, splits = (nst + per - 1) / per, all = n * splits;
+      if (want > 1 && n * (want - 1) >= 512) break;                // two rounds of tiles need no further shares
       if (splits != want || (splits > 1 && per < 16)) continue;
       // 128 x 128 stands twice: 8 slots, one workgroup per CU, for a single round; 4 slots, two per CU, for more
       if (t.bm == 128 && t.bn == 128 && t.pair != (all > 256)) continue;
@@ -66,6 +67,10 @@ static GemmPlan plan_shared(int M, int N, int K, int section, bool may_split, in
   return best;
 }
 
+static bool takes_shared(int M, int N, int K) {
+  return N % 128 == 0 && ((M > 192 && ((M + 127) / 128) * (N / 128) >= 160) || ((size_t)N * K * 2 >= kStreamed && (M > 32 || K >= 2048)));
+}
+
 GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section, bool may_split, int min_bn) {
   GemmPlan p{64, 64, 1};
   if (c->cfg.dtype != VVS_BF16) return p;           // fp32 path: one wave per output column, no split
@@ -75,8 +80,7 @@ GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section, bool may_spli
   p.bm = M <= 32 ? 32 : 64;
   // Operands shared through LDS where a launch has many 128 x 128 tiles, or where the weights are large and the rows more than one
   // row-block: a CU then has whole rows of stages to work through, and each weight byte feeds twice the MFMAs
-  if (N % 128 == 0 && ((M > 192 && ((M + 127) / 128) * (N / 128) >= 160) || ((size_t)N * K * 2 >= kStreamed && (M > 32 || K >= 2048))))
-    return plan_shared(M, N, K, section, may_split, min_bn);
+  if (takes_shared(M, N, K)) return plan_shared(M, N, K, section, may_split, min_bn);
   // 64 x 128 tiles when they give one workgroup for (nearly) every CU and no second round: a CU then
   // pulls (64 + 128) K-rows through its L1 instead of 2 x (64 + 64)
   if (p.bm == 64 && N % 128 == 0) {
@@ -215,6 +219,7 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   for (int M = 32; M <= c->Mmax; M += 32)
     for (auto& sh : shapes) {
       if (sh[1] == 2 * d && !g.draft_input) continue;
+      if (g.dtype == VVS_BF16 && sh[0] != d && takes_shared(M, sh[0], sh[1])) continue;   // whole sums, written by the projection's own epilogue
       GemmPlan p = sh[0] == 3 * d ? plan_qkv(c, M) : sh[0] == 2 * F ? plan_gate_up(c, M) : plan_gemm(c, M, sh[0], sh[1], 0, true);
       if (g.dtype == VVS_BF16 && p.splits == 1 && sh[0] != d) continue;   // written by the projection's own epilogue
       go = std::max(go, (size_t)p.splits * M * sh[0]);
