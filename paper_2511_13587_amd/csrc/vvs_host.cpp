@@ -102,6 +102,9 @@ GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section, bool may_spli
   return p;
 }
 
+// A projection that leaves partial sums for the kernel behind it (run_gemm)
+GemmPlan plan_partial(const Ctx* c, int M, int N, int K) { return plan_gemm(c, M, N, K, 0, true); }
+
 // q/k/v: 32 x 32 tiles on 8 waves while every tile has a CU of its own - a launch of few tiles lasts as long as one CU takes to pull its
 // operands in.  us per launch, 64 x 64 on 4 waves / 32 x 32 on 8: d 1280, 54 rows 10.2 / 9.0 (240 tiles); a step of 96 rows (360 tiles) 1823 / 1913.
 bool qkv_small_tiles(const Ctx* c, int M) {
@@ -211,19 +214,21 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   c->kv_row_stride = c->kv_head_stride * c->H;
   c->kv_layer_stride = c->kv_row_stride * c->R;
   c->kv_v_off = c->kv_layer_stride * c->L;
-  // GEMM partial-sum buffer: worst case over every M this context can be asked for.  All limits of a plan lie on multiples of 32
-  // rows, so the largest M of each block of 32 stands for the block.
+  // GEMM partial-sum buffer: worst case over every M this context can be asked for, projection by projection, each with the plan that its
+  // launch takes (run_gemm; told apart by their sizes, two with the same columns or contraction would get one plan).  Sums that come whole
+  // are written by the projection's own epilogue where it has one.  All limits of a plan lie on multiples of 32 rows, so the largest M of
+  // each block of 32 stands for the block.
   size_t go = 0;
-  int d = c->d, F = c->F;
-  const int shapes[5][2] = {{3 * d, d}, {d, d}, {2 * F, d}, {d, F}, {d, 2 * d}};   // the last one: a drafter's input map
-  for (int M = 32; M <= c->Mmax; M += 32)
-    for (auto& sh : shapes) {
-      if (sh[1] == 2 * d && !g.draft_input) continue;
-      if (g.dtype == VVS_BF16 && sh[0] != d && takes_shared(M, sh[0], sh[1])) continue;   // whole sums, written by the projection's own epilogue
-      GemmPlan p = sh[0] == 3 * d ? plan_qkv(c, M) : sh[0] == 2 * F ? plan_gate_up(c, M) : plan_gemm(c, M, sh[0], sh[1], 0, true);
-      if (g.dtype == VVS_BF16 && p.splits == 1 && sh[0] != d) continue;   // written by the projection's own epilogue
-      go = std::max(go, (size_t)p.splits * M * sh[0]);
-    }
+  const int d = c->d, F = c->F;
+  for (int M = 32; M <= c->Mmax; M += 32) {
+    auto sums = [&](int N, int K) { go = std::max(go, (size_t)plan_partial(c, M, N, K).splits * M * N); };
+    const bool bf16 = g.dtype == VVS_BF16;
+    if (!bf16 || (!takes_shared(M, 3 * d, d) && plan_qkv(c, M).splits > 1)) sums(3 * d, d);   // (the shared-operand tiles of the two: whole sums)
+    if (!bf16 || (!takes_shared(M, 2 * F, d) && plan_gate_up(c, M).splits > 1)) sums(2 * F, d);
+    sums(d, d);                              // O
+    sums(d, F);                              // down
+    if (g.draft_input) sums(d, 2 * d);       // a drafter's input map
+  }
   c->gemm_out_elems = go;
   // workspace carve-up
   Workspace& w = c->w;
@@ -845,7 +850,7 @@ vvs_status vvs_debug_fill_probe(vvs_ctx* ctx, const void* d_src, size_t region_b
 size_t vvs_debug_gemm_scratch_bytes(const vvs_ctx* ctx, int32_t m, int32_t n, int32_t k) {
   const Ctx* c = reinterpret_cast<const Ctx*>(ctx);
   if (!c || m < 1 || n < 1 || k < 1) return 0;
-  GemmPlan p = plan_gemm(c, m, n, k, 0, true);
+  GemmPlan p = plan_partial(c, m, n, k);
   return align_up((size_t)n * k * c->esz, 256) + align_up(align_up((size_t)m, 32) * k * c->esz, 256) +
          align_up((size_t)p.splits * m * n * sizeof(float), 256);
 }

@@ -93,6 +93,7 @@ struct Timed {
 vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err);
 GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section = 0 /* > 0: no tile may reach across a multiple of it */,
                    bool may_split = false /* operands shared through LDS: the contraction may be split (else the epilogue takes whole sums) */, int min_bn = 64);
+GemmPlan plan_partial(const Ctx* c, int M, int N, int K);
 bool qkv_small_tiles(const Ctx* c, int M);   // the q/k/v projection of M rows runs on 32 x 32 tiles, each on a CU of its own
 GemmPlan plan_qkv(const Ctx* c, int M);
 GemmPlan plan_gate_up(const Ctx* c, int M);

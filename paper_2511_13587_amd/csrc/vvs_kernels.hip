@@ -670,7 +670,7 @@ static void gemm_small(Ctx* c, const float* A, const char* W, const char* g, flo
 
 // C[splits][M][N] (fp32 partial sums) = A[M][K] * W[N][K]^T (bf16: both operands in packed fragment order)
 static int run_gemm(Ctx* c, const void* A, const void* W, float* C, int M, int N, int K, bool allow_split, hipStream_t s, RowMap out = RowMap{}) {
-  GemmPlan p = plan_gemm(c, M, N, K, 0, allow_split);
+  GemmPlan p = allow_split ? plan_partial(c, M, N, K) : plan_gemm(c, M, N, K);
   if (!allow_split) p.splits = 1;
   Timed timed(c, VVS_K_GEMM, s);
   if (c->cfg.dtype == VVS_BF16) {

@@ -191,6 +191,35 @@ int main() {
           if ((p.splits > 1 || sh[0] == d) && (size_t)p.splits * m * sh[0] > k.gemm_out_elems) { printf("%d rows: partial sums do not fit\n", m); return 1; }
         }
     }
+    // ... and every projection of every shape, also where two have the same columns or the same contraction (d_ff of d / 2, 1.5 d, 2 d):
+    // what forward_t launches with partial sums, each with the plan its launch takes
+    long undersized = 0, checked = 0;
+    for (int it = 0; it < 2000; ++it) {
+      vvs_config w = base_config(true, it % 5 == 4);
+      const int dh = ri(0, 1) ? 128 : 64, d = w.d_model = ri(1, 4096 / 128) * 128;
+      w.n_layers = 1; w.n_heads = d / dh; w.max_nodes = ri(0, dh == 128 ? 31 : 63); w.n_prompts = ri(1, 8); w.grid_h = w.grid_w = ri(4, 24);
+      w.prefix_len = ri(1, 120); w.norm_mode = it / 4 & 1;
+      if (it % 8 == 6) { w.n_prompts = 1; w.grid_h = w.grid_w = 4; w.prefix_len = 1; }   // a verify call is the widest there is
+      const int F = w.d_ff = it % 4 == 0 ? 2 * d : it % 4 == 1 ? d / 2 : it % 4 == 2 ? d / 2 * 3 : ri(std::max(1, d / 256), d / 64 * 3) * 64;
+      vvs::Ctx k;
+      if (vvs::plan_sizes(&w, &k, &err) != VVS_OK) { printf("plan: %s\n", err.c_str()); return 1; }
+      if (vvs::plan_fused(&k, 1)) continue;                  // takes no partial sums
+      auto need = [&](int m, int n, int kk) {
+        ++checked;
+        if ((size_t)vvs::plan_gemm(&k, m, n, kk, 0, true).splits * m * n <= k.gemm_out_elems) return;
+        if (++undersized <= 3) printf("d %d, d_ff %d, norm mode %d, %d rows: partial sums of %d columns over %d do not fit\n", d, F, w.norm_mode, m, n, kk);
+      };
+      for (int m32 = 32; m32 <= k.Mmax; m32 += 32)
+        for (int m : {m32, m32 - ri(1, 31)}) {
+          const vvs::GemmPlan q = vvs::plan_qkv(&k, m), gu = vvs::plan_gate_up(&k, m);
+          if (q.splits > 1 && (m + q.bm - 1) / q.bm * (3 * d / q.bn) < 160) need(m, 3 * d, d);
+          if (gu.splits > 1) need(m, 2 * F, d);
+          need(m, d, d);
+          need(m, d, F);
+          if (w.draft_input) need(m, d, 2 * d);
+        }
+    }
+    if (undersized || checked < 300000) { printf("%ld of %ld launches overrun the partial sums\n", undersized, checked); return 1; }
     vvs::Ctx odd = xl;                                       // a third of 640 columns: 256-column tiles would cross it
     odd.d = 640;
     for (int m = 1; m <= 20000; m += 97)

@@ -40,9 +40,20 @@ def test_product_of_large_weights_bf16(gc, m, n, k):
 @pytest.mark.parametrize("d,heads,d_ff,tokens", [(2048, 32, 3072, 24), (2048, 16, 3072, 65), (2048, 16, 3072, 150), (2048, 32, 3072, 200),
                                                  (2048, 32, 3072, 345), (2048, 16, 3072, 497), (4096, 32, 1536, 90)])
 def test_epilogues_of_large_weights_bf16(gc, d, heads, d_ff, tokens):
+    check_prefill(gc, d, heads, d_ff, tokens)
+
+
+# Projections of one shape: d_ff of 2 d has the down projection's contraction in common with a drafter's input map, d_ff of d / 2 the columns of
+# gate/up with O's.  These row counts take more partial sums than the widest call.
+@pytest.mark.parametrize("d,heads,d_ff,tokens,norm_mode", [(2560, 20, 5120, 464, 0), (3584, 28, 1792, 288, 0), (512, 8, 1024, 512, 1)])
+def test_partial_sums_of_projections_alike_bf16(gc, d, heads, d_ff, tokens, norm_mode):
+    check_prefill(gc, d, heads, d_ff, tokens, norm_mode)
+
+
+def check_prefill(gc, d, heads, d_ff, tokens, norm_mode=0):
     shape = synth.SEVEN_B.replace(d_model=d, n_heads=heads, d_ff=d_ff, n_layers=1, n_prompts=1, n_nodes=2, tree_widths=None, vocab=1024, logit_lo=0,
                                   logit_hi=1024, grid_h=32, grid_w=32, prefix_len=1, prefix_kind=synth.PREFIX_CLASS)
-    pair = gc.Pair(shape, gain_jitter=0.1, shadow=True, sample=[0])
+    pair = gc.Pair(shape, gain_jitter=0.1, shadow=True, sample=[0], norm_mode=norm_mode)
     pair.prefill(n_forced=tokens - 1)
     raw, _, _ = pair.gpu_logits()
     diff = raw[pair.rows(), 0] - pair.oracle.prefill_logits
