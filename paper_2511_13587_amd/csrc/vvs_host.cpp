@@ -67,8 +67,12 @@ static GemmPlan plan_shared(int M, int N, int K, int section, bool may_split, in
   return best;
 }
 
+// Beyond 512 tiles of 64 x 64 some CUs work through a third of them (as at plan_resid), whichever the projection.  us per pass, own / shared
+// operands: d 768, 12 heads, 4 layers, 960 to 1024 rows (540 to 576 q/k/v tiles) 387 / 366 and 400 / 373, 880 rows (504) 347 / 348; d 512, 1584
+// rows 704 / 647; d 1024, 672 rows 708 / 654; a prefix of d 1280 with 520 tiles 494 / 449.  (At 160 tiles of 128 x 128, where the line stood, calls of
+// 896 to 1024 rows of d 768 with more (head, prompt) pairs than CUs had become up to 3.8 % slower when their projection left the attention's launch.)
 static bool takes_shared(int M, int N, int K) {
-  return N % 128 == 0 && ((M > 192 && ((M + 127) / 128) * (N / 128) >= 160) || ((size_t)N * K * 2 >= kStreamed && (M > 32 || K >= 2048)));
+  return N % 128 == 0 && ((M > 192 && ((M + 63) / 64) * (N / 64) > 512) || ((size_t)N * K * 2 >= kStreamed && (M > 32 || K >= 2048)));
 }
 
 GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section, bool may_split, int min_bn) {
