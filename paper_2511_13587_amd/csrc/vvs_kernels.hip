@@ -589,13 +589,12 @@ __global__ __launch_bounds__(256) void k_gemm_small(const float* __restrict__ A,
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       if (u == 1 && k0 + 64 >= K4) break;
-      if (k0 + 64 * u + lane >= K4) {        // ... and add nothing
+      if (k0 + 64 * u + lane >= K4) {        // ... and add nothing, not even where that piece holds an infinity
 #pragma unroll
         for (int c = 0; c < NC; ++c) wv[u][c] = zero;
-        if constexpr (NORM) {
+        if constexpr (NORM) gv[u] = zero;
 #pragma unroll
-          for (int i = 0; i < 8; ++i) av[u][i] = zero;
-        }
+        for (int i = 0; i < 8; ++i) av[u][i] = zero;
       }
       if constexpr (NORM) {
 #pragma unroll

@@ -39,3 +39,29 @@ def test_small_layer_fp32(gc, d, heads, d_ff, prompts, nodes, tokens):
             assert np.abs(v.cpu().numpy() - pair.oracle.vc[r][1][:n].reshape(n, -1)).max() < 1e-4
         pair.commit()
     pair.close()
+
+
+# d and d_ff of 264 values: 66 pieces of 4, so most lanes stand past the end of the second 64 and must add nothing, whatever the row's last piece
+def test_infinities_in_the_last_piece(gc):
+    shape = synth.TINY.replace(n_layers=1, d_model=264, n_heads=3, d_ff=264, tree_widths=None)
+    w = synth.make_weights(shape)
+    w["gf"][-1] = np.inf                       # final norm and head
+    pair = gc.Pair(shape, weights=w)
+    pair.prefill(n_forced=9, run_oracle=False)
+    raw, _, _ = pair.gpu_logits()
+    assert np.isinf(raw).all()                 # one infinite term beside finite ones
+    sign = np.sign(raw[:, 0] * w["wout"][-1, shape.logit_lo:shape.logit_hi])
+    assert (sign == sign[:, :1]).all()         # the sign of the row's last value, which every column shares
+    pair.close()
+    w = synth.make_weights(shape)
+    w["l0.wg"][:, -1] *= 1e24                  # the last hidden unit leaves the range of fp32 where its gate is open
+    w["l0.wu"][:, -1] *= 1e24
+    pair = gc.Pair(shape, weights=w, feature_pre_norm=1)
+    for n_forced in range(1, 8):
+        pair.prefill(n_forced=n_forced)
+        got = pair.ctx.vvs_read_features()[0][:, 0]
+        want = np.stack([pair.oracle.features(r)[-1] for r in range(shape.n_rows)])
+        far = np.abs(want) > 1e39
+        assert np.array_equal(np.isposinf(got), far & (want > 0)) and np.array_equal(np.isneginf(got), far & (want < 0)), n_forced
+        assert np.isfinite(got[~far]).all()
+    pair.close()
