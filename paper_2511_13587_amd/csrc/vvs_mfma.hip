@@ -1676,22 +1676,28 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
 // when a verify call of T block tokens per row does not take that kernel.
 int mfma_qkv_attention_rows(const Ctx* c, const PosDesc& pos, int T) {
   if (c->cfg.dtype != VVS_BF16 || c->dh != 64 || T > 64 || !pos.kv_len || !pos.n_emitted || c->d % 64 || c->d > 2560) return 0;
-  // A workgroup fills a CU, so (head, prompt) pairs beyond the 256 CUs run in rounds and lose to the separate kernels; of few pairs
-  // each CU pulls 655 KB of weights while most stand idle, where a projection of its own deals them to all.  ms per step fused /
-  // separate: 20 heads, 27 tokens, 1 prompt 1.58 / 1.45, 6 2.29 / 2.39, 16 4.06 / 3.83, 24 5.19 / 5.11, 32 6.32 / 5.95; 61 tokens, 1 2.19 / 1.81,
-  // 8 3.71 / 3.93, 16 6.37 / 5.81, 24 8.39 / 8.26; 6 tokens, 8 1.833 / 1.822, 13 2.72 / 2.12, 32 3.94 / 3.15; 12 heads, 6 tokens,
-  // 16 prompts 0.449 / 0.481, 22 0.685 / 0.580.  (40 and 80 pairs: separate 5 and 2 % faster at 27 tokens, 18 and 9 % at 61; the launches of
-  // 2 prompts are pinned by test_which_launches_a_layer_takes.)
+  // A workgroup fills a CU and computes 32 or 64 rows per row of the batch, so pairs beyond the 256 CUs run in rounds, and what is idle or
+  // padding in them is lost; the separate kernels pay for neither, but for 12 more launches and a pass through memory.  The fused launch is
+  // taken while the rounds are full enough.  Step, separate against fused (below 0: separate faster), by share of two rounds:
+  //   12 heads (d 768): 61 tokens 0.67 +1.7 %, 0.60 -2.7; 57 0.67 +1.7, 0.63 -2.7; 53 0.68 +2.3, 0.62 -2.3; 49 0.68 +2.5, 0.63 -1.4; 32 0.70 +1.8, 0.63
+  //     -1.7; 30 0.70 +1.4, 0.59 -1.9; 27 0.69 +2.0, 0.63 -2.1; 24 0.67 +1.8, 0.62 -0.9; 16 0.49 -1.9; 6 0.18 -3.3
+  //   16 (d 1024): 61 0.71 +1.4, 0.63 -3.3; 57 0.67 +1.3; 32 0.75 +1.3, 0.66 -2.4; 27 0.74 +1.4, 0.63 -2.6; 24 0.66 -1.9
+  //   20 (d 1280): 61 0.71 +0.9, 0.60 -6.7; 57 0.77 +1.6, 0.66 -5.2; 32 0.74 -0.9, 0.86 +0.9; 27 0.73 +0.6, 0.63 -2.8; 22 (d 1408): 64 0.69 +1.8; 57 0.61 -4.1;
+  //     32 0.69 -1.4, 0.86 +0.4; 61 0.66 +2.3 (the one point on the wrong side by more than 1.5 %)
+  // by share of three: d 768 32 0.91 +2.5, 0.84 -1.5; 30 0.92 +2.3; 61 0.94 +3.2, 0.86 +1.7; d 1024 32 0.92 +2.3; 57 0.89 +3.6; 61 0.87 -0.7; d 1280 61 0.89
+  // +2.7, 0.84 -1.3; 32 0.89 -3.3, 0.94 +1.0.  Of four (900 to 1020 pairs) the two are level: -2.7 to +2.3 %.
+  const int pairs = c->H * c->B, rounds = (pairs + 255) / 256, pad = T <= 32 ? 32 : 64;
+  const int least = rounds == 1 ? 0 : rounds == 2 ? 665 : 890;     // thousandths
+  if (rounds > 3 || (long)pairs * T * 1000 < (long)least * rounds * 256 * pad) return 0;
+  // Of few pairs each CU pulls 655 KB of weights while most stand idle, where a projection of its own deals them to all: 20 heads, 1 prompt, 27
+  // tokens 1.58 (fused) / 1.45 ms, 61 tokens 2.19 / 1.81.  (40 and 80 pairs: separate 5 and 2 % faster at 27 tokens, 18 and 9 % at 61; the one
+  // launch of 2 prompts is what test_which_launches_a_layer_takes holds, and the line stands below it.)
   // The same where the projection's 32 x 32 tiles all have a CU of their own (up to 64 rows at d 1280): 20 heads, 6 tokens, 2 prompts
   // 1.51 / 1.34, 4 1.55 / 1.45; the drafting call of 8 prompts 0.462 / 0.446.  Not at small d, where the fused launch pulls no more than a
   // launch's worth through a CU: 12 heads, 4 prompts x 6 0.390 / 0.383, 8 x 5 0.412 / 0.418, and a first pass on new buffers, which waits
   // for the host, 0.54 / 0.63.
-  const int pairs = c->H * c->B;
-  // (a narrow model fills a second round of nearly whole tiles well: 12 heads, 32 prompts x 61 tokens 1.94 / 2.01, but 30 x 51 1.77 / 1.70 and
-  // 24 x 41 1.40 / 1.30)
-  const bool two_rounds = c->d < 1024 && T > 56 && pairs > 372 && pairs <= 512;
-  if ((pairs > 256 && !two_rounds) || (c->d >= 1024 && (pairs < 40 || qkv_small_tiles(c, c->R * T)))) return 0;
-  return T <= 32 ? 32 : 64;
+  if (c->d >= 1024 && (pairs < 40 || qkv_small_tiles(c, c->R * T))) return 0;
+  return pad;
 }
 
 // q/k/v projection of the row-padded operand A, rotary embedding, cache write and attention in one launch; the result is the

@@ -1,4 +1,4 @@
-"""GPU parity of verify calls whose q/k/v projection and attention are launches of their own at head size 64: few (head, prompt)
+"""GPU parity of verify calls on both sides of the lines between one launch for q/k/v projection and attention and two: few (head, prompt)
 pairs, with the projection on 32 x 32 tiles and attention workgroups that read ahead, and more pairs than CUs."""
 import pytest
 
@@ -17,3 +17,28 @@ def test_projection_and_attention_apart(gc, model, prompts, n_nodes, widths, n_f
     shape = base.replace(n_layers=2, n_prompts=prompts, n_nodes=n_nodes, tree_widths=widths)
     sample = [0, prompts - 1] if prompts > 8 else None
     show(f"{model} {prompts} x {n_nodes + 1}", run_bf16_case(gc, shape, n_forced=n_forced, calls=2, **({"sample": sample} if sample else {})))
+
+
+# 12 heads: up to 256 pairs one round of CUs, whatever the tokens; two and three rounds while pairs and tokens fill 0.665 and 0.89 of them
+@pytest.mark.parametrize("prompts,tokens,together", [(21, 1, True), (22, 21, False), (30, 61, True), (30, 60, False), (36, 27, True), (36, 25, False), (42, 32, True),
+                                                     (43, 32, False), (60, 32, True), (60, 30, False), (64, 56, False), (64, 57, True), (66, 64, False)])
+def test_rounds_of_projection_and_attention_together(gc, prompts, tokens, together):  # noqa: F811
+    shape = synth.B_SHAPE.replace(n_layers=1, n_prompts=prompts, n_nodes=tokens - 1, vocab=1024, logit_hi=1024)
+    pair = gc.Pair(shape, with_oracle=False)
+    pair.prefill(n_forced=3, run_oracle=False)
+    q, toks = synth.make_draft(shape, synth.tree_parents(None, tokens - 1), 0) if tokens > 1 else (None, None)
+    pair.ctx.vvs_timing_enable(True)
+    pair.verify(None, toks, q, synth.make_uniforms(shape, tokens - 1, 0), run_oracle=False)
+    n_attention, _ = pair.ctx.vvs_timing_read(gc.vb.VVS_K_ATTENTION)
+    pair.ctx.vvs_timing_enable(False)
+    assert n_attention == (0 if together else 1)
+    pair.close()
+
+
+# Two rounds, the second two thirds full, and three.  K and V of layer 0, whose bound is derived (check_kv): deeper ones add 3 x the shadow's own
+# change, which is the few roundings that happen to flip there, and the prefilled K of prompt 59 holds one element in 16128 at 5 ulps - here and with
+# the projection and attention apart alike - where those flips allow 4.75.  The logits behind both layers keep their bounds.
+@pytest.mark.parametrize("prompts,n_nodes,widths", [(36, 26, (4, 6, 6, 5, 5)), (60, 31, (4, 6, 8, 8, 5))])
+def test_projection_and_attention_together_in_rounds(gc, prompts, n_nodes, widths):  # noqa: F811
+    shape = synth.B_SHAPE.replace(n_layers=2, n_prompts=prompts, n_nodes=n_nodes, tree_widths=widths)
+    show(f"b {prompts} x {n_nodes + 1}", run_bf16_case(gc, shape, n_forced=20, calls=2, sample=[0, prompts - 1], kv_layers=[0]))
