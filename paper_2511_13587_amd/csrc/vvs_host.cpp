@@ -36,23 +36,25 @@ static vvs_status fail(std::string* err, vvs_status st, const std::string& msg) 
 // down, mean, 22.4 / 21.2 (128 x 64, K in 4); 388 rows gate/up 112 / 94, O 26 / 23.5 (128 x 128, K in 2), down 66 / 50 (256 x 128, K in 4).
 static GemmPlan plan_shared(int M, int N, int K, int section, bool may_split, int min_bn) {
   struct Tile { int bm, bn; double stage, lone; bool pair; };      // pair: two workgroups fit a CU; lone: one of such a pair by itself
-  static const Tile tiles[] = {{64, 64, 0.155, 0.155, true},   {64, 128, 0.21, 0.21, true},    {128, 64, 0.19, 0.19, true},  {128, 128, 0.215, 0.34, true},
-                               {128, 128, 0.245, 0.245, false}, {192, 64, 0.23, 0.23, false},   {192, 128, 0.31, 0.31, false},
-                               {256, 128, 0.385, 0.385, false}, {256, 256, 0.62, 0.62, false}};
+  static const Tile tiles[] = {{256, 256, 0.62, 0.62, false}, {256, 128, 0.385, 0.385, false}, {192, 128, 0.31, 0.31, false},
+                               {192, 64, 0.23, 0.23, false},   {128, 128, 0.245, 0.245, false}, {128, 128, 0.215, 0.34, true},
+                               {128, 64, 0.19, 0.19, true},    {64, 128, 0.21, 0.21, true},     {64, 64, 0.155, 0.155, true}};
   const double area = section ? 4.8e-4 : min_bn > 64 ? 2.1e-4 : 4.5e-4;   // us per value: q/k/v in cache order, one bf16 for two, fp32
   const int rows = (int)align_up(M, 32), nst = K / 32;             // limits on multiples of 32 rows (plan_sizes)
+  const double stream = 2e-6 * N * K / 6.0, again = may_split ? 4e-6 * rows * N / 5.0 : 0.0;   // the weights from memory; the sums read again, per share
   GemmPlan best{0, 0, 1};
   double least = 1e30;
   for (const Tile& t : tiles) {
     if (t.bn < min_bn || N % t.bn || section % t.bn) continue;
     const int n = (rows + t.bm - 1) / t.bm * (N / t.bn);
+    const double once = 1.5 + area * t.bm * t.bn;                  // start and epilogue
+    const double even = std::max(t.stage * nst * n * (1.0 / 256), stream) + 1.5;   // no launch is shorter than its stages dealt evenly to all CUs
     for (int want = 1; want <= (may_split ? 8 : 1); ++want) {
+      if ((want > 1 && n * (want - 1) >= 512) || even + want * again > least) break;   // two rounds of tiles need no further shares
       const int per = (nst + want - 1) / want, splits = (nst + per - 1) / per, all = n * splits;
-      if (want > 1 && n * (want - 1) >= 512) break;                // two rounds of tiles need no further shares
       if (splits != want || (splits > 1 && per < 16)) continue;
       // 128 x 128 stands twice: 8 slots, one workgroup per CU, for a single round; 4 slots, two per CU, for more
       if (t.bm == 128 && t.bn == 128 && t.pair != (all > 256)) continue;
-      const double once = 1.5 + area * t.bm * t.bn;                // start and epilogue
       double us;
       if (t.pair && all > 256) {                                   // rounds of two per CU; a rest of up to one per CU runs beside the others' epilogues
         const int pairs = all / 512 + (all % 512 > 256), rest = all % 512 > 256 ? 0 : all % 512;
@@ -60,8 +62,8 @@ static GemmPlan plan_shared(int M, int N, int K, int section, bool may_split, in
       } else {
         us = (all + 255) / 256 * (t.stage * per + once);
       }
-      us = std::max(us, 2e-6 * N * K / 6.0 + once) + (may_split ? 4e-6 * rows * N * splits / 5.0 : 0.0);   // ... and the sums are read again
-      if (us < least) { least = us; best = GemmPlan{t.bm, t.bn, splits, false, true}; }
+      us = std::max(us, stream + once) + again * splits;
+      if (us <= least) { least = us; best = GemmPlan{t.bm, t.bn, splits, false, true}; }
     }
   }
   return best;
@@ -224,8 +226,10 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   // each block of 32 stands for the block.
   size_t go = 0;
   const int d = c->d, F = c->F;
-  for (int M = 32; M <= c->Mmax; M += 32) {
-    auto sums = [&](int N, int K) { go = std::max(go, (size_t)plan_partial(c, M, N, K).splits * M * N); };
+  for (int M = c->Mmax; M >= 32; M -= 32) {                // (downwards: few rows can only need more by many shares of 15 stages and more)
+    auto sums = [&](int N, int K) {
+      if ((size_t)std::min(8, K / 32 / 15 + 1) * M * N > go) go = std::max(go, (size_t)plan_partial(c, M, N, K).splits * M * N);
+    };
     const bool bf16 = g.dtype == VVS_BF16;
     if (!bf16 || (!takes_shared(M, 3 * d, d) && plan_qkv(c, M).splits > 1)) sums(3 * d, d);   // (the shared-operand tiles of the two: whole sums)
     if (!bf16 || (!takes_shared(M, 2 * F, d) && plan_gate_up(c, M).splits > 1)) sums(2 * F, d);
