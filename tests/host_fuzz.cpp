@@ -7,6 +7,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <algorithm>
 #include <random>
 #include <vector>
 #include "vvs_internal.h"
@@ -28,6 +29,8 @@ hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 // ---- launcher stand-ins: no arithmetic; the ones that have a size touch their buffers
 namespace vvs {
 static long g_launches = 0;
+static DraftLevel g_level;                                      // of the drafting call under way
+static bool g_draft_begins = false;
 void launch_fill_zero(void* p, size_t bytes, hipStream_t) { memset(p, 0, bytes); ++g_launches; }
 void launch_copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t) { memmove(dst, src, bytes); ++g_launches; }
 void launch_fill_probe(const void*, size_t, size_t, int, int, int, int, uint32_t*, hipStream_t) { ++g_launches; }
@@ -36,6 +39,8 @@ void launch_forward(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, con
                     int, hipStream_t, bool from_din) {
   if (T < 1 || T > c->Tmax && T > c->chunk) abort();            // a forward never exceeds what the workspace was sized for
   if (tree.T != T) abort();
+  // a drafting level is a forward of its new tokens in the block's slots and logit rows; every other call is one of all tokens in rows of its own
+  if (from_din ? tree.first != g_level.first || tree.all != g_level.all || T != g_level.Tq : tree.first || tree.all) abort();
   for (int t = 0; t < T; ++t)
     if (!((tree.anc[t] >> t) & 1ull) || (t && tree.parent[t] >= t)) abort();
   memset(c->ws + c->w.x, 0, sizeof(float) * (size_t)c->R * T * c->d);
@@ -60,17 +65,23 @@ void launch_set_state(Ctx*, const int32_t*, hipStream_t) { ++g_launches; }
 void launch_debug_logits(Ctx*, float*, float*, float*, hipStream_t) { ++g_launches; }
 void launch_debug_kv(Ctx*, int, int, int, float*, float*, hipStream_t) { ++g_launches; }
 void launch_debug_gemm(Ctx*, int, int, int, const void*, const void*, void*, float*, hipStream_t) { ++g_launches; }
-void launch_draft_state(Ctx*, const Ctx*, int, int, hipStream_t) { ++g_launches; }
+void launch_draft_state(Ctx*, const Ctx*, int, int, hipStream_t) { g_draft_begins = true; ++g_launches; }
 void launch_draft_zero_leaves(Ctx*, const TreeDesc&, float*, hipStream_t) { ++g_launches; }
 void launch_draft_input(Ctx* dr, const Ctx*, const DraftLevel& lv, const int32_t*, const int32_t*, hipStream_t) {
   if (lv.Tq < lv.k || lv.Tq > dr->Tmax) abort();
-  for (int t = lv.k; t < lv.Tq; ++t)
-    if (lv.node[t] < 1 || lv.node[t] > lv.n_nodes || lv.parent_slot[t] < lv.k - 1 || lv.parent_slot[t] >= t || lv.parent_slot[t] >= lv.Tq_prev) abort();
+  // level 0 brings the pairs; every further one what follows the tokens so far, whose parents are among the new ones of the level before (the
+  // input rows are read from its residual stream, which holds no others)
+  if (lv.first >= lv.Tq || lv.Tq > lv.all || lv.all > dr->Tmax) abort();
+  if (g_draft_begins ? lv.first != 0 || lv.Tq != lv.k : lv.first != lv.Tq_prev || lv.first_prev != g_level.first || lv.Tq_prev != g_level.Tq || lv.all != g_level.all) abort();
+  for (int t = std::max(lv.k, lv.first); t < lv.Tq; ++t)
+    if (lv.node[t] < 1 || lv.node[t] > lv.n_nodes || lv.parent_slot[t] < lv.k - 1 || lv.parent_slot[t] < lv.first_prev || lv.parent_slot[t] >= lv.Tq_prev) abort();
+  g_level = lv;
+  g_draft_begins = false;
   ++g_launches;
 }
 void launch_draft_select(Ctx*, const DraftLevel& lv, const TreeDesc& shape, const int32_t*, int32_t*, float*, hipStream_t) {
-  for (int i = 0; i < lv.n_sel; ++i)
-    if (lv.sel_slot[i] < lv.k - 1 || lv.sel_slot[i] >= lv.Tq || shape.first_child[lv.sel_node[i]] < 0) abort();
+  for (int i = 0; i < lv.n_sel; ++i)                            // (this level's logits)
+    if (lv.sel_slot[i] < lv.k - 1 || lv.sel_slot[i] < lv.first || lv.sel_slot[i] >= lv.Tq || shape.first_child[lv.sel_node[i]] < 0) abort();
   ++g_launches;
 }
 }  // namespace vvs
