@@ -123,7 +123,24 @@ static void random_tree(int n, std::vector<int32_t>& parent, bool valid) {
   for (int j = 1; j <= n; ++j) parent[j - 1] = valid ? ri(0, j - 1) : ri(-2, j + 2);
 }
 
-int main() {
+// `host_fuzz plans`: for every line "partial N K M", "qkv d F M" or "gate_up d F M" on the standard input the tile and the shares of that launch
+static int print_plans() {
+  vvs_config cfg = base_config(true, false);
+  vvs::Ctx c;
+  std::string err;
+  if (vvs::plan_sizes(&cfg, &c, &err) != VVS_OK) return 1;
+  char kind[16];
+  for (int a, b, m; scanf("%15s %d %d %d", kind, &a, &b, &m) == 4;) {
+    c.d = a;
+    c.F = b;
+    const vvs::GemmPlan p = !strcmp(kind, "partial") ? vvs::plan_partial(&c, m, a, b) : !strcmp(kind, "qkv") ? vvs::plan_qkv(&c, m) : vvs::plan_gate_up(&c, m);
+    printf("%d %d %d %d\n", p.bm, p.bn, p.splits, (int)p.shared);
+  }
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  if (argc > 1 && !strcmp(argv[1], "plans")) return print_plans();
   // 1. topology checks and the verification-free step on random input, valid and not
   for (int it = 0; it < 4000; ++it) {
     const int n = ri(-2, 70);

@@ -42,3 +42,15 @@ def test_rounds_of_projection_and_attention_together(gc, prompts, tokens, togeth
 def test_projection_and_attention_together_in_rounds(gc, prompts, n_nodes, widths):  # noqa: F811
     shape = synth.B_SHAPE.replace(n_layers=2, n_prompts=prompts, n_nodes=n_nodes, tree_widths=widths)
     show(f"b {prompts} x {n_nodes + 1}", run_bf16_case(gc, shape, n_forced=20, calls=2, sample=[0, prompts - 1], kv_layers=[0]))
+
+
+# q/k/v on 32 x 32 tiles with positions and rotary factors from memory instead of LDS (head size 128), and behind a normalisation of its own:
+# d_model, heads, d_ff, tokens, norm mode; 18 and 54 rows (a row-block and a part of one, two)
+SMALL_TILES = [(1024, 8, 2752, 9, 0), (1024, 8, 2752, 27, 0), (1024, 8, 2752, 27, 1), (1024, 16, 2752, 27, 1), (1280, 20, 3456, 27, 1)]
+
+
+@pytest.mark.parametrize("d,heads,d_ff,tokens,norm_mode", SMALL_TILES)
+def test_small_tiles_of_the_projection(gc, d, heads, d_ff, tokens, norm_mode):  # noqa: F811
+    shape = synth.SEVEN_B.replace(d_model=d, n_heads=heads, d_ff=d_ff, n_layers=2, n_prompts=1, n_nodes=tokens - 1, tree_widths=None, vocab=1024,
+                                  logit_lo=0, logit_hi=1024)
+    show(f"d {d} heads {heads} tokens {tokens}", run_bf16_case(gc, shape, n_forced=40, calls=2, norm_mode=norm_mode))

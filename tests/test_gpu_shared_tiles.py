@@ -18,10 +18,15 @@ def bf16_round(a):
     return synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(np.asarray(a, dtype=np.float32)))
 
 
-# 64 x 64, 128 x 64, 192 x 64, 128 x 128, 192 x 128 and 256 x 128 tiles, one row into the next tile, and 130 stages of the
-# contraction in 4 (the last share is shorter)
-@pytest.mark.parametrize("m,n,k", [(33, 4096, 4096), (64, 4096, 4160), (65, 4096, 4096), (128, 4096, 4160), (129, 4096, 4096), (192, 4096, 11008),
-                                   (193, 4096, 4096), (257, 4096, 4160), (388, 4096, 11008), (513, 4096, 4096)])
+# rows, columns, contraction; the tile and the shares of the contraction that the planner takes (test_host_sanitized.py checks these on the CPU, so
+# that a case cannot drift off its tile).  One row into the next tile, and 130 stages of the contraction in 4 shares (the last one is shorter).
+PRODUCTS = [(33, 4096, 4096, (64, 64, 4)), (64, 4096, 4160, (64, 64, 4)), (65, 4096, 4096, (128, 64, 4)), (128, 4096, 4160, (128, 64, 4)),
+            (129, 4096, 4096, (192, 64, 4)), (192, 4096, 11008, (192, 64, 4)), (193, 4096, 4096, (128, 64, 2)), (257, 4096, 4160, (192, 64, 2)),
+            (388, 4096, 11008, (128, 128, 2)), (513, 4096, 4096, (192, 128, 2)), (130, 1536, 8192, (64, 128, 7)), (769, 4096, 11008, (256, 128, 2)),
+            (1025, 4096, 11008, (256, 256, 3)), (1537, 4096, 11008, (256, 256, 2)), (1025, 4096, 4096, (192, 128, 1)), (2457, 2560, 512, (128, 128, 1))]
+
+
+@pytest.mark.parametrize("m,n,k", [case[:3] for case in PRODUCTS])
 def test_product_of_large_weights_bf16(gc, m, n, k):
     pair = gc.Pair(synth.B_SHAPE.replace(n_layers=1, n_prompts=1, vocab=1024, logit_hi=1024), with_oracle=False)
     rng = np.random.default_rng(m + n + k)
@@ -35,10 +40,13 @@ def test_product_of_large_weights_bf16(gc, m, n, k):
     pair.close()
 
 
-# rows = 2 x tokens.  d 2048: q/k/v on 64 x 64, 128 x 64, 64 x 128, 128 x 128, 192 x 128 and 256 x 128 tiles, gate/up on 64 x 128,
-# 128 x 128, 192 x 128 and 256 x 128; d 4096: q/k/v on 192 x 64, and gate/up on 64 x 128
-@pytest.mark.parametrize("d,heads,d_ff,tokens", [(2048, 32, 3072, 24), (2048, 16, 3072, 65), (2048, 16, 3072, 150), (2048, 32, 3072, 200),
-                                                 (2048, 32, 3072, 345), (2048, 16, 3072, 497), (4096, 32, 1536, 90)])
+# d_model, heads, d_ff, tokens (rows = 2 x tokens); the tiles of q/k/v and of gate/up, both with whole sums (checked on the CPU as above)
+EPILOGUES = [(2048, 32, 3072, 24, (64, 64), (64, 128)), (2048, 16, 3072, 65, (128, 64), (64, 128)), (2048, 16, 3072, 150, (64, 128), (64, 128)),
+             (2048, 32, 3072, 200, (128, 128), (128, 128)), (2048, 32, 3072, 345, (192, 128), (192, 128)), (2048, 16, 3072, 497, (128, 128), (256, 128)),
+             (4096, 32, 1536, 90, (192, 64), (64, 128)), (4096, 32, 1536, 193, (256, 128), (64, 128)), (4096, 64, 1536, 194, (256, 128), (64, 128))]
+
+
+@pytest.mark.parametrize("d,heads,d_ff,tokens", [case[:4] for case in EPILOGUES])
 def test_epilogues_of_large_weights_bf16(gc, d, heads, d_ff, tokens):
     check_prefill(gc, d, heads, d_ff, tokens)
 

@@ -8,14 +8,18 @@ import subprocess
 
 import pytest
 
+import test_gpu_few_pairs
+import test_gpu_shared_tiles
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_host_side_is_clean_under_sanitizers(tmp_path):
+@pytest.fixture(scope="module")
+def host_fuzz(tmp_path_factory):
     gxx = shutil.which("g++")
     if gxx is None or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
         pytest.skip("needs g++ and the HIP headers")
-    exe = str(tmp_path / "host_fuzz")
+    exe = str(tmp_path_factory.mktemp("host") / "host_fuzz")
     cmd = [gxx, "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
            "-I", os.path.join(ROOT, "paper_2511_13587_amd", "csrc"), "-fsanitize=address,undefined",
            "-fno-sanitize-recover=undefined", "-static-libasan", "-g", "-O1", "-w",
@@ -25,5 +29,22 @@ def test_host_side_is_clean_under_sanitizers(tmp_path):
         pytest.skip("the sanitizer runtime is not installed")
     assert r.returncode == 0, r.stderr[-3000:]
     env = dict(os.environ, ASAN_OPTIONS="verify_asan_link_order=0:detect_leaks=1", UBSAN_OPTIONS="print_stacktrace=1")
-    r = subprocess.run([exe], capture_output=True, text=True, timeout=300, env=env)
+    return lambda *args, **kw: subprocess.run([exe, *args], capture_output=True, text=True, timeout=300, env=env, **kw)
+
+
+def test_host_side_is_clean_under_sanitizers(host_fuzz):
+    r = host_fuzz()
     assert r.returncode == 0 and "host fuzz ok" in r.stdout, (r.stdout[-2000:], r.stderr[-3000:])
+
+
+def test_gpu_tests_reach_the_tiles_they_name(host_fuzz):
+    want = [(f"partial {n} {k} {m}", (*tile, 1)) for m, n, k, tile in test_gpu_shared_tiles.PRODUCTS]
+    for d, _, d_ff, tokens, qkv, gate_up in test_gpu_shared_tiles.EPILOGUES:
+        want += [(f"qkv {d} {d_ff} {2 * tokens}", (*qkv, 1, 1)), (f"gate_up {d} {d_ff} {2 * tokens}", (*gate_up, 1, 1))]
+    want += [(f"qkv {d} {d_ff} {2 * tokens}", (32, 32, 1, 0)) for d, _, d_ff, tokens, _ in test_gpu_few_pairs.SMALL_TILES]
+    r = host_fuzz("plans", input="\n".join(line for line, _ in want))
+    assert r.returncode == 0, r.stderr[-3000:]
+    got = [tuple(int(v) for v in line.split()) for line in r.stdout.splitlines()]
+    assert len(got) == len(want)
+    wrong = [(line, plan, tile) for (line, tile), plan in zip(want, got) if plan != tile]
+    assert not wrong, wrong
