@@ -129,7 +129,7 @@ GemmPlan plan_resid(const Ctx* c, int M) {
   // many rows: 192 x 128 tiles with the operands shared through LDS (a quarter of the bytes per flop that 64 x 64 tiles pull
   // through a CU's L1), when they give most CUs a tile - at d = 1280 and 3904 rows: 210 tiles, one round.
   // Tile order by fabric traffic: the operand an XCD does not own is fetched by all 8 of them (M + 8 d rows against 8 M + d)
-  if (d % 128 == 0 && ((M + 191) / 192) * (d / 128) >= 160) return GemmPlan{192, 128, 1, M > d};
+  if (d % 128 == 0 && ((M + 191) / 192) * (d / 128) >= 160) return GemmPlan{192, 128, 1, M > d, true};
   // Two 64 x 64 workgroups fit a CU, so up to 512 of them run at once; beyond that some CUs work through a third tile while the
   // others wait, and 128 x 128 tiles through LDS, which leave 90 to 130 CUs without a tile, are the better choice.  us per launch, mean of
   // O and down, 64 x 64 / 128 x 128:
@@ -140,7 +140,7 @@ GemmPlan plan_resid(const Ctx* c, int M) {
   //   1568 (550) 32.8 / 30.8;  d 1536, d_ff 2048: 1280 (480) 19.6 / 25.2, 1360 (528) 24.1 / 24.9, 1440 (552) 25.0 / 24.2
   // (A whole pass is faster from 513 tiles on also where the two are level: the launches before have CUs free to read ahead.)
   // Column tiles per XCD: the transposed order took 3 % less (d 768, 3520 rows: 22.9 -> 22.2) to 2 % more (d 1280, 1920 rows: 30.8 -> 31.4).
-  if (d % 128 == 0 && ((M + 63) / 64) * (d / 64) > 512) return GemmPlan{128, 128, 1};
+  if (d % 128 == 0 && ((M + 63) / 64) * (d / 64) > 512) return GemmPlan{128, 128, 1, false, true};
   // 32 x 32 tiles on 8 waves while that gives at most 448 workgroups - a launch of few tiles lasts as long as one CU takes to
   // pull its operands in, so smaller tiles on more CUs win until two workgroups share most CUs - else 64 x 64 on 4.  us per launch,
   // O and down mean, 64 x 64 on 4 waves / 32 x 32 on 8: d 768, 48 rows 7.3 / 4.9; d 1280, 54 rows 10.4 / 7.2, 300 rows (400 tiles)

@@ -203,7 +203,7 @@ int main(int argc, char** argv) {
     for (int m = 1; m <= 6000; ++m) {
       const int want = m <= 352 ? 32 : m <= 1600 ? 64 : m <= 2880 ? 128 : 192;
       const vvs::GemmPlan r = vvs::plan_resid(&xl, m), q = vvs::plan_gemm(&xl, m, 3 * 1280, 1280, 1280), g = vvs::plan_gemm(&xl, m, 2 * 3456, 1280);
-      if (r.bm != want || 1280 % r.bn) { printf("residual projection of %d rows: tiles of %d x %d\n", m, r.bm, r.bn); return 1; }
+      if (r.bm != want || 1280 % r.bn || r.shared != (r.bm >= 128)) { printf("residual projection of %d rows: tiles of %d x %d\n", m, r.bm, r.bn); return 1; }
       // (more than two 64 x 64 workgroups per CU: no projection but the residual ones stays on tiles with operands of their own)
       const int rows64 = (m + 63) / 64;
       if (m > 192 && (q.shared != (rows64 * 60 > 512) || g.shared != (rows64 * 108 > 512))) { printf("%d rows: q/k/v or gate/up on the wrong side of 512 tiles\n", m); return 1; }
