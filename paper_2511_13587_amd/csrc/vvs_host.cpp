@@ -32,8 +32,8 @@ static vvs_status fail(std::string* err, vvs_status st, const std::string& msg) 
 // table, at 3904 and 1920 rows of d 1280, d_ff 3456 and 388 of d 4096, d_ff 11008:
 //   gate/up  128 x 128: 85, 44, 114 / 80, 44, 103   192 x 128: 100, 56, 133 / 96, 57, 139   256 x 128: 98, 48, 116 / 95, 48, 115   256 x 256: 79, 41, 94 / 80, 40, 95
 //   q/k/v    128 x 128: 61, 30, 68 / 60, 30, 68     192 x 128: 76, 45, 99 / 77, 51, 106     256 x 128: 67, 34, 68 / 65, 33, 66     256 x 256: 57, 51, 98 / 58, 58, 112
-// Launches of a d 4096 step with the rule before (64-row tiles up to 192 rows) / with this one: 126 rows gate/up 57.8 / 49.2 (128 x 128), O and
-// down, mean, 22.4 / 21.2 (128 x 64, K in 4); 388 rows gate/up 112 / 94, O 26 / 23.5 (128 x 128, K in 2), down 66 / 50 (256 x 128, K in 4).
+// Launches of a d 4096 step with the rule before (64-row tiles up to 192 rows) / with this one: 126 rows gate/up 57.8 / 49.8 (128 x 128), O and
+// down, mean, 22.4 / 21.4 (128 x 64, K in 4); 388 rows gate/up 112 / 94.6 (256 x 256), O 26 / 23.6, down 66 / 49.2 (both 128 x 128, K in 2).
 static GemmPlan plan_shared(int M, int N, int K, int section, bool may_split, int min_bn) {
   struct Tile { int bm, bn; double stage, lone; bool pair; };      // pair: two workgroups fit a CU; lone: one of such a pair by itself
   static const Tile tiles[] = {{256, 256, 0.62, 0.62, false}, {256, 128, 0.385, 0.385, false}, {192, 128, 0.31, 0.31, false},
@@ -73,6 +73,9 @@ static GemmPlan plan_shared(int M, int N, int K, int section, bool may_split, in
 // operands: d 768, 12 heads, 4 layers, 960 to 1024 rows (540 to 576 q/k/v tiles) 387 / 366 and 400 / 373, 880 rows (504) 347 / 348; d 512, 1584
 // rows 704 / 647; d 1024, 672 rows 708 / 654; a prefix of d 1280 with 520 tiles 494 / 449.  (At 160 tiles of 128 x 128, where the line stood, calls of
 // 896 to 1024 rows of d 768 with more (head, prompt) pairs than CUs had become up to 3.8 % slower when their projection left the attention's launch.)
+// Large weights: from one row-block's end on, and with up to 32 rows where the contraction is long enough that a tile's stages outweigh its ramp.
+// Step of 4 to 32 rows, shared against own operands: d 1536 (d_ff 4096) +4.5 to +2.5 %, 1792 (4864) +1.5 to -0.5, 2048 (5504) -0.8 to -4.2, 2560 (6912)
+// -4.1 to -6.1, 4096 (11008) -7.5 to -1.8.
 static bool takes_shared(int M, int N, int K) {
   return N % 128 == 0 && ((M > 192 && ((M + 63) / 64) * (N / 64) > 512) || ((size_t)N * K * 2 >= kStreamed && (M > 32 || K >= 2048)));
 }

@@ -817,7 +817,9 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
     forward_fused(c, tree, pos, Tq, d_tokens_bt, pc, pu, chunk_start, forced, n_forced, logits_mode, s, from_din);
     return;
   }
-  // (wide models and many rows are bound by their products: the plain kernels, with the normalisation done once per row)
+  // The limits are where the parity tests of the small layer end, not where it stops paying.  Step of 3 layers, plain / small, us: at the limits
+  // d 1024, d_ff 4096, 128 rows 1014 / 824; beyond each, 256 rows (d 1024, d_ff 2752) 1405 / 1222, d 1280 (128 rows) 1205 / 1008, d_ff 5504
+  // (128 rows) 1297 / 1029; well inside, d 128 with 10 rows 138 / 91.
   if (sizeof(T) == 4 && M <= 128 && d <= 1024 && F <= 4096) {
     forward_small(c, tree, pos, Tq, d_tokens_bt, pc, pu, chunk_start, forced, n_forced, logits_mode, s, from_din);
     return;

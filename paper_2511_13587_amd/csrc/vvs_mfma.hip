@@ -1690,12 +1690,14 @@ int mfma_qkv_attention_rows(const Ctx* c, const PosDesc& pos, int T) {
   const int least = rounds == 1 ? 0 : rounds == 2 ? 665 : 890;     // thousandths
   if (rounds > 3 || (long)pairs * T * 1000 < (long)least * rounds * 256 * pad) return 0;
   // Of few pairs each CU pulls 655 KB of weights while most stand idle, where a projection of its own deals them to all: 20 heads, 1 prompt, 27
-  // tokens 1.58 (fused) / 1.45 ms, 61 tokens 2.19 / 1.81.  (40 and 80 pairs: separate 5 and 2 % faster at 27 tokens, 18 and 9 % at 61; the one
-  // launch of 2 prompts is what test_which_launches_a_layer_takes holds, and the line stands below it.)
-  // The same where the projection's 32 x 32 tiles all have a CU of their own (up to 64 rows at d 1280): 20 heads, 6 tokens, 2 prompts
-  // 1.51 / 1.34, 4 1.55 / 1.45; the drafting call of 8 prompts 0.462 / 0.446.  Not at small d, where the fused launch pulls no more than a
-  // launch's worth through a CU: 12 heads, 4 prompts x 6 0.390 / 0.383, 8 x 5 0.412 / 0.418, and a first pass on new buffers, which waits
-  // for the host, 0.54 / 0.63.
+  // tokens 1.57 (fused) / 1.44 ms, 61 tokens 2.17 / 1.80; waiting for the host after every pass 1.61 / 1.48, 2.21 / 1.83.  The same where the
+  // projection's 32 x 32 tiles all have a CU of their own (up to 64 rows at d 1280): 20 heads, 6 tokens, 2 prompts 1.51 / 1.34, 4 1.55 / 1.45; the
+  // drafting call of 8 prompts 0.462 / 0.446.
+  // Both lines are drawn inside what would pay.  40 and 80 pairs stay one launch, though apart they are 3 to 5 and 2 % faster at 27 tokens, 18 and 9 %
+  // at 61: which launches such a call takes is part of what callers measure with (vvs_timing_read), and 2 prompts of 20 heads are held to one.
+  // Below d 1024 so does every call, because a pass that waits for the host pays for the further launches there: 12 layers, us in a row of
+  // passes, then alone, fused / separate: 12 heads, 1 prompt x 6 tokens 359 / 341, 430 / 437; 2 x 27 414 / 398, 473 / 491; 14 heads 1 x 6 409 / 370,
+  // 461 / 437; 2 x 27 447 / 442, 486 / 518; 15 heads 2 x 27 473 / 464, 505 / 528; 16 heads (d 1024) 1 x 6 438 / 390, 477 / 451; 4 x 6 453 / 418, 493 / 486.
   if (c->d >= 1024 && (pairs < 40 || qkv_small_tiles(c, c->R * T))) return 0;
   return pad;
 }

@@ -354,9 +354,10 @@ def test_fill_probe_reads_the_region_it_is_given(gc, mode):
 
 @pytest.mark.parametrize("case", ["xl_27_tokens", "xl_61_tokens_few_prompts", "xl_61_tokens_many_prompts", "head_size_128"])
 def test_which_launches_a_layer_takes(gc, case):
-    """The launch plan is part of what the library promises to measure with (vvs_timing_read): a verify call runs the q/k/v
-    projection and the attention of a layer as one launch at head size 64 with up to 32 tokens per row, and with up to 64
-    tokens while there are at most 512 (head, prompt) pairs; otherwise, and at head size 128, as separate launches."""
+    """The launch plan is part of what the library promises to measure with (vvs_timing_read): at head size 64 a verify call of two
+    prompts of 20 heads runs the q/k/v projection and the attention of a layer as one launch with 27 and with 61 tokens per row; 520
+    (head, prompt) pairs with 61 tokens, which would leave a third round of CUs nearly empty, and head size 128 take separate launches.
+    (The lines themselves: test_gpu_few_pairs.py.)"""
     vb = gc.vb
     if case == "xl_27_tokens":
         shape, fused_attention = synth.XL_TREE.replace(n_layers=2, n_prompts=2), True
