@@ -80,16 +80,10 @@ static bool takes_shared(int M, int N, int K) {
   return N % 128 == 0 && ((M > 192 && ((M + 63) / 64) * (N / 64) > 512) || ((size_t)N * K * 2 >= kStreamed && (M > 32 || K >= 2048)));
 }
 
-GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section, bool may_split, int min_bn) {
-  GemmPlan p{64, 64, 1};
-  if (c->cfg.dtype != VVS_BF16) return p;           // fp32 path: one wave per output column, no split
-  // bf16: 64 x 64 output tiles (32 x 64 for up to 32 rows); every workgroup already splits its K range
-  // over its 4 waves.  Add grid-level K splits until there is about one workgroup per CU, keeping at
-  // least 8 k-steps of 16 per wave.
-  p.bm = M <= 32 ? 32 : 64;
-  // Operands shared through LDS where a launch has many 128 x 128 tiles, or where the weights are large and the rows more than one
-  // row-block: a CU then has whole rows of stages to work through, and each weight byte feeds twice the MFMAs
-  if (takes_shared(M, N, K)) return plan_shared(M, N, K, section, may_split, min_bn);
+// Tiles whose waves stream operands of their own: 64 x 64 (32 x 64 for up to 32 rows); every workgroup already splits its K range over its 4
+// waves.  Add grid-level K splits until there is about one workgroup per CU, keeping at least 8 k-steps of 16 per wave.
+static GemmPlan plan_own(int M, int N, int K) {
+  GemmPlan p{M <= 32 ? 32 : 64, 64, 1};
   // 64 x 128 tiles when they give one workgroup for (nearly) every CU and no second round: a CU then
   // pulls (64 + 128) K-rows through its L1 instead of 2 x (64 + 64)
   if (p.bm == 64 && N % 128 == 0) {
@@ -101,14 +95,18 @@ GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section, bool may_spli
   if (p.bm == 32 && N % 128 == 0 && N / 128 >= 160 && N / 128 <= 256) { p.bn = 128; return p; }
   const int tiles = ((M + p.bm - 1) / p.bm) * (N / 64);
   const int kb = K / 16;
-  int splits = 1;
   if (tiles < 256) {
-    splits = std::min({(256 + tiles - 1) / tiles, 8, std::max(1, kb / 32)});
-    const int per = (kb + splits - 1) / splits;
-    splits = (kb + per - 1) / per;
+    const int want = std::min({(256 + tiles - 1) / tiles, 8, std::max(1, kb / 32)}), per = (kb + want - 1) / want;
+    p.splits = (kb + per - 1) / per;
   }
-  p.splits = splits;
   return p;
+}
+
+GemmPlan plan_gemm(const Ctx* c, int M, int N, int K, int section, bool may_split, int min_bn) {
+  if (c->cfg.dtype != VVS_BF16) return GemmPlan{64, 64, 1};   // fp32 path: one wave per output column, no split
+  // Operands shared through LDS where a launch has many 128 x 128 tiles, or where the weights are large and the rows more than one
+  // row-block: a CU then has whole rows of stages to work through, and each weight byte feeds twice the MFMAs
+  return takes_shared(M, N, K) ? plan_shared(M, N, K, section, may_split, min_bn) : plan_own(M, N, K);
 }
 
 // A projection that leaves partial sums for the kernel behind it (run_gemm)
@@ -123,8 +121,27 @@ GemmPlan plan_qkv(const Ctx* c, int M) {
   if (qkv_small_tiles(c, M)) return GemmPlan{32, 32, 1};
   return plan_gemm(c, M, 3 * c->d, c->d, c->d);
 }
-// a tile of the SwiGLU epilogue holds gate and up of its hidden units in one wave: 128 columns
-GemmPlan plan_gate_up(const Ctx* c, int M) { return plan_gemm(c, M, 2 * c->F, c->d, 0, false, 128); }
+// Gate/up of large weights on tiles with operands of their own.  A shared tile holds gate and up of its hidden units in one wave, 128 columns; its
+// own has 64, so where these are one round of CUs the shared ones leave half of the CUs idle; and with up to 32 rows (both read one
+// row-block) three 64-column tiles on the fullest CU are less than two of 128.  us per layer, shared / own whole sums / own split:
+//   one round:  d 2048, d_ff 4096, 14 rows 67.0 / 62.3 / 65.7, 96 rows 71.7 / 69.0; d 2560, d_ff 5120, 64 rows 85.9 / 81.6 / 86.8; d 3072, d_ff 6144, 30 rows 94.3 /
+//     87.2 / 91.9; d 4096, d_ff 8192, 30 rows 122.5 / 115.0, 40 rows 133.8 / 125.4; d_ff 4096, 30 rows 108.8 / 100.7 / 100.7, 40 rows 121.6 / 114.4 / 111.7
+//   two:        d 3072, d_ff 8256, 28 rows 97.2 / 100.5; d 4096, d_ff 11008, 28 rows 124.6 / 125.1; d 2560, d_ff 5120, 96 rows 90.3 / 91.3
+//   three:      d 4096, 2 layers, 30 rows, d_ff 18432 359 / 339, 20480 369 / 358; four: d_ff 32768 450 / 450
+static int gate_up_own_tiles(const Ctx* c, int M) { return (M <= 32 ? 1 : (M + 63) / 64) * (2 * c->F / 64); }
+static bool gate_up_own(const Ctx* c, int M) {
+  const int n = gate_up_own_tiles(c, M);
+  return c->cfg.dtype == VVS_BF16 && (n <= 256 || (M <= 32 && n > 512 && n <= 768));
+}
+GemmPlan plan_gate_up(const Ctx* c, int M) {
+  const int N = 2 * c->F, K = c->d;
+  if (!takes_shared(M, N, K) || !gate_up_own(c, M)) return plan_gemm(c, M, N, K, 0, false, 128);
+  GemmPlan p = plan_own(M, N, K);
+  // whole sums, unless half of the CUs have no tile and the contraction is long.  30 rows, whole / split: d 4096, d_ff 2048 (64 tiles) 94.9 / 91.5, d 8192,
+  // d_ff 4096 (128) 217 / 209; d 3584, d_ff 3584 (112) 90.4 / 91.9; d 3072, d_ff 6144 (192) 87.2 / 91.9, d 4096, d_ff 5504 (172) 104 / 108
+  if (gate_up_own_tiles(c, M) > 128 || K < 4096) p.splits = 1;
+  return p;
+}
 
 // The projections that end in the residual epilogue (fused layer: O, down, a drafter's input map); d columns.
 GemmPlan plan_resid(const Ctx* c, int M) {
@@ -235,7 +252,10 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
     };
     const bool bf16 = g.dtype == VVS_BF16;
     if (!bf16 || (!takes_shared(M, 3 * d, d) && plan_qkv(c, M).splits > 1)) sums(3 * d, d);   // (the shared-operand tiles of the two: whole sums)
-    if (!bf16 || (!takes_shared(M, 2 * F, d) && plan_gate_up(c, M).splits > 1)) sums(2 * F, d);
+    if (!bf16 || !takes_shared(M, 2 * F, d) || gate_up_own(c, M)) {
+      const int shares = plan_gate_up(c, M).splits;
+      if (!bf16 || shares > 1) go = std::max(go, (size_t)shares * M * 2 * F);
+    }
     sums(d, d);                              // O
     sums(d, F);                              // down
     if (g.draft_input) sums(d, 2 * d);       // a drafter's input map

@@ -668,9 +668,7 @@ static void gemm_small(Ctx* c, const float* A, const char* W, const char* g, flo
 }
 
 // C[splits][M][N] (fp32 partial sums) = A[M][K] * W[N][K]^T (bf16: both operands in packed fragment order)
-static int run_gemm(Ctx* c, const void* A, const void* W, float* C, int M, int N, int K, bool allow_split, hipStream_t s, RowMap out = RowMap{}) {
-  GemmPlan p = allow_split ? plan_partial(c, M, N, K) : plan_gemm(c, M, N, K);
-  if (!allow_split) p.splits = 1;
+static int run_gemm(Ctx* c, const void* A, const void* W, float* C, int M, int N, int K, GemmPlan p, hipStream_t s, RowMap out = RowMap{}) {
   Timed timed(c, VVS_K_GEMM, s);
   if (c->cfg.dtype == VVS_BF16) {
     mfma_gemm((const bf16_t*)A, (const bf16_t*)W, C, M, N, K, p, s, out);
@@ -837,7 +835,7 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
   size_t sstride = 0;
   if (from_din) {             // drafter: x = 0 + [embedding ; feature] W_fc, added by the first norm kernel
     launch_fill_zero(x, sizeof(float) * (size_t)M * d, s);
-    splits = run_gemm(c, c->ws + c->w.din, c->pw + c->p.fc, go, M, d, 2 * d, true, s);
+    splits = run_gemm(c, c->ws + c->w.din, c->pw + c->p.fc, go, M, d, 2 * d, plan_partial(c, M, d, 2 * d), s);
     sstride = (size_t)M * d;
   } else {
     Timed timed(c, VVS_K_ELEMENTWISE, s);
@@ -860,7 +858,7 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
       Timed timed(c, VVS_K_GEMM, s);           // projection + rotary + cache write in one kernel
       mfma_gemm_qkv(c, l, (const bf16_t*)h, (const bf16_t*)(lw + c->p.wqkv), nullptr, tree, pos, Tq, pq, s);
     } else {
-      sp = run_gemm(c, h, lw + c->p.wqkv, go, M, 3 * d, d, true, s);
+      sp = run_gemm(c, h, lw + c->p.wqkv, go, M, 3 * d, d, pq, s);
       Timed timed(c, VVS_K_ELEMENTWISE, s);
       hipLaunchKernelGGL(k_rope_kv<T>, dim3(M, ((d >> 1) + 255) / 256), dim3(256), 0, s, go, sp, (size_t)M * 3 * d, q, kc, vc, rope, tree, pos, Tq, d, c->dh,
                          c->kv_row_stride, c->kv_head_stride, c->S_cap, c->rope_pos);
@@ -874,7 +872,7 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
       hipLaunchKernelGGL(k_attn_simple, dim3(Tq, c->H, c->R), dim3(256), lds, s, q, kc, vc, attn, tree, pos, Tq, d, c->dh,
                          c->kv_row_stride, c->kv_head_stride, c->S_cap);
     }
-    sp = run_gemm(c, attn, lw + c->p.wo, go, M, d, d, true, s);
+    sp = run_gemm(c, attn, lw + c->p.wo, go, M, d, d, plan_partial(c, M, d, d), s);
     { Timed timed(c, VVS_K_ELEMENTWISE, s);
     launch_add_rmsnorm<T>(M, x, go, sp, (size_t)M * d, d, (const float*)(lw + c->p.g2), c->cfg.rms_eps, h, 1, 0, s);
     }
@@ -883,13 +881,13 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
       Timed timed(c, VVS_K_GEMM, s);           // projection + SwiGLU in one kernel
       mfma_gemm_swiglu(c, (const bf16_t*)h, (const bf16_t*)(lw + c->p.wgu), (bf16_t*)act, nullptr, M, F, d, pg, s, WeightPrefetch{});
     } else {
-      sp = run_gemm(c, h, lw + c->p.wgu, go, M, 2 * F, d, true, s);
+      sp = run_gemm(c, h, lw + c->p.wgu, go, M, 2 * F, d, pg, s);
       size_t n = (size_t)M * (F / 8);
       Timed timed(c, VVS_K_ELEMENTWISE, s);
       hipLaunchKernelGGL(k_swiglu<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, go, sp, (size_t)M * 2 * F, act, M, F,
                          c->cfg.dtype == VVS_BF16 ? 1 : 0);
     }
-    splits = run_gemm(c, act, lw + c->p.wd, go, M, d, F, true, s);
+    splits = run_gemm(c, act, lw + c->p.wd, go, M, d, F, plan_partial(c, M, d, F), s);
     sstride = (size_t)M * d;
   }
   if (logits_mode == 0) return;
@@ -908,7 +906,9 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
     launch_add_rmsnorm<T>(Ml, x, go, splits, sstride, d, gf, c->cfg.rms_eps, hf, Tq, Tq - 1, s);
     }
   }
-  run_gemm(c, hf, c->pw + c->p.wout, logits, Ml, c->veff, d, false, s, logits_mode == 1 ? RowMap{Tq, tree.all, tree.first} : RowMap{});
+  GemmPlan pl = plan_gemm(c, Ml, c->veff, d);
+  pl.splits = 1;
+  run_gemm(c, hf, c->pw + c->p.wout, logits, Ml, c->veff, d, pl, s, logits_mode == 1 ? RowMap{Tq, tree.all, tree.first} : RowMap{});
 }
 
 void launch_forward(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, const int32_t* d_tokens_bt, const void* pc,
@@ -1193,7 +1193,7 @@ void launch_debug_gemm(Ctx* c, int m, int n, int k, const void* a, const void* w
   } else {
     transpose_into<float>(w, wt, k, n, n, 0, s);
   }
-  int sp = run_gemm(c, a, wt, part, m, n, k, true, s);
+  int sp = run_gemm(c, a, wt, part, m, n, k, plan_partial(c, m, n, k), s);
   size_t cnt = (size_t)m * n;
   hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, part, sp, cnt, out);
 }

@@ -235,16 +235,17 @@ int main(int argc, char** argv) {
       vvs::Ctx k;
       if (vvs::plan_sizes(&w, &k, &err) != VVS_OK) { printf("plan: %s\n", err.c_str()); return 1; }
       if (vvs::plan_fused(&k, 1)) continue;                  // takes no partial sums
-      auto need = [&](int m, int n, int kk) {
+      auto sums = [&](int m, int n, int kk, int splits) {
         ++checked;
-        if ((size_t)vvs::plan_gemm(&k, m, n, kk, 0, true).splits * m * n <= k.gemm_out_elems) return;
+        if ((size_t)splits * m * n <= k.gemm_out_elems) return;
         if (++undersized <= 3) printf("d %d, d_ff %d, norm mode %d, %d rows: partial sums of %d columns over %d do not fit\n", d, F, w.norm_mode, m, n, kk);
       };
+      auto need = [&](int m, int n, int kk) { sums(m, n, kk, vvs::plan_partial(&k, m, n, kk).splits); };
       for (int m32 = 32; m32 <= k.Mmax; m32 += 32)
         for (int m : {m32, m32 - ri(1, 31)}) {
           const vvs::GemmPlan q = vvs::plan_qkv(&k, m), gu = vvs::plan_gate_up(&k, m);
-          if (q.splits > 1 && (m + q.bm - 1) / q.bm * (3 * d / q.bn) < 160) need(m, 3 * d, d);
-          if (gu.splits > 1) need(m, 2 * F, d);
+          if (q.splits > 1 && (m + q.bm - 1) / q.bm * (3 * d / q.bn) < 160) sums(m, 3 * d, d, q.splits);
+          if (gu.splits > 1) sums(m, 2 * F, d, gu.splits);
           need(m, d, d);
           need(m, d, F);
           if (w.draft_input) need(m, d, 2 * d);

@@ -40,14 +40,26 @@ def test_product_of_large_weights_bf16(gc, m, n, k):
     pair.close()
 
 
-# d_model, heads, d_ff, tokens (rows = 2 x tokens); the tiles of q/k/v and of gate/up, both with whole sums (checked on the CPU as above)
-EPILOGUES = [(2048, 32, 3072, 24, (64, 64), (64, 128)), (2048, 16, 3072, 65, (128, 64), (64, 128)), (2048, 16, 3072, 150, (64, 128), (64, 128)),
+# d_model, heads, d_ff, tokens (rows = 2 x tokens); the tiles of q/k/v and of gate/up, both with whole sums (checked on the CPU as above; gate/up on
+# 64 columns has operands of its own)
+EPILOGUES = [(2048, 32, 3072, 24, (64, 64), (64, 64)), (2048, 16, 3072, 65, (128, 64), (64, 128)), (2048, 16, 3072, 150, (64, 128), (64, 128)),
              (2048, 32, 3072, 200, (128, 128), (128, 128)), (2048, 32, 3072, 345, (192, 128), (192, 128)), (2048, 16, 3072, 497, (128, 128), (256, 128)),
-             (4096, 32, 1536, 90, (192, 64), (64, 128)), (4096, 32, 1536, 193, (256, 128), (64, 128)), (4096, 64, 1536, 194, (256, 128), (64, 128))]
+             (4096, 32, 1536, 90, (192, 64), (64, 64)), (4096, 32, 1536, 193, (256, 128), (64, 128)), (4096, 64, 1536, 194, (256, 128), (64, 128))]
 
 
 @pytest.mark.parametrize("d,heads,d_ff,tokens", [case[:4] for case in EPILOGUES])
 def test_epilogues_of_large_weights_bf16(gc, d, heads, d_ff, tokens):
+    check_prefill(gc, d, heads, d_ff, tokens)
+
+
+# d_model, heads, d_ff, tokens; tile and shares of gate/up where it keeps operands of its own (checked on the CPU as above): one round of CUs with whole sums,
+# with sums in two shares, one row into the next row-block, and three rounds
+OWN_GATE_UP = [(2048, 16, 4096, 14, (32, 64, 1)), (2048, 32, 4096, 33, (64, 64, 1)), (4096, 32, 4096, 15, (32, 64, 2)), (4096, 32, 4096, 17, (64, 64, 2)),
+               (2048, 16, 16448, 9, (32, 64, 1))]
+
+
+@pytest.mark.parametrize("d,heads,d_ff,tokens", [case[:4] for case in OWN_GATE_UP])
+def test_gate_up_with_operands_of_its_own_bf16(gc, d, heads, d_ff, tokens):
     check_prefill(gc, d, heads, d_ff, tokens)
 
 
