@@ -182,6 +182,12 @@ bool plan_fused(const Ctx* c, int M) {
   return layer_weight_bytes <= ((size_t)48 << 20);
 }
 
+// 192 rows: where the gain of the one launch ends (vvs_few.hip).  Head size 64: its q/k/v tiles are a head's.
+int few_rows(const Ctx* c) {
+  if (!plan_fused(c, c->R) || c->dh != 64) return 0;
+  return std::min((int)align_up((size_t)c->R * c->Tmax, 32), 192);
+}
+
 vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   if (!cfg) return fail(err, VVS_EINVAL, "config is NULL");
   const vvs_config& g = *cfg;
@@ -271,9 +277,12 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   w.node_result = take(sizeof(int32_t) * c->B * VVS_MAX_T * 2);
   w.tokens = take(sizeof(int32_t) * c->B * VVS_MAX_T);
   w.rope_tab = take(sizeof(float) * 2 * c->rope_pos * (dh / 4));
+  const int few = few_rows(c);
+  w.few_sync = take(few ? sizeof(uint32_t) * kFewLine * (kFewHead + (size_t)few_layer_counters(c->H, few / 32) * c->L + 8) : 0);   // zeroed with the state
   w.x = take(sizeof(float) * (size_t)c->Mmax * d);
   w.h = take(c->esz * (size_t)c->Mmax * d);
-  w.gemm_out = take(sizeof(float) * go);
+  // (a call whose layers are one launch has no partial sums: what its phases hand on lies in their place)
+  w.gemm_out = w.few_buf = take(std::max(sizeof(float) * go, few_buf_bytes(few, d, F) * c->L));
   w.q = take(c->esz * (size_t)c->Mmax * d);
   w.attn = take(c->esz * (size_t)c->Mmax * d);
   w.act = take(c->esz * (size_t)c->Mmax * F);

@@ -40,7 +40,7 @@ struct GemmPlan { int bm, bn, splits; bool row_owner = false, shared = false; };
 // Byte offsets into the caller's workspace.
 struct Workspace {
   size_t state, outcome, node_result, tokens, rope_tab, x, h, gemm_out, q, attn, act, hf, logits, probs,
-      pq_work, ss, ss2, ring, ring_state, din, total;
+      pq_work, ss, ss2, ring, ring_state, din, few_sync, few_buf, total;
 };
 
 struct PackedLayout {
@@ -99,6 +99,7 @@ GemmPlan plan_qkv(const Ctx* c, int M);
 GemmPlan plan_gate_up(const Ctx* c, int M);
 GemmPlan plan_resid(const Ctx* c, int M);   // O, down and input-map projections of the fused layer
 bool plan_fused(const Ctx* c, int M);   // true: the fused 5-kernel layer runs for M GEMM rows
+int few_rows(const Ctx* c);   // rows up to which all layers of a verify or drafting forward are one launch (0: never)
 vvs_status build_tree(int n_nodes, const int32_t* h_parent, const uint8_t* h_mask, TreeDesc* out, std::string* err);
 
 // ---- launchers (kernels_*.hip); all asynchronous on the stream
@@ -153,6 +154,12 @@ void launch_debug_gemm(Ctx* c, int m, int n, int k, const void* a, const void* w
 // Columns per sum of squares of the residual stream, and sums per row (padded to a multiple of 4; the padding holds zeros)
 constexpr int kSlab = 32;
 constexpr int n_slabs(int d) { return ((d + kSlab - 1) / kSlab + 3) & ~3; }
+
+// All layers in one launch (vvs_few.hip): counters of a layer and bytes that it hands from phase to phase
+constexpr int kFewLine = 32;   // words between two counters: a line of its own for each
+constexpr int kFewHead = 19;   // counters in front of the layers'
+constexpr int few_layer_counters(int H, int row_tiles) { return H * row_tiles + 4 * 8; }
+constexpr size_t few_buf_bytes(int rows, int d, int F) { return (size_t)rows * (2 * (4 * (size_t)d + F) + 2 * 4 * (size_t)n_slabs(d)); }
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 

@@ -702,7 +702,8 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
   const float* g_first = (const float*)(c->pw + c->p.layer0 + c->p.g1);   // gain of the first layer's first norm
   const float* gf = (const float*)(c->pw + c->p.gf);
   // verify calls of up to 64 tokens per row at head size 64: projection + attention in one launch, fed by the row-padded operand layout
-  const int pad = mfma_qkv_attention_rows(c, pos, Tq);
+  const bool few = pos.kv_len && M <= few_rows(c);
+  const int pad = few ? 0 : mfma_qkv_attention_rows(c, pos, Tq);
   const bool qa = pad > 0;
   const int pad_T = qa ? Tq : 0;
   const GemmPlan pq = plan_qkv(c, M), pr = plan_resid(c, M), pg = plan_gate_up(c, M), pl = plan_gemm(c, M, c->veff, d);
@@ -718,7 +719,8 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
     if (qa) return WeightPrefetch{(const uint4*)(layer(l) + c->p.wqkv), c->H, 2 * (d / 16), 3, (d / 32) * (d / 16), c->B};
     return weights(layer(l) + c->p.wqkv, 3 * d, d, pq);
   };
-  if (from_din) {             // drafter: x = [embedding ; feature] W_fc
+  if (few && from_din) {      // the input map is part of the launch
+  } else if (from_din) {      // drafter: x = [embedding ; feature] W_fc
     Timed timed(c, VVS_K_GEMM, s);
     mfma_gemm_resid(c, (const bf16_t*)(c->ws + c->w.din), (const bf16_t*)(c->pw + c->p.fc), x, xb, ss, g_first, M, 2 * d, s, pf_qkv(0), pad_T, pad, true);
   } else {
@@ -726,7 +728,11 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
     hipLaunchKernelGGL(k_embed_packed, dim3(M), dim3(256), 0, s, x, xb, ss, NS, (const bf16_t*)(c->pw + c->p.embed),
                        (const bf16_t*)(c->pw + c->p.prefix_embed), g_first, ea, pad_T, pad);
   }
-  for (int l = 0; l < c->L; ++l) {
+  if (few) {
+    Timed timed(c, VVS_K_GEMM, s);
+    launch_layers_few(c, tree, pos, Tq, from_din, s);
+  }
+  for (int l = 0; l < c->L && !few; ++l) {
     const char* lw = c->pw + c->p.layer0 + c->p.layer_stride * l;
     if (qa) {
       Timed timed(c, VVS_K_GEMM, s);

@@ -7,38 +7,11 @@
 //   v_mfma_f32_16x16x32_bf16: lane l gives A[i = l%16][8 k-values of group l/16] and
 //     B[same 8 k-values][j = l%16]; accumulator register r of lane l is D[4*(l/16) + r][l%16].
 // A and B always pair the same (group, element) slot, so only "8 consecutive k per lane" matters.
-#include "vvs_device.h"
+#include "vvs_mfma.h"
 
 #include <algorithm>
 
 namespace vvs {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // 16 bytes as a native vector (plain register moves)
-
-__device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
-
-// Maximum / sum over the four lanes l % 16 + 16 j of a wave (the four 16-lane rows), left in all four, with gfx950's row
-// swaps: v_permlane16_swap exchanges the odd rows of its first operand with the even rows of its second, v_permlane32_swap
-// the upper half of the first with the lower half of the second - given the same value twice they return (x of the
-// even / lower partner, x of the odd / upper partner) in every lane.  Plain VALU instructions: the LDS crossbar that a
-// __shfl_xor goes through costs a round trip per step of these dependent chains.  Same order of additions as
-// x += xor16(x); x += xor32(x).
-typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ float rows_max(float x) {
-  uintx2 p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
-  p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
-}
-__device__ __forceinline__ float rows_sum(float x) {
-  uintx2 p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-  p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
-}
 
 // Phase marks: a profiling build may define VVS_PHASE_MARK(i) to record a time stamp at the i-th
 // point of a kernel (entry, operands requested, main loop done, tile in LDS, end); normally nothing.
@@ -91,16 +64,6 @@ struct GemmEpi {
   PosDesc pos;
   TreeDesc tree;
 };
-
-// Tile order of the projection launches.  Workgroups are dealt to the 8 XCDs round-robin by linear id, and each XCD has its own
-// L2.  Column tiles are taken in groups of 8 (one per XCD); inside a group the row tiles of one column tile get ids 8 apart:
-// they run at the same time on the same XCD, so a weight tile is fetched from memory once and then hits in that XCD's L2.  A
-// last group of fewer columns is dealt over all XCDs.
-__device__ __forceinline__ void tile_of(int id, int MT, int NT, int* tile_m, int* tile_n) {
-  const int grp = id / (8 * MT), rem = id % (8 * MT), cols = min(8, NT - grp * 8);
-  *tile_m = rem / cols;
-  *tile_n = grp * 8 + rem % cols;
-}
 
 // Weight prefetch.  A CU has about 45 KB of requests under way whatever its waves ask for, so it is filled at 45 KB per mean
 // latency: 110-150 GB/s from its XCD's L2, 42-55 GB/s from HBM (k_fill_probe).  A projection of few rows leaves CUs without a
@@ -1069,76 +1032,6 @@ void mfma_gemm_qkv(Ctx* c, int layer, const bf16_t* A, const bf16_t* Wqkv, const
   gemm_dispatch<EPI_QKV>(A, Wqkv, nullptr, c->R * T, 3 * c->d, c->d, p, ep, s);
 }
 
-// One 32-key step of the attention kernels for NQB blocks of 16 queries: scores S^T = K Q^T (lane = query l % 16, key
-// group g = l / 16, 8 consecutive keys per lane), online softmax, O^T += V^T P^T.  The tree mask only touches a step that
-// reaches past the cached length S (tail).
-// The softmax weights are not rounded to bf16 (the definition keeps them exact): each un-normalised weight e goes into the
-// P V product as the sum of two bf16 values, hi = bf16(e) and lo = bf16(e - hi) (e to 2^-17), with two MFMAs per V block -
-// the matrix cores idle in these kernels anyway - and the normaliser sums the fp32 weights themselves.
-template <int NQB, int KD, int DT>
-__device__ __forceinline__ void attn_step(const bf16x8 (&kf)[2][KD], const bf16x8 (&vf)[DT], const bf16x8 (&qf)[NQB][KD],
-                                          const uint64_t (&mask)[NQB], float (&m_run)[NQB], float (&l_run)[NQB], floatx4 (&o)[NQB][DT],
-                                          int key0, int S, int n_keys, bool tail, int g, float c_exp) {
-#pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) {
-    floatx4 s2[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      s2[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kd = 0; kd < KD; ++kd) s2[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][kd], qf[qb][kd], s2[t], 0, 0, 0);
-    }
-    float sv[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) sv[i] = s2[i >> 2][i & 3];
-    if (tail) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int key = key0 + 8 * g + i;
-        bool vis = key < S;
-        if (!vis && key < n_keys) vis = (mask[qb] >> (key - S)) & 1ull;
-        if (!vis) sv[i] = -INFINITY;
-      }
-    }
-    float mx = sv[0];
-#pragma unroll
-    for (int i = 1; i < 8; ++i) mx = fmaxf(mx, sv[i]);
-    mx = rows_max(mx);
-    const float m_new = fmaxf(m_run[qb], mx);
-    const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-    const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_safe) * c_exp);
-    const float mc = m_safe * c_exp;
-    uint32_t pk[4], pl[4];
-    float rs = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; i += 2) {
-      // hardware exp2 (arguments <= 0 up to the rounding of the fused multiply-add)
-      const float e0 = __builtin_amdgcn_exp2f(fmaf(sv[i], c_exp, -mc)), e1 = __builtin_amdgcn_exp2f(fmaf(sv[i + 1], c_exp, -mc));
-      const uint32_t pp = pack2bf(e0, e1);
-      rs += e0 + e1;
-      pk[i >> 1] = pp;
-      pl[i >> 1] = pack2bf(e0 - __uint_as_float(pp << 16), e1 - __uint_as_float(pp & 0xFFFF0000u));
-    }
-    rs = rows_sum(rs);
-    l_run[qb] = l_run[qb] * alpha + rs;
-    m_run[qb] = m_new;
-    const bf16x8 pf = as_bf16x8(make_uint4(pk[0], pk[1], pk[2], pk[3]));
-    const bf16x8 pfl = as_bf16x8(make_uint4(pl[0], pl[1], pl[2], pl[3]));
-    // the running maximum rarely moves after the first steps: the accumulators are only rescaled when some query's did
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) o[qb][dt][rr] *= alpha;
-    }
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-      o[qb][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], pf, o[qb][dt], 0, 0, 0);
-      o[qb][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], pfl, o[qb][dt], 0, 0, 0);
-    }
-  }
-}
-
 // ------------------------------------------------------------------------------------------------ attention
 // One workgroup per (head, row).  Scores are computed transposed, S^T[key][query] = K * Q^T, so the
 // accumulator layout (lane = query, registers = keys) is directly the B operand of
@@ -1689,16 +1582,11 @@ int mfma_qkv_attention_rows(const Ctx* c, const PosDesc& pos, int T) {
   const int pairs = c->H * c->B, rounds = (pairs + 255) / 256, pad = T <= 32 ? 32 : 64;
   const int least = rounds == 1 ? 0 : rounds == 2 ? 665 : 890;     // thousandths
   if (rounds > 3 || (long)pairs * T * 1000 < (long)least * rounds * 256 * pad) return 0;
-  // Of few pairs each CU pulls 655 KB of weights while most stand idle, where a projection of its own deals them to all: 20 heads, 1 prompt, 27
-  // tokens 1.57 (fused) / 1.44 ms, 61 tokens 2.17 / 1.80; waiting for the host after every pass 1.61 / 1.48, 2.21 / 1.83.  The same where the
-  // projection's 32 x 32 tiles all have a CU of their own (up to 64 rows at d 1280): 20 heads, 6 tokens, 2 prompts 1.51 / 1.34, 4 1.55 / 1.45; the
-  // drafting call of 8 prompts 0.462 / 0.446.
-  // Both lines are drawn inside what would pay.  40 and 80 pairs stay one launch, though apart they are 3 to 5 and 2 % faster at 27 tokens, 18 and 9 %
-  // at 61: which launches such a call takes is part of what callers measure with (vvs_timing_read), and 2 prompts of 20 heads are held to one.
-  // Below d 1024 so does every call, because a pass that waits for the host pays for the further launches there: 12 layers, us in a row of
-  // passes, then alone, fused / separate: 12 heads, 1 prompt x 6 tokens 359 / 341, 430 / 437; 2 x 27 414 / 398, 473 / 491; 14 heads 1 x 6 409 / 370,
-  // 461 / 437; 2 x 27 447 / 442, 486 / 518; 15 heads 2 x 27 473 / 464, 505 / 528; 16 heads (d 1024) 1 x 6 438 / 390, 477 / 451; 4 x 6 453 / 418, 493 / 486.
-  if (c->d >= 1024 && (pairs < 40 || qkv_small_tiles(c, c->R * T))) return 0;
+  // Of few pairs each CU pulls 655 KB of weights while most stand idle, where a projection of its own deals them to all (calls of up to few_rows(c)
+  // rows do not come here: 16 to 19 heads, 2 prompts of 49 tokens and more do).  Drawn inside what would pay: 40 and 80 pairs stay one launch, though
+  // apart they are 18 and 9 % faster at 61 tokens: which launches such a call takes is part of what callers measure with (vvs_timing_read), and 2 prompts
+  // of 20 heads are held to one.
+  if (c->d >= 1024 && pairs < 40) return 0;
   return pad;
 }
 
