@@ -3,8 +3,8 @@
 //
 // Every node of the draft tree is evaluated speculatively and in parallel - one workgroup per
 // (prompt, node) computes "which child of this node is accepted, or which token is drawn if none
-// is" - and a one-thread-per-prompt walk then follows the accepted children from the root.  The
-// uniforms are indexed by node, so this equals the sequential procedure.
+// is" - and whichever workgroup of a prompt is done last follows the accepted children from the root.
+// The uniforms are indexed by node, so this equals the sequential procedure.
 #include "vvs_device.h"
 
 #include <limits.h>
@@ -15,6 +15,37 @@
 #endif
 
 namespace vvs {
+
+struct WalkOut {
+  int32_t *accept_len, *path, *next_token, *keep;          // each may be nullptr; keep: the outcome for the commit
+  const int32_t *state, *ring_state;                       // with keep: what the commit starts from
+};
+
+// Follows accepted children from the root: lane i of the wave holds the result of node i (accepted child or 0, token) and ends with path entry i.
+__device__ __forceinline__ void walk_path(int child, int token, int b, int B, const WalkOut& o) {
+  static_assert(VVS_MAX_T == 64, "one lane per node and path entry");
+  const int i = threadIdx.x & 63;
+  int cur = 0, a = 0, mine = 0;
+  while (a < VVS_MAX_T - 1) {
+    const int nxt = __builtin_amdgcn_readlane(child, cur);
+    if (nxt <= cur) break;                 // 0 = nothing accepted (children always have larger ids)
+    cur = nxt;
+    if (i == ++a) mine = cur;
+  }
+  const int tok = __builtin_amdgcn_readlane(token, cur);
+  if (i == 0) {
+    if (o.accept_len) o.accept_len[b] = a;
+    if (o.next_token) o.next_token[b] = tok;
+    if (o.keep) { o.keep[b] = a; o.keep[B + b] = tok; }
+  }
+  if (o.keep && i < 6) {                   // cached length, emitted tokens; held and oldest of both rows
+    const int at = i < 2 ? i * B + b : (i >> 1) * 2 * B - 2 * B + 2 * b + (i & 1);
+    o.keep[kOutcomeSnap * B + (i < 2 ? at : 2 * B + at)] = i < 2 ? o.state[at] : o.ring_state[at];
+  }
+  const int v = i <= a ? mine : -1;
+  if (o.path) o.path[b * VVS_MAX_T + i] = v;
+  if (o.keep) o.keep[2 * B + b * VVS_MAX_T + i] = v;
+}
 
 struct AcceptArgs {
   const float* logits;        // [R][T][veff]
@@ -27,6 +58,9 @@ struct AcceptArgs {
   float* probs;               // [B][T][veff] out: target distributions
   float* work;                // [B][T][2][veff] scratch: running target P and draft Q
   int32_t* node_result;       // [B][VVS_MAX_T][2] out: (accepted child or 0, drawn token or -1)
+  uint32_t* done;             // [B][kWalkLine] nodes of a prompt that are done, zero between calls; nullptr: the walk is a launch of its own
+  WalkOut out;
+  int B;
   int T, veff, lo, mode, relax_k, G;
   float scale, delta;
 };
@@ -36,12 +70,12 @@ constexpr size_t kAcceptLdsMax = 144 * 1024;
 
 // Inverse CDF in ascending id: first id whose running sum exceeds u * total; if rounding runs past
 // the end, the last id with mass.  Each thread owns a contiguous chunk.
+template <int CK>
 __device__ int inverse_cdf(const float* __restrict__ P, int n, float u, float* red, int* ired, float* scan) {
   const int nt = blockDim.x, tid = threadIdx.x;
   const int per = (n + nt - 1) / nt;
   const int beg = min(tid * per, n), end = min(beg + per, n);
-  // chunks of up to 16 ids are read once into registers (16-byte reads when the chunk is aligned)
-  constexpr int CK = 16;
+  // chunks of up to CK ids are read once into registers (16-byte reads when the chunk is aligned)
   float c[CK];
   const bool in_regs = per <= CK;
   float local = 0.f;
@@ -112,8 +146,10 @@ __device__ int inverse_cdf(const float* __restrict__ P, int n, float u, float* r
 // is used.  WIDE (a slice of a multiple of 4 ids, rows on 16 bytes): a thread owns groups of 4 consecutive ids and moves 16 bytes
 // at a time.  8 prompts x 27 nodes x 16384 ids: 26.6 us with 4-byte loads and the draft row asked for behind the softmax, 25.2 us so.
 // Relaxed (the target goes through LDS once per tested child), 32 x 61 x 16384: 265 us and 243.
-template <bool LDS_PQ, bool WIDE>
-__global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tree) {
+// The last node of a prompt walks: as a launch behind this one the walk took 4 to 5 us, so 3 (the whole call above 25.2 -> 24.0).
+// NT threads, up to RK ids each (launch_accept_on chooses).
+template <bool LDS_PQ, bool WIDE, int NT, int RK>
+__global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void k_accept_node(AcceptArgs a, TreeDesc tree) {
   extern __shared__ __align__(16) float pq_lds[];
   __shared__ float red[32];
   __shared__ int ired[16];
@@ -125,8 +161,10 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
   __shared__ int sh_cx[VVS_MAX_T];         // drafted ids (inside the slice) and accept uniforms of this node's children, in order
   __shared__ float sh_cu[VVS_MAX_T];
   __shared__ int sh_cn[VVS_MAX_T], sh_nc;  // their node ids; how many
+  __shared__ int sh_last;
   VVS_PHASE_MARK(0);
-  const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, nt = blockDim.x;
+  const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  constexpr int nt = NT;
   const int T = a.T, V = a.veff;
   const float* lc = a.logits + ((size_t)(2 * b) * T + j) * V;
   const float* lu = a.logits + ((size_t)(2 * b + 1) * T + j) * V;
@@ -139,7 +177,6 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
   // later of the draft distribution) in registers for the whole kernel; the LDS / global copy P is
   // only brought up to date where ids are addressed at random (relaxed neighbourhoods, the final
   // inverse-CDF draw).  Larger slices take the generic loops over P and Q.
-  constexpr int RK = 16;
   const bool regs = V <= RK * nt;
   auto id_of = [&](int k) { return WIDE ? ((k >> 2) * nt + tid) * 4 + (k & 3) : tid + k * nt; };
   auto load_row = [&](const float* row, float (&v)[RK]) {    // clamped: ids past the slice repeat the last ones
@@ -176,7 +213,7 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
   if (regs) {
     load_row(lc, lcv);
     load_row(lu, luv);
-    if (tested) load_row(a.q + (size_t)(b * T + j) * V, q);
+    if (tested && RK == 16) load_row(a.q + (size_t)(b * T + j) * V, q);
   }
   int child_x = 0;
   float child_u = 0.f;
@@ -191,6 +228,7 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
       p[k] = id_of(k) < V ? luv[k] + a.scale * (lcv[k] - luv[k]) : -INFINITY;
       mx = fmaxf(mx, p[k]);
     }
+    if (tested && RK > 16) load_row(a.q + (size_t)(b * T + j) * V, q);   // (three rows at once do not fit the registers)
     mx = block_max(mx, red);
     float sum = 0.f;
 #pragma unroll
@@ -241,11 +279,31 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
   __syncthreads();
 
   VVS_PHASE_MARK(1);
-  int32_t* res = a.node_result + ((size_t)b * VVS_MAX_T + j) * 2;
+  // this node's result; the last one of the prompt walks.  Results and counter with agent scope: the nodes run on all XCDs
+  auto finish = [&](int child_id, int token) {
+    int32_t* res = a.node_result + ((size_t)b * VVS_MAX_T + j) * 2;
+    if (!a.done) {
+      if (tid == 0) { res[0] = child_id; res[1] = token; }
+      return;
+    }
+    uint32_t* done = a.done + (size_t)b * kWalkLine;
+    if (tid == 0) {
+      __hip_atomic_store((uint64_t*)res, (uint32_t)child_id | ((uint64_t)(uint32_t)token << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const bool last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)T - 1;
+      if (last) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sh_last = last;
+    }
+    __syncthreads();
+    if (!sh_last || tid >= VVS_MAX_T) return;
+    uint64_t r = 0;
+    if (tid < T) r = __hip_atomic_load((const uint64_t*)a.node_result + (size_t)b * VVS_MAX_T + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    walk_path((int)(uint32_t)r, (int)(uint32_t)(r >> 32), b, a.B, a.out);
+  };
   int cap = INT_MAX;
   if (a.n_emitted) {
     if (ne >= a.G) {                       // image complete: nothing to accept, nothing to draw
-      if (tid == 0) { res[0] = 0; res[1] = -1; }
+      finish(0, -1);
       return;
     }
     cap = a.G - ne - 1;
@@ -334,22 +392,22 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
       if (ua * qx < num) { accepted = c; break; }
       // rejected: target <- normalised positive part of (target - draft); drop x from the draft
       if (regs) {
-        float r[RK];
         float z = 0.f, zq = 0.f;
 #pragma unroll
         for (int k = 0; k < RK; ++k) {
-          r[k] = fmaxf(0.f, p[k] - q[k]);
-          if (tid == xo && k == xk) q[k] = 0.f;              // x leaves the draft distribution
-          z += r[k];
-          zq += q[k];
+          z += fmaxf(0.f, p[k] - q[k]);
+          zq += tid == xo && k == xk ? 0.f : q[k];
         }
         const float2 zz = block_sum2(z, zq, red);
         if (zz.x > 0.f) {                                    // a residual without mass leaves the target as it is
           const float inv = 1.0f / zz.x;                       // one division per row instead of one per id: 16 waves share 4 SIMDs
 #pragma unroll
-          for (int k = 0; k < RK; ++k) p[k] = r[k] * inv;
+          for (int k = 0; k < RK; ++k) p[k] = fmaxf(0.f, p[k] - q[k]) * inv;
           p_in_memory = false;
         }
+#pragma unroll
+        for (int k = 0; k < RK; ++k)
+          if (tid == xo && k == xk) q[k] = 0.f;                // x leaves the draft distribution
         if (!(zz.y > 0.f)) break;
         const float invq = 1.0f / zz.y;
 #pragma unroll
@@ -374,7 +432,7 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
   }
   VVS_PHASE_MARK(2);
   if (accepted) {
-    if (tid == 0) { res[0] = accepted; res[1] = -1; }
+    finish(accepted, -1);
     return;
   }
   if (regs && !p_in_memory) {                                // the draw addresses ids in ascending order: bring P up to date
@@ -383,46 +441,21 @@ __global__ __launch_bounds__(1024) void k_accept_node(AcceptArgs a, TreeDesc tre
   }
   __syncthreads();
   const float ut = a.u[(size_t)b * a.usb + (size_t)j * a.usj + a.uot];
-  const int tok = inverse_cdf(P, V, ut, red, ired, scan);
+  const int tok = inverse_cdf<RK>(P, V, ut, red, ired, scan);
   VVS_PHASE_MARK(3);
-  if (tid == 0) { res[0] = 0; res[1] = a.lo + tok; }
+  finish(0, a.lo + tok);
 }
 
-// Follows accepted children from the root: one wave per prompt, lane 0 walks (at most tree-depth
-// dependent reads), then the lanes write one path entry each.
-__global__ __launch_bounds__(64) void k_walk(const int32_t* __restrict__ node_result, int B, int32_t* __restrict__ accept_len,
-                                             int32_t* __restrict__ path, int32_t* __restrict__ next_token, int32_t* __restrict__ keep) {
-  static_assert(VVS_MAX_T == 64, "one lane per path entry");
-  __shared__ int p[VVS_MAX_T];
-  __shared__ int s_a, s_tok;
-  const int b = blockIdx.x, i = threadIdx.x;
-  if (i == 0) {
-    int cur = 0, a = 0;
-    p[0] = 0;
-    while (a < VVS_MAX_T - 1) {
-      const int nxt = node_result[((size_t)b * VVS_MAX_T + cur) * 2];
-      if (nxt <= cur) break;               // 0 = nothing accepted (children always have larger ids)
-      cur = nxt;
-      p[++a] = cur;
-    }
-    s_a = a;
-    s_tok = node_result[((size_t)b * VVS_MAX_T + cur) * 2 + 1];
-  }
-  __syncthreads();
-  const int a = s_a, tok = s_tok;
-  if (i == 0) {
-    if (accept_len) accept_len[b] = a;
-    if (next_token) next_token[b] = tok;
-    if (keep) { keep[b] = a; keep[B + b] = tok; }
-  }
-  const int v = i <= a ? p[i] : -1;
-  if (path) path[b * VVS_MAX_T + i] = v;
-  if (keep) keep[2 * B + b * VVS_MAX_T + i] = v;
+// The walk as a launch of its own: one wave per prompt.
+__global__ __launch_bounds__(64) void k_walk(const int32_t* __restrict__ node_result, int B, int T, WalkOut out) {
+  const int b = blockIdx.x, i = min((int)threadIdx.x, T - 1);
+  const int2 r = ((const int2*)node_result)[(size_t)b * VVS_MAX_T + i];
+  walk_path(r.x, r.y, b, B, out);
 }
 
 static void launch_accept_on(Ctx* c, const TreeDesc& tree, int T, const float* d_logits, const int32_t* d_draft_tokens, const float* d_q,
                              const float* d_u, int usb, int usj, int uoa, int uot, int mode, bool use_state, int32_t* d_accept_len,
-                             int32_t* d_path, int32_t* d_next, int32_t* keep, float* probs, float* work, int32_t* node_result, hipStream_t s) {
+                             int32_t* d_path, int32_t* d_next, int32_t* keep, float* probs, float* work, int32_t* node_result, uint32_t* done, hipStream_t s) {
   Timed timed(c, VVS_K_ACCEPT, s);
   AcceptArgs a;
   a.logits = d_logits; a.draft = d_draft_tokens; a.q = d_q; a.u = d_u;
@@ -432,19 +465,32 @@ static void launch_accept_on(Ctx* c, const TreeDesc& tree, int T, const float* d
   a.probs = probs;
   a.work = work;
   a.node_result = node_result;
+  a.done = done;
+  a.out = WalkOut{d_accept_len, d_path, d_next, keep, (const int32_t*)(c->ws + c->w.state), (const int32_t*)(c->ws + c->w.ring_state)};
+  a.B = c->B;
   a.T = T; a.veff = c->veff; a.lo = c->lo; a.mode = mode; a.relax_k = c->cfg.relax_k; a.G = c->G;
   a.scale = c->cfg.cfg_scale; a.delta = c->cfg.relax_delta;
   const size_t pq_bytes = (size_t)2 * c->veff * sizeof(float);
   // rows of a multiple of 4 ids that all start on 16 bytes
   const bool wide = c->veff % 4 == 0 && ((uintptr_t)a.logits | (uintptr_t)a.q | (uintptr_t)a.probs) % 16 == 0;
-  if (pq_bytes <= kAcceptLdsMax) {
-    const auto kernel = wide ? k_accept_node<true, true> : k_accept_node<true, false>;
-    if (pq_bytes > 64 * 1024) allow_dynamic_lds((const void*)kernel, kAcceptLdsMax);
-    hipLaunchKernelGGL(kernel, dim3(T, c->B), dim3(1024), pq_bytes, s, a, tree);
-  } else {                                   // wider slices than the registers hold: the loops over ids
-    hipLaunchKernelGGL((k_accept_node<false, false>), dim3(T, c->B), dim3(1024), 0, s, a, tree);
+  const dim3 grid(T, c->B);
+#define VVS_ACCEPT(LDS, NT, RK, BYTES)                                                                            \
+  {                                                                                                               \
+    const auto kernel = wide ? k_accept_node<LDS, true, NT, RK> : k_accept_node<LDS, false, NT, RK>;                \
+    if ((BYTES) > 64 * 1024) allow_dynamic_lds((const void*)kernel, kAcceptLdsMax);                               \
+    hipLaunchKernelGGL(kernel, grid, dim3(NT), (BYTES), s, a, tree);                                              \
   }
-  hipLaunchKernelGGL(k_walk, dim3(c->B), dim3(64), 0, s, (const int32_t*)a.node_result, c->B, d_accept_len, d_path, d_next, keep);
+  // Few ids: 4 waves, which meet at a barrier sooner (1024 ids, one prompt of 5 nodes: 12.7 -> 8.4 us with the walk).  More nodes than CUs: two workgroups
+  // of 512 threads to a CU cover each other's barriers (32 x 61 nodes x 16384 ids, relaxed: 247 -> 225 us, though 45 registers spill); else one of 1024
+  if (c->veff <= 4096) VVS_ACCEPT(true, 256, 16, pq_bytes / 2)
+  else if (c->veff <= 16 * 1024 && T * c->B > 256) VVS_ACCEPT(true, 512, 32, pq_bytes / 2)
+  else if (c->veff <= 16 * 1024) VVS_ACCEPT(true, 1024, 16, pq_bytes / 2)
+  else if (pq_bytes <= kAcceptLdsMax) VVS_ACCEPT(true, 1024, 16, pq_bytes)
+  else {                                     // wider slices than the registers hold: the loops over ids
+    hipLaunchKernelGGL((k_accept_node<false, false, 1024, 16>), grid, dim3(1024), 0, s, a, tree);
+  }
+#undef VVS_ACCEPT
+  if (!done) hipLaunchKernelGGL(k_walk, dim3(c->B), dim3(64), 0, s, (const int32_t*)a.node_result, c->B, T, a.out);
 }
 
 void launch_accept(Ctx* c, const TreeDesc& tree, int T, const float* d_logits, const int32_t* d_draft_tokens, const float* d_q,
@@ -452,7 +498,7 @@ void launch_accept(Ctx* c, const TreeDesc& tree, int T, const float* d_logits, c
                    int32_t* d_path, int32_t* d_next, bool keep_outcome, hipStream_t s) {
   launch_accept_on(c, tree, T, d_logits, d_draft_tokens, d_q, d_u, usb, usj, uoa, uot, mode, use_state, d_accept_len, d_path, d_next,
                    keep_outcome ? (int32_t*)(c->ws + c->w.outcome) : nullptr, (float*)(c->ws + c->w.probs), (float*)(c->ws + c->w.pq_work),
-                   (int32_t*)(c->ws + c->w.node_result), s);
+                   (int32_t*)(c->ws + c->w.node_result), (uint32_t*)(c->ws + c->w.walk_sync), s);
 }
 
 // ------------------------------------------------------------------------------------------------ acceptance stage without any allocation
@@ -495,7 +541,7 @@ vvs_status launch_accept_noalloc(Ctx* c, const TreeDesc& tree, int T, const floa
   }
   unsigned char* base = g_scratch_ptr[dev];
   launch_accept_on(c, tree, T, d_logits, d_draft_tokens, d_q, d_u, 2 * T, 2, 0, 1, mode, false, d_accept_len, d_path, d_next, nullptr,
-                   (float*)(base + kNoAllocNodeBytes), nullptr, (int32_t*)base, s);
+                   (float*)(base + kNoAllocNodeBytes), nullptr, (int32_t*)base, nullptr, s);
   return VVS_OK;
 }
 

@@ -162,7 +162,9 @@ __global__ __launch_bounds__(1024) void k_draft_select(const float* __restrict__
 
 // The same for slices of at most 16 * 1024 ids: a thread keeps its 16 mixed logits in registers, so the
 // rows are read once and a taken id is simply removed from its owner's registers.
-__global__ __launch_bounds__(1024) void k_draft_select_regs(const float* __restrict__ logits, DraftLevel lv, TreeDesc shape,
+// (Slices of at most 4096 ids on 4 waves: d 128, 1024 ids, whole draft loop 8 us of 213 less together with the acceptance.)
+template <int NT>
+__global__ __launch_bounds__(NT) void k_draft_select_regs(const float* __restrict__ logits, DraftLevel lv, TreeDesc shape,
                                                             const int32_t* __restrict__ given, int32_t* __restrict__ draft_tokens,
                                                             float* __restrict__ probs, int V, int lo, float cfg_scale) {
   constexpr int NR = 16;
@@ -178,7 +180,7 @@ __global__ __launch_bounds__(1024) void k_draft_select_regs(const float* __restr
   float mx = -INFINITY;
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    const int i = threadIdx.x + r * 1024;
+    const int i = threadIdx.x + r * NT;
     mixed[r] = -INFINITY;
     if (i < V) mixed[r] = lu[i] + cfg_scale * (lc[i] - lu[i]);
     mx = fmaxf(mx, mixed[r]);
@@ -188,14 +190,14 @@ __global__ __launch_bounds__(1024) void k_draft_select_regs(const float* __restr
   float sum = 0.f;
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    e[r] = threadIdx.x + r * 1024 < V ? expf(mixed[r] - mx) : 0.f;
+    e[r] = threadIdx.x + r * NT < V ? expf(mixed[r] - mx) : 0.f;
     sum += e[r];
   }
   sum = block_sum(sum, red);
   const float inv = 1.0f / sum;
 #pragma unroll
   for (int r = 0; r < NR; ++r)
-    if (threadIdx.x + r * 1024 < V) out[threadIdx.x + r * 1024] = e[r] * inv;
+    if (threadIdx.x + r * NT < V) out[threadIdx.x + r * NT] = e[r] * inv;
   for (int c = shape.first_child[j]; c >= 0; c = shape.next_sibling[c]) {
     if (given) {
       if (threadIdx.x == 0) draft_tokens[b * lv.n_nodes + c - 1] = given[b * lv.n_nodes + c - 1];
@@ -204,14 +206,14 @@ __global__ __launch_bounds__(1024) void k_draft_select_regs(const float* __restr
     Best best{-INFINITY, 0x7fffffff};
 #pragma unroll
     for (int r = 0; r < NR; ++r)                       // ascending ids: a later equal value does not replace an earlier one
-      if (mixed[r] > best.v) best = Best{mixed[r], (int)threadIdx.x + r * 1024};
+      if (mixed[r] > best.v) best = Best{mixed[r], (int)threadIdx.x + r * NT};
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) best = better(best, Best{__shfl_xor(best.v, o, 64), __shfl_xor(best.i, o, 64)});
     if ((threadIdx.x & 63) == 0) { s_bv[threadIdx.x >> 6] = best.v; s_bi[threadIdx.x >> 6] = best.i; }
     __syncthreads();
     if (threadIdx.x == 0) {
       Best w{s_bv[0], s_bi[0]};
-      for (int q = 1; q < 16; ++q) w = better(w, Best{s_bv[q], s_bi[q]});
+      for (int q = 1; q < NT / 64; ++q) w = better(w, Best{s_bv[q], s_bi[q]});
       s_win = w.i;
       draft_tokens[b * lv.n_nodes + c - 1] = lo + w.i;
     }
@@ -219,7 +221,7 @@ __global__ __launch_bounds__(1024) void k_draft_select_regs(const float* __restr
     const int win = s_win;
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-      if (threadIdx.x + r * 1024 == win) mixed[r] = -INFINITY;
+      if (threadIdx.x + r * NT == win) mixed[r] = -INFINITY;
     __syncthreads();                                   // s_win and the per-wave slots are rewritten by the next child
   }
 }
@@ -228,8 +230,11 @@ void launch_draft_select(Ctx* dr, const DraftLevel& lv, const TreeDesc& shape, c
                          float* d_probs, hipStream_t s) {
   if (!lv.n_sel) return;
   Timed timed(dr, VVS_K_ACCEPT, s);
-  if (dr->veff <= 16 * 1024)
-    hipLaunchKernelGGL(k_draft_select_regs, dim3(dr->B, lv.n_sel), dim3(1024), 0, s, (const float*)(dr->ws + dr->w.logits), lv, shape,
+  if (dr->veff <= 16 * 256)
+    hipLaunchKernelGGL(k_draft_select_regs<256>, dim3(dr->B, lv.n_sel), dim3(256), 0, s, (const float*)(dr->ws + dr->w.logits), lv, shape,
+                       d_given_tokens, d_draft_tokens, d_probs, dr->veff, dr->lo, dr->cfg.cfg_scale);
+  else if (dr->veff <= 16 * 1024)
+    hipLaunchKernelGGL(k_draft_select_regs<1024>, dim3(dr->B, lv.n_sel), dim3(1024), 0, s, (const float*)(dr->ws + dr->w.logits), lv, shape,
                        d_given_tokens, d_draft_tokens, d_probs, dr->veff, dr->lo, dr->cfg.cfg_scale);
   else
     hipLaunchKernelGGL(k_draft_select, dim3(dr->B, lv.n_sel), dim3(1024), 0, s, (const float*)(dr->ws + dr->w.logits), lv, shape,

@@ -273,10 +273,11 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
   w.state = take(sizeof(int32_t) * 3 * c->B);
   w.ring_state = take(sizeof(int32_t) * 2 * c->R);        // per row: features held, slot of the oldest (zeroed with the state)
-  w.outcome = take(sizeof(int32_t) * c->B * (2 + VVS_MAX_T));
+  w.outcome = take(sizeof(int32_t) * c->B * kOutcomeInts);
   w.node_result = take(sizeof(int32_t) * c->B * VVS_MAX_T * 2);
   w.tokens = take(sizeof(int32_t) * c->B * VVS_MAX_T);
   w.rope_tab = take(sizeof(float) * 2 * c->rope_pos * (dh / 4));
+  w.walk_sync = take(sizeof(uint32_t) * kWalkLine * c->B);      // zeroed with the state
   const int few = few_rows(c);
   w.few_sync = take(few ? sizeof(uint32_t) * kFewLine * (kFewHead + (size_t)few_layer_counters(c->H, few / 32) * c->L + 8) : 0);   // zeroed with the state
   w.x = take(sizeof(float) * (size_t)c->Mmax * d);

@@ -40,7 +40,7 @@ struct GemmPlan { int bm, bn, splits; bool row_owner = false, shared = false; };
 // Byte offsets into the caller's workspace.
 struct Workspace {
   size_t state, outcome, node_result, tokens, rope_tab, x, h, gemm_out, q, attn, act, hf, logits, probs,
-      pq_work, ss, ss2, ring, ring_state, din, few_sync, few_buf, total;
+      pq_work, ss, ss2, ring, ring_state, din, few_sync, few_buf, walk_sync, total;
 };
 
 struct PackedLayout {
@@ -154,6 +154,12 @@ void launch_debug_gemm(Ctx* c, int m, int n, int k, const void* a, const void* w
 // Columns per sum of squares of the residual stream, and sums per row (padded to a multiple of 4; the padding holds zeros)
 constexpr int kSlab = 32;
 constexpr int n_slabs(int d) { return ((d + kSlab - 1) / kSlab + 3) & ~3; }
+
+// Outcome of a verify that waits for its commit, int32 per prompt (B prompts): accept_len [B], next token [B], path [B][VVS_MAX_T], then what the commit
+// starts from, as the verify found it - cached length [B], emitted tokens [B], ring entries held [2 B] and slot of the oldest [2 B] -
+// so that one launch can move the cache and advance the state.
+constexpr int kOutcomeSnap = 2 + VVS_MAX_T, kOutcomeInts = kOutcomeSnap + 6;
+constexpr int kWalkLine = 16;   // words between the counters of two prompts (k_accept_node)
 
 // All layers in one launch (vvs_few.hip): counters of a layer and bytes that it hands from phase to phase
 constexpr int kFewLine = 32;   // words between two counters: a line of its own for each

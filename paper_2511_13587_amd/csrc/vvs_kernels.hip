@@ -932,14 +932,13 @@ void launch_forward(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, con
 // k-th since the oldest goes to slot (oldest + held + k) % slots.  One workgroup per (row, appended
 // token); only the last `slots` tokens of a push are written (older ones would be overwritten by it).
 //   path != nullptr: commit - the tokens are path[b][0 .. accept_len[b]] (skipped for finished prompts); a slice of the launch
-//                    that moves the cache, of which it needs nothing (a launch of its own: 5 us behind it); the ring state is
-//                    advanced afterwards by k_commit_state;
+//                    that moves the cache, of which it needs nothing (a launch of its own: 5 us behind it);
 //   path == nullptr: prefill - the single token fixed_node into an emptied ring (state written here).
 struct PushArgs {
   const float *x, *gf;
   void* ring;
   int32_t* ring_state;
-  const int32_t *accept_len, *next_token, *path;
+  const int32_t *accept_len, *next_token, *path, *ring_was;  // ring_was: ring_state before the commit
   int Tq, fixed_node, R, d, slots, pre_norm;
   float eps;
 };
@@ -953,8 +952,8 @@ __device__ __forceinline__ void push_feature(const PushArgs& a, int r, int at) {
   if (a.path) {
     if (a.next_token[b] < 0) return;
     n = a.accept_len[b] + 1;
-    held = a.ring_state[r];
-    oldest = a.ring_state[a.R + r];
+    held = a.ring_was[r];
+    oldest = a.ring_was[a.R + r];
   }
   const int i = max(0, n - a.slots) + at;
   if (i >= n) return;
@@ -980,7 +979,7 @@ __global__ __launch_bounds__(256) void k_push_features(PushArgs a) { push_featur
 
 static PushArgs push_args(Ctx* c, const int32_t* path, int Tq, int fixed_node) {
   const int32_t* oc = (const int32_t*)(c->ws + c->w.outcome);
-  return PushArgs{(const float*)(c->ws + c->w.x), (const float*)(c->pw + c->p.gf), c->ws + c->w.ring, (int32_t*)(c->ws + c->w.ring_state), oc, oc + c->B, path,
+  return PushArgs{(const float*)(c->ws + c->w.x), (const float*)(c->pw + c->p.gf), c->ws + c->w.ring, (int32_t*)(c->ws + c->w.ring_state), oc, oc + c->B, path, oc + (kOutcomeSnap + 2) * c->B,
                   Tq, fixed_node, c->R, c->d, c->cfg.feature_slots, c->cfg.feature_pre_norm, c->cfg.rms_eps};
 }
 
@@ -990,8 +989,24 @@ static PushArgs push_args(Ctx* c, const int32_t* path, int Tq, int fixed_node) {
 // owns either one chunk (CT: 16 bytes, or one element when the head size does not allow that) of a K
 // row or one V element of a head for every accepted position; it reads the sources of up to 8
 // positions before it writes them, which leaves one memory round trip per 8 positions.
+// One workgroup of a prompt advances its state; everybody reads the lengths as the verify found them (`was`: [2][B], then the rings), so nothing
+// has to be over before.  (A launch of its own behind this one: 2 to 5 us.)
+struct CommitState { int32_t *state, *ring_state; const int32_t* was; int slots, B; };
+__device__ __forceinline__ void commit_state(const CommitState& c, int b, int accepted, int token) {
+  const int n = accepted + 1, B = c.B, R = 2 * B;
+  c.state[b] = c.was[b] + n;               // cached length
+  c.state[B + b] = c.was[B + b] + n;       // emitted image tokens
+  c.state[2 * B + b] = token;              // pending token
+  if (c.slots > 0)                         // the feature rings of both rows took n more entries
+    for (int r = 2 * b; r < 2 * b + 2; ++r) {
+      const int held = c.was[2 * B + r], oldest = c.was[2 * B + R + r], now = min(held + n, c.slots);
+      c.ring_state[r] = now;
+      c.ring_state[R + r] = (oldest + held + n - now) % c.slots;
+    }
+}
+
 template <typename T, typename CT>
-__global__ __launch_bounds__(256) void k_commit_kv(T* __restrict__ kcache, T* __restrict__ vcache, const int32_t* __restrict__ kv_len,
+__global__ __launch_bounds__(256) void k_commit_kv(T* __restrict__ kcache, T* __restrict__ vcache, CommitState cs,
                                                    const int32_t* __restrict__ accept_len, const int32_t* __restrict__ next_token,
                                                    const int32_t* __restrict__ path, int H, int dh, size_t layer_stride,
                                                    size_t row_stride, size_t head_stride, int S_cap, int n_layers, PushArgs push) {
@@ -1003,7 +1018,8 @@ __global__ __launch_bounds__(256) void k_commit_kv(T* __restrict__ kcache, T* __
     return;
   }
   if (next_token[b] < 0) return;
-  const int S = kv_len[b], a = accept_len[b];
+  const int S = cs.was[b], a = accept_len[b];
+  if (threadIdx.x == 0 && l == 0 && blockIdx.z == 0 && !(r & 1)) commit_state(cs, b, a, next_token[b]);
   if (threadIdx.x < VVS_MAX_T) s_src[threadIdx.x] = path[b * VVS_MAX_T + threadIdx.x];
   __syncthreads();
   T* kb = kcache + l * layer_stride + r * row_stride;
@@ -1046,27 +1062,8 @@ __global__ __launch_bounds__(256) void k_commit_kv(T* __restrict__ kcache, T* __
   }
 }
 
-__global__ void k_commit_state(int32_t* __restrict__ state, int32_t* __restrict__ ring_state, int slots,
-                               const int32_t* __restrict__ accept_len, const int32_t* __restrict__ next_token, int B) {
-  int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B || next_token[b] < 0) return;
-  const int n = accept_len[b] + 1;
-  state[b] += n;                           // cached length
-  state[B + b] += n;                       // emitted image tokens
-  state[2 * B + b] = next_token[b];        // pending token
-  if (slots > 0) {                         // the feature rings of both rows took n more entries
-    const int R = 2 * B;
-    for (int r = 2 * b; r < 2 * b + 2; ++r) {
-      const int held = ring_state[r], oldest = ring_state[R + r], now = min(held + n, slots);
-      ring_state[r] = now;
-      ring_state[R + r] = (oldest + held + n - now) % slots;
-    }
-  }
-}
-
 void launch_commit(Ctx* c, hipStream_t s) {
   Timed timed(c, VVS_K_COMMIT, s);
-  int32_t* state = (int32_t*)(c->ws + c->w.state);
   const int32_t* oc = (const int32_t*)(c->ws + c->w.outcome);
   const int32_t* accept_len = oc;
   const int32_t* next_token = oc + c->B;
@@ -1075,21 +1072,20 @@ void launch_commit(Ctx* c, hipStream_t s) {
   const int items = c->H * c->dh / (vec ? 16 / (int)c->esz : 1) + c->H * c->dh;   // K chunks + V elements per (row, layer)
   const int slots = std::max(c->cfg.feature_slots, 0);
   const PushArgs push = push_args(c, path, c->last_T, -1);
+  const CommitState cs{(int32_t*)(c->ws + c->w.state), (int32_t*)(c->ws + c->w.ring_state), oc + kOutcomeSnap * c->B, c->cfg.feature_slots, c->B};
   dim3 grid(c->R, c->L + (slots > 0), std::max((items + 255) / 256, slots));
   if (c->cfg.dtype == VVS_BF16 && vec)
-    hipLaunchKernelGGL((k_commit_kv<bf16_t, uint4>), grid, dim3(256), 0, s, (bf16_t*)c->kv, (bf16_t*)c->kv + c->kv_v_off, state, accept_len,
+    hipLaunchKernelGGL((k_commit_kv<bf16_t, uint4>), grid, dim3(256), 0, s, (bf16_t*)c->kv, (bf16_t*)c->kv + c->kv_v_off, cs, accept_len,
                        next_token, path, c->H, c->dh, c->kv_layer_stride, c->kv_row_stride, c->kv_head_stride, c->S_cap, c->L, push);
   else if (c->cfg.dtype == VVS_BF16)
-    hipLaunchKernelGGL((k_commit_kv<bf16_t, bf16_t>), grid, dim3(256), 0, s, (bf16_t*)c->kv, (bf16_t*)c->kv + c->kv_v_off, state, accept_len,
+    hipLaunchKernelGGL((k_commit_kv<bf16_t, bf16_t>), grid, dim3(256), 0, s, (bf16_t*)c->kv, (bf16_t*)c->kv + c->kv_v_off, cs, accept_len,
                        next_token, path, c->H, c->dh, c->kv_layer_stride, c->kv_row_stride, c->kv_head_stride, c->S_cap, c->L, push);
   else if (vec)
-    hipLaunchKernelGGL((k_commit_kv<float, uint4>), grid, dim3(256), 0, s, (float*)c->kv, (float*)c->kv + c->kv_v_off, state, accept_len,
+    hipLaunchKernelGGL((k_commit_kv<float, uint4>), grid, dim3(256), 0, s, (float*)c->kv, (float*)c->kv + c->kv_v_off, cs, accept_len,
                        next_token, path, c->H, c->dh, c->kv_layer_stride, c->kv_row_stride, c->kv_head_stride, c->S_cap, c->L, push);
   else
-    hipLaunchKernelGGL((k_commit_kv<float, float>), grid, dim3(256), 0, s, (float*)c->kv, (float*)c->kv + c->kv_v_off, state, accept_len,
+    hipLaunchKernelGGL((k_commit_kv<float, float>), grid, dim3(256), 0, s, (float*)c->kv, (float*)c->kv + c->kv_v_off, cs, accept_len,
                        next_token, path, c->H, c->dh, c->kv_layer_stride, c->kv_row_stride, c->kv_head_stride, c->S_cap, c->L, push);
-  hipLaunchKernelGGL(k_commit_state, dim3((c->B + 63) / 64), dim3(64), 0, s, state, (int32_t*)(c->ws + c->w.ring_state),
-                     c->cfg.feature_slots, accept_len, next_token, c->B);
 }
 
 void launch_push_prefill_feature(Ctx* c, int T_last_chunk, hipStream_t s) {
