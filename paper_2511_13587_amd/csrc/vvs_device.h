@@ -195,6 +195,7 @@ void mfma_gemm_swiglu(Ctx* c, const bf16_t* A, const bf16_t* Wgu, bf16_t* act, c
 void mfma_gemm_qkv(Ctx* c, int layer, const bf16_t* A, const bf16_t* Wqkv, const float* ss, const TreeDesc& tree, const PosDesc& pos, int T,
                    GemmPlan p, hipStream_t s);
 void launch_layers_few(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, bool from_din, hipStream_t s);
+void launch_layers_wide(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, hipStream_t s);
 void mfma_attention(Ctx* c, int layer, const TreeDesc& tree, const PosDesc& pos, int T, hipStream_t s, const WeightPrefetch& pf = WeightPrefetch{});
 
 }  // namespace vvs

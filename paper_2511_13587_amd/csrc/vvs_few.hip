@@ -5,7 +5,7 @@
 // depend on nothing that the forward computes, so a workgroup asks for them at once and only then waits until the tiles of the phase
 // before are done.
 //
-// Phases of a layer, each a list of tiles (one workgroup of 8 waves takes one):
+// Phases of a layer, each a list of tiles (one workgroup of 8 waves takes one; wide layers: k_layers_wide):
 //   input map (drafter, once)   32 x 32 tiles of x = [embedding ; feature] W_fc
 //   q/k/v                       32 x 32 tiles, rotary embedding, K / V cache write
 //   attention                   16 or 32 queries of a head, 1, 2 or 4 rows
@@ -44,7 +44,7 @@ namespace vvs {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-enum { PH_INPUT = 0, PH_QKV, PH_ATTN, PH_O, PH_GU, PH_DOWN };
+enum { PH_INPUT = 0, PH_QKV, PH_ATTN, PH_O, PH_GU, PH_DOWN, PH_PART };
 constexpr int kGroups = 256;               // workgroups: one per CU (fewer CUs: see below)
 constexpr int kWaves = 8, kThreads = kWaves * 64;
 constexpr int kPolls = 1 << 21;            // more than a second: by then something else is broken, and the results are not valid
@@ -69,6 +69,7 @@ __device__ __forceinline__ void barrier() {          // of the workgroup; nothin
 }
 
 constexpr int kLine = kFewLine;
+constexpr int kWideShares = kFewWideShares;
 
 struct FewArgs {
   const char* layer0;                      // packed weights
@@ -87,6 +88,7 @@ struct FewArgs {
                                            // are done, [8] workgroups that are there, [8] done; then the layers' counters, then 8 of the input map
   int L, M, MT, T, d, H, F, R, NS, S_cap, rope_pos;
   int rows_per_unit;                       // rows that share an attention unit: 1, 2 or 4
+  float* part;                             // wide layers: partial sums of O and of down [kWideShares][M][d]
   float eps, c_exp;
   PosDesc pos;
   TreeDesc tree;
@@ -168,14 +170,18 @@ __device__ __forceinline__ bf16x8 few_load(__amdgpu_buffer_rsrc_t r, int off, in
 // are asked for; what it waits for are the tiles that wrote A.
 //   16 x 16 x 32 products; a wave takes 1/8 of the contraction.  Its weights are asked for NS steps of 32 ahead (for the usual widths that is
 //   all of them), its part of A, which may be asked for only after the wait, NA steps ahead.  No request goes past a wave's last step.
-template <int PH, int CN, int NS, int NA, typename Wait>
+//   DH: head size (q/k/v).  SCALED: A is a row's residual values, un-normalised; its RMSNorm factor multiplies the result.  PH_PART: share `share` of
+//   kWideShares of the contraction, whose sums go to a.part.
+template <int PH, int CN, int NS, int NA, int DH = 64, bool SCALED = PH == PH_QKV || PH == PH_GU, typename Wait>
 __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, const bf16_t* W, int K, int mt, int nt, const float* ss, float* ss_out,
-                                         bf16_t* out, const float* g_next, int l, float* red, FewShared* sh, uint32_t* done, Wait wait) {
+                                         bf16_t* out, const float* g_next, int l, float* red, FewShared* sh, uint32_t* done, Wait wait, int share = 0) {
   constexpr int CW = PH == PH_GU ? CN * 8 : CN * 16, CPT = PH == PH_GU ? 2 : CW / 16;       // columns of the result, neighbouring ones per thread
   constexpr int LDC = CN * 16 + 4, WS = 32 * LDC;                  // row and wave stride of the partial sums
   static_assert(NS % NA == 0 && (CPT == 2 || CPT == 4), "");
   const int tid = few_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int KB = K >> 4, per = ((K >> 5) + kWaves - 1) / kWaves, s0 = min(wave * per, K >> 5), n = min(per, (K >> 5) - s0);
+  const int KB = K >> 4, all = K >> 5, of_share = PH == PH_PART ? (all + kWideShares - 1) / kWideShares : all;
+  const int s_first = min(share * of_share, all), s_end = min(s_first + of_share, all);
+  const int per = (of_share + kWaves - 1) / kWaves, s0 = min(s_first + wave * per, s_end), n = min(per, s_end - s0);
   const int i16 = lane & 15, g = lane >> 4;
   const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + ((size_t)mt * KB + 2 * s0) * 512), 0, n * 2048, 0x00020000);
   // 16-column groups of W.  Gate/up: the gate columns of CN / 2 groups of hidden units, then their up columns; both stand in blocks of 32,
@@ -203,7 +209,8 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
   const int row = tid >> 4, c0 = (tid & 15) * CPT;
   const int m = mt * 32 + row, mc = min(m, a.M - 1);
   const int n0 = nt * CW;                                          // first column
-  const int sec = PH == PH_QKV ? n0 / a.d : 0, hd = PH == PH_QKV ? (n0 - sec * a.d) >> 6 : 0;      // a q/k/v tile is a head's q, k or v
+  const int sec = PH == PH_QKV ? n0 / a.d : 0, hd = PH == PH_QKV ? (n0 - sec * a.d) / DH : 0;      // a q/k/v tile is a head's q, k or v, or half of it
+  const int e0 = DH == 64 ? 0 : n0 % DH;                           // its first dimension of the head
   float4 cs = make_float4(1.f, 0.f, 1.f, 0.f);
   int slot[4] = {0, 0, 0, 0}, rr[4] = {0, 0, 0, 0};
   if constexpr (PH == PH_QKV) {
@@ -215,7 +222,8 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
       const int img = a.pos.n_emitted[r >> 1] - 1 + a.tree.depth[a.tree.first + t];
       if (img >= 0) {
         const int gr = min(img / a.pos.grid_w, a.rope_pos - 1), gc = img % a.pos.grid_w;
-        cs = *(const float4*)(a.rope + ((size_t)(c0 >= 32 ? gc : gr) * 16 + ((c0 & 31) >> 1)) * 2);
+        constexpr int HALF = DH / 2;
+        cs = *(const float4*)(a.rope + ((size_t)(e0 + c0 >= HALF ? gc : gr) * (HALF / 2) + (((e0 + c0) & (HALF - 1)) >> 1)) * 2);
       }
     } else {
 #pragma unroll
@@ -251,7 +259,7 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
 #pragma unroll
     for (int i = 0; i < CPT; ++i) gv[i] = g_next[n0 + c0 + i];
   }
-  if constexpr (PH == PH_QKV || PH == PH_GU) {
+  if constexpr (SCALED) {
 #pragma unroll
     for (int i = 0; i < 3; ++i)            // 48 slabs: d 1536; wider rows: the rest in the epilogue
       if ((tid & 15) + 16 * i < a.NS) sq[i] = ss[(size_t)mc * a.NS + (tid & 15) + 16 * i];
@@ -303,7 +311,7 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
     return v + dpp_move<0xB1>(v);
   };
   float sc = 1.f;                          // RMSNorm row factor of this thread's row
-  if constexpr (PH == PH_QKV || PH == PH_GU) {
+  if constexpr (SCALED) {
     float t = sq[0] + sq[1] + sq[2];
     for (int i = (tid & 15) + 48; i < a.NS; i += 16) t += ss[(size_t)mc * a.NS + i];
     t += dpp_move<0x128>(t);
@@ -331,7 +339,7 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
       const uint32_t lo = pack2bf(v[0] * cs.x - v[1] * cs.y, v[0] * cs.y + v[1] * cs.x), hi = pack2bf(v[2] * cs.z - v[3] * cs.w, v[2] * cs.w + v[3] * cs.z);
       if (m < a.M) {
         if (sec == 0) put64(out + (size_t)m * a.d + n0 + c0, lo, hi);
-        else if (slot[0] >= 0 && slot[0] < a.S_cap) put64(a.kc + a.kv_layer * l + rr[0] * a.kv_row + hd * a.kv_head + k_index(slot[0], c0, 64), lo, hi);
+        else if (slot[0] >= 0 && slot[0] < a.S_cap) put64(a.kc + a.kv_layer * l + rr[0] * a.kv_row + hd * a.kv_head + k_index(slot[0], e0 + c0, DH), lo, hi);
       }
     } else {
       // v: the 8 slots of a dim are contiguous, so neighbouring lanes take the rows of a dim
@@ -341,7 +349,13 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (mt * 32 + r0 + i < a.M && slot[i] >= 0 && slot[i] < a.S_cap)
-          put(a.vc + a.kv_layer * l + rr[i] * a.kv_row + hd * a.kv_head + v_index(slot[i], col, 64), f2bf(red[(r0 + i) * LDC + col]));
+          put(a.vc + a.kv_layer * l + rr[i] * a.kv_row + hd * a.kv_head + v_index(slot[i], e0 + col, DH), f2bf(red[(r0 + i) * LDC + col]));
+    }
+  } else if constexpr (PH == PH_PART) {
+    if (m < a.M) {
+      float* p = a.part + ((size_t)share * a.M + m) * a.d + n0 + c0;
+#pragma unroll
+      for (int i = 0; i < CPT; i += 2) put64(p + i, __float_as_uint(v[i]), __float_as_uint(v[i + 1]));
     }
   } else {
     float s2 = 0.f;
@@ -373,9 +387,9 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
 
 // Attention of head hd, queries q0 .. q0 + 16 NQB - 1 of rows r0 .. r0 + 8 / NW - 1 (those there are): see k_attn_mfma.  NW waves to a row, which
 // take 32-key steps round-robin; steps that lie below the cached length are asked for before the wait.
-template <int NQB, int NW, typename Wait>
+template <int NQB, int NW, int DH = 64, typename Wait>
 __device__ __forceinline__ bool few_attention(const FewArgs& a, const FewBuf& b, int hd, int r0, int q0, int l, float* red, FewShared* sh, uint32_t* done, Wait wait) {
-  constexpr int DH = 64, KD = DH / 32, DT = DH / 16, NQ = NQB * 16, PD = 2;
+  constexpr int KD = DH / 32, DT = DH / 16, NQ = NQB * 16, PD = DH > 64 ? 1 : 2;
   constexpr int LDO = DH + 4;
   float* s_o = red;                        // [8 waves][NQ][LDO]
   float* s_m = s_o + kWaves * NQ * LDO;
@@ -491,6 +505,19 @@ __device__ __attribute__((noinline)) int few_dealing(uint32_t* sync, int id) {
   return (int)mode;
 }
 
+// The last workgroup leaves the counters as it found them: zero
+__device__ __forceinline__ void few_leave(FewShared* sh) {
+  const FewArgs& e = few_args();
+  barrier();
+  if (threadIdx.x == 0) {
+    auto last = [](uint32_t* counter, uint32_t n) { return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1; };
+    sh->last = last(e.sync + (11 + (blockIdx.x & 7)) * kLine, kGroups / 8) && last(e.sync + 2 * kLine, 8);
+  }
+  barrier();
+  if (sh->last)
+    for (size_t i = threadIdx.x; i < (kFewHead + (size_t)few_layer_counters(e.H, e.MT) * e.L + 8) * kLine / 4; i += kThreads) ((uint4*)e.sync)[i] = make_uint4(0, 0, 0, 0);
+}
+
 template <int NQB>
 __global__ __launch_bounds__(kThreads, 2) void k_layers_few(const FewArgs args) {
   extern __shared__ float red[];
@@ -572,21 +599,142 @@ __global__ __launch_bounds__(kThreads, 2) void k_layers_few(const FewArgs args) 
     }
     if (!ok) break;
   }
-  // the last workgroup leaves the counters as it found them: zero
-  const FewArgs& e = few_args();
+  few_leave(&sh);
+}
+
+// Row m: x += the partial sums in front of it (has_part), out = bf16(x / rms * g), in packed order
+template <typename Wait>
+__device__ __forceinline__ bool few_norm(const FewArgs& a, int m, bool has_part, const float* g, bf16_t* out, float* red, uint32_t* done, Wait wait) {
+  const int tid = few_tid(), k0 = min(tid * 8, a.d - 8);
+  const bool mine = tid * 8 < a.d;
+  const float4 ga = *(const float4*)(g + k0), gb = *(const float4*)(g + k0 + 4);
+  if (!wait()) return false;
+  float v[8];
+  float* xr = a.x + (size_t)m * a.d + k0;
+  float2 x2[4], p2[kWideShares][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) x2[i] = get2(xr + 2 * i);
+  if (has_part) {
+#pragma unroll
+    for (int s = 0; s < kWideShares; ++s)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p2[s][i] = get2(a.part + ((size_t)s * a.M + m) * a.d + k0 + 2 * i);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { v[2 * i] = x2[i].x; v[2 * i + 1] = x2[i].y; }
+  if (has_part) {
+#pragma unroll
+    for (int s = 0; s < kWideShares; ++s)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { v[2 * i] += p2[s][i].x; v[2 * i + 1] += p2[s][i].y; }
+    if (mine)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) put64(xr + 2 * i, __float_as_uint(v[2 * i]), __float_as_uint(v[2 * i + 1]));
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) ss += v[i] * v[i];
+  ss = wave_sum(mine ? ss : 0.f);
+  if ((tid & 63) == 0) red[tid >> 6] = ss;
   barrier();
+  float t = 0.f;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) t += red[w];
+  const float scale = 1.0f / sqrtf(t / (float)a.d + a.eps);
+  if (mine) {
+    bf16_t* o = out + pack_index(m, k0, a.d);
+    put64(o, pack2bf(v[0] * scale * ga.x, v[1] * scale * ga.y), pack2bf(v[2] * scale * ga.z, v[3] * scale * ga.w));
+    put64(o + 4, pack2bf(v[4] * scale * gb.x, v[5] * scale * gb.y), pack2bf(v[6] * scale * gb.z, v[7] * scale * gb.w));
+  }
+  few_done(done);
+  return true;
+}
+
+// The same for wide layers, whose weights stream from HBM and whose norms round their output (plan_fused): normalisations are phases of their own, one
+// row to a tile, and O and down leave partial sums of kWideShares shares of the contraction, which the normalisation behind them adds to x.  The last
+// layer's are left to the caller.
+//   Bound by HBM: 404 MB a layer at d 4096, d_ff 11008.  Launches left it idle at every start and end and for normalisation and attention (23 us of 113);
+//   here the weights of a workgroup's next tile, up to 256 KB, are on their way while it waits.  d 4096, 32 layers, 28 rows 3604 -> 3350 us, 2 rows 3406 ->
+//   2990 (4.3 TB/s over all).  Where the rest goes (one layer of 105 us, 28 rows): normalisation 10 and 8 us, during which the weights arrive that are asked
+//   for ahead; q/k/v 19 (192 tiles: a CU gets 25 GB/s from HBM), attention 10, O 12, gate/up 30 (4.3 TB/s: a quarter of what a CU
+//   pulls in are activations), down 18.  Two shares of 32 columns: 4 shares of 64 columns 1 % slower (twice the sums), 8 of 128 5 %.
+//   Requested ahead, steps of q/k/v 8, of gate/up 5, of O and down 8: 6 to 16 the same within 1 %, q/k/v all 16 steps (spilled) 18 % slower.
+template <int NQB, int DH>
+__global__ __launch_bounds__(kThreads, 2) void k_layers_wide(const FewArgs args) {
+  extern __shared__ float red[];
+  __shared__ FewShared sh;
+  uint32_t* sync = few_args().sync;
   if (threadIdx.x == 0) {
-    auto last = [](uint32_t* counter, uint32_t n) { return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1; };
-    sh.last = last(e.sync + (11 + (blockIdx.x & 7)) * kLine, kGroups / 8) && last(e.sync + 2 * kLine, 8);
+    sh.stop = 0;
+    sh.mode = few_dealing(sync, blockIdx.x);
   }
   barrier();
-  if (sh.last)
-    for (size_t i = threadIdx.x; i < (kFewHead + (size_t)few_layer_counters(e.H, e.MT) * e.L + 8) * kLine / 4; i += kThreads) ((uint4*)e.sync)[i] = make_uint4(0, 0, 0, 0);
+  const bool dealt = __builtin_amdgcn_readfirstlane(sh.mode) == 1;
+  for (int tk = blockIdx.x;; tk += kGroups) {
+    if (!dealt) {
+      uint32_t* next = few_args().sync + kLine;
+      if (threadIdx.x == 0) sh.ticket = (int)__hip_atomic_fetch_add(next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      barrier();
+      tk = sh.ticket;
+      barrier();
+    }
+    tk = __builtin_amdgcn_readfirstlane(tk);
+    const FewArgs& a = few_args();
+    const int d = a.d, MT = a.MT, n_norm = a.M;
+    const int cols = d >> 6, n_qkv = 3 * MT * cols, per_row = (a.T + 16 * NQB - 1) / (16 * NQB), row_groups = (a.R + a.rows_per_unit - 1) / a.rows_per_unit;
+    const int n_att = a.H * row_groups * per_row, pcols = d >> 5, n_whole = MT * pcols, n_part = n_whole * kWideShares, gu_tiles = (a.F + 47) / 48, n_gu = MT * gu_tiles;
+    const int per_layer = 2 * n_norm + n_qkv + n_att + 2 * n_part + n_gu;
+    if (tk >= per_layer * a.L) break;
+    const int l = tk / per_layer, lc = few_layer_counters(a.H, MT);
+    int j = tk - l * per_layer;
+    const char* lw = a.layer0 + a.layer_stride * l;
+    uint32_t* ch = a.sync + (kFewHead + (size_t)lc * l) * kLine;     // q/k/v: [head][row tile]
+    uint32_t* cp = ch + (size_t)a.H * MT * kLine;                    // attention, O, gate/up, down, the two norms: 8 each
+    const FewBuf b = few_buf(a, l);
+    int mt, nt;
+    bool ok;
+    if (j < n_norm) {
+      ok = few_norm(a, j, l > 0, (const float*)(lw + a.o_g1), b.xb1, red, cp + (32 + (j & 7)) * kLine,
+                    [&] { return l ? few_wait_phase(cp + (24 - lc) * kLine, n_part, &sh) : true; });
+    } else if ((j -= n_norm) < n_qkv) {
+      tile_of(j, MT, 3 * cols, &mt, &nt);
+      ok = few_tile<PH_QKV, 4, 8, 4, DH, false>(a, b.xb1, (const bf16_t*)(lw + a.o_wqkv), d, mt, nt, nullptr, nullptr, b.q, nullptr, l, red, &sh,
+                                                ch + ((size_t)(nt % cols / (DH / 64)) * MT + mt) * kLine,
+                                                [&] { return few_wait_phase(cp + 32 * kLine, n_norm, &sh); });
+    } else if ((j -= n_qkv) < n_att) {
+      const int hd = j % a.H, rq = j / a.H, rg = rq / per_row, r0 = rg * a.rows_per_unit, q0 = (rq - rg * per_row) * 16 * NQB;
+      const int first = r0 * a.T >> 5, n = ((min(a.M, (r0 + a.rows_per_unit) * a.T) - 1) >> 5) - first + 1;
+      auto wait = [&] { return few_wait(ch + ((size_t)hd * MT + first) * kLine, n, 3u * (DH / 64), &sh); };
+      uint32_t* done = cp + (j & 7) * kLine;
+      if (a.rows_per_unit == 1) ok = few_attention<NQB, 8, DH>(a, b, hd, r0, q0, l, red, &sh, done, wait);
+      else if (a.rows_per_unit == 2) ok = few_attention<NQB, 4, DH>(a, b, hd, r0, q0, l, red, &sh, done, wait);
+      else ok = few_attention<NQB, 2, DH>(a, b, hd, r0, q0, l, red, &sh, done, wait);
+    } else if ((j -= n_att) < n_part) {
+      tile_of(j % n_whole, MT, pcols, &mt, &nt);
+      ok = few_tile<PH_PART, 2, 8, 8>(a, b.att, (const bf16_t*)(lw + a.o_wo), d, mt, nt, nullptr, nullptr, nullptr, nullptr, l, red, &sh,
+                                      cp + (8 + (j & 7)) * kLine, [&] { return few_wait_phase(cp, n_att, &sh); }, j / n_whole);
+    } else if ((j -= n_part) < n_norm) {
+      ok = few_norm(a, j, true, (const float*)(lw + a.o_g2), b.xb2, red, cp + (40 + (j & 7)) * kLine,
+                    [&] { return few_wait_phase(cp + 8 * kLine, n_part, &sh); });
+    } else if ((j -= n_norm) < n_gu) {
+      tile_of(j, MT, gu_tiles, &mt, &nt);
+      ok = few_tile<PH_GU, 6, 5, 5, 64, false>(a, b.xb2, (const bf16_t*)(lw + a.o_wgu), d, mt, nt, nullptr, nullptr, b.act, nullptr, l, red, &sh,
+                                               cp + (16 + (j & 7)) * kLine, [&] { return few_wait_phase(cp + 40 * kLine, n_norm, &sh); });
+    } else {
+      j -= n_gu;
+      tile_of(j % n_whole, MT, pcols, &mt, &nt);
+      ok = few_tile<PH_PART, 2, 8, 8>(a, b.act, (const bf16_t*)(lw + a.o_wd), a.F, mt, nt, nullptr, nullptr, nullptr, nullptr, l, red, &sh,
+                                      cp + (24 + (j & 7)) * kLine, [&] { return few_wait_phase(cp + 16 * kLine, n_gu, &sh); }, j / n_whole);
+    }
+    if (!ok) break;
+  }
+  few_leave(&sh);
 }
+constexpr size_t kWideLds = sizeof(float) * kWaves * 32 * (128 + 4 + 2);
 
 // All layers of a verify or drafting forward of at most few_rows(c) rows.  In: x, its packed operand bf16(x g1) (rows unpadded) and sums of
 // squares, or the drafter's input rows.  Out: the same of the last layer, with the gain of the final norm.
-void launch_layers_few(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, bool from_din, hipStream_t s) {
+static FewArgs few_arguments(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, bool from_din) {
   const int M = c->R * T, MT = (M + 31) / 32;
   FewArgs a{};
   a.layer0 = c->pw + c->p.layer0;
@@ -613,6 +761,12 @@ void launch_layers_few(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, 
   a.c_exp = 1.4426950408889634f / sqrtf((float)c->dh);
   a.pos = pos;
   a.tree = tree;
+  a.part = (float*)(c->ws + c->w.gemm_out);
+  return a;
+}
+
+void launch_layers_few(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, bool from_din, hipStream_t s) {
+  FewArgs a = few_arguments(c, tree, pos, T, from_din);
 #define VVS_FEW(NQB)                                                                                                            \
   {                                                                                                                             \
     allow_dynamic_lds(reinterpret_cast<const void*>(&k_layers_few<NQB>), kFewLds);                                               \
@@ -623,6 +777,22 @@ void launch_layers_few(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, 
   a.rows_per_unit = units <= 256 ? 1 : units <= 512 ? 2 : 4;
   if (T <= 16 || nqb == 1) VVS_FEW(1) else VVS_FEW(2)
 #undef VVS_FEW
+}
+
+// The same for wide layers, of at most few_wide_rows(c) rows.  In: x.  Out: x of the last layer without its down projection, whose kFewWideShares partial
+// sums [M][d] are in gemm_out.
+void launch_layers_wide(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, hipStream_t s) {
+  FewArgs a = few_arguments(c, tree, pos, T, false);
+  const int nqb = T <= 16 ? 1 : 2, units = c->H * c->R * ((T + 16 * nqb - 1) / (16 * nqb));
+  a.rows_per_unit = units <= 256 ? 1 : units <= 512 ? 2 : 4;
+#define VVS_WIDE(NQB, DH)                                                                                                       \
+  {                                                                                                                             \
+    allow_dynamic_lds(reinterpret_cast<const void*>(&k_layers_wide<NQB, DH>), kWideLds);                                         \
+    hipLaunchKernelGGL((k_layers_wide<NQB, DH>), dim3(kGroups), dim3(kThreads), kWideLds, s, a);                                  \
+  }
+  if (c->dh == 64) { if (nqb == 1) VVS_WIDE(1, 64) else VVS_WIDE(2, 64) }
+  else { if (nqb == 1) VVS_WIDE(1, 128) else VVS_WIDE(2, 128) }
+#undef VVS_WIDE
 }
 
 }  // namespace vvs

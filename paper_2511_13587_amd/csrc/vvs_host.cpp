@@ -188,6 +188,17 @@ int few_rows(const Ctx* c) {
   return std::min((int)align_up((size_t)c->R * c->Tmax, 32), 192);
 }
 
+// Wide layers: one row-block, two while the layer is small enough that its weights, read from L2 once more, cost less than the launches.  us per layer, a
+// launch each / one launch:  28 and 32 rows, d 1536 (d_ff 4096) 52.4 / 35.1, 2048 (5504) 59.3 / 45.4, 3072 (8192) 84.9 / 72.0, 4096 (4096) 90.8 /
+// 82.8, (11008) 115 / 102, (12288, 436 MB) 117.5 / 111.8, but (14336, 486 MB) 130 / 133 and (16384) 134 / 136;  64 rows, d 2048 (101 MB) 64.9 / 51.4, 3072
+// (226 MB) 96.3 / 111.5;  96 rows, d 1536 61.3 / 55.9, 2048 67.3 / 77.2.
+int few_wide_rows(const Ctx* c) {
+  if (plan_fused(c, c->R) || c->cfg.dtype != VVS_BF16 || c->cfg.draft_input || c->d > 4096) return 0;
+  const size_t layer_weight_bytes = c->esz * ((size_t)4 * c->d * c->d + (size_t)3 * c->d * c->F);
+  if (layer_weight_bytes > (size_t)440 << 20) return 0;
+  return std::min((int)align_up((size_t)c->R * c->Tmax, 32), layer_weight_bytes <= (size_t)128 << 20 ? 64 : 32);
+}
+
 vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   if (!cfg) return fail(err, VVS_EINVAL, "config is NULL");
   const vvs_config& g = *cfg;
@@ -266,7 +277,6 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
     sums(d, F);                              // down
     if (g.draft_input) sums(d, 2 * d);       // a drafter's input map
   }
-  c->gemm_out_elems = go;
   // workspace carve-up
   Workspace& w = c->w;
   size_t off = 0;
@@ -278,12 +288,15 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   w.tokens = take(sizeof(int32_t) * c->B * VVS_MAX_T);
   w.rope_tab = take(sizeof(float) * 2 * c->rope_pos * (dh / 4));
   w.walk_sync = take(sizeof(uint32_t) * kWalkLine * c->B);      // zeroed with the state
-  const int few = few_rows(c);
+  c->gemm_out_elems = go;
+  const int wide = few_wide_rows(c), few = std::max(few_rows(c), wide);
+  go = std::max(go, (size_t)kFewWideShares * wide * d);
   w.few_sync = take(few ? sizeof(uint32_t) * kFewLine * (kFewHead + (size_t)few_layer_counters(c->H, few / 32) * c->L + 8) : 0);   // zeroed with the state
   w.x = take(sizeof(float) * (size_t)c->Mmax * d);
   w.h = take(c->esz * (size_t)c->Mmax * d);
   // (a call whose layers are one launch has no partial sums: what its phases hand on lies in their place)
-  w.gemm_out = w.few_buf = take(std::max(sizeof(float) * go, few_buf_bytes(few, d, F) * c->L));
+  w.gemm_out = w.few_buf = take(std::max(sizeof(float) * go, wide ? 0 : few_buf_bytes(few, d, F) * c->L));
+  if (wide) w.few_buf = take(few_buf_bytes(few, d, F) * c->L);
   w.q = take(c->esz * (size_t)c->Mmax * d);
   w.attn = take(c->esz * (size_t)c->Mmax * d);
   w.act = take(c->esz * (size_t)c->Mmax * F);

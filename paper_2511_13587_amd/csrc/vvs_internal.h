@@ -100,6 +100,7 @@ GemmPlan plan_gate_up(const Ctx* c, int M);
 GemmPlan plan_resid(const Ctx* c, int M);   // O, down and input-map projections of the fused layer
 bool plan_fused(const Ctx* c, int M);   // true: the fused 5-kernel layer runs for M GEMM rows
 int few_rows(const Ctx* c);   // rows up to which all layers of a verify or drafting forward are one launch (0: never)
+int few_wide_rows(const Ctx* c);   // the same for layers with separate normalisations
 vvs_status build_tree(int n_nodes, const int32_t* h_parent, const uint8_t* h_mask, TreeDesc* out, std::string* err);
 
 // ---- launchers (kernels_*.hip); all asynchronous on the stream
@@ -164,7 +165,8 @@ constexpr int kWalkLine = 16;   // words between the counters of two prompts (k_
 // All layers in one launch (vvs_few.hip): counters of a layer and bytes that it hands from phase to phase
 constexpr int kFewLine = 32;   // words between two counters: a line of its own for each
 constexpr int kFewHead = 19;   // counters in front of the layers'
-constexpr int few_layer_counters(int H, int row_tiles) { return H * row_tiles + 4 * 8; }
+constexpr int few_layer_counters(int H, int row_tiles) { return H * row_tiles + 6 * 8; }
+constexpr int kFewWideShares = 2;   // shares of the contraction of O and down in wide layers
 constexpr size_t few_buf_bytes(int rows, int d, int F) { return (size_t)rows * (2 * (4 * (size_t)d + F) + 2 * 4 * (size_t)n_slabs(d)); }
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }

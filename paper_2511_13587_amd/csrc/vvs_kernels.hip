@@ -848,7 +848,14 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
     hipLaunchKernelGGL(k_embed<T>, dim3(M), dim3(256), 0, s, x, (const T*)(c->pw + c->p.embed),
                        (const T*)(c->pw + c->p.prefix_embed), ea);
   }
-  for (int l = 0; l < c->L; ++l) {
+  const bool wide = sizeof(T) == 2 && pos.kv_len && M <= few_wide_rows(c);
+  if (wide) {
+    Timed timed(c, VVS_K_GEMM, s);
+    launch_layers_wide(c, tree, pos, Tq, s);
+    splits = kFewWideShares;
+    sstride = (size_t)M * d;
+  }
+  for (int l = 0; l < c->L && !wide; ++l) {
     const char* lw = c->pw + c->p.layer0 + c->p.layer_stride * l;
     T* kc = (T*)c->kv + c->kv_layer_stride * l;
     T* vc = (T*)c->kv + c->kv_v_off + c->kv_layer_stride * l;
