@@ -171,8 +171,9 @@ __device__ __forceinline__ bf16x8 few_load(__amdgpu_buffer_rsrc_t r, int off, in
 //   16 x 16 x 32 products; a wave takes 1/8 of the contraction.  Its weights are asked for NS steps of 32 ahead (for the usual widths that is
 //   all of them), its part of A, which may be asked for only after the wait, NA steps ahead.  No request goes past a wave's last step.
 //   DH: head size (q/k/v).  SCALED: A is a row's residual values, un-normalised; its RMSNorm factor multiplies the result.  PH_PART: share `share` of
-//   kWideShares of the contraction, whose sums go to a.part.
-template <int PH, int CN, int NS, int NA, int DH = 64, bool SCALED = PH == PH_QKV || PH == PH_GU, typename Wait>
+//   kWideShares of the contraction, whose sums go to a.part.  RB: row-blocks of the tile, mt counts such tiles; they share the weights' registers, and their
+//   sums go through LDS one after the other.
+template <int PH, int CN, int NS, int NA, int DH = 64, bool SCALED = PH == PH_QKV || PH == PH_GU, int RB = 1, typename Wait>
 __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, const bf16_t* W, int K, int mt, int nt, const float* ss, float* ss_out,
                                          bf16_t* out, const float* g_next, int l, float* red, FewShared* sh, uint32_t* done, Wait wait, int share = 0) {
   constexpr int CW = PH == PH_GU ? CN * 8 : CN * 16, CPT = PH == PH_GU ? 2 : CW / 16;       // columns of the result, neighbouring ones per thread
@@ -183,7 +184,10 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
   const int s_first = min(share * of_share, all), s_end = min(s_first + of_share, all);
   const int per = (of_share + kWaves - 1) / kWaves, s0 = min(s_first + wave * per, s_end), n = min(per, s_end - s0);
   const int i16 = lane & 15, g = lane >> 4;
-  const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + ((size_t)mt * KB + 2 * s0) * 512), 0, n * 2048, 0x00020000);
+  __amdgpu_buffer_rsrc_t ra[RB];           // (row-blocks past the last repeat it)
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+    ra[rb] = __builtin_amdgcn_make_buffer_rsrc((void*)(A + ((size_t)(RB > 1 ? min(mt * RB + rb, a.MT - 1) : mt) * KB + 2 * s0) * 512), 0, n * 2048, 0x00020000);
   // 16-column groups of W.  Gate/up: the gate columns of CN / 2 groups of hidden units, then their up columns; both stand in blocks of 32,
   // alternating; groups past the end repeat the last
   int group[CN];
@@ -198,28 +202,35 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
     rw[t] = __builtin_amdgcn_make_buffer_rsrc((void*)(W + ((size_t)(group[t] >> 1) * KB + 2 * s0) * 512 + (group[t] & 1) * 128), 0, n * 2048, 0x00020000);
   // lane l supplies row l % 16 (+ 16: the block's second half) and the contraction values 8 (l / 16) .. + 7 of a step of two blocks
   const int off = (g >> 1) * 1024 + (i16 + 32 * (g & 1)) * 16;
-  bf16x8 fw[NS][CN], fa[NA][2];
+  bf16x8 fw[NS][CN], fa[NA][2 * RB];
 #pragma unroll
   for (int i = 0; i < NS; ++i)
     if (i < n) {
 #pragma unroll
       for (int t = 0; t < CN; ++t) fw[i][t] = few_load(rw[t], off, i);
     }
-  // this thread's part of the result: CPT neighbouring columns of a row (v: of a column's rows)
+  auto request = [&](int i, int step) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      fa[i][2 * rb] = few_load(ra[rb], off, step);
+      fa[i][2 * rb + 1] = few_load(ra[rb], off + 256, step);
+    }
+  };
+  // this thread's part of the result: CPT neighbouring columns of a row (v: of a column's rows) in each row-block
   const int row = tid >> 4, c0 = (tid & 15) * CPT;
-  const int m = mt * 32 + row, mc = min(m, a.M - 1);
+  int base = mt * RB * 32, m = base + row, mc = min(m, a.M - 1);   // of the row-block that is at hand
   const int n0 = nt * CW;                                          // first column
   const int sec = PH == PH_QKV ? n0 / a.d : 0, hd = PH == PH_QKV ? (n0 - sec * a.d) / DH : 0;      // a q/k/v tile is a head's q, k or v, or half of it
   const int e0 = DH == 64 ? 0 : n0 % DH;                           // its first dimension of the head
-  float4 cs = make_float4(1.f, 0.f, 1.f, 0.f);
+  float4 cs;
   int slot[4] = {0, 0, 0, 0}, rr[4] = {0, 0, 0, 0};
-  if constexpr (PH == PH_QKV) {
-    static_assert(CW == 64, "one head");
+  auto position = [&] {
     if (sec < 2) {
       const int r = mc / a.T, t = mc - r * a.T;
       rr[0] = r;
       slot[0] = a.pos.kv_len[r >> 1] + a.tree.first + t;
       const int img = a.pos.n_emitted[r >> 1] - 1 + a.tree.depth[a.tree.first + t];
+      cs = make_float4(1.f, 0.f, 1.f, 0.f);
       if (img >= 0) {
         const int gr = min(img / a.pos.grid_w, a.rope_pos - 1), gc = img % a.pos.grid_w;
         constexpr int HALF = DH / 2;
@@ -228,19 +239,20 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
     } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int mv = min(mt * 32 + (tid & 7) * 4 + i, a.M - 1), r = mv / a.T;
+        const int mv = min(base + (tid & 7) * 4 + i, a.M - 1), r = mv / a.T;
         rr[i] = r;
         slot[i] = a.pos.kv_len[r >> 1] + a.tree.first + mv - r * a.T;
       }
     }
+  };
+  if constexpr (PH == PH_QKV) {
+    static_assert(CW == 64, "one head");
+    position();
   }
   if (!wait()) return false;
 #pragma unroll
   for (int i = 0; i < NA; ++i)
-    if (i < n) {
-      fa[i][0] = few_load(ra, off, i);
-      fa[i][1] = few_load(ra, off + 256, i);
-    }
+    if (i < n) request(i, i);
   __builtin_amdgcn_sched_barrier(0);
   // inputs of the epilogue, behind the operands
   float xv[CPT], gv[CPT], sq[3] = {0.f, 0.f, 0.f};
@@ -265,9 +277,10 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
       if ((tid & 15) + 16 * i < a.NS) sq[i] = ss[(size_t)mc * a.NS + (tid & 15) + 16 * i];
   }
   __builtin_amdgcn_sched_barrier(0);
-  floatx4 acc[2][CN];
+  static_assert(RB == 1 || PH == PH_PART || !SCALED && (PH == PH_QKV || PH == PH_GU), "these inputs are asked for once");
+  floatx4 acc[2 * RB][CN];
 #pragma unroll
-  for (int r = 0; r < 2; ++r)
+  for (int r = 0; r < 2 * RB; ++r)
 #pragma unroll
     for (int t = 0; t < CN; ++t) acc[r][t] = floatx4{0.f, 0.f, 0.f, 0.f};
   for (int c = 0; c < n; c += NS) {
@@ -276,108 +289,115 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
       if (c + i < n) {
         // W A^T: a lane holds one row (lane % 16) and, per accumulator, the columns 4 (lane / 16) .. + 3
 #pragma unroll
-        for (int r = 0; r < 2; ++r)
+        for (int r = 0; r < 2 * RB; ++r)
 #pragma unroll
           for (int t = 0; t < CN; ++t) acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i][t], fa[i % NA][r], acc[r][t], 0, 0, 0);
-        if (c + i + NA < n) {
-          fa[i % NA][0] = few_load(ra, off, c + i + NA);
-          fa[i % NA][1] = few_load(ra, off + 256, c + i + NA);
-        }
+        if (c + i + NA < n) request(i % NA, c + i + NA);
         if (c + i + NS < n) {
 #pragma unroll
           for (int t = 0; t < CN; ++t) fw[i][t] = few_load(rw[t], off, c + i + NS);
         }
       }
   }
-  {
-    float* mine = red + (size_t)wave * WS + i16 * LDC + 4 * g;
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int t = 0; t < CN; ++t) *(floatx4*)(mine + r * 16 * LDC + t * 16) = acc[r][t];
-  }
-  barrier();
-  auto sum = [&](const float* p, float (&v)[CPT]) {       // the partial sums of this thread's columns, in a fixed order
-    typedef float vec __attribute__((ext_vector_type(CPT)));
-    vec s = *(const vec*)p;
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) s += *(const vec*)(p + w * WS);
-#pragma unroll
-    for (int i = 0; i < CPT; ++i) v[i] = s[i];
-  };
-  auto sum8 = [](float v) {                // over 8 neighbouring lanes
-    v += dpp_move<0x141>(v);
-    v += dpp_move<0x4E>(v);
-    return v + dpp_move<0xB1>(v);
-  };
-  float sc = 1.f;                          // RMSNorm row factor of this thread's row
-  if constexpr (SCALED) {
-    float t = sq[0] + sq[1] + sq[2];
-    for (int i = (tid & 15) + 48; i < a.NS; i += 16) t += ss[(size_t)mc * a.NS + i];
-    t += dpp_move<0x128>(t);
-    sc = 1.0f / sqrtf(sum8(t) / (float)a.d + a.eps);
-  }
-  float v[CPT];
-  sum(red + row * LDC + c0, v);
-  if constexpr (PH == PH_GU) {
-#pragma unroll
-    for (int c = c0; c < CW; c += 32) {    // two hidden units, 32 further on two more
-      float up[CPT];
-      if (c != c0) sum(red + row * LDC + c, v);
-      sum(red + row * LDC + CW + c, up);
-#pragma unroll
-      for (int i = 0; i < CPT; ++i) {
-        const float gate = v[i] * sc;
-        v[i] = gate * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gate)) * (up[i] * sc);
-      }
-      if (m < a.M && n0 + c < a.F) put32(out + pack_index(m, n0 + c, a.F), pack2bf(v[0], v[1]));
+  for (int rb = 0; rb < RB; ++rb) {
+    if (rb) {
+      base += 32;
+      m += 32;
+      mc = min(m, a.M - 1);
+      if constexpr (PH == PH_QKV) position();
+      barrier();                             // the sums of the row-block before are read
     }
-  } else if constexpr (PH == PH_QKV) {
+    {
+      float* mine = red + (size_t)wave * WS + i16 * LDC + 4 * g;
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) v[i] *= sc;
-    if (sec < 2) {
-      const uint32_t lo = pack2bf(v[0] * cs.x - v[1] * cs.y, v[0] * cs.y + v[1] * cs.x), hi = pack2bf(v[2] * cs.z - v[3] * cs.w, v[2] * cs.w + v[3] * cs.z);
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int t = 0; t < CN; ++t) *(floatx4*)(mine + r * 16 * LDC + t * 16) = acc[2 * rb + r][t];
+    }
+    barrier();
+    auto sum = [&](const float* p, float (&v)[CPT]) {       // the partial sums of this thread's columns, in a fixed order
+      typedef float vec __attribute__((ext_vector_type(CPT)));
+      vec s = *(const vec*)p;
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) s += *(const vec*)(p + w * WS);
+#pragma unroll
+      for (int i = 0; i < CPT; ++i) v[i] = s[i];
+    };
+    auto sum8 = [](float v) {                // over 8 neighbouring lanes
+      v += dpp_move<0x141>(v);
+      v += dpp_move<0x4E>(v);
+      return v + dpp_move<0xB1>(v);
+    };
+    float sc = 1.f;                          // RMSNorm row factor of this thread's row
+    if constexpr (SCALED) {
+      float t = sq[0] + sq[1] + sq[2];
+      for (int i = (tid & 15) + 48; i < a.NS; i += 16) t += ss[(size_t)mc * a.NS + i];
+      t += dpp_move<0x128>(t);
+      sc = 1.0f / sqrtf(sum8(t) / (float)a.d + a.eps);
+    }
+    float v[CPT];
+    sum(red + row * LDC + c0, v);
+    if constexpr (PH == PH_GU) {
+#pragma unroll
+      for (int c = c0; c < CW; c += 32) {    // two hidden units, 32 further on two more
+        float up[CPT];
+        if (c != c0) sum(red + row * LDC + c, v);
+        sum(red + row * LDC + CW + c, up);
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) {
+          const float gate = v[i] * sc;
+          v[i] = gate * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gate)) * (up[i] * sc);
+        }
+        if (m < a.M && n0 + c < a.F) put32(out + pack_index(m, n0 + c, a.F), pack2bf(v[0], v[1]));
+      }
+    } else if constexpr (PH == PH_QKV) {
+#pragma unroll
+      for (int i = 0; i < CPT; ++i) v[i] *= sc;
+      if (sec < 2) {
+        const uint32_t lo = pack2bf(v[0] * cs.x - v[1] * cs.y, v[0] * cs.y + v[1] * cs.x), hi = pack2bf(v[2] * cs.z - v[3] * cs.w, v[2] * cs.w + v[3] * cs.z);
+        if (m < a.M) {
+          if (sec == 0) put64(out + (size_t)m * a.d + n0 + c0, lo, hi);
+          else if (slot[0] >= 0 && slot[0] < a.S_cap) put64(a.kc + a.kv_layer * l + rr[0] * a.kv_row + hd * a.kv_head + k_index(slot[0], e0 + c0, DH), lo, hi);
+        }
+      } else {
+        // v: the 8 slots of a dim are contiguous, so neighbouring lanes take the rows of a dim
+        *(float4*)(red + row * LDC + c0) = make_float4(v[0], v[1], v[2], v[3]);      // (this thread's own first partial sums)
+        barrier();
+        const int col = tid >> 3, r0 = (tid & 7) * 4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (base + r0 + i < a.M && slot[i] >= 0 && slot[i] < a.S_cap)
+            put(a.vc + a.kv_layer * l + rr[i] * a.kv_row + hd * a.kv_head + v_index(slot[i], e0 + col, DH), f2bf(red[(r0 + i) * LDC + col]));
+      }
+    } else if constexpr (PH == PH_PART) {
       if (m < a.M) {
-        if (sec == 0) put64(out + (size_t)m * a.d + n0 + c0, lo, hi);
-        else if (slot[0] >= 0 && slot[0] < a.S_cap) put64(a.kc + a.kv_layer * l + rr[0] * a.kv_row + hd * a.kv_head + k_index(slot[0], e0 + c0, DH), lo, hi);
+        float* p = a.part + ((size_t)share * a.M + m) * a.d + n0 + c0;
+#pragma unroll
+        for (int i = 0; i < CPT; i += 2) put64(p + i, __float_as_uint(v[i]), __float_as_uint(v[i + 1]));
       }
     } else {
-      // v: the 8 slots of a dim are contiguous, so neighbouring lanes take the rows of a dim
-      *(float4*)(red + row * LDC + c0) = make_float4(v[0], v[1], v[2], v[3]);      // (this thread's own first partial sums)
-      barrier();
-      const int col = tid >> 3, r0 = (tid & 7) * 4;
+      float s2 = 0.f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (mt * 32 + r0 + i < a.M && slot[i] >= 0 && slot[i] < a.S_cap)
-          put(a.vc + a.kv_layer * l + rr[i] * a.kv_row + hd * a.kv_head + v_index(slot[i], e0 + col, DH), f2bf(red[(r0 + i) * LDC + col]));
-    }
-  } else if constexpr (PH == PH_PART) {
-    if (m < a.M) {
-      float* p = a.part + ((size_t)share * a.M + m) * a.d + n0 + c0;
+      for (int i = 0; i < CPT; ++i) {
+        v[i] += xv[i];
+        s2 += v[i] * v[i];
+      }
+      s2 = sum8(s2);
+      if (CPT == 2) s2 += dpp_move<0x128>(s2);                       // a slab of the sums of squares: 32 columns
+      if (m < a.M) {
 #pragma unroll
-      for (int i = 0; i < CPT; i += 2) put64(p + i, __float_as_uint(v[i]), __float_as_uint(v[i + 1]));
-    }
-  } else {
-    float s2 = 0.f;
-#pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      v[i] += xv[i];
-      s2 += v[i] * v[i];
-    }
-    s2 = sum8(s2);
-    if (CPT == 2) s2 += dpp_move<0x128>(s2);                       // a slab of the sums of squares: 32 columns
-    if (m < a.M) {
-#pragma unroll
-      for (int i = 0; i < CPT; i += 2) put64(a.x + (size_t)m * a.d + n0 + c0 + i, __float_as_uint(v[i]), __float_as_uint(v[i + 1]));
-      bf16_t* o = out + pack_index(m, n0 + c0, a.d);
-      if constexpr (CPT == 4) put64(o, pack2bf(v[0] * gv[0], v[1] * gv[1]), pack2bf(v[2] * gv[2], v[3] * gv[3]));
-      else put32(o, pack2bf(v[0] * gv[0], v[1] * gv[1]));
-      static_assert(kSlab == 32, "");
-      if ((c0 & 31) == 0) {
-        float* so = ss_out + (size_t)m * a.NS + (n0 + c0) / kSlab;
-        put(so, s2);
-        if (n0 + c0 + kSlab == a.d)                                // the row's padding
-          for (int i = a.d / kSlab; i < a.NS; ++i) put(++so, 0.f);
+        for (int i = 0; i < CPT; i += 2) put64(a.x + (size_t)m * a.d + n0 + c0 + i, __float_as_uint(v[i]), __float_as_uint(v[i + 1]));
+        bf16_t* o = out + pack_index(m, n0 + c0, a.d);
+        if constexpr (CPT == 4) put64(o, pack2bf(v[0] * gv[0], v[1] * gv[1]), pack2bf(v[2] * gv[2], v[3] * gv[3]));
+        else put32(o, pack2bf(v[0] * gv[0], v[1] * gv[1]));
+        static_assert(kSlab == 32, "");
+        if ((c0 & 31) == 0) {
+          float* so = ss_out + (size_t)m * a.NS + (n0 + c0) / kSlab;
+          put(so, s2);
+          if (n0 + c0 + kSlab == a.d)                                // the row's padding
+            for (int i = a.d / kSlab; i < a.NS; ++i) put(++so, 0.f);
+        }
       }
     }
   }
@@ -654,12 +674,12 @@ __device__ __forceinline__ bool few_norm(const FewArgs& a, int m, bool has_part,
 // row to a tile, and O and down leave partial sums of kWideShares shares of the contraction, which the normalisation behind them adds to x.  The last
 // layer's are left to the caller.
 //   Bound by HBM: 404 MB a layer at d 4096, d_ff 11008.  Launches left it idle at every start and end and for normalisation and attention (23 us of 113);
-//   here the weights of a workgroup's next tile, up to 256 KB, are on their way while it waits.  d 4096, 32 layers, 28 rows 3604 -> 3350 us, 2 rows 3406 ->
+//   here the weights of a workgroup's next tile, up to 256 KB, are on their way while it waits.  d 4096, 32 layers, 28 rows 3601 -> 3311 us, 2 rows 3406 ->
 //   2990 (4.3 TB/s over all).  Where the rest goes (one layer of 105 us, 28 rows): normalisation 10 and 8 us, during which the weights arrive that are asked
 //   for ahead; q/k/v 19 (192 tiles: a CU gets 25 GB/s from HBM), attention 10, O 12, gate/up 30 (4.3 TB/s: a quarter of what a CU
 //   pulls in are activations), down 18.  Two shares of 32 columns: 4 shares of 64 columns 1 % slower (twice the sums), 8 of 128 5 %.
 //   Requested ahead, steps of q/k/v 8, of gate/up 5, of O and down 8: 6 to 16 the same within 1 %, q/k/v all 16 steps (spilled) 18 % slower.
-template <int NQB, int DH>
+template <int NQB, int DH, int RB>
 __global__ __launch_bounds__(kThreads, 2) void k_layers_wide(const FewArgs args) {
   extern __shared__ float red[];
   __shared__ FewShared sh;
@@ -680,16 +700,16 @@ __global__ __launch_bounds__(kThreads, 2) void k_layers_wide(const FewArgs args)
     }
     tk = __builtin_amdgcn_readfirstlane(tk);
     const FewArgs& a = few_args();
-    const int d = a.d, MT = a.MT, n_norm = a.M;
+    const int d = a.d, MT = (a.MT + RB - 1) / RB, n_norm = a.M;
     const int cols = d >> 6, n_qkv = 3 * MT * cols, per_row = (a.T + 16 * NQB - 1) / (16 * NQB), row_groups = (a.R + a.rows_per_unit - 1) / a.rows_per_unit;
     const int n_att = a.H * row_groups * per_row, pcols = d >> 5, n_whole = MT * pcols, n_part = n_whole * kWideShares, gu_tiles = (a.F + 47) / 48, n_gu = MT * gu_tiles;
     const int per_layer = 2 * n_norm + n_qkv + n_att + 2 * n_part + n_gu;
     if (tk >= per_layer * a.L) break;
-    const int l = tk / per_layer, lc = few_layer_counters(a.H, MT);
+    const int l = tk / per_layer, lc = few_layer_counters(a.H, a.MT);
     int j = tk - l * per_layer;
     const char* lw = a.layer0 + a.layer_stride * l;
     uint32_t* ch = a.sync + (kFewHead + (size_t)lc * l) * kLine;     // q/k/v: [head][row tile]
-    uint32_t* cp = ch + (size_t)a.H * MT * kLine;                    // attention, O, gate/up, down, the two norms: 8 each
+    uint32_t* cp = ch + (size_t)a.H * a.MT * kLine;                    // attention, O, gate/up, down, the two norms: 8 each
     const FewBuf b = few_buf(a, l);
     int mt, nt;
     bool ok;
@@ -698,12 +718,12 @@ __global__ __launch_bounds__(kThreads, 2) void k_layers_wide(const FewArgs args)
                     [&] { return l ? few_wait_phase(cp + (24 - lc) * kLine, n_part, &sh) : true; });
     } else if ((j -= n_norm) < n_qkv) {
       tile_of(j, MT, 3 * cols, &mt, &nt);
-      ok = few_tile<PH_QKV, 4, 8, 4, DH, false>(a, b.xb1, (const bf16_t*)(lw + a.o_wqkv), d, mt, nt, nullptr, nullptr, b.q, nullptr, l, red, &sh,
+      ok = few_tile<PH_QKV, 4, RB == 1 ? 8 : 6, RB == 1 ? 4 : 3, DH, false, RB>(a, b.xb1, (const bf16_t*)(lw + a.o_wqkv), d, mt, nt, nullptr, nullptr, b.q, nullptr, l, red, &sh,
                                                 ch + ((size_t)(nt % cols / (DH / 64)) * MT + mt) * kLine,
                                                 [&] { return few_wait_phase(cp + 32 * kLine, n_norm, &sh); });
     } else if ((j -= n_qkv) < n_att) {
       const int hd = j % a.H, rq = j / a.H, rg = rq / per_row, r0 = rg * a.rows_per_unit, q0 = (rq - rg * per_row) * 16 * NQB;
-      const int first = r0 * a.T >> 5, n = ((min(a.M, (r0 + a.rows_per_unit) * a.T) - 1) >> 5) - first + 1;
+      const int first = r0 * a.T / (32 * RB), n = (min(a.M, (r0 + a.rows_per_unit) * a.T) - 1) / (32 * RB) - first + 1;
       auto wait = [&] { return few_wait(ch + ((size_t)hd * MT + first) * kLine, n, 3u * (DH / 64), &sh); };
       uint32_t* done = cp + (j & 7) * kLine;
       if (a.rows_per_unit == 1) ok = few_attention<NQB, 8, DH>(a, b, hd, r0, q0, l, red, &sh, done, wait);
@@ -711,19 +731,19 @@ __global__ __launch_bounds__(kThreads, 2) void k_layers_wide(const FewArgs args)
       else ok = few_attention<NQB, 2, DH>(a, b, hd, r0, q0, l, red, &sh, done, wait);
     } else if ((j -= n_att) < n_part) {
       tile_of(j % n_whole, MT, pcols, &mt, &nt);
-      ok = few_tile<PH_PART, 2, 8, 8>(a, b.att, (const bf16_t*)(lw + a.o_wo), d, mt, nt, nullptr, nullptr, nullptr, nullptr, l, red, &sh,
+      ok = few_tile<PH_PART, 2, 8, RB == 1 ? 8 : 4, 64, false, RB>(a, b.att, (const bf16_t*)(lw + a.o_wo), d, mt, nt, nullptr, nullptr, nullptr, nullptr, l, red, &sh,
                                       cp + (8 + (j & 7)) * kLine, [&] { return few_wait_phase(cp, n_att, &sh); }, j / n_whole);
     } else if ((j -= n_part) < n_norm) {
       ok = few_norm(a, j, true, (const float*)(lw + a.o_g2), b.xb2, red, cp + (40 + (j & 7)) * kLine,
                     [&] { return few_wait_phase(cp + 8 * kLine, n_part, &sh); });
     } else if ((j -= n_norm) < n_gu) {
       tile_of(j, MT, gu_tiles, &mt, &nt);
-      ok = few_tile<PH_GU, 6, 5, 5, 64, false>(a, b.xb2, (const bf16_t*)(lw + a.o_wgu), d, mt, nt, nullptr, nullptr, b.act, nullptr, l, red, &sh,
+      ok = few_tile<PH_GU, 6, RB == 1 ? 5 : 3, RB == 1 ? 5 : 3, 64, false, RB>(a, b.xb2, (const bf16_t*)(lw + a.o_wgu), d, mt, nt, nullptr, nullptr, b.act, nullptr, l, red, &sh,
                                                cp + (16 + (j & 7)) * kLine, [&] { return few_wait_phase(cp + 40 * kLine, n_norm, &sh); });
     } else {
       j -= n_gu;
       tile_of(j % n_whole, MT, pcols, &mt, &nt);
-      ok = few_tile<PH_PART, 2, 8, 8>(a, b.act, (const bf16_t*)(lw + a.o_wd), a.F, mt, nt, nullptr, nullptr, nullptr, nullptr, l, red, &sh,
+      ok = few_tile<PH_PART, 2, 8, RB == 1 ? 8 : 4, 64, false, RB>(a, b.act, (const bf16_t*)(lw + a.o_wd), a.F, mt, nt, nullptr, nullptr, nullptr, nullptr, l, red, &sh,
                                       cp + (24 + (j & 7)) * kLine, [&] { return few_wait_phase(cp + 16 * kLine, n_gu, &sh); }, j / n_whole);
     }
     if (!ok) break;
@@ -785,14 +805,20 @@ void launch_layers_wide(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T,
   FewArgs a = few_arguments(c, tree, pos, T, false);
   const int nqb = T <= 16 ? 1 : 2, units = c->H * c->R * ((T + 16 * nqb - 1) / (16 * nqb));
   a.rows_per_unit = units <= 256 ? 1 : units <= 512 ? 2 : 4;
-#define VVS_WIDE(NQB, DH)                                                                                                       \
+#define VVS_WIDE1(NQB, DH, RB)                                                                                                       \
   {                                                                                                                             \
-    allow_dynamic_lds(reinterpret_cast<const void*>(&k_layers_wide<NQB, DH>), kWideLds);                                         \
-    hipLaunchKernelGGL((k_layers_wide<NQB, DH>), dim3(kGroups), dim3(kThreads), kWideLds, s, a);                                  \
+    allow_dynamic_lds(reinterpret_cast<const void*>(&k_layers_wide<NQB, DH, RB>), kWideLds);                                         \
+    hipLaunchKernelGGL((k_layers_wide<NQB, DH, RB>), dim3(kGroups), dim3(kThreads), kWideLds, s, a);                                  \
   }
+  // Two row-blocks to a tile read the weights once instead of twice, and leave half as many tiles: from where O and down have more than one for each
+  // CU.  us per layer, one / two, 40 and 64 rows: d 1536 40.1 / 49.0, 40.9 / 47.5; 2048 (d_ff 8192) 62.0 / 68.9, 64.7 / 70.2; 2560 86.1 / 77.0, 88.8 /
+  // 78.6; 3072 (3072) 81.9 / 76.6, 83.2 / 76.8;  96 and 128 rows, d 1536 55.9 / 52.6, 67.0 / 54.5, 2048 78.0 / 63.6, 82.9 / 69.2.
+  const bool two = a.MT > 1 && (a.MT > 2 || c->d > 2048);
+#define VVS_WIDE(NQB, DH) { if (two) VVS_WIDE1(NQB, DH, 2) else VVS_WIDE1(NQB, DH, 1) }
   if (c->dh == 64) { if (nqb == 1) VVS_WIDE(1, 64) else VVS_WIDE(2, 64) }
   else { if (nqb == 1) VVS_WIDE(1, 128) else VVS_WIDE(2, 128) }
 #undef VVS_WIDE
+#undef VVS_WIDE1
 }
 
 }  // namespace vvs

@@ -188,15 +188,17 @@ int few_rows(const Ctx* c) {
   return std::min((int)align_up((size_t)c->R * c->Tmax, 32), 192);
 }
 
-// Wide layers: one row-block, two while the layer is small enough that its weights, read from L2 once more, cost less than the launches.  us per layer, a
-// launch each / one launch:  28 and 32 rows, d 1536 (d_ff 4096) 52.4 / 35.1, 2048 (5504) 59.3 / 45.4, 3072 (8192) 84.9 / 72.0, 4096 (4096) 90.8 /
-// 82.8, (11008) 115 / 102, (12288, 436 MB) 117.5 / 111.8, but (14336, 486 MB) 130 / 133 and (16384) 134 / 136;  64 rows, d 2048 (101 MB) 64.9 / 51.4, 3072
-// (226 MB) 96.3 / 111.5;  96 rows, d 1536 61.3 / 55.9, 2048 67.3 / 77.2.
+// Wide layers.  us per layer, a launch each / one launch:
+//   up to 32 rows:  24 and 32 rows, d 1536 (d_ff 4096) 52.4 / 35.1, 2048 (5504) 59.3 / 45.4, 3072 (8192) 84.9 / 72.0, 4096 (4096) 90.8 / 82.8, (11008) 115 / 102,
+//     (12288, 436 MB a layer) 117.5 / 111.8, but (14336, 486 MB) 130 / 133 and (16384) 134 / 136: gate/up tiles in a second round
+//   64 rows:   d 1536 58.4 / 40.9, 2048 65.1 / 51.4, 2560 (6912) 81.5 / 78.6, 3072 94.5 / 89.4, 4096 130 / 123;  40 rows, d 2560 77.1 / 77.0, 3072 88.7 / 89.7, 4096 125 / 119
+//   96 rows:   d 1536 61.6 / 52.6, 2048 67.7 / 63.6, (8192, 134 MB) 77.8 / 79.0, 2560 89.1 / 104;  128 rows, d 1536 66.7 / 54.5, (8192, 94 MB) 74.1 / 71.1, 2048
+//     75.1 / 69.2, (8192) 84.6 / 86.4, 3072 117 / 140
 int few_wide_rows(const Ctx* c) {
   if (plan_fused(c, c->R) || c->cfg.dtype != VVS_BF16 || c->cfg.draft_input || c->d > 4096) return 0;
   const size_t layer_weight_bytes = c->esz * ((size_t)4 * c->d * c->d + (size_t)3 * c->d * c->F);
   if (layer_weight_bytes > (size_t)440 << 20) return 0;
-  return std::min((int)align_up((size_t)c->R * c->Tmax, 32), layer_weight_bytes <= (size_t)128 << 20 ? 64 : 32);
+  return std::min((int)align_up((size_t)c->R * c->Tmax, 32), c->d <= 2048 && layer_weight_bytes <= (size_t)104 << 20 ? 128 : 64);
 }
 
 vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
