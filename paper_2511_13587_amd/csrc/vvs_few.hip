@@ -23,8 +23,8 @@
 //   us per step, one launch per projection and for attention / one launch for all layers:  d 1280, 36 layers: 1 prompt x 27 tokens 1437 / 1046, 1 x 6
 //   1311 / 950, 1 x 1 1304 / 944, 2 x 27 (108 rows) 1797 / 1490, 8 x 6 (96) 1807 / 1331, 3 x 27 (162) 1886 / 1743, 16 x 6 (192) 2157 / 2024; beyond: 4 x
 //   27 (216 rows) 2027 / 2012, 2 x 61 (244) 2402 / 2274.  d 768, 12 layers: 4 x 6 396 / 311, 1 x 27 419 / 315, 3 x 27 (162) 448 / 415, 16 x 6 (192) 447 /
-//   443.  Drafting calls of one layer, 5 pairs: 8 prompts, 26 nodes 460 / 402; 32 prompts (64 to 192 rows a level but the first) 634 / 623.  The limit
-//   is drawn at 192 rows, where the least of these gains 1 %.
+//   443.  Drafting calls of one layer, 5 pairs: 8 prompts, 26 nodes 460 / 402; 32 prompts (64 to 192 rows a level but the first) 634 / 623.  Where it
+//   ends stands at few_rows.  (Tiles of two row-blocks, as wide layers have, do not carry it further: XL, 300 rows +8 %, 432 +25 %.)
 //   A phase of 54 rows takes 4.3 to 7.2 us (8.5 before): 1.2 to 1.7 from the last tile counted to the next phase's first load, 1.5 to 3 for the operand
 //   and the products, 1 for sum and epilogue, 0.5 to 0.8 until the stores are acknowledged.
 //   Handing on alone, with 80 / 240 tiles of a phase: 1.3 / 2.4 us from one phase's last store to the next phase's first load; one

@@ -182,10 +182,16 @@ bool plan_fused(const Ctx* c, int M) {
   return layer_weight_bytes <= ((size_t)48 << 20);
 }
 
-// 192 rows: where the gain of the one launch ends (vvs_few.hip).  Head size 64: its q/k/v tiles are a head's.
+// Where the gain of the one launch (vvs_few.hip) ends: 192 rows; with up to 64 (head, prompt) pairs, which leave most CUs idle in the launch of projection and
+// attention, 224, and 256 at d 512, whose weights fit the L2s.  us per step, a launch each / one launch (8 layers; XL whole):
+//   d 768, 200 rows (48 pairs) 286 / 260, (24) 327 / 258, 256 rows (48) 290 / 296;  d 1280, 220 rows (40) 492 / 452, 210 (60) 479 / 450, 240 (60) 495 / 515, 256 (40) 500 /
+//   520;  d 1024, 216 rows (64) 402 / 339, 256 (32) 332 / 359;  d 512, 252 rows (48) 253 / 209, 256 (16) 297 / 202, 240 (64) 241 / 203;  d 1536, 200 rows (48) 500 / 491;
+//   XL, 216 rows (80 pairs) 2079 / 2071, 256 (320) 2366 / 2598
+// Head size 64: its q/k/v tiles are a head's.
 int few_rows(const Ctx* c) {
   if (!plan_fused(c, c->R) || c->dh != 64) return 0;
-  return std::min((int)align_up((size_t)c->R * c->Tmax, 32), 192);
+  const int most = c->H * c->B > 64 ? 192 : c->d <= 512 ? 256 : 224;
+  return std::min((int)align_up((size_t)c->R * c->Tmax, 32), most);
 }
 
 // Wide layers.  us per layer, a launch each / one launch:

@@ -1,4 +1,4 @@
-"""All layers of a forward in one launch (up to 192 rows, head size 64): parity at the edges of its tiles, and the same bits whoever computes a
+"""All layers of a forward in one launch (up to 192 or 224 rows, head size 64): parity at the edges of its tiles, and the same bits whoever computes a
 tile - dealt to workgroups, drawn by them where another kernel keeps CUs, beside another launch of its kind."""
 import numpy as np
 import pytest
@@ -11,9 +11,10 @@ pytestmark = pytest.mark.gpu
 
 
 # rows 2 (one row of a block), 32, 34 (a block, and two rows more), 64 (34 tokens: two units of 32 queries, then 64), 96 and 192 of 2 and 4 rows to an
-# attention unit (320 and 640 pairs), 192 (32 queries to a unit), 194 (one launch per projection again); d_ff no multiple of 48 (2048) and one (3456)
+# attention unit (320 and 640 pairs), 192 (32 queries to a unit), 194 (one launch per projection again), 208 and 220 (48 and 40 pairs: one launch up to 224), 232 (again
+# not); d_ff no multiple of 48 (2048) and one (3456)
 @pytest.mark.parametrize("model,prompts,tokens,n_forced", [("b", 1, 1, 9), ("b", 2, 8, 30), ("b", 1, 17, 40), ("xl", 1, 32, 31), ("xl", 1, 34, 20), ("xl", 8, 6, 33),
-                                                           ("xl", 16, 6, 20), ("xl", 3, 32, 64), ("b", 8, 12, 11), ("b", 1, 64, 32), ("b", 97, 1, 5)])
+                                                           ("xl", 16, 6, 20), ("xl", 3, 32, 64), ("b", 8, 12, 11), ("b", 1, 64, 32), ("b", 97, 1, 5), ("b", 4, 26, 20), ("xl", 2, 55, 31), ("b", 4, 29, 8)])
 def test_layers_in_one_launch(gc, model, prompts, tokens, n_forced):  # noqa: F811
     base = synth.XL_TREE if model == "xl" else synth.B_SHAPE
     shape = base.replace(n_layers=2, n_prompts=prompts, n_nodes=max(tokens - 1, 1), tree_widths=None, vocab=1024, logit_hi=1024)
