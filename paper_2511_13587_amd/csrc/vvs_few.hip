@@ -23,7 +23,7 @@
 //   us per step, one launch per projection and for attention / one launch for all layers:  d 1280, 36 layers: 1 prompt x 27 tokens 1437 / 1046, 1 x 6
 //   1311 / 950, 1 x 1 1304 / 944, 2 x 27 (108 rows) 1797 / 1490, 8 x 6 (96) 1807 / 1331, 3 x 27 (162) 1886 / 1743, 16 x 6 (192) 2157 / 2024; beyond: 4 x
 //   27 (216 rows) 2027 / 2012, 2 x 61 (244) 2402 / 2274.  d 768, 12 layers: 4 x 6 396 / 311, 1 x 27 419 / 315, 3 x 27 (162) 448 / 415, 16 x 6 (192) 447 /
-//   443.  Drafting calls of one layer, 5 pairs: 8 prompts, 26 nodes 460 / 402; 32 prompts (64 to 192 rows a level but the first) 634 / 623.  Where it
+//   443.  Prefix and first tokens of the d 768 shape: 1 prompt x 1 token 336 / 267, 4 x 16 373 / 293, 32 x 1 404 / 300, 1 x 64 387 / 295.  Drafting calls of one layer, 5 pairs: 8 prompts, 26 nodes 460 / 402; 32 prompts (64 to 192 rows a level but the first) 634 / 623.  Where it
 //   ends stands at few_rows.  (Tiles of two row-blocks, as wide layers have, do not carry it further: XL, 300 rows +8 %, 432 +25 %.)
 //   A phase of 54 rows takes 4.3 to 7.2 us (8.5 before): 1.2 to 1.7 from the last tile counted to the next phase's first load, 1.5 to 3 for the operand
 //   and the products, 1 for sum and epilogue, 0.5 to 0.8 until the stores are acknowledged.
@@ -166,6 +166,8 @@ __device__ __forceinline__ bf16x8 few_load(__amdgpu_buffer_rsrc_t r, int off, in
   return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, off, step * 2048, 0));
 }
 
+__device__ __forceinline__ int few_cached(const FewArgs& a, int r) { return a.pos.kv_len ? a.pos.kv_len[r >> 1] : a.pos.kv_base; }   // cached length
+
 // Tile (row-block mt, column tile nt) of A W^T, 32 rows x CN * 16 columns of W.  PH says what becomes of it.  wait: called when the weights
 // are asked for; what it waits for are the tiles that wrote A.
 //   16 x 16 x 32 products; a wave takes 1/8 of the contraction.  Its weights are asked for NS steps of 32 ahead (for the usual widths that is
@@ -228,8 +230,8 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
     if (sec < 2) {
       const int r = mc / a.T, t = mc - r * a.T;
       rr[0] = r;
-      slot[0] = a.pos.kv_len[r >> 1] + a.tree.first + t;
-      const int img = a.pos.n_emitted[r >> 1] - 1 + a.tree.depth[a.tree.first + t];
+      int img;
+      token_pos(a.pos, a.tree, r, t, &slot[0], &img);
       cs = make_float4(1.f, 0.f, 1.f, 0.f);
       if (img >= 0) {
         const int gr = min(img / a.pos.grid_w, a.rope_pos - 1), gc = img % a.pos.grid_w;
@@ -241,7 +243,7 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
       for (int i = 0; i < 4; ++i) {
         const int mv = min(base + (tid & 7) * 4 + i, a.M - 1), r = mv / a.T;
         rr[i] = r;
-        slot[i] = a.pos.kv_len[r >> 1] + a.tree.first + mv - r * a.T;
+        slot[i] = few_cached(a, r) + a.tree.first + mv - r * a.T;
       }
     }
   };
@@ -417,7 +419,7 @@ __device__ __forceinline__ bool few_attention(const FewArgs& a, const FewBuf& b,
   const int tid = few_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), aw = wave % NW;
   const int r = min(r0 + wave / NW, a.R - 1);        // (past the last row: its work once more, not stored)
   const int g = lane >> 4, ql = lane & 15, T = a.T;
-  const int S = a.pos.kv_len[r >> 1], n_keys = S + a.tree.first + T, nsteps = min((n_keys + 31) >> 5, a.S_cap >> 5);
+  const int S = few_cached(a, r), n_keys = S + a.tree.first + T, nsteps = min((n_keys + 31) >> 5, a.S_cap >> 5);
   const bf16_t* kb = a.kc + a.kv_layer * l + r * a.kv_row + hd * a.kv_head;
   const bf16_t* vb = a.vc + a.kv_layer * l + r * a.kv_row + hd * a.kv_head;
 #define VVS_ATTN_LOAD(STEP, KF, VF)                                                                                   \
@@ -752,7 +754,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_layers_wide(const FewArgs args)
 }
 constexpr size_t kWideLds = sizeof(float) * kWaves * 32 * (128 + 4 + 2);
 
-// All layers of a verify or drafting forward of at most few_rows(c) rows.  In: x, its packed operand bf16(x g1) (rows unpadded) and sums of
+// All layers of a forward of at most few_rows(c) rows and VVS_MAX_T tokens per row.  In: x, its packed operand bf16(x g1) (rows unpadded) and sums of
 // squares, or the drafter's input rows.  Out: the same of the last layer, with the gain of the final norm.
 static FewArgs few_arguments(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, bool from_din) {
   const int M = c->R * T, MT = (M + 31) / 32;

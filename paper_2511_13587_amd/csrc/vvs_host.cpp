@@ -191,7 +191,8 @@ bool plan_fused(const Ctx* c, int M) {
 int few_rows(const Ctx* c) {
   if (!plan_fused(c, c->R) || c->dh != 64) return 0;
   const int most = c->H * c->B > 64 ? 192 : c->d <= 512 ? 256 : 224;
-  return std::min((int)align_up((size_t)c->R * c->Tmax, 32), most);
+  const int tokens = c->cfg.draft_input ? c->Tmax : std::max(c->Tmax, std::min(c->chunk, (int)VVS_MAX_T));   // the longest call of either kind
+  return std::min((int)align_up((size_t)c->R * tokens, 32), most);
 }
 
 // Wide layers.  us per layer, a launch each / one launch:

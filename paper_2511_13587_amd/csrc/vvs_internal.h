@@ -99,7 +99,7 @@ GemmPlan plan_qkv(const Ctx* c, int M);
 GemmPlan plan_gate_up(const Ctx* c, int M);
 GemmPlan plan_resid(const Ctx* c, int M);   // O, down and input-map projections of the fused layer
 bool plan_fused(const Ctx* c, int M);   // true: the fused 5-kernel layer runs for M GEMM rows
-int few_rows(const Ctx* c);   // rows up to which all layers of a verify or drafting forward are one launch (0: never)
+int few_rows(const Ctx* c);   // rows up to which all layers of a forward of at most VVS_MAX_T tokens per row are one launch (0: never)
 int few_wide_rows(const Ctx* c);   // the same for layers with separate normalisations
 vvs_status build_tree(int n_nodes, const int32_t* h_parent, const uint8_t* h_mask, TreeDesc* out, std::string* err);
 

@@ -108,3 +108,17 @@ def test_two_launches_of_the_kind_at_once(gc):  # noqa: F811
         assert same(s.result(), w)
     for s in steps:
         s.pair.close()
+
+
+# 2 rows; 62 and 64 tokens of one prompt (the last that the masks hold), 65 (projections and attention apart again); 224 rows
+@pytest.mark.parametrize("tokens,prompts", [(1, 1), (62, 1), (64, 1), (65, 1), (28, 4)])
+def test_prefill_of_few_rows(gc, tokens, prompts):  # noqa: F811
+    shape = synth.B_SHAPE.replace(n_layers=2, n_prompts=prompts, n_nodes=2, tree_widths=None, vocab=1024, logit_lo=0, logit_hi=1024)
+    pair = gc.Pair(shape, gain_jitter=0.1, shadow=True)
+    pair.prefill(n_forced=tokens - 1)
+    raw, _, _ = pair.gpu_logits()
+    d = raw[pair.rows(), 0] - pair.oracle.prefill_logits
+    assert float(np.abs(d).max()) <= gc.logit_tol(shape, pair.floor, pair.fused)
+    assert gc.rms(d) <= gc.logit_rms_tol(shape, pair.floor_rms, pair.fused)
+    gc.check_kv(pair, 0, tokens, "prefill")
+    pair.close()
