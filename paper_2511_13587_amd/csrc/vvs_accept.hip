@@ -480,10 +480,11 @@ static void launch_accept_on(Ctx* c, const TreeDesc& tree, int T, const float* d
     if ((BYTES) > 64 * 1024) allow_dynamic_lds((const void*)kernel, kAcceptLdsMax);                               \
     hipLaunchKernelGGL(kernel, grid, dim3(NT), (BYTES), s, a, tree);                                              \
   }
-  // Few ids: 4 waves, which meet at a barrier sooner (1024 ids, one prompt of 5 nodes: 12.7 -> 8.4 us with the walk).  More nodes than CUs: two workgroups
-  // of 512 threads to a CU cover each other's barriers (32 x 61 nodes x 16384 ids, relaxed: 247 -> 225 us, though 45 registers spill); else one of 1024
+  // Few ids: 4 waves, which meet at a barrier sooner (1024 ids, one prompt of 5 nodes: 12.7 -> 8.4 us with the walk).  More than four
+  // rounds of nodes: two workgroups of 512 threads to a CU cover each other's barriers, though 45 registers spill (B shape step, relaxed, one of 1024 / two of
+  // 512: 32 x 61 nodes 2070 / 2027 us, 20 x 61 1461 / 1432, 17 x 61 1350 / 1338; 7 x 53 748 / 756)
   if (c->veff <= 4096) VVS_ACCEPT(true, 256, 16, pq_bytes / 2)
-  else if (c->veff <= 16 * 1024 && T * c->B > 256) VVS_ACCEPT(true, 512, 32, pq_bytes / 2)
+  else if (c->veff <= 16 * 1024 && T * c->B > 1024) VVS_ACCEPT(true, 512, 32, pq_bytes / 2)
   else if (c->veff <= 16 * 1024) VVS_ACCEPT(true, 1024, 16, pq_bytes / 2)
   else if (pq_bytes <= kAcceptLdsMax) VVS_ACCEPT(true, 1024, 16, pq_bytes)
   else {                                     // wider slices than the registers hold: the loops over ids

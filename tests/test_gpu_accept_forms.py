@@ -10,8 +10,8 @@ from paper_2511_13587_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-# ids: 4 waves up to 4096, then 16; nodes: 256 on one workgroup per CU, more on two (16 x 17 = 272, 4 x 64 = 256)
-@pytest.mark.parametrize("ids,prompts,nodes", [(1024, 1, 4), (4096, 3, 12), (4160, 3, 12), (16384, 4, 63), (16384, 16, 16), (16320, 5, 60), (16448, 2, 7)])
+# ids: 4 waves up to 4096, then 16; nodes: up to 1024 (16 x 64) in workgroups of 1024 threads, more (17 x 64) of 512
+@pytest.mark.parametrize("ids,prompts,nodes", [(1024, 1, 4), (4096, 3, 12), (4160, 3, 12), (16384, 4, 63), (16384, 16, 63), (16384, 17, 63), (16320, 17, 62), (16320, 5, 60), (16448, 2, 7)])
 @pytest.mark.parametrize("mode", [vb.VVS_STRICT, vb.VVS_RELAXED])
 def test_forms(ids, prompts, nodes, mode):
     shape = synth.TINY.replace(n_layers=1, vocab=ids, logit_hi=ids, n_prompts=prompts, n_nodes=nodes, relax_k=8, relax_delta=0.2)
