@@ -25,6 +25,14 @@
  *
  * Errors: every function returns a vvs_status; nothing is launched when the status is not VVS_OK
  * (arguments and call order are checked on the host first).  vvs_last_error gives the message.
+ *
+ * A forward of few rows runs all layers in one launch, whose workgroups wait for each other's results.  Should such a wait not
+ * end (after some 2 million looks, 1 to 2 s; nothing in the library's own work leads there), the launch ends without its
+ * results, and the call behind it says so in its outputs, since its status has been returned long before:
+ *   vvs_verify, vvs_verify_post: accept_len, next_token and the whole path of every prompt are -1 (of a prompt whose image is
+ *     complete: as ever); vvs_kv_commit then changes nothing, so that the call can be made again;
+ *   vvs_prefill: d_first_token is -1 and every prompt counts as complete (vvs_read_state: n_emitted = G, pending token -1);
+ *   vvs_draft: all distributions of the levels from there on are NaN, the tokens (unless given) the first ids of the slice.
  */
 #ifndef VVS_H
 #define VVS_H
@@ -340,6 +348,9 @@ vvs_status vvs_debug_gemm(vvs_ctx* ctx, int32_t m, int32_t n, int32_t k, const v
 /* Plain device-to-device copy of `bytes` bytes (multiple of 16; 16-byte aligned pointers) with one
  * grid-stride kernel.  Reads and writes exactly `bytes`: used to calibrate hardware traffic counters. */
 vvs_status vvs_debug_copy(vvs_ctx* ctx, void* d_dst, const void* d_src, size_t bytes, vvs_stream s);
+
+/* Looks after which a wait inside a launch of all layers gives up (see the top of this file); 0: the default.  For unit tests. */
+vvs_status vvs_debug_wait_limit(vvs_ctx* ctx, int32_t polls);
 
 /* Measures how fast a compute unit pulls bytes through its L1 - the figure that bounds the projection kernels of this
  * library.  Launches `n_workgroups` workgroups of `waves` waves (1..16); workgroup w reads the `region_bytes` (a multiple of

@@ -78,6 +78,7 @@ def _load():
         "vvs_debug_gemm_scratch_bytes": (sz, [vp, i32, i32, i32]),
         "vvs_debug_gemm": (i32, [vp, i32, i32, i32, vp, vp, vp, vp, vp]),
         "vvs_debug_copy": (i32, [vp, vp, vp, sz, vp]),
+        "vvs_debug_wait_limit": (i32, [vp, i32]),
         "vvs_debug_fill_probe": (i32, [vp, vp, sz, sz, i32, i32, i32, i32, vp, vp]),
     }
     for name, (res, args) in sigs.items():
@@ -338,6 +339,9 @@ class Context:
         nbytes = src.numel() * src.element_size()
         assert dst.numel() * dst.element_size() == nbytes
         self._check(lib.vvs_debug_copy(self.h, _ptr(dst), _ptr(src), nbytes, _stream()))
+
+    def vvs_debug_wait_limit(self, polls: int):
+        self._check(lib.vvs_debug_wait_limit(self.h, int(polls)))
 
     def vvs_debug_fill_probe(self, src: torch.Tensor, reps: int, mode: int, n_workgroups: int, waves: int,
                              region_bytes: int = 0, wg_stride_bytes: int = 0) -> torch.Tensor:

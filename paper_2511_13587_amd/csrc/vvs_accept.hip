@@ -32,7 +32,8 @@ __device__ __forceinline__ void walk_path(int child, int token, int b, int B, co
     cur = nxt;
     if (i == ++a) mine = cur;
   }
-  const int tok = __builtin_amdgcn_readlane(token, cur);
+  int tok = __builtin_amdgcn_readlane(token, cur);
+  if (tok == kGaveUp) a = tok = -1;        // nothing is known of this prompt: no path, and no commit
   if (i == 0) {
     if (o.accept_len) o.accept_len[b] = a;
     if (o.next_token) o.next_token[b] = tok;
@@ -59,6 +60,7 @@ struct AcceptArgs {
   float* work;                // [B][T][2][veff] scratch: running target P and draft Q
   int32_t* node_result;       // [B][VVS_MAX_T][2] out: (accepted child or 0, drawn token or -1)
   uint32_t* done;             // [B][kWalkLine] nodes of a prompt that are done, zero between calls; nullptr: the walk is a launch of its own
+  const uint32_t* gave_up;    // not zero: the logits are not valid; or nullptr
   WalkOut out;
   int B;
   int T, veff, lo, mode, relax_k, G;
@@ -204,6 +206,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void k_accept_node(AcceptArg
   };
   const bool tested = tree.first_child[j] > tree.n_forced;   // this node's children are tested (unless the image ends first)
   const int ne = a.n_emitted ? a.n_emitted[b] : 0;
+  const bool invalid = a.gave_up && *a.gave_up;
   // the children (ascending node id = the order in which they are tried), their drafted ids and uniforms: one lane each
   const bool child = tested && tid < VVS_MAX_T && tid > 0 && tid < T && tree.parent[tid] == j;
   float p[RK], q[RK];
@@ -307,6 +310,10 @@ __global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void k_accept_node(AcceptArg
       return;
     }
     cap = a.G - ne - 1;
+  }
+  if (invalid) {
+    finish(0, kGaveUp);
+    return;
   }
 
   int accepted = 0;
@@ -455,7 +462,7 @@ __global__ __launch_bounds__(64) void k_walk(const int32_t* __restrict__ node_re
 
 static void launch_accept_on(Ctx* c, const TreeDesc& tree, int T, const float* d_logits, const int32_t* d_draft_tokens, const float* d_q,
                              const float* d_u, int usb, int usj, int uoa, int uot, int mode, bool use_state, int32_t* d_accept_len,
-                             int32_t* d_path, int32_t* d_next, int32_t* keep, float* probs, float* work, int32_t* node_result, uint32_t* done, hipStream_t s) {
+                             int32_t* d_path, int32_t* d_next, int32_t* keep, const uint32_t* gave_up, float* probs, float* work, int32_t* node_result, uint32_t* done, hipStream_t s) {
   Timed timed(c, VVS_K_ACCEPT, s);
   AcceptArgs a;
   a.logits = d_logits; a.draft = d_draft_tokens; a.q = d_q; a.u = d_u;
@@ -466,6 +473,7 @@ static void launch_accept_on(Ctx* c, const TreeDesc& tree, int T, const float* d
   a.work = work;
   a.node_result = node_result;
   a.done = done;
+  a.gave_up = gave_up;
   a.out = WalkOut{d_accept_len, d_path, d_next, keep, (const int32_t*)(c->ws + c->w.state), (const int32_t*)(c->ws + c->w.ring_state)};
   a.B = c->B;
   a.T = T; a.veff = c->veff; a.lo = c->lo; a.mode = mode; a.relax_k = c->cfg.relax_k; a.G = c->G;
@@ -496,9 +504,9 @@ static void launch_accept_on(Ctx* c, const TreeDesc& tree, int T, const float* d
 
 void launch_accept(Ctx* c, const TreeDesc& tree, int T, const float* d_logits, const int32_t* d_draft_tokens, const float* d_q,
                    const float* d_u, int usb, int usj, int uoa, int uot, int mode, bool use_state, int32_t* d_accept_len,
-                   int32_t* d_path, int32_t* d_next, bool keep_outcome, hipStream_t s) {
+                   int32_t* d_path, int32_t* d_next, bool keep_outcome, const uint32_t* gave_up, hipStream_t s) {
   launch_accept_on(c, tree, T, d_logits, d_draft_tokens, d_q, d_u, usb, usj, uoa, uot, mode, use_state, d_accept_len, d_path, d_next,
-                   keep_outcome ? (int32_t*)(c->ws + c->w.outcome) : nullptr, (float*)(c->ws + c->w.probs), (float*)(c->ws + c->w.pq_work),
+                   keep_outcome ? (int32_t*)(c->ws + c->w.outcome) : nullptr, gave_up, (float*)(c->ws + c->w.probs), (float*)(c->ws + c->w.pq_work),
                    (int32_t*)(c->ws + c->w.node_result), (uint32_t*)(c->ws + c->w.walk_sync), s);
 }
 
@@ -541,16 +549,20 @@ vvs_status launch_accept_noalloc(Ctx* c, const TreeDesc& tree, int T, const floa
     g_scratch_ptr[dev] = p;
   }
   unsigned char* base = g_scratch_ptr[dev];
-  launch_accept_on(c, tree, T, d_logits, d_draft_tokens, d_q, d_u, 2 * T, 2, 0, 1, mode, false, d_accept_len, d_path, d_next, nullptr,
+  launch_accept_on(c, tree, T, d_logits, d_draft_tokens, d_q, d_u, 2 * T, 2, 0, 1, mode, false, d_accept_len, d_path, d_next, nullptr, nullptr,
                    (float*)(base + kNoAllocNodeBytes), nullptr, (int32_t*)base, nullptr, s);
   return VVS_OK;
 }
 
 __global__ void k_prefill_finish(const int32_t* __restrict__ node_result, int32_t* __restrict__ state, int32_t* __restrict__ first,
-                                 int B, int kv_len, int n_emitted) {
+                                 int B, int kv_len, int n_emitted, int grid) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B) return;
-  const int tok = node_result[((size_t)b * VVS_MAX_T) * 2 + 1];
+  int tok = node_result[((size_t)b * VVS_MAX_T) * 2 + 1];
+  if (tok == kGaveUp) {                    // no image to continue: it counts as complete
+    tok = -1;
+    n_emitted = grid;
+  }
   first[b] = tok;
   state[b] = kv_len;
   state[B + b] = n_emitted;
@@ -559,7 +571,7 @@ __global__ void k_prefill_finish(const int32_t* __restrict__ node_result, int32_
 
 void launch_prefill_finish(Ctx* c, int n_forced, int32_t* d_first, hipStream_t s) {
   hipLaunchKernelGGL(k_prefill_finish, dim3((c->B + 63) / 64), dim3(64), 0, s, (const int32_t*)(c->ws + c->w.node_result),
-                     (int32_t*)(c->ws + c->w.state), d_first, c->B, c->P + n_forced, n_forced + 1);
+                     (int32_t*)(c->ws + c->w.state), d_first, c->B, c->P + n_forced, n_forced + 1, c->G);
 }
 
 }  // namespace vvs

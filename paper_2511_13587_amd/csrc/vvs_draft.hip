@@ -11,9 +11,10 @@ namespace vvs {
 
 // Per prompt: cached length 0 and the number of emitted tokens that puts block token t at image index
 // first + depth(t), first = max(0, root - (k - 1)), root = emitted tokens of the target - 1 + n_unverified.
-__global__ void k_draft_state(int32_t* __restrict__ state, const int32_t* __restrict__ target_state, int B, int k, int n_unverified) {
+__global__ void k_draft_state(int32_t* __restrict__ state, const int32_t* __restrict__ target_state, uint32_t* __restrict__ gave_up, int B, int k, int n_unverified) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B) return;
+  if (b == 0) *gave_up = 0;
   const int root = target_state[B + b] - 1 + n_unverified;
   state[b] = 0;
   state[B + b] = max(0, root - (k - 1)) + 1;
@@ -22,7 +23,7 @@ __global__ void k_draft_state(int32_t* __restrict__ state, const int32_t* __rest
 
 void launch_draft_state(Ctx* dr, const Ctx* tg, int k, int n_unverified, hipStream_t s) {
   hipLaunchKernelGGL(k_draft_state, dim3((dr->B + 63) / 64), dim3(64), 0, s, (int32_t*)(dr->ws + dr->w.state),
-                     (const int32_t*)(tg->ws + tg->w.state), dr->B, k, n_unverified);
+                     (const int32_t*)(tg->ws + tg->w.state), (uint32_t*)(dr->ws + dr->w.few_gave_up), dr->B, k, n_unverified);
 }
 
 struct LeafList { int32_t n; int8_t node[VVS_MAX_T]; };
@@ -109,13 +110,14 @@ void launch_draft_input(Ctx* dr, const Ctx* tg, const DraftLevel& lv, const int3
 
 // One workgroup per (prompt, node expanded at this level): mixes the node's conditional and unconditional
 // logit rows, writes the softmax as the distribution of the node's children, and gives the c-th child the
-// id with the c-th largest mixed logit (ties to the lower id) - or the caller's token.
+// id with the c-th largest mixed logit (ties to the lower id) - or the caller's token.  Where a forward of the call is not whole: NaN, and the
+// lowest ids of the slice.
 struct Best { float v; int i; };
 __device__ __forceinline__ Best better(Best a, Best b) { return (b.v > a.v || (b.v == a.v && b.i < a.i)) ? b : a; }
 
 __global__ __launch_bounds__(1024) void k_draft_select(const float* __restrict__ logits, DraftLevel lv, TreeDesc shape,
                                                        const int32_t* __restrict__ given, int32_t* __restrict__ draft_tokens,
-                                                       float* __restrict__ probs, int V, int lo, float cfg_scale) {
+                                                       float* __restrict__ probs, const uint32_t* __restrict__ gave_up, int V, int lo, float cfg_scale) {
   __shared__ float red[16];
   __shared__ float s_bv[16];
   __shared__ int s_bi[16];
@@ -130,7 +132,8 @@ __global__ __launch_bounds__(1024) void k_draft_select(const float* __restrict__
   float sum = 0.f;
   for (int i = threadIdx.x; i < V; i += blockDim.x) sum += expf(lu[i] + cfg_scale * (lc[i] - lu[i]) - mx);
   sum = block_sum(sum, red);
-  const float inv = 1.0f / sum;
+  const bool invalid = *gave_up;
+  const float inv = invalid ? NAN : 1.0f / sum;
   for (int i = threadIdx.x; i < V; i += blockDim.x) out[i] = expf(lu[i] + cfg_scale * (lc[i] - lu[i]) - mx) * inv;
   int n_taken = 0;
   for (int c = shape.first_child[j]; c >= 0; c = shape.next_sibling[c]) {
@@ -152,6 +155,7 @@ __global__ __launch_bounds__(1024) void k_draft_select(const float* __restrict__
     if (threadIdx.x == 0) {
       Best w{s_bv[0], s_bi[0]};
       for (int q = 1; q < (int)(blockDim.x >> 6); ++q) w = better(w, Best{s_bv[q], s_bi[q]});
+      if (invalid) w.i = min(n_taken, V - 1);
       s_taken[n_taken] = w.i;
       draft_tokens[b * lv.n_nodes + c - 1] = lo + w.i;
     }
@@ -166,7 +170,7 @@ __global__ __launch_bounds__(1024) void k_draft_select(const float* __restrict__
 template <int NT>
 __global__ __launch_bounds__(NT) void k_draft_select_regs(const float* __restrict__ logits, DraftLevel lv, TreeDesc shape,
                                                             const int32_t* __restrict__ given, int32_t* __restrict__ draft_tokens,
-                                                            float* __restrict__ probs, int V, int lo, float cfg_scale) {
+                                                            float* __restrict__ probs, const uint32_t* __restrict__ gave_up, int V, int lo, float cfg_scale) {
   constexpr int NR = 16;
   __shared__ float red[16];
   __shared__ float s_bv[16];
@@ -176,6 +180,7 @@ __global__ __launch_bounds__(NT) void k_draft_select_regs(const float* __restric
   const float* lc = logits + ((size_t)(2 * b) * lv.all + t) * V;
   const float* lu = logits + ((size_t)(2 * b + 1) * lv.all + t) * V;
   float* out = probs + ((size_t)b * shape.T + j) * V;
+  const bool invalid = *gave_up;
   float mixed[NR];
   float mx = -INFINITY;
 #pragma unroll
@@ -194,11 +199,12 @@ __global__ __launch_bounds__(NT) void k_draft_select_regs(const float* __restric
     sum += e[r];
   }
   sum = block_sum(sum, red);
-  const float inv = 1.0f / sum;
+  const float inv = invalid ? NAN : 1.0f / sum;
 #pragma unroll
   for (int r = 0; r < NR; ++r)
     if (threadIdx.x + r * NT < V) out[threadIdx.x + r * NT] = e[r] * inv;
-  for (int c = shape.first_child[j]; c >= 0; c = shape.next_sibling[c]) {
+  int n_taken = 0;
+  for (int c = shape.first_child[j]; c >= 0; c = shape.next_sibling[c], ++n_taken) {
     if (given) {
       if (threadIdx.x == 0) draft_tokens[b * lv.n_nodes + c - 1] = given[b * lv.n_nodes + c - 1];
       continue;
@@ -214,6 +220,7 @@ __global__ __launch_bounds__(NT) void k_draft_select_regs(const float* __restric
     if (threadIdx.x == 0) {
       Best w{s_bv[0], s_bi[0]};
       for (int q = 1; q < NT / 64; ++q) w = better(w, Best{s_bv[q], s_bi[q]});
+      if (invalid) w.i = min(n_taken, V - 1);
       s_win = w.i;
       draft_tokens[b * lv.n_nodes + c - 1] = lo + w.i;
     }
@@ -230,15 +237,16 @@ void launch_draft_select(Ctx* dr, const DraftLevel& lv, const TreeDesc& shape, c
                          float* d_probs, hipStream_t s) {
   if (!lv.n_sel) return;
   Timed timed(dr, VVS_K_ACCEPT, s);
+  const uint32_t* gave_up = (const uint32_t*)(dr->ws + dr->w.few_gave_up);
   if (dr->veff <= 16 * 256)
     hipLaunchKernelGGL(k_draft_select_regs<256>, dim3(dr->B, lv.n_sel), dim3(256), 0, s, (const float*)(dr->ws + dr->w.logits), lv, shape,
-                       d_given_tokens, d_draft_tokens, d_probs, dr->veff, dr->lo, dr->cfg.cfg_scale);
+                       d_given_tokens, d_draft_tokens, d_probs, gave_up, dr->veff, dr->lo, dr->cfg.cfg_scale);
   else if (dr->veff <= 16 * 1024)
     hipLaunchKernelGGL(k_draft_select_regs<1024>, dim3(dr->B, lv.n_sel), dim3(1024), 0, s, (const float*)(dr->ws + dr->w.logits), lv, shape,
-                       d_given_tokens, d_draft_tokens, d_probs, dr->veff, dr->lo, dr->cfg.cfg_scale);
+                       d_given_tokens, d_draft_tokens, d_probs, gave_up, dr->veff, dr->lo, dr->cfg.cfg_scale);
   else
     hipLaunchKernelGGL(k_draft_select, dim3(dr->B, lv.n_sel), dim3(1024), 0, s, (const float*)(dr->ws + dr->w.logits), lv, shape,
-                       d_given_tokens, d_draft_tokens, d_probs, dr->veff, dr->lo, dr->cfg.cfg_scale);
+                       d_given_tokens, d_draft_tokens, d_probs, gave_up, dr->veff, dr->lo, dr->cfg.cfg_scale);
 }
 
 }  // namespace vvs

@@ -35,7 +35,9 @@
 // owns it runs.  Where all workgroups of the launch are seen to run (they count themselves in at the start) tile t belongs to workgroup
 // t % 256.  Where they do not within a bounded time - another program or stream keeps CUs, perhaps with a launch of this very
 // kind that waits for the same CUs - nobody owns a tile beforehand: workgroups draw tile numbers from a counter, so that whoever runs
-// works on the lowest one that is left.  Either way a wait also ends after kPolls polls.
+// works on the lowest one that is left.  Either way a wait also ends after FewArgs.polls looks: by then something else is broken, and what the
+// forward leaves is not valid.  Its workgroups leave, the last one notes it (FewArgs.gave_up), and the kernels behind turn that into an outcome of
+// its own: k_accept_node, k_prefill_finish, k_draft_select.
 #include "vvs_mfma.h"
 
 #include <algorithm>
@@ -47,7 +49,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 enum { PH_INPUT = 0, PH_QKV, PH_ATTN, PH_O, PH_GU, PH_DOWN, PH_PART };
 constexpr int kGroups = 256;               // workgroups: one per CU (fewer CUs: see below)
 constexpr int kWaves = 8, kThreads = kWaves * 64;
-constexpr int kPolls = 1 << 21;            // more than a second: by then something else is broken, and the results are not valid
 constexpr long kAdmission = 20000;         // 100 MHz ticks that a workgroup waits for all others to be there
 
 // ---- agent scope: written through, read from behind the L2s
@@ -85,8 +86,10 @@ struct FewArgs {
   size_t kv_layer, kv_row, kv_head;
   const float* rope;
   uint32_t* sync;                          // kLine apart: how tiles are dealt (1: tile t to workgroup t % 256, 2: drawn), next tile to draw, eighths of the workgroups that
-                                           // are done, [8] workgroups that are there, [8] done; then the layers' counters, then 8 of the input map
+                                           // are done, [8] workgroups that are there, [8] done, those that gave up a wait; then the layers' counters, then 8 of the input map
+  uint32_t* gave_up;                       // not zero: a wait of this launch (drafter: or of an earlier level's) was given up
   int L, M, MT, T, d, H, F, R, NS, S_cap, rope_pos;
+  int polls;                               // looks at a counter before a wait gives up
   int rows_per_unit;                       // rows that share an attention unit: 1, 2 or 4
   float* part;                             // wide layers: partial sums of O and of down [kWideShares][M][d]
   float eps, c_exp;
@@ -140,12 +143,13 @@ __device__ __forceinline__ bool few_wait(const uint32_t* counter, int n, uint32_
   const int lane = threadIdx.x & 63;
   if (threadIdx.x < 64) {
     int poll = 0;
+    const int polls = few_args().polls;
     const uint32_t* first = counter + (size_t)(blockIdx.x % n) * kLine;
-    for (; poll < kPolls && get32(first) == 0; ++poll) __builtin_amdgcn_s_sleep(36);
+    for (; poll < polls && get32(first) == 0; ++poll) __builtin_amdgcn_s_sleep(36);
     for (;; ++poll) {
       const uint32_t v = lane < n ? get32(counter + (size_t)lane * kLine) : want;
       if (__builtin_amdgcn_ballot_w64(v != want) == 0) break;
-      if (poll >= kPolls) { sh->stop = 1; break; }
+      if (poll >= polls) { sh->stop = 1; break; }
     }
   }
   barrier();
@@ -527,13 +531,22 @@ __device__ __attribute__((noinline)) int few_dealing(uint32_t* sync, int id) {
   return (int)mode;
 }
 
-// The last workgroup leaves the counters as it found them: zero
+// The last workgroup notes whether all tiles were computed, and leaves the counters as it found them: zero
 __device__ __forceinline__ void few_leave(FewShared* sh) {
   const FewArgs& e = few_args();
   barrier();
   if (threadIdx.x == 0) {
     auto last = [](uint32_t* counter, uint32_t n) { return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1; };
+    uint32_t* stopped = e.sync + 19 * kLine;
+    if (sh->stop) {
+      __hip_atomic_fetch_add(stopped, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // ... before this workgroup counts as done
+    }
     sh->last = last(e.sync + (11 + (blockIdx.x & 7)) * kLine, kGroups / 8) && last(e.sync + 2 * kLine, 8);
+    if (sh->last) {
+      const uint32_t n = get32(stopped);
+      *e.gave_up = e.fc ? *e.gave_up | n : n;
+    }
   }
   barrier();
   if (sh->last)
@@ -777,6 +790,8 @@ static FewArgs few_arguments(Ctx* c, const TreeDesc& tree, const PosDesc& pos, i
   a.kv_layer = c->kv_layer_stride; a.kv_row = c->kv_row_stride; a.kv_head = c->kv_head_stride;
   a.rope = (const float*)(c->ws + c->w.rope_tab);
   a.sync = (uint32_t*)(c->ws + c->w.few_sync);
+  a.gave_up = (uint32_t*)(c->ws + c->w.few_gave_up);
+  a.polls = c->wait_polls;
   a.L = c->L; a.M = M; a.MT = MT; a.T = T; a.d = c->d; a.H = c->H; a.F = c->F; a.R = c->R; a.NS = n_slabs(c->d); a.S_cap = c->S_cap;
   a.rope_pos = c->rope_pos;
   a.eps = c->cfg.rms_eps;

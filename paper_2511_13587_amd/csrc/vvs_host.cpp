@@ -208,6 +208,9 @@ int few_wide_rows(const Ctx* c) {
   return std::min((int)align_up((size_t)c->R * c->Tmax, 32), c->d <= 2048 && layer_weight_bytes <= (size_t)104 << 20 ? 128 : 64);
 }
 
+// (More than VVS_MAX_T tokens have no masks.)
+bool layers_in_one_launch(const Ctx* c, int T) { return T <= VVS_MAX_T && c->R * T <= std::max(few_rows(c), few_wide_rows(c)); }
+
 vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   if (!cfg) return fail(err, VVS_EINVAL, "config is NULL");
   const vvs_config& g = *cfg;
@@ -301,6 +304,7 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   const int wide = few_wide_rows(c), few = std::max(few_rows(c), wide);
   go = std::max(go, (size_t)kFewWideShares * wide * d);
   w.few_sync = take(few ? sizeof(uint32_t) * kFewLine * (kFewHead + (size_t)few_layer_counters(c->H, few / 32) * c->L + 8) : 0);   // zeroed with the state
+  w.few_gave_up = take(sizeof(uint32_t));
   w.x = take(sizeof(float) * (size_t)c->Mmax * d);
   w.h = take(c->esz * (size_t)c->Mmax * d);
   // (a call whose layers are one launch has no partial sums: what its phases hand on lies in their place)
@@ -414,6 +418,9 @@ static vvs_status check_launch(Ctx* c, const char* what) {
   return VVS_OK;
 }
 
+// Where the forward of T tokens per row that was just launched says that it is not whole (nullptr: it has no waits that could give up)
+static const uint32_t* gave_up(const Ctx* c, int T) { return layers_in_one_launch(c, T) ? (const uint32_t*)(c->ws + c->w.few_gave_up) : nullptr; }
+
 }  // namespace vvs
 
 using namespace vvs;
@@ -467,6 +474,7 @@ vvs_status vvs_create(const vvs_config* cfg, void* d_kv, void* d_workspace, void
   c->nbr = nullptr;
   c->codebook = nullptr;
   c->code_dim = 0;
+  c->wait_polls = kFewPolls;
   // zero the KV cache (padded slots are read, multiplied by zero weights) and the state block
   launch_fill_zero(c->kv, 2 * c->kv_v_off * c->esz, nullptr);
   launch_fill_zero(c->ws, c->w.x, nullptr);
@@ -587,7 +595,7 @@ vvs_status vvs_prefill(vvs_ctx* ctx, const void* d_prefix_cond, const void* d_pr
       TreeDesc one;
       causal_tree(1, &one);
       launch_accept(c, one, 1, (const float*)(c->ws + c->w.logits), nullptr, nullptr, d_uniform, 1, 0, 0, 0, VVS_STRICT,
-                    false, nullptr, nullptr, nullptr, false, st);
+                    false, nullptr, nullptr, nullptr, false, gave_up(c, T), st);
       launch_prefill_finish(c, n_forced, d_first_token, st);
       launch_push_prefill_feature(c, T, st);
     }
@@ -642,7 +650,7 @@ vvs_status vvs_verify_post(vvs_ctx* ctx, int32_t n_nodes, int32_t n_post, const 
   launch_build_tokens(c, T, d_draft_tokens, st);
   launch_forward(c, tree, pos, T, (const int32_t*)(c->ws + c->w.tokens), nullptr, nullptr, 0, nullptr, 0, 1, st);
   launch_accept(c, tree, T, (const float*)(c->ws + c->w.logits), d_draft_tokens, d_draft_probs, d_uniforms, 2 * T, 2, 0, 1,
-                mode, true, d_accept_len, d_path, d_next_token, true, st);
+                mode, true, d_accept_len, d_path, d_next_token, true, gave_up(c, T), st);
   rc = check_launch(c, "verify");
   if (rc != VVS_OK) return rc;
   c->verify_pending = true;
@@ -671,7 +679,7 @@ vvs_status vvs_accept_from_logits(vvs_ctx* ctx, int32_t n_nodes, const int32_t* 
   rc = build_tree(n_nodes, h_parent, h_tree_mask, &tree, &c->err);
   if (rc != VVS_OK) return rc;
   launch_accept(c, tree, n_nodes + 1, d_raw_logits, d_draft_tokens, d_draft_probs, d_uniforms, 2 * (n_nodes + 1), 2, 0, 1,
-                mode, false, d_accept_len, d_path, d_next_token, false, (hipStream_t)s);
+                mode, false, d_accept_len, d_path, d_next_token, false, nullptr, (hipStream_t)s);
   return check_launch(c, "accept_from_logits");
 }
 
@@ -908,6 +916,14 @@ vvs_status vvs_debug_fill_probe(vvs_ctx* ctx, const void* d_src, size_t region_b
     return fail(&c->err, VVS_EINVAL, "debug_fill_probe: reps, mode, workgroups or waves out of range");
   launch_fill_probe(d_src, region_bytes, wg_stride_bytes, reps, mode, n_workgroups, waves, d_sink, (hipStream_t)s);
   return check_launch(c, "debug_fill_probe");
+}
+
+vvs_status vvs_debug_wait_limit(vvs_ctx* ctx, int32_t polls) {
+  Ctx* c = reinterpret_cast<Ctx*>(ctx);
+  if (!c) return VVS_EINVAL;
+  if (polls < 0) return fail(&c->err, VVS_EINVAL, "debug_wait_limit: polls < 0");
+  c->wait_polls = polls ? polls : kFewPolls;
+  return VVS_OK;
 }
 
 size_t vvs_debug_gemm_scratch_bytes(const vvs_ctx* ctx, int32_t m, int32_t n, int32_t k) {

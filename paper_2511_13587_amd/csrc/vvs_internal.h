@@ -40,7 +40,7 @@ struct GemmPlan { int bm, bn, splits; bool row_owner = false, shared = false; };
 // Byte offsets into the caller's workspace.
 struct Workspace {
   size_t state, outcome, node_result, tokens, rope_tab, x, h, gemm_out, q, attn, act, hf, logits, probs,
-      pq_work, ss, ss2, ring, ring_state, din, few_sync, few_buf, walk_sync, total;
+      pq_work, ss, ss2, ring, ring_state, din, few_sync, few_buf, few_gave_up, walk_sync, total;
 };
 
 struct PackedLayout {
@@ -66,6 +66,7 @@ struct Ctx {
   const float* codebook; int code_dim;   // latent codebook of the path-similarity kernel (by reference)
   bool weights_loaded, prefilled, verify_pending;
   int last_T;                            // T of the last verify / prefill (for debug export)
+  int wait_polls;                        // looks after which a wait of vvs_few.hip gives up
   std::string err;
   bool timing;                           // bracket launches with events
   std::vector<TimedLaunch> timed;        // recorded launches (events are reused across enables)
@@ -101,6 +102,7 @@ GemmPlan plan_resid(const Ctx* c, int M);   // O, down and input-map projections
 bool plan_fused(const Ctx* c, int M);   // true: the fused 5-kernel layer runs for M GEMM rows
 int few_rows(const Ctx* c);   // rows up to which all layers of a forward of at most VVS_MAX_T tokens per row are one launch (0: never)
 int few_wide_rows(const Ctx* c);   // the same for layers with separate normalisations
+bool layers_in_one_launch(const Ctx* c, int T);   // a forward of T tokens per row takes that launch
 vvs_status build_tree(int n_nodes, const int32_t* h_parent, const uint8_t* h_mask, TreeDesc* out, std::string* err);
 
 // ---- launchers (kernels_*.hip); all asynchronous on the stream
@@ -115,7 +117,7 @@ void launch_build_tokens(Ctx* c, int T, const int32_t* d_draft, hipStream_t s);
 void launch_accept(Ctx* c, const TreeDesc& tree, int T, const float* d_logits, const int32_t* d_draft_tokens,
                    const float* d_q, const float* d_u, int u_stride_b, int u_stride_j, int u_off_acc, int u_off_term,
                    int mode, bool use_state, int32_t* d_accept_len, int32_t* d_path, int32_t* d_next,
-                   bool keep_outcome, hipStream_t s);
+                   bool keep_outcome, const uint32_t* gave_up /*of the forward that the logits are from, or nullptr*/, hipStream_t s);
 vvs_status launch_accept_noalloc(Ctx* c, const TreeDesc& tree, int T, const float* d_logits, const int32_t* d_draft_tokens,
                                  const float* d_q, const float* d_u, int mode, int32_t* d_accept_len, int32_t* d_path, int32_t* d_next,
                                  hipStream_t s, std::string* err);
@@ -164,8 +166,10 @@ constexpr int kWalkLine = 16;   // words between the counters of two prompts (k_
 
 // All layers in one launch (vvs_few.hip): counters of a layer and bytes that it hands from phase to phase
 constexpr int kFewLine = 32;   // words between two counters: a line of its own for each
-constexpr int kFewHead = 19;   // counters in front of the layers'
+constexpr int kFewHead = 20;   // counters in front of the layers'
 constexpr int few_layer_counters(int H, int row_tiles) { return H * row_tiles + 6 * 8; }
+constexpr int kFewPolls = 1 << 21;   // looks at a counter, about 1 us each, before a wait gives up
+constexpr int kGaveUp = -2;    // in place of a node's token: the forward in front is not whole
 constexpr int kFewWideShares = 2;   // shares of the contraction of O and down in wide layers
 constexpr size_t few_buf_bytes(int rows, int d, int F) { return (size_t)rows * (2 * (4 * (size_t)d + F) + 2 * 4 * (size_t)n_slabs(d)); }
 

@@ -702,7 +702,7 @@ static void forward_fused(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int 
   const float* g_first = (const float*)(c->pw + c->p.layer0 + c->p.g1);   // gain of the first layer's first norm
   const float* gf = (const float*)(c->pw + c->p.gf);
   // verify calls of up to 64 tokens per row at head size 64: projection + attention in one launch, fed by the row-padded operand layout
-  const bool few = Tq <= VVS_MAX_T && M <= few_rows(c);   // (a prefill of more tokens has no mask)
+  const bool few = layers_in_one_launch(c, Tq);
   const int pad = few ? 0 : mfma_qkv_attention_rows(c, pos, Tq);
   const bool qa = pad > 0;
   const int pad_T = qa ? Tq : 0;
@@ -848,7 +848,7 @@ static void forward_t(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int Tq, 
     hipLaunchKernelGGL(k_embed<T>, dim3(M), dim3(256), 0, s, x, (const T*)(c->pw + c->p.embed),
                        (const T*)(c->pw + c->p.prefix_embed), ea);
   }
-  const bool wide = sizeof(T) == 2 && Tq <= VVS_MAX_T && M <= few_wide_rows(c);
+  const bool wide = layers_in_one_launch(c, Tq);
   if (wide) {
     Timed timed(c, VVS_K_GEMM, s);
     launch_layers_wide(c, tree, pos, Tq, s);

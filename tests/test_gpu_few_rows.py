@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2511_13587_amd import synth
+from test_gpu_drafter import DraftSide
 from test_gpu_parity import gc, run_bf16_case, show  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -121,4 +122,66 @@ def test_prefill_of_few_rows(gc, tokens, prompts):  # noqa: F811
     assert float(np.abs(d).max()) <= gc.logit_tol(shape, pair.floor, pair.fused)
     assert gc.rms(d) <= gc.logit_rms_tol(shape, pair.floor_rms, pair.fused)
     gc.check_kv(pair, 0, tokens, "prefill")
+    pair.close()
+
+
+# A limit of one look ends the first wait for a tile that is still being computed: what the workgroups left undone must be said by the call's
+# outputs, and the next call must be as if nothing had been.  Narrow layers and wide ones.
+@pytest.mark.parametrize("model", ["b", "7b"])
+def test_a_wait_that_gives_up_is_told(gc, model):  # noqa: F811
+    base = synth.B_SHAPE if model == "b" else synth.SEVEN_B.replace(d_model=1536, n_heads=12, d_ff=4096, prefix_len=8, logit_lo=0)
+    shape = base.replace(n_layers=2, n_prompts=2, n_nodes=13, tree_widths=None, vocab=1024, logit_hi=1024)
+    step = Step(gc, shape, 0)
+    pair, ctx = step.pair, step.pair.ctx
+    step.run()
+    want = step.result(), pair.accept_len.clone(), pair.path.clone(), pair.next_token.clone()
+    features = ctx.vvs_read_features()
+    ctx.vvs_debug_wait_limit(1)
+    step.run()
+    torch.cuda.synchronize()
+    assert pair.accept_len.tolist() == [-1, -1] and pair.next_token.tolist() == [-1, -1] and bool((pair.path == -1).all())
+    ctx.vvs_kv_commit()
+    assert np.array_equal(ctx.vvs_read_state(), step.state.cpu().numpy())
+    assert all(np.array_equal(a, b) for a, b in zip(ctx.vvs_read_features(), features))
+    ctx.vvs_debug_wait_limit(0)
+    step.run()
+    assert same(step.result(), want[0])
+    assert all(torch.equal(a, b) for a, b in zip((pair.accept_len, pair.path, pair.next_token), want[1:]))
+    # a prefill: its prompts count as complete, until the next one
+    ctx.vvs_debug_wait_limit(1)
+    first, _, u = pair.prefill(n_forced=4, run_oracle=False)
+    assert first.tolist() == [-1, -1]
+    assert ctx.vvs_read_state()[1:].tolist() == [[shape.grid] * 2, [-1] * 2]
+    ctx.vvs_debug_wait_limit(0)
+    ctx.vvs_verify(shape.n_nodes, None, None, *step.args, 0, pair.accept_len, pair.path, pair.next_token)
+    assert pair.accept_len.tolist() == [0, 0] and pair.next_token.tolist() == [-1, -1]
+    first, _, _ = pair.prefill(n_forced=4, u=u, run_oracle=False)
+    assert (first >= 0).all() and ctx.vvs_read_state()[1].tolist() == [5, 5]
+    pair.close()
+
+
+def test_a_drafting_call_that_gives_up_is_told(gc):  # noqa: F811
+    shape = synth.B_SHAPE.replace(n_layers=1, n_prompts=2, n_nodes=10, tree_widths=(3, 4, 3), vocab=1024, logit_lo=64, logit_hi=1024)
+    parent = np.asarray(synth.tree_parents(shape.tree_widths, 10), dtype=np.int32)
+    inner = sorted({int(p) for p in parent})
+    pair = gc.Pair(shape, with_oracle=False)
+    pair.prefill(n_forced=10, run_oracle=False)
+    side = DraftSide(gc, pair, max_block=3 + len(inner) - 1)
+    recent = torch.full((2, 3), 70, dtype=torch.int32, device=pair.dev)
+
+    def draft():
+        tok = torch.full((2, 10), -1, dtype=torch.int32, device=pair.dev)
+        q = torch.full((2, 11, shape.v_eff), -1.0, dtype=torch.float32, device=pair.dev)
+        side.ctx.vvs_draft(pair.ctx, 10, parent, None, 3, recent, 0, None, tok, q)
+        return tok.cpu().numpy(), q.cpu().numpy()
+
+    want = draft()
+    side.ctx.vvs_debug_wait_limit(1)
+    tok, q = draft()
+    assert np.isnan(q[:, inner]).all()
+    rank = [list(parent[:j]).count(p) for j, p in enumerate(parent)]
+    assert tok.tolist() == [[64 + r for r in rank]] * 2                     # ids of the slice, siblings distinct
+    side.ctx.vvs_debug_wait_limit(0)
+    assert same(draft(), want)
+    side.close()
     pair.close()
