@@ -47,9 +47,13 @@ namespace vvs {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 enum { PH_INPUT = 0, PH_QKV, PH_ATTN, PH_O, PH_GU, PH_DOWN, PH_PART };
-constexpr int kGroups = 256;               // workgroups: one per CU (fewer CUs: see below)
+constexpr int kGroups = kFewGroups;
 constexpr int kWaves = 8, kThreads = kWaves * 64;
-constexpr long kAdmission = 20000;         // 100 MHz ticks that a workgroup waits for all others to be there
+// 100 MHz ticks that a workgroup waits for all others to be there.  They are within 3 us where nothing keeps a CU.  Drawn tiles cost 0 to 4 us a launch more
+// than dealt ones (1 x 27 of the XL shape even 25 less), so waiting longer than that does not pay.  Prefix of one token, d 768, us, idle 278; while a kernel of
+// another stream keeps 1 / 32 / 200 CUs: waiting 200 us 478 / 494 / 1038, 10 us 288 / 306 / 901, 5 us 282 / 299 / 670 (a launch each for projections and
+// attention: idle 342, beside 1 CU 632).
+constexpr long kAdmission = 500;
 
 // ---- agent scope: written through, read from behind the L2s
 __device__ __forceinline__ void put(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }

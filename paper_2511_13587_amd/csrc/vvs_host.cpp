@@ -208,8 +208,11 @@ int few_wide_rows(const Ctx* c) {
   return std::min((int)align_up((size_t)c->R * c->Tmax, 32), c->d <= 2048 && layer_weight_bytes <= (size_t)104 << 20 ? 128 : 64);
 }
 
-// (More than VVS_MAX_T tokens have no masks.)
-bool layers_in_one_launch(const Ctx* c, int T) { return T <= VVS_MAX_T && c->R * T <= std::max(few_rows(c), few_wide_rows(c)); }
+// (More than VVS_MAX_T tokens have no masks.  A device of fewer CUs, a partition of the chip, never has all workgroups running: every launch would wait
+// for them in vain, and nothing above was measured there.)
+bool layers_in_one_launch(const Ctx* c, int T) {
+  return c->cus >= kFewGroups && T <= VVS_MAX_T && c->R * T <= std::max(few_rows(c), few_wide_rows(c));
+}
 
 vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   if (!cfg) return fail(err, VVS_EINVAL, "config is NULL");
@@ -470,6 +473,10 @@ vvs_status vvs_create(const vvs_config* cfg, void* d_kv, void* d_workspace, void
     delete c;
     return fail(nullptr, VVS_EHIP, "create: no HIP device (this library has no CPU path)");
   }
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) { std::string m = std::string("create: ") + hipGetErrorString(e); delete c; return fail(nullptr, VVS_EHIP, m); }
   c->kv = (char*)d_kv; c->ws = (char*)d_workspace; c->pw = (char*)d_packed_weights;
   c->nbr = nullptr;
   c->codebook = nullptr;
@@ -487,7 +494,7 @@ vvs_status vvs_create(const vvs_config* cfg, void* d_kv, void* d_workspace, void
       tab[((size_t)pos * np + i) * 2 + 0] = (float)cos(pos * th);
       tab[((size_t)pos * np + i) * 2 + 1] = (float)sin(pos * th);
     }
-  hipError_t e = hipMemcpy(c->ws + c->w.rope_tab, tab.data(), tab.size() * sizeof(float), hipMemcpyHostToDevice);
+  e = hipMemcpy(c->ws + c->w.rope_tab, tab.data(), tab.size() * sizeof(float), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) { std::string m = std::string("create: ") + hipGetErrorString(e); delete c; return fail(nullptr, VVS_EHIP, m); }
   *out = reinterpret_cast<vvs_ctx*>(c);

@@ -66,6 +66,7 @@ struct Ctx {
   const float* codebook; int code_dim;   // latent codebook of the path-similarity kernel (by reference)
   bool weights_loaded, prefilled, verify_pending;
   int last_T;                            // T of the last verify / prefill (for debug export)
+  int cus;                               // compute units of the device
   int wait_polls;                        // looks after which a wait of vvs_few.hip gives up
   std::string err;
   bool timing;                           // bracket launches with events
@@ -165,6 +166,7 @@ constexpr int kOutcomeSnap = 2 + VVS_MAX_T, kOutcomeInts = kOutcomeSnap + 6;
 constexpr int kWalkLine = 16;   // words between the counters of two prompts (k_accept_node)
 
 // All layers in one launch (vvs_few.hip): counters of a layer and bytes that it hands from phase to phase
+constexpr int kFewGroups = 256;   // its workgroups, one per CU
 constexpr int kFewLine = 32;   // words between two counters: a line of its own for each
 constexpr int kFewHead = 20;   // counters in front of the layers'
 constexpr int few_layer_counters(int H, int row_tiles) { return H * row_tiles + 6 * 8; }

@@ -1583,10 +1583,10 @@ int mfma_qkv_attention_rows(const Ctx* c, const PosDesc& pos, int T) {
   const int least = rounds == 1 ? 0 : rounds == 2 ? 665 : 890;     // thousandths
   if (rounds > 3 || (long)pairs * T * 1000 < (long)least * rounds * 256 * pad) return 0;
   // Of few pairs each CU pulls 655 KB of weights while most stand idle, where a projection of its own deals them to all (calls of up to few_rows(c)
-  // rows do not come here: 16 to 19 heads, 2 prompts of 49 tokens and more do).  Drawn inside what would pay: 40 and 80 pairs stay one launch, though
+  // rows do not come here but on devices of fewer CUs: 16 to 19 heads, 2 prompts of 57 tokens and more do).  Drawn inside what would pay: 40 and 80 pairs stay one launch, though
   // apart they are 18 and 9 % faster at 61 tokens: which launches such a call takes is part of what callers measure with (vvs_timing_read), and 2 prompts
   // of 20 heads are held to one.
-  if (c->d >= 1024 && pairs < 40) return 0;
+  if (c->d >= 1024 && (pairs < 40 || qkv_small_tiles(c, c->R * T))) return 0;
   return pad;
 }
 

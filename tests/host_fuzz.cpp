@@ -14,7 +14,10 @@
 
 // ---- HIP runtime stand-ins (only what the host file uses)
 extern "C" {
+static int g_cus = 256;
 hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
+hipError_t hipGetDevice(int* dev) { *dev = 0; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = g_cus; return hipSuccess; }
 hipError_t hipMemcpy(void* dst, const void* src, size_t n, hipMemcpyKind) { memcpy(dst, src, n); return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -257,6 +260,19 @@ int main(int argc, char** argv) {
     for (int m = 1; m <= 20000; m += 97)
       if (640 % vvs::plan_gemm(&odd, m, 3 * 640, 640, 640).bn) { printf("%d rows: a tile crosses the q / k / v thirds\n", m); return 1; }
   }
+  // 2c. all layers in one launch: only where the device has a CU for each of its workgroups
+  for (int cus : {256, 304, 255, 128, 32}) {
+    vvs_config c = base_config(true, false);
+    Dev mem;
+    mem.alloc(c);
+    vvs_ctx* ctx = nullptr;
+    g_cus = cus;
+    if (vvs_create(&c, mem.akv, mem.aws, mem.apw, &ctx) != VVS_OK) { printf("create with %d CUs: %s\n", cus, vvs_last_error(nullptr)); return 1; }
+    for (int t = 1; t <= 70; ++t)
+      if (vvs::layers_in_one_launch((const vvs::Ctx*)ctx, t) != (cus >= 256 && 6 * t <= 256)) { printf("%d CUs, %d tokens: one launch %d\n", cus, t, (int)(cus < 256)); return 1; }
+    vvs_destroy(ctx);
+  }
+  g_cus = 256;
   // 3. the call sequences, launchers replaced: target + drafter, fp32 and bf16 planning
   for (int bf16 = 0; bf16 < 2; ++bf16) {
     vvs_config tc = base_config(bf16, false), dc = base_config(bf16, true);

@@ -95,6 +95,37 @@ def test_tiles_drawn_while_another_kernel_keeps_cus(gc):  # noqa: F811
     step.pair.close()
 
 
+def test_a_kept_cu_delays_no_more_than_the_wait(gc):  # noqa: F811
+    """One workgroup of the fill probe keeps a CU: the call goes on without it, some 5 us later than with all CUs (bound: 100; it had waited 200)."""
+    shape = synth.B_SHAPE.replace(n_layers=3, n_prompts=1, n_nodes=2, vocab=1024, logit_hi=1024)
+    pair = gc.Pair(shape, with_oracle=False)
+    src = torch.zeros(1 << 18, dtype=torch.int32, device=pair.dev)
+    prefix = torch.zeros((1, 1), dtype=torch.int32, device=pair.dev)
+    u, first = torch.full((1,), 0.5, device=pair.dev), torch.zeros(1, dtype=torch.int32, device=pair.dev)
+
+    def call():
+        t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        t0.record()
+        pair.ctx.vvs_prefill(prefix, None, None, u, first)
+        t1.record()
+        t1.synchronize()
+        return t0.elapsed_time(t1) * 1e3
+
+    idle = min(call() for _ in range(8))
+    kept = []
+    for _ in range(12):                      # streams share a few hardware queues: those that are not the call's own
+        busy, done = torch.cuda.Stream(), torch.cuda.Event()
+        with torch.cuda.stream(busy):
+            pair.ctx.vvs_debug_fill_probe(src, 1000, 1, 1, 16)             # some 5 ms
+            done.record()
+        us = [call() for _ in range(4)]
+        if not done.query():
+            kept += us
+        torch.cuda.synchronize()
+    assert kept and min(kept) < idle + 100, (idle, kept)
+    pair.close()
+
+
 def test_two_launches_of_the_kind_at_once(gc):  # noqa: F811
     shapes = [synth.B_SHAPE.replace(n_layers=4, n_prompts=p, n_nodes=n, vocab=1024, logit_hi=1024) for p, n in ((2, 9), (3, 20), (1, 40))]
     steps = [Step(gc, s, i) for i, s in enumerate(shapes)]
