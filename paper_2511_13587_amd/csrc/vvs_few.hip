@@ -90,7 +90,7 @@ struct FewArgs {
   size_t kv_layer, kv_row, kv_head;
   const float* rope;
   uint32_t* sync;                          // kLine apart: how tiles are dealt (1: tile t to workgroup t % 256, 2: drawn), next tile to draw, eighths of the workgroups that
-                                           // are done, [8] workgroups that are there, [8] done, those that gave up a wait; then the layers' counters, then 8 of the input map
+                                           // are done (beside it: workgroups that gave up a wait), [8] workgroups that are there, [8] done; then the layers' counters, then 8 of the input map
   uint32_t* gave_up;                       // not zero: a wait of this launch (drafter: or of an earlier level's) was given up
   int L, M, MT, T, d, H, F, R, NS, S_cap, rope_pos;
   int polls;                               // looks at a counter before a wait gives up
@@ -149,7 +149,7 @@ __device__ __forceinline__ bool few_wait(const uint32_t* counter, int n, uint32_
     int poll = 0;
     const int polls = few_args().polls;
     const uint32_t* first = counter + (size_t)(blockIdx.x % n) * kLine;
-    for (; poll < polls && get32(first) == 0; ++poll) __builtin_amdgcn_s_sleep(36);
+    for (; get32(first) == 0 && poll < polls; ++poll) __builtin_amdgcn_s_sleep(36);
     for (;; ++poll) {
       const uint32_t v = lane < n ? get32(counter + (size_t)lane * kLine) : want;
       if (__builtin_amdgcn_ballot_w64(v != want) == 0) break;
@@ -541,7 +541,7 @@ __device__ __forceinline__ void few_leave(FewShared* sh) {
   barrier();
   if (threadIdx.x == 0) {
     auto last = [](uint32_t* counter, uint32_t n) { return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1; };
-    uint32_t* stopped = e.sync + 19 * kLine;
+    uint32_t* stopped = e.sync + 2 * kLine + 1;
     if (sh->stop) {
       __hip_atomic_fetch_add(stopped, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // ... before this workgroup counts as done

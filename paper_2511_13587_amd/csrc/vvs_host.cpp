@@ -303,11 +303,11 @@ vvs_status plan_sizes(const vvs_config* cfg, Ctx* c, std::string* err) {
   w.tokens = take(sizeof(int32_t) * c->B * VVS_MAX_T);
   w.rope_tab = take(sizeof(float) * 2 * c->rope_pos * (dh / 4));
   w.walk_sync = take(sizeof(uint32_t) * kWalkLine * c->B);      // zeroed with the state
+  w.few_gave_up = w.walk_sync + sizeof(uint32_t);               // (a line has room for it behind its counter)
   c->gemm_out_elems = go;
   const int wide = few_wide_rows(c), few = std::max(few_rows(c), wide);
   go = std::max(go, (size_t)kFewWideShares * wide * d);
   w.few_sync = take(few ? sizeof(uint32_t) * kFewLine * (kFewHead + (size_t)few_layer_counters(c->H, few / 32) * c->L + 8) : 0);   // zeroed with the state
-  w.few_gave_up = take(sizeof(uint32_t));
   w.x = take(sizeof(float) * (size_t)c->Mmax * d);
   w.h = take(c->esz * (size_t)c->Mmax * d);
   // (a call whose layers are one launch has no partial sums: what its phases hand on lies in their place)

@@ -168,7 +168,7 @@ constexpr int kWalkLine = 16;   // words between the counters of two prompts (k_
 // All layers in one launch (vvs_few.hip): counters of a layer and bytes that it hands from phase to phase
 constexpr int kFewGroups = 256;   // its workgroups, one per CU
 constexpr int kFewLine = 32;   // words between two counters: a line of its own for each
-constexpr int kFewHead = 20;   // counters in front of the layers'
+constexpr int kFewHead = 19;   // counters in front of the layers'
 constexpr int few_layer_counters(int H, int row_tiles) { return H * row_tiles + 6 * 8; }
 constexpr int kFewPolls = 1 << 21;   // looks at a counter, about 1 us each, before a wait gives up
 constexpr int kGaveUp = -2;    // in place of a node's token: the forward in front is not whole
