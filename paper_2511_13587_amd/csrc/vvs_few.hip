@@ -96,6 +96,10 @@ struct FewArgs {
   int polls;                               // looks at a counter before a wait gives up
   int rows_per_unit;                       // rows that share an attention unit: 1, 2 or 4
   float* part;                             // wide layers: partial sums of O and of down [kWideShares][M][d]
+  // SwiGLU by expf and a division, as k_swiglu has it: where gate/up as a launch of its own is split, whose sums that kernel takes.  Else by the
+  // instructions for 2^x and 1 / x, as in the epilogue of whole sums (below a gate of -87.3 the latter's result is flushed to zero); d_ff 11008: 5 to 10 us
+  // of 3000 less, 32 layers
+  bool exact_gate;
   float eps, c_exp;
   PosDesc pos;
   TreeDesc tree;
@@ -357,7 +361,8 @@ __device__ __forceinline__ bool few_tile(const FewArgs& a, const bf16_t* A, cons
 #pragma unroll
         for (int i = 0; i < CPT; ++i) {
           const float gate = v[i] * sc;
-          v[i] = gate * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gate)) * (up[i] * sc);
+          if (!SCALED && a.exact_gate) v[i] = gate / (1.0f + expf(-gate)) * up[i];
+          else v[i] = gate * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gate)) * (up[i] * sc);
         }
         if (m < a.M && n0 + c < a.F) put32(out + pack_index(m, n0 + c, a.F), pack2bf(v[0], v[1]));
       }
@@ -824,6 +829,7 @@ void launch_layers_few(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, 
 // sums [M][d] are in gemm_out.
 void launch_layers_wide(Ctx* c, const TreeDesc& tree, const PosDesc& pos, int T, hipStream_t s) {
   FewArgs a = few_arguments(c, tree, pos, T, false);
+  a.exact_gate = plan_gate_up(c, a.M).splits > 1;
   const int nqb = T <= 16 ? 1 : 2, units = c->H * c->R * ((T + 16 * nqb - 1) / (16 * nqb));
   a.rows_per_unit = units <= 256 ? 1 : units <= 512 ? 2 : 4;
 #define VVS_WIDE1(NQB, DH, RB)                                                                                                       \
