@@ -304,15 +304,9 @@ __global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void k_accept_node(AcceptArg
     walk_path((int)(uint32_t)r, (int)(uint32_t)(r >> 32), b, a.B, a.out);
   };
   int cap = INT_MAX;
-  if (a.n_emitted) {
-    if (ne >= a.G) {                       // image complete: nothing to accept, nothing to draw
-      finish(0, -1);
-      return;
-    }
-    cap = a.G - ne - 1;
-  }
-  if (invalid) {
-    finish(0, kGaveUp);
+  if (a.n_emitted) cap = a.G - ne - 1;
+  if (cap < 0 || invalid) {                // image complete: nothing to accept, nothing to draw
+    finish(0, cap < 0 ? -1 : kGaveUp);
     return;
   }
 
