@@ -482,11 +482,14 @@ static void launch_accept_on(Ctx* c, const TreeDesc& tree, int T, const float* d
     if ((BYTES) > 64 * 1024) allow_dynamic_lds((const void*)kernel, kAcceptLdsMax);                               \
     hipLaunchKernelGGL(kernel, grid, dim3(NT), (BYTES), s, a, tree);                                              \
   }
-  // Few ids: 4 waves, which meet at a barrier sooner (1024 ids, one prompt of 5 nodes: 12.7 -> 8.4 us with the walk).  More than four
-  // rounds of nodes: two workgroups of 512 threads to a CU cover each other's barriers, though 45 registers spill (B shape step, relaxed, one of 1024 / two of
-  // 512: 32 x 61 nodes 2070 / 2027 us, 20 x 61 1461 / 1432, 17 x 61 1350 / 1338; 7 x 53 748 / 756)
+  // Few ids: 4 waves, which meet at a barrier sooner (1024 ids, one prompt of 5 nodes: 12.7 -> 8.4 us with the walk).  Many nodes: two workgroups of 512
+  // threads to a CU cover each other's barriers, though 45 registers spill; the more a node does, the sooner.  Acceptance of 16384 ids, us, one of 1024 / two of 512:
+  //   strict   8 x 41 nodes 36.6 / 37.2, 8 x 61 40.9 / 45.7, 12 x 61 57.3 / 59.6, 16 x 61 67.2 / 70.0, 17 x 61 72.0 / 75.4, 20 x 61 80.4 / 81.6, 32 x 41 90.0 / 88.5, 32 x 61 128.1 / 120.9
+  //   relaxed  8 x 41 76.7 / 79.0, 8 x 61 99.4 / 102.1, 9 x 61 100.1 / 102.5, 10 x 61 116.8 / 109.7, 12 x 61 121.1 / 114.5, 16 x 61 132.9 / 128.8, 17 x 61 128.4 / 126.2, 20 x 61
+  //     171 / 153, 32 x 61 224 / 189 (12 x 41, below the line, 88.4 / 83.7)
+  const int many = mode == VVS_RELAXED && a.relax_k > 0 ? 576 : 1280;
   if (c->veff <= 4096) VVS_ACCEPT(true, 256, 16, pq_bytes / 2)
-  else if (c->veff <= 16 * 1024 && T * c->B > 1024) VVS_ACCEPT(true, 512, 32, pq_bytes / 2)
+  else if (c->veff <= 16 * 1024 && T * c->B > many) VVS_ACCEPT(true, 512, 32, pq_bytes / 2)
   else if (c->veff <= 16 * 1024) VVS_ACCEPT(true, 1024, 16, pq_bytes / 2)
   else if (pq_bytes <= kAcceptLdsMax) VVS_ACCEPT(true, 1024, 16, pq_bytes)
   else {                                     // wider slices than the registers hold: the loops over ids
