@@ -158,20 +158,6 @@ __device__ __forceinline__ void token_pos(const PosDesc& pos, const TreeDesc& tr
   }
 }
 
-// A kernel that uses more than 64 KiB of dynamic LDS has to be allowed to, once per device: remembers per
-// (kernel, device) that it has been done.  Host code; launches of one context come from one thread at a time.
-inline void allow_dynamic_lds(const void* kernel, size_t bytes) {
-  struct Done { const void* fn; int dev; };
-  static std::vector<Done> done;
-  int dev = 0;
-  (void)hipGetDevice(&dev);
-  for (const Done& d : done)
-    if (d.fn == kernel && d.dev == dev) return;
-  // a failure shows up as an invalid-configuration error of the launch that follows
-  (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  done.push_back(Done{kernel, dev});
-}
-
 // MFMA attention / GEMM launchers (vvs_mfma.hip)
 // What the next projection launch reads of its packed weights, for the idle CUs of this one (w == nullptr: nothing): n_tiles
 // column tiles, each `sections` runs of `blocks` 1 KiB blocks, section_blocks apart; row_tiles: the next launch's row tiles.

@@ -8,6 +8,7 @@
 #include <string.h>
 #include <algorithm>
 #include <cmath>
+#include <mutex>
 #include <vector>
 
 namespace vvs {
@@ -409,6 +410,21 @@ static void causal_tree(int T, TreeDesc* t) {
     t->depth[j] = (int8_t)j;
     t->anc[j] = (j == 63) ? ~0ull : ((1ull << (j + 1)) - 1);
   }
+}
+
+// Such a kernel has to be allowed to, once per device: remembers per (kernel, device) that it has been done.  Contexts may be used on threads of their own.
+void allow_dynamic_lds(const void* kernel, size_t bytes) {
+  struct Done { const void* fn; int dev; };
+  static std::mutex lock;
+  static std::vector<Done> done;
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  std::lock_guard<std::mutex> hold(lock);
+  for (const Done& d : done)
+    if (d.fn == kernel && d.dev == dev) return;
+  // a failure shows up as an invalid-configuration error of the launch that follows
+  (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  done.push_back(Done{kernel, dev});
 }
 
 static vvs_status hip_fail(Ctx* c, hipError_t e, const char* what) {

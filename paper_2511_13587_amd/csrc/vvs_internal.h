@@ -106,6 +106,8 @@ int few_wide_rows(const Ctx* c);   // the same for layers with separate normalis
 bool layers_in_one_launch(const Ctx* c, int T);   // a forward of T tokens per row takes that launch
 vvs_status build_tree(int n_nodes, const int32_t* h_parent, const uint8_t* h_mask, TreeDesc* out, std::string* err);
 
+void allow_dynamic_lds(const void* kernel, size_t bytes);   // in front of every launch of a kernel that uses more than 64 KiB of dynamic LDS
+
 // ---- launchers (kernels_*.hip); all asynchronous on the stream
 void launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 void launch_copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t s);

@@ -9,6 +9,7 @@
 #include <string.h>
 #include <algorithm>
 #include <random>
+#include <thread>
 #include <vector>
 #include "vvs_internal.h"
 
@@ -18,6 +19,7 @@ static int g_cus = 256;
 hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
 hipError_t hipGetDevice(int* dev) { *dev = 0; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = g_cus; return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipMemcpy(void* dst, const void* src, size_t n, hipMemcpyKind) { memcpy(dst, src, n); return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -142,7 +144,20 @@ static int print_plans() {
   return 0;
 }
 
+// `host_fuzz threads`, built with ThreadSanitizer: what contexts on different threads share
+static int run_threads() {
+  std::vector<std::thread> all;
+  for (int t = 0; t < 4; ++t)
+    all.emplace_back([t] {
+      for (int i = 0; i < 2000; ++i) vvs::allow_dynamic_lds((const void*)(uintptr_t)(1 + (i * (t + 1)) % 97), 1 << 17);
+    });
+  for (auto& t : all) t.join();
+  printf("threads ok\n");
+  return 0;
+}
+
 int main(int argc, char** argv) {
+  if (argc > 1 && !strcmp(argv[1], "threads")) return run_threads();
   if (argc > 1 && !strcmp(argv[1], "plans")) return print_plans();
   // 1. topology checks and the verification-free step on random input, valid and not
   for (int it = 0; it < 4000; ++it) {

@@ -14,22 +14,30 @@ import test_gpu_shared_tiles
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.fixture(scope="module")
-def host_fuzz(tmp_path_factory):
+def build_and_run(tmp_path_factory, sanitize):
     gxx = shutil.which("g++")
     if gxx is None or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
         pytest.skip("needs g++ and the HIP headers")
     exe = str(tmp_path_factory.mktemp("host") / "host_fuzz")
     cmd = [gxx, "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
-           "-I", os.path.join(ROOT, "paper_2511_13587_amd", "csrc"), "-fsanitize=address,undefined",
-           "-fno-sanitize-recover=undefined", "-static-libasan", "-g", "-O1", "-w",
+           "-I", os.path.join(ROOT, "paper_2511_13587_amd", "csrc"), *sanitize, "-g", "-O1", "-w", "-pthread",
            os.path.join(ROOT, "paper_2511_13587_amd", "csrc", "vvs_host.cpp"), os.path.join(ROOT, "tests", "host_fuzz.cpp"), "-o", exe]
     r = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
-    if r.returncode != 0 and "asan" in r.stderr.lower() and "cannot find" in r.stderr.lower():
+    if r.returncode != 0 and "san" in r.stderr.lower() and "cannot find" in r.stderr.lower():
         pytest.skip("the sanitizer runtime is not installed")
     assert r.returncode == 0, r.stderr[-3000:]
     env = dict(os.environ, ASAN_OPTIONS="verify_asan_link_order=0:detect_leaks=1", UBSAN_OPTIONS="print_stacktrace=1")
     return lambda *args, **kw: subprocess.run([exe, *args], capture_output=True, text=True, timeout=300, env=env, **kw)
+
+
+@pytest.fixture(scope="module")
+def host_fuzz(tmp_path_factory):
+    return build_and_run(tmp_path_factory, ["-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-static-libasan"])
+
+
+def test_contexts_on_threads_of_their_own_share_nothing_unguarded(tmp_path_factory):
+    r = build_and_run(tmp_path_factory, ["-fsanitize=thread"])("threads")
+    assert r.returncode == 0 and "threads ok" in r.stdout, (r.stdout[-2000:], r.stderr[-3000:])
 
 
 def test_host_side_is_clean_under_sanitizers(host_fuzz):
