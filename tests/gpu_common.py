@@ -26,6 +26,7 @@ Decisions (accept length, path, next token) must be identical whenever every dra
 consulted was farther than the guard from its threshold; the final inverse-CDF draw is compared in
 interval form; inside the guard the outcome must still be one the checker reaches with the consulted
 uniforms moved by at most the guard."""
+import contextlib
 import dataclasses
 import math
 
@@ -212,6 +213,20 @@ class Pair:
 
     def close(self):
         self.ctx.close()
+
+
+@contextlib.contextmanager
+def layer_launches(pair, one_launch):
+    """Asserts that the forward made inside runs (one_launch) all its layers in one launch, which leaves two of the projection class with the output
+    head's, or (not one_launch) three launches of that class and more per layer.  None: asserts nothing."""
+    if one_launch is None:
+        yield
+        return
+    pair.ctx.vvs_timing_enable(True)
+    yield
+    n, _ = pair.ctx.vvs_timing_read(vb.VVS_K_GEMM)
+    pair.ctx.vvs_timing_enable(False)
+    assert n == 2 if one_launch else n > 3 * pair.shape.n_layers, f"{n} launches of the projection class"
 
 
 def check_logits(pair, label="", sharp=None):

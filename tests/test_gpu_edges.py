@@ -355,18 +355,18 @@ def test_fill_probe_reads_the_region_it_is_given(gc, mode):
 @pytest.mark.parametrize("case", ["xl_27_tokens", "xl_61_tokens_few_prompts", "xl_61_tokens_many_prompts", "head_size_128"])
 def test_which_launches_a_layer_takes(gc, case):
     """The launch plan is part of what the library promises to measure with (vvs_timing_read): at head size 64 a verify call of two
-    prompts of 20 heads runs the q/k/v projection and the attention of a layer as one launch with 27 and with 61 tokens per row; 520
-    (head, prompt) pairs with 61 tokens, which would leave a third round of CUs nearly empty, and head size 128 take separate launches.
-    (The lines themselves: test_gpu_few_pairs.py.)"""
+    prompts of 20 heads runs all layers as one launch with 27 tokens per row, and the q/k/v projection and the attention of a layer as one with
+    61; 520 (head, prompt) pairs with 61 tokens, which would leave a third round of CUs nearly empty, and head size 128 take separate launches.
+    (The lines themselves: test_gpu_few_rows.py, test_gpu_few_pairs.py.)"""
     vb = gc.vb
     if case == "xl_27_tokens":
-        shape, fused_attention = synth.XL_TREE.replace(n_layers=2, n_prompts=2), True
+        shape, fused_attention, n_projection = synth.XL_TREE.replace(n_layers=2, n_prompts=2), True, 1
     elif case == "xl_61_tokens_few_prompts":
-        shape, fused_attention = synth.XL_STRESS.replace(n_layers=2, n_prompts=2), True
+        shape, fused_attention, n_projection = synth.XL_STRESS.replace(n_layers=2, n_prompts=2), True, 2 * 4
     elif case == "xl_61_tokens_many_prompts":
-        shape, fused_attention = synth.XL_STRESS.replace(n_layers=1, n_prompts=26), False     # 520 pairs
+        shape, fused_attention, n_projection = synth.XL_STRESS.replace(n_layers=1, n_prompts=26), False, 4     # 520 pairs
     else:
-        shape, fused_attention = synth.SEVEN_B.replace(n_layers=2, d_model=1024, n_heads=8, d_ff=2752), False
+        shape, fused_attention, n_projection = synth.SEVEN_B.replace(n_layers=2, d_model=1024, n_heads=8, d_ff=2752), False, 2 * 4
     parent = synth.tree_parents(shape.tree_widths, shape.n_nodes)
     pair = gc.Pair(shape, with_oracle=False)
     pair.prefill(n_forced=10, run_oracle=False)
@@ -375,5 +375,7 @@ def test_which_launches_a_layer_takes(gc, case):
     pair.ctx.vvs_timing_enable(True)
     pair.verify(parent, toks, q, u, run_oracle=False)
     n_attention, _ = pair.ctx.vvs_timing_read(vb.VVS_K_ATTENTION)
+    n_gemm, _ = pair.ctx.vvs_timing_read(vb.VVS_K_GEMM)
     pair.ctx.vvs_timing_enable(False)
     assert n_attention == (0 if fused_attention else shape.n_layers)
+    assert n_gemm == n_projection + 1                                           # and the output head

@@ -128,13 +128,14 @@ def scaled_guard(shape, e_mix):
 
 
 def run_bf16_case(gc, shape, n_forced, calls=2, mode=0, nbr=None, correlated=True, sharp=None, std=0.02, sample=None, kv_layers=None,
-                  gain_jitter=0.0, norm_mode=0, expect_fused=None):
+                  gain_jitter=0.0, norm_mode=0, expect_fused=None, one_launch=None):
     """Prefill to a chosen cache length, then `calls` verify + commit calls in lockstep with the checker.
     Per call: raw / mixed logits and probabilities (max-abs and rms bounds of the parity contract), the
     cache of the draft block (layer 0 to 2 bf16 ulps, other layers to the checker's own noise), the
     acceptance stage end to end on the kernel's own probabilities for every prompt, and the decisions
     against the checker's with a guard scaled from the measured logit error.
-    sharp: optional extra bound on the raw-logit error as a multiple of the checker's noise floor."""
+    sharp: optional extra bound on the raw-logit error as a multiple of the checker's noise floor.
+    one_launch: whether the verify calls run all layers in one launch."""
     pair = gc.Pair(shape, shadow=True, std=std, sample=sample, gain_jitter=gain_jitter, norm_mode=norm_mode)
     if expect_fused is not None:
         assert pair.fused == expect_fused
@@ -159,7 +160,8 @@ def run_bf16_case(gc, shape, n_forced, calls=2, mode=0, nbr=None, correlated=Tru
                                       base_logits=pair.oracle.mixed_logits.astype(np.float32))
             q[pair.sample], toks[pair.sample] = qs, ts
         u = synth.make_uniforms(shape, shape.n_nodes, it)
-        out, oout = pair.verify(parent, toks, q, u, mode=mode, mask=mask)
+        with gc.layer_launches(pair, one_launch):
+            out, oout = pair.verify(parent, toks, q, u, mode=mode, mask=mask)
         st = gc.check_logits(pair, f"{shape.name} call {it}", sharp=sharp)
         # cache contents including the draft block (before commit): slots 0 .. S + T - 1 do not exist on the
         # checker's side before its commit, so compare the cached part: slots 0 .. S - 1

@@ -53,9 +53,9 @@ def test_epilogues_of_large_weights_bf16(gc, d, heads, d_ff, tokens):
 
 
 # d_model, heads, d_ff, tokens; tile and shares of gate/up where it keeps operands of its own (checked on the CPU as above): one round of CUs with whole sums,
-# with sums in two shares, one row into the next row-block, and three rounds
-OWN_GATE_UP = [(2048, 16, 4096, 14, (32, 64, 1)), (2048, 32, 4096, 33, (64, 64, 1)), (4096, 32, 4096, 15, (32, 64, 2)), (4096, 32, 4096, 17, (64, 64, 2)),
-               (2048, 16, 16448, 9, (32, 64, 1))]
+# with sums in two shares, one row into the next row-block, and three rounds.  Up to 32 rows beyond d 4096, where not all layers are one launch
+OWN_GATE_UP = [(4160, 65, 4160, 14, (32, 64, 1)), (2048, 32, 4096, 33, (64, 64, 1)), (4160, 65, 4096, 15, (32, 64, 2)), (4096, 32, 4096, 17, (64, 64, 2)),
+               (4160, 65, 16448, 9, (32, 64, 1))]
 
 
 @pytest.mark.parametrize("d,heads,d_ff,tokens", [case[:4] for case in OWN_GATE_UP])
@@ -70,11 +70,12 @@ def test_partial_sums_of_projections_alike_bf16(gc, d, heads, d_ff, tokens, norm
     check_prefill(gc, d, heads, d_ff, tokens, norm_mode)
 
 
-def check_prefill(gc, d, heads, d_ff, tokens, norm_mode=0):
+def check_prefill(gc, d, heads, d_ff, tokens, norm_mode=0, one_launch=False):
     shape = synth.SEVEN_B.replace(d_model=d, n_heads=heads, d_ff=d_ff, n_layers=1, n_prompts=1, n_nodes=2, tree_widths=None, vocab=1024, logit_lo=0,
                                   logit_hi=1024, grid_h=32, grid_w=32, prefix_len=1, prefix_kind=synth.PREFIX_CLASS)
     pair = gc.Pair(shape, gain_jitter=0.1, shadow=True, sample=[0], norm_mode=norm_mode)
-    pair.prefill(n_forced=tokens - 1)
+    with gc.layer_launches(pair, one_launch):
+        pair.prefill(n_forced=tokens - 1)
     raw, _, _ = pair.gpu_logits()
     diff = raw[pair.rows(), 0] - pair.oracle.prefill_logits
     err = float(np.abs(diff).max())

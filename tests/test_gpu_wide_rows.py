@@ -5,6 +5,7 @@ import torch
 
 from paper_2511_13587_amd import synth
 from test_gpu_parity import gc, run_bf16_case, show  # noqa: F401
+from test_gpu_shared_tiles import check_prefill
 
 pytestmark = pytest.mark.gpu
 
@@ -19,7 +20,15 @@ def test_wide_layers_in_one_launch(gc, d, heads, d_ff, prompts, tokens, n_forced
     shape = synth.SEVEN_B.replace(d_model=d, n_heads=heads, d_ff=d_ff, n_layers=2, vocab=1024, logit_lo=0, logit_hi=1024, prefix_len=8, n_prompts=prompts,
                                   n_nodes=tokens - 1, tree_widths=None)
     sample = {"sample": [0, prompts - 1]} if prompts > 4 else {}
-    show(f"d {d} heads {heads} d_ff {d_ff} {prompts} x {tokens}", run_bf16_case(gc, shape, n_forced=n_forced, calls=2, **sample))
+    together = 2 * prompts * tokens <= (128 if d <= 2048 else 64)
+    show(f"d {d} heads {heads} d_ff {d_ff} {prompts} x {tokens}", run_bf16_case(gc, shape, n_forced=n_forced, calls=2, one_launch=together, **sample))
+
+
+# Prefills (positions from the prefill's base, one class token in front): 2, 28, 30 and 32 rows, one row-block to a tile, both head sizes; d_ff that gate/up
+# as a launch of its own would split at d 4096 (SwiGLU by a division), and one of 16448 columns; a chunk of 512 tokens and one of 2 behind it
+@pytest.mark.parametrize("d,heads,d_ff,tokens", [(1536, 12, 4096, 1), (2048, 16, 4096, 14), (4096, 32, 4096, 15), (1536, 24, 4160, 16), (2048, 16, 16448, 9), (1536, 12, 1536, 514)])
+def test_prefill_of_wide_layers_in_one_launch(gc, d, heads, d_ff, tokens):  # noqa: F811
+    check_prefill(gc, d, heads, d_ff, tokens, norm_mode=1 if d_ff == 1536 else 0, one_launch=tokens < 512 or None)
 
 
 def test_gate_below_the_normal_range(gc):  # noqa: F811

@@ -49,7 +49,8 @@ def test_gpu_tests_reach_the_tiles_they_name(host_fuzz):
     want = [(f"partial {n} {k} {m}", (*tile, 1)) for m, n, k, tile in test_gpu_shared_tiles.PRODUCTS]
     for d, _, d_ff, tokens, qkv, gate_up in test_gpu_shared_tiles.EPILOGUES:
         want += [(f"qkv {d} {d_ff} {2 * tokens}", (*qkv, 1, 1)), (f"gate_up {d} {d_ff} {2 * tokens}", (*gate_up, 1, int(gate_up[1] >= 128)))]
-    want += [(f"qkv {d} {d_ff} {2 * tokens}", (32, 32, 1, 0)) for d, _, d_ff, tokens, _ in test_gpu_few_pairs.SMALL_TILES]
+    want += [(f"qkv {d} {d_ff} {2 * prompts * tokens}", (32, 32, 1, 0)) for d, _, d_ff, prompts, tokens, _ in test_gpu_few_pairs.SMALL_TILES]
+    want += [("qkv 512 1408 140", (32, 32, 1, 0))]
     want += [(f"gate_up {d} {d_ff} {2 * tokens}", (*plan, 0)) for d, _, d_ff, tokens, plan in test_gpu_shared_tiles.OWN_GATE_UP]
     # ... and where gate/up shares its operands: more than one round of 32 x 64 tiles, four rounds, and more than one of 64 x 64
     want += [("gate_up 2048 8256 32", (64, 128, 1, 1)), ("gate_up 2048 32768 32", (64, 128, 1, 1)), ("gate_up 4096 8256 64", (64, 128, 1, 1))]
