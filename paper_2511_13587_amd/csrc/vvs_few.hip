@@ -44,8 +44,6 @@
 
 namespace vvs {
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
 enum { PH_INPUT = 0, PH_QKV, PH_ATTN, PH_O, PH_GU, PH_DOWN, PH_PART };
 constexpr int kGroups = kFewGroups;
 constexpr int kWaves = 8, kThreads = kWaves * 64;
@@ -435,14 +433,6 @@ __device__ __forceinline__ bool few_attention(const FewArgs& a, const FewBuf& b,
   const int S = few_cached(a, r), n_keys = S + a.tree.first + T, nsteps = min((n_keys + 31) >> 5, a.S_cap >> 5);
   const bf16_t* kb = a.kc + a.kv_layer * l + r * a.kv_row + hd * a.kv_head;
   const bf16_t* vb = a.vc + a.kv_layer * l + r * a.kv_row + hd * a.kv_head;
-#define VVS_ATTN_LOAD(STEP, KF, VF)                                                                                   \
-  {                                                                                                                   \
-    _Pragma("unroll") for (int t = 0; t < 2; ++t)                                                                     \
-        _Pragma("unroll") for (int kd = 0; kd < KD; ++kd)                                                             \
-            KF[t][kd] = as_bf16x8(*(const uint4*)(kb + ((((size_t)(STEP) * 2 + t) * KD + kd) * 64 + lane) * 8));      \
-    _Pragma("unroll") for (int dt = 0; dt < DT; ++dt)                                                                 \
-        VF[dt] = as_bf16x8(*(const uint4*)(vb + (((size_t)(STEP) * DT + dt) * 64 + lane) * 8));                       \
-  }
   bf16x8 kf[PD][2][KD], vf[PD][DT];
   bool early[PD];
 #pragma unroll
@@ -484,7 +474,6 @@ __device__ __forceinline__ bool few_attention(const FewArgs& a, const FewBuf& b,
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-#undef VVS_ATTN_LOAD
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) {
     const int ui = wave * NQ + qb * 16 + ql;

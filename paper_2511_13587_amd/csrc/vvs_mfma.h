@@ -41,6 +41,16 @@ __device__ __forceinline__ void tile_of(int id, int MT, int NT, int* tile_m, int
   *tile_n = grp * 8 + rem % cols;
 }
 
+// K and V of 32-key step STEP of the head whose caches start at kb and vb, into the operand registers of lane `lane`
+#define VVS_ATTN_LOAD(STEP, KF, VF)                                                                                   \
+  {                                                                                                                   \
+    _Pragma("unroll") for (int t = 0; t < 2; ++t)                                                                     \
+        _Pragma("unroll") for (int kd = 0; kd < KD; ++kd)                                                             \
+            KF[t][kd] = as_bf16x8(*(const uint4*)(kb + ((((size_t)(STEP) * 2 + t) * KD + kd) * 64 + lane) * 8));      \
+    _Pragma("unroll") for (int dt = 0; dt < DT; ++dt)                                                                 \
+        VF[dt] = as_bf16x8(*(const uint4*)(vb + (((size_t)(STEP) * DT + dt) * 64 + lane) * 8));                       \
+  }
+
 // One 32-key step of the attention kernels for NQB blocks of 16 queries: scores S^T = K Q^T (lane = query l % 16, key
 // group g = l / 16, 8 consecutive keys per lane), online softmax, O^T += V^T P^T.  The tree mask only touches a step that
 // reaches past the cached length S (tail).

@@ -1097,14 +1097,6 @@ __global__ __launch_bounds__(NW * QG * 64, (DH * NQB >= 256 ? 1 : 2)) void k_att
   // K and V of one 32-key step, straight into MFMA operand registers: the cache is kept in operand
   // order (k_index / v_index), so every load instruction of a wave reads 1 KiB of contiguous memory.
   // S^T tile t, row i holds key 8*(i/4) + 4*t + i%4 of the step: a lane's 8 score values are 8 consecutive keys.
-#define VVS_ATTN_LOAD(STEP, KF, VF)                                                                                   \
-  {                                                                                                                   \
-    _Pragma("unroll") for (int t = 0; t < 2; ++t)                                                                     \
-        _Pragma("unroll") for (int kd = 0; kd < KD; ++kd)                                                             \
-            KF[t][kd] = as_bf16x8(*(const uint4*)(kb + ((((size_t)(STEP) * 2 + t) * KD + kd) * 64 + lane) * 8));      \
-    _Pragma("unroll") for (int dt = 0; dt < DT; ++dt)                                                                 \
-        VF[dt] = as_bf16x8(*(const uint4*)(vb + (((size_t)(STEP) * DT + dt) * 64 + lane) * 8));                       \
-  }
   // Ring of PD operand sets: a wave's steps wave, wave + NW, ... ; the operands of a step are requested
   // PD steps ahead, right after the set's previous step has been multiplied, so that the cache streams
   // in while the wave computes.  Requests past the row's last step repeat that step (never used).
@@ -1130,7 +1122,6 @@ __global__ __launch_bounds__(NW * QG * 64, (DH * NQB >= 256 ? 1 : 2)) void k_att
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-#undef VVS_ATTN_LOAD
 
   VVS_PHASE_MARK(2);
   // merge the waves' partial results (waves 1.. publish, wave 0 combines and writes)
@@ -1260,14 +1251,6 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
   const int cap_steps = ep.S_cap >> 5;
   const bf16_t* kb = ep.kc + (size_t)r * ep.row_stride + (size_t)hd * ep.head_stride;
   const bf16_t* vb = ep.vc + (size_t)r * ep.row_stride + (size_t)hd * ep.head_stride;
-#define VVS_ATTN_LOAD(STEP, KF, VF)                                                                                   \
-  {                                                                                                                   \
-    _Pragma("unroll") for (int t = 0; t < 2; ++t)                                                                     \
-        _Pragma("unroll") for (int kd = 0; kd < KD; ++kd)                                                             \
-            KF[t][kd] = as_bf16x8(*(const uint4*)(kb + ((((size_t)(STEP) * 2 + t) * KD + kd) * 64 + lane) * 8));      \
-    _Pragma("unroll") for (int dt = 0; dt < DT; ++dt)                                                                 \
-        VF[dt] = as_bf16x8(*(const uint4*)(vb + (((size_t)(STEP) * DT + dt) * 64 + lane) * 8));                       \
-  }
   bf16x8 kf[PD][2][KD], vf[PD][DT];
   bool early[PD];
   floatx16 acc[WM][WN];
@@ -1518,7 +1501,6 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const uint4* __restrict__ Ap, 
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-#undef VVS_ATTN_LOAD
   VVS_PHASE_MARK(5);
   // merge the partial results of a group's waves: every wave publishes (running maximum, sum, accumulators), then wave aw
   // combines and writes the 16-dim blocks dt = aw, aw + NW, ... for all queries of the group.  The buffers lie where the
