@@ -394,7 +394,11 @@ def main():
     ctx.vvs_timing_enable(False)
     S_mean = float(state0[0].mean())
     cnt = algorithmic_counts(shape, S_mean)
-    if not ctx.vvs_plan_is_fused(N + 1):
+    one_launch = classes["gemm"]["launches_per_step"] == 2       # all layers, and the output head
+    norms = "normalisation in the projections" if ctx.vvs_plan_is_fused(N + 1) else "separate normalisations"
+    if one_launch:
+        layer_plan = f"all layers in one launch ({norms})"
+    elif not ctx.vvs_plan_is_fused(N + 1):
         layer_plan = "separate normalisation kernels (7 launches per layer)"
     elif classes["attention"]["launches_per_step"] == 0:
         layer_plan = "fused (4 launches per layer: projection + attention in one)"
@@ -407,10 +411,12 @@ def main():
         bytes_launch, flops_launch = cnt["w_bytes"] / n_launch, cnt["gemm_flops"] / n_launch
         kernel = "k_gemm_direct + k_gemm_shared_dma (all bf16 projection GEMMs of one verify call)"
         if classes["attention"]["launches_per_step"] == 0:
-            # the q/k/v projection and attention run in one launch (k_qkv_attn): its cache traffic and flops belong to these launches
+            # the q/k/v projection and attention, or all layers, run in one launch: its cache traffic and flops belong to these launches
             bytes_launch += (cnt["kv_read"] + cnt["kv_write"]) / n_launch
             flops_launch += cnt["attn_flops"] / n_launch
             kernel = "k_qkv_attn + k_gemm_direct + k_gemm_shared_dma (all projection launches of one verify call; attention runs inside the first)"
+        if one_launch:
+            kernel = ("k_layers_few" if ctx.vvs_plan_is_fused(N + 1) else "k_layers_wide") + " + the output head (all launches of one verify call that hold projections)"
     else:
         n_launch = classes["attention"]["launches_per_step"]
         t_launch = classes["attention"]["ms_per_step"] * 1e-3 / n_launch

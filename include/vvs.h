@@ -105,7 +105,8 @@ enum { VVS_NORM_AUTO = 0, VVS_NORM_SEPARATE = 1 };
  * supported (bf16 needs d_model % 64 == 0, d_ff % 64 == 0, V_eff % 64 == 0, head size 64 or 128;
  * any dtype needs head size % 4 == 0, max_nodes < VVS_MAX_T).  The workspace holds the activations of the widest call: a
  * verify or drafting call of max_nodes + 1 tokens per row or, in a target context, a prefill chunk - in bf16 up to 512 tokens per
- * row (about 4096 rows in all), never more than the prefix and the grid. */
+ * row (about 4096 rows in all), never more than the prefix and the grid - and, in bf16, what the layers hand on where a forward of few
+ * rows runs them all in one launch: buffers of every layer's own, up to 256 rows (121 MB for 36 layers of d 1280, d_ff 3456 with 192 rows). */
 vvs_status vvs_query_sizes(const vvs_config* cfg, size_t* kv_bytes, size_t* workspace_bytes,
                            size_t* packed_weight_bytes);
 
@@ -319,8 +320,11 @@ vvs_status vvs_set_state(vvs_ctx* ctx, const int32_t* d_state, vvs_stream s);
  * commit is bracketed by HIP events recorded on the caller's stream (host objects; no device
  * memory).  vvs_timing_read waits for the recorded events and returns the number of launches and
  * their summed duration for one class since timing was enabled.  Where a layer's q/k/v projection and its
- * attention run as one launch (bf16, head size 64; not with few rows, nor with more (head, prompt) pairs than CUs unless
- * they fill their rounds well), that launch counts as VVS_K_GEMM and the attention class stays empty. */
+ * attention run as one launch (bf16, head size 64; not with more (head, prompt) pairs than CUs unless
+ * they fill their rounds well), that launch counts as VVS_K_GEMM and the attention class stays empty.  Where all layers of a
+ * forward are one launch (bf16, few rows of up to VVS_MAX_T tokens: up to 192 to 256 rows at head size 64 where vvs_plan_is_fused, up to 64 or
+ * 128 with separate normalisations and either head size), that launch, with its attention, normalisations and SwiGLU, and a
+ * drafter's input map, is one of VVS_K_GEMM: such a verify call has two of them, the layers and the output head. */
 enum { VVS_K_GEMM = 0, VVS_K_ATTENTION = 1, VVS_K_ACCEPT = 2, VVS_K_ELEMENTWISE = 3, VVS_K_COMMIT = 4, VVS_K_CLASSES = 5 };
 vvs_status vvs_timing_enable(vvs_ctx* ctx, int32_t on);
 vvs_status vvs_timing_read(vvs_ctx* ctx, int32_t kernel_class, int32_t* n_launches, float* total_ms);
