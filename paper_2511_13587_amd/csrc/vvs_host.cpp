@@ -188,10 +188,15 @@ bool plan_fused(const Ctx* c, int M) {
 //   d 768, 200 rows (48 pairs) 286 / 260, (24) 327 / 258, 256 rows (48) 290 / 296;  d 1280, 220 rows (40) 492 / 452, 210 (60) 479 / 450, 240 (60) 495 / 515, 256 (40) 500 /
 //   520;  d 1024, 216 rows (64) 402 / 339, 256 (32) 332 / 359;  d 512, 252 rows (48) 253 / 209, 256 (16) 297 / 202, 240 (64) 241 / 203;  d 1536, 200 rows (48) 500 / 491;
 //   XL, 216 rows (80 pairs) 2079 / 2071, 256 (320) 2366 / 2598
+// Gate/up tiles of 32 rows x 48 hidden units fill the CUs in more and more rounds as d_ff grows, each pulling its operands anew, so the line falls with
+// its square.  12 layers, one launch / a launch each by time (more than 1: the one launch is slower), at the last row-block taken and behind:  d 768, d_ff
+// 7680 160 rows 0.93, 192 1.01 to 1.03; 8192 120 rows 1.00, 144 1.01; 9216 128 rows 1.06;  d 640, 10240 64 rows 0.97, 100 1.16;  d 704, 9856 64 rows 0.96, 120 1.12;
+// d 512, 12288 64 rows 1.03, 100 1.20;  inside: d 896, 7168 192 rows 0.93, d 1024, 6144 192 rows 0.99 to 1.01.
 // Head size 64: its q/k/v tiles are a head's.
 int few_rows(const Ctx* c) {
   if (!plan_fused(c, c->R) || c->dh != 64) return 0;
-  const int most = c->H * c->B > 64 ? 192 : c->d <= 512 ? 256 : 224;
+  const int blocks = std::max(1, (int)(310000000 / ((long)c->F * c->F)));
+  const int most = std::min((long)32 * blocks, (long)(c->H * c->B > 64 ? 192 : c->d <= 512 ? 256 : 224));
   const int tokens = c->cfg.draft_input ? c->Tmax : std::max(c->Tmax, std::min(c->chunk, (int)VVS_MAX_T));   // the longest call of either kind
   return std::min((int)align_up((size_t)c->R * tokens, 32), most);
 }
@@ -202,11 +207,27 @@ int few_rows(const Ctx* c) {
 //   64 rows:   d 1536 58.4 / 40.9, 2048 65.1 / 51.4, 2560 (6912) 81.5 / 78.6, 3072 94.5 / 89.4, 4096 130 / 123;  40 rows, d 2560 77.1 / 77.0, 3072 88.7 / 89.7, 4096 125 / 119
 //   96 rows:   d 1536 61.6 / 52.6, 2048 67.7 / 63.6, (8192, 134 MB) 77.8 / 79.0, 2560 89.1 / 104;  128 rows, d 1536 66.7 / 54.5, (8192, 94 MB) 74.1 / 71.1, 2048
 //     75.1 / 69.2, (8192) 84.6 / 86.4, 3072 117 / 140
+// Few and many hidden units, us per call of 2 to 7 layers, a launch each / one launch:
+//   33 to 64 rows, d above 2048, gate/up of two row-blocks to a tile in a second round (d_ff 12800 and more):  d 2176 (13056) 217 / 238, 2560 (12800) 231 / 253, 3072 (13824)
+//     268 / 300, 3840 (12800) 306 / 338, 2304 (24576) 284 / 297, 2816 (20480) 316 / 312; one round: 4096 (12288) 318 / 312
+//   the same, few hidden units, where normalisation and attention are most of a layer:  3584 (1024) 0.97 to 0.99, 3840 (1536) 0.97 to 0.99 of the one launch's time, 4096
+//     (1024) 317 / 326, (1536) 0.94 to 0.95, (2048) 332 / 336; inside: 3840 (1920) 1.22, (2048) 314 / 331, 3328 (832) 1.06, 4096 (3072) 261 / 251
+//   up to 32 rows, d 3584 (12544) 254 / 264, 3840 (12800) 271 / 280, (13440) 265 / 274; 3520 (13440) 279 / 263
+//   33 to 64 rows, d up to 2048:  1792 (23040) 251 / 249, (25088) 243 / 258;  65 to 128: 960 (9600) 1.03 of its time, (11520) 0.95 to 0.99, (13440) 442 / 510, 1024 (11264) 0.97, 1152
+//     (13440) 356 / 398, 768 (6144) 570 / 543, (7680) 589 / 634, 896 (8960) 541 / 570, 1024 (8192) 1.14, (10240) 484 / 494, 1280 (10240) 1.02 (O and down share
+//     their operands through LDS where d is a multiple of 128)
 int few_wide_rows(const Ctx* c) {
   if (plan_fused(c, c->R) || c->cfg.dtype != VVS_BF16 || c->cfg.draft_input || c->d > 4096) return 0;
   const size_t layer_weight_bytes = c->esz * ((size_t)4 * c->d * c->d + (size_t)3 * c->d * c->F);
-  if (layer_weight_bytes > (size_t)440 << 20) return 0;
-  return std::min((int)align_up((size_t)c->R * c->Tmax, 32), c->d <= 2048 && layer_weight_bytes <= (size_t)104 << 20 ? 128 : 64);
+  const int d = c->d, F = c->F;
+  if (layer_weight_bytes > (size_t)440 << 20 || (d >= 3584 && F > 12288)) return 0;
+  int most = 32;
+  if (d > 2048) {
+    if (F <= 12288 && F > (d > 4032 ? 2048 : d > 3456 ? 1536 : 0)) most = 64;
+  } else if (F <= 23040) {
+    most = layer_weight_bytes <= (size_t)104 << 20 && (F <= 7168 || (d >= 896 && F < 11264 && F <= (d % 128 ? 10 : 8) * d)) ? 128 : 64;
+  }
+  return std::min((int)align_up((size_t)c->R * c->Tmax, 32), most);
 }
 
 // (More than VVS_MAX_T tokens have no masks.  A device of fewer CUs, a partition of the chip, never has all workgroups running: every launch would wait

@@ -8,6 +8,7 @@
 #include <stdlib.h>
 #include <string.h>
 #include <algorithm>
+#include <array>
 #include <random>
 #include <thread>
 #include <vector>
@@ -288,6 +289,22 @@ int main(int argc, char** argv) {
     vvs_destroy(ctx);
   }
   g_cus = 256;
+  // ... up to the rows where it stops paying: d, heads, d_ff, norm mode, the limit; each side of every line of few_rows and few_wide_rows
+  for (const auto& s : {std::array<int, 5>{768, 12, 2048, 0, 224}, {768, 12, 7680, 0, 160}, {768, 12, 8192, 0, 128}, {768, 12, 9216, 0, 96}, {512, 8, 12288, 0, 64}, {512, 8, 2048, 0, 256},
+                        {256, 4, 24576, 0, 32}, {1280, 20, 3456, 0, 192}, {768, 12, 7168, 1, 128}, {768, 12, 7680, 1, 64}, {960, 15, 9600, 0, 128}, {1024, 16, 8192, 0, 128},
+                        {1024, 16, 10240, 0, 64}, {1088, 17, 11264, 0, 64}, {1792, 14, 23040, 0, 64}, {1792, 14, 25088, 0, 32}, {2048, 16, 5504, 0, 128}, {2048, 16, 8192, 0, 64},
+                        {2560, 20, 12288, 0, 64}, {2560, 20, 12800, 0, 32}, {3520, 55, 13440, 0, 32}, {3584, 28, 12544, 0, 0}, {3584, 28, 12288, 0, 64}, {3840, 60, 12800, 0, 0}, {3840, 30, 1920, 0, 64}, {3840, 30, 1536, 0, 32},
+                        {4096, 32, 2048, 0, 32}, {4096, 32, 11008, 0, 64}, {4096, 32, 12288, 0, 64}, {4096, 32, 14336, 0, 0}, {4160, 65, 4160, 0, 0}}) {
+    vvs_config c = base_config(true, false);
+    c.n_layers = 1; c.d_model = s[0]; c.n_heads = s[1]; c.d_ff = s[2]; c.norm_mode = s[3]; c.n_prompts = 4; c.max_nodes = 63; c.grid_h = c.grid_w = 16;
+    if (s[0] / s[1] == 128) { c.n_prompts = 8; c.max_nodes = 31; }
+    vvs::Ctx k;
+    std::string err;
+    if (vvs::plan_sizes(&c, &k, &err) != VVS_OK) { printf("plan: %s\n", err.c_str()); return 1; }
+    k.cus = 256;
+    for (int t = 1; t <= k.Tmax; ++t)
+      if (vvs::layers_in_one_launch(&k, t) != (k.R * t <= s[4])) { printf("d %d, d_ff %d, %d rows: one launch %d\n", s[0], s[2], k.R * t, (int)vvs::layers_in_one_launch(&k, t)); return 1; }
+  }
   // 3. the call sequences, launchers replaced: target + drafter, fp32 and bf16 planning
   for (int bf16 = 0; bf16 < 2; ++bf16) {
     vvs_config tc = base_config(bf16, false), dc = base_config(bf16, true);
