@@ -166,7 +166,8 @@ __global__ __launch_bounds__(1024) void k_draft_select(const float* __restrict__
 
 // The same for slices of at most 16 * 1024 ids: a thread keeps its 16 mixed logits in registers, so the
 // rows are read once and a taken id is simply removed from its owner's registers.
-// (Slices of at most 4096 ids on 4 waves: d 128, 1024 ids, whole draft loop 8 us of 213 less together with the acceptance.)
+// Few waves meet at a barrier sooner, more hold fewer ids each.  A call of a d 768 drafter, 8 prompts x 26 nodes, us, on 4 / 8 / 16 waves: 1024 ids 283.2 /
+// 281.6 / 285.6, 2048 290.5 / 285.3 / 288.4, 4096 304.5 / 293.3 / 293.0; d 512: 6144 - / 284.7 / 281.2, 8192 - / 290.9 / 284.2.
 template <int NT>
 __global__ __launch_bounds__(NT) void k_draft_select_regs(const float* __restrict__ logits, DraftLevel lv, TreeDesc shape,
                                                             const int32_t* __restrict__ given, int32_t* __restrict__ draft_tokens,
@@ -180,7 +181,6 @@ __global__ __launch_bounds__(NT) void k_draft_select_regs(const float* __restric
   const float* lc = logits + ((size_t)(2 * b) * lv.all + t) * V;
   const float* lu = logits + ((size_t)(2 * b + 1) * lv.all + t) * V;
   float* out = probs + ((size_t)b * shape.T + j) * V;
-  const bool invalid = *gave_up;
   float mixed[NR];
   float mx = -INFINITY;
 #pragma unroll
@@ -190,6 +190,8 @@ __global__ __launch_bounds__(NT) void k_draft_select_regs(const float* __restric
     if (i < V) mixed[r] = lu[i] + cfg_scale * (lc[i] - lu[i]);
     mx = fmaxf(mx, mixed[r]);
   }
+  // (a vector load behind the others: a scalar one would stand in front of them, 0.25 us)
+  const bool invalid = __hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
   mx = block_max(mx, red);
   float e[NR];
   float sum = 0.f;
@@ -238,8 +240,8 @@ void launch_draft_select(Ctx* dr, const DraftLevel& lv, const TreeDesc& shape, c
   if (!lv.n_sel) return;
   Timed timed(dr, VVS_K_ACCEPT, s);
   const uint32_t* gave_up = (const uint32_t*)(dr->ws + dr->w.few_gave_up);
-  if (dr->veff <= 16 * 256)
-    hipLaunchKernelGGL(k_draft_select_regs<256>, dim3(dr->B, lv.n_sel), dim3(256), 0, s, (const float*)(dr->ws + dr->w.logits), lv, shape,
+  if (dr->veff <= 4096)
+    hipLaunchKernelGGL(k_draft_select_regs<512>, dim3(dr->B, lv.n_sel), dim3(512), 0, s, (const float*)(dr->ws + dr->w.logits), lv, shape,
                        d_given_tokens, d_draft_tokens, d_probs, gave_up, dr->veff, dr->lo, dr->cfg.cfg_scale);
   else if (dr->veff <= 16 * 1024)
     hipLaunchKernelGGL(k_draft_select_regs<1024>, dim3(dr->B, lv.n_sel), dim3(1024), 0, s, (const float*)(dr->ws + dr->w.logits), lv, shape,
