@@ -194,7 +194,9 @@ bool plan_fused(const Ctx* c, int M) {
 // d 512, 12288 64 rows 1.03, 100 1.20;  inside: d 896, 7168 192 rows 0.93, d 1024, 6144 192 rows 0.99 to 1.01.
 // Head size 64: its q/k/v tiles are a head's.
 int few_rows(const Ctx* c) {
-  if (!plan_fused(c, c->R) || c->dh != 64) return 0;
+  // (a narrow drafter has one layer to save launches in: 1 prompt x 4 nodes, us, a launch each / one launch, d 64 142 / 150, 128 146 / 152, 192 151 / 154, 256 158 / 155, 512
+  // 174 / 166)
+  if (!plan_fused(c, c->R) || c->dh != 64 || (c->cfg.draft_input && c->d < 256)) return 0;
   const int blocks = std::max(1, (int)(310000000 / ((long)c->F * c->F)));
   const int most = std::min((long)32 * blocks, (long)(c->H * c->B > 64 ? 192 : c->d <= 512 ? 256 : 224));
   const int tokens = c->cfg.draft_input ? c->Tmax : std::max(c->Tmax, std::min(c->chunk, (int)VVS_MAX_T));   // the longest call of either kind

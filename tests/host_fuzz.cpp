@@ -291,7 +291,7 @@ int main(int argc, char** argv) {
   g_cus = 256;
   // ... up to the rows where it stops paying: d, heads, d_ff, norm mode, the limit; each side of every line of few_rows and few_wide_rows
   for (const auto& s : {std::array<int, 5>{768, 12, 2048, 0, 224}, {768, 12, 7680, 0, 160}, {768, 12, 8192, 0, 128}, {768, 12, 9216, 0, 96}, {512, 8, 12288, 0, 64}, {512, 8, 2048, 0, 256},
-                        {256, 4, 24576, 0, 32}, {1280, 20, 3456, 0, 192}, {768, 12, 7168, 1, 128}, {768, 12, 7680, 1, 64}, {960, 15, 9600, 0, 128}, {1024, 16, 8192, 0, 128},
+                        {256, 4, 24576, 0, 32}, {192, 3, 512, 0, 256}, {1280, 20, 3456, 0, 192}, {768, 12, 7168, 1, 128}, {768, 12, 7680, 1, 64}, {960, 15, 9600, 0, 128}, {1024, 16, 8192, 0, 128},
                         {1024, 16, 10240, 0, 64}, {1088, 17, 11264, 0, 64}, {1792, 14, 23040, 0, 64}, {1792, 14, 25088, 0, 32}, {2048, 16, 5504, 0, 128}, {2048, 16, 8192, 0, 64},
                         {2560, 20, 12288, 0, 64}, {2560, 20, 12800, 0, 32}, {3520, 55, 13440, 0, 32}, {3584, 28, 12544, 0, 0}, {3584, 28, 12288, 0, 64}, {3840, 60, 12800, 0, 0}, {3840, 30, 1920, 0, 64}, {3840, 30, 1536, 0, 32},
                         {4096, 32, 2048, 0, 32}, {4096, 32, 11008, 0, 64}, {4096, 32, 12288, 0, 64}, {4096, 32, 14336, 0, 0}, {4160, 65, 4160, 0, 0}}) {
@@ -302,6 +302,12 @@ int main(int argc, char** argv) {
     std::string err;
     if (vvs::plan_sizes(&c, &k, &err) != VVS_OK) { printf("plan: %s\n", err.c_str()); return 1; }
     k.cus = 256;
+    vvs_config drafter = c;
+    drafter.draft_input = 1;
+    vvs::Ctx dr;
+    if (vvs::plan_sizes(&drafter, &dr, &err) != VVS_OK) { printf("plan: %s\n", err.c_str()); return 1; }
+    dr.cus = 256;                                              // wide drafters and narrow ones never, the others as targets
+    if (vvs::layers_in_one_launch(&dr, 1) != (vvs::plan_fused(&k, 1) && s[0] / s[1] == 64 && s[0] >= 256)) { printf("drafter of d %d, d_ff %d\n", s[0], s[2]); return 1; }
     for (int t = 1; t <= k.Tmax; ++t)
       if (vvs::layers_in_one_launch(&k, t) != (k.R * t <= s[4])) { printf("d %d, d_ff %d, %d rows: one launch %d\n", s[0], s[2], k.R * t, (int)vvs::layers_in_one_launch(&k, t)); return 1; }
   }
